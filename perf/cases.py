@@ -30,7 +30,7 @@ def listed():
         dict(name="round large", kind="round", calls=16384, prefill=256, decode=256, types=8, workflows=4096, small_dags=False,
              near_capacity=True, one_call=True),
         # a ragged pool, the round made of its separate library calls (horizons, search with the ratio, commit)
-        dict(name="round ragged, three calls", kind="round", calls=1537, prefill=47, decode=101, types=5, workflows=389,
+        dict(name="round ragged three calls", kind="round", calls=1537, prefill=47, decode=101, types=5, workflows=389,
              small_dags=False, near_capacity=True, one_call=False),
         # a live system: what is live is appended to an empty store, then consecutive rounds reveal, score and commit, then
         # observed costs replace estimates and the urgencies of the last round are formed again
@@ -40,7 +40,7 @@ def listed():
         # horizons of a very large workflow set from scratch: standalone costs, then the single-pass critical path
         dict(name="horizons of 100000 workflows", kind="horizons", workflows=100000, sweeps=0),
         # the critical path of graphs in arbitrary numbering: level-synchronous sweeps up to the depth limit
-        dict(name="horizons, any numbering", kind="horizons", workflows=1000, sweeps=14),
+        dict(name="horizons any numbering", kind="horizons", workflows=1000, sweeps=14),
         # the decode stage of a large queue: one scoring pass with half the calls locked, then the one-pass ordering
         dict(name="decode pass", kind="decode", calls=16384, decode=256, types=8, resident=112, planned=12),
         # the decode stage's recomputing greedy on a small queue
