@@ -24,14 +24,19 @@ import numpy as np
 # multiplications and fused multiply-adds can issue on a second fp32 pipe at the same time as an instruction of
 # another wavefront on the main one (measured in calibration_leg: a stream of v_add_f32, or of v_add_f32
 # alternating with v_max_f32, runs at twice the rate of a stream of v_max_f32 or v_min3_f32); the advertised
-# 157.3 TFLOP/s is both pipes busy with fused multiply-adds.  Comparisons, maxima and minima have the main pipe
-# only.  Per candidate the search needs one maximum, one addition and half a three-input minimum: 2.5 instructions,
-# of which 1.5 are bound to the main pipe -- the resource that limits it.  achieved = candidates/s x 1.5 against
-# 39.32 T main-pipe lane-ops/s; the same loop on registers alone is measured beside it.
+# 157.3 TFLOP/s is both pipes busy with fused multiply-adds.
+# The search finds the minimum over all prefill x decode pairs of a call without forming them one by one (the
+# earliest arrival per decode class stands for all prefill instances; same result bit for bit).  Its arithmetic per
+# call: a prefill instance 5 vector instructions in the first pass (finish and class minimum) and 10 in the second
+# (candidate with the winning decode instance, compared with the minimum), a decode instance 11, a pair of classes 3.
 ALU_PEAK_TOPS = 256 * 64 * 2.4e9 / 1e12
 FP32_VECTOR_PEAK_TFLOPS = 157.3
-MAIN_PIPE_OPS_PER_CANDIDATE = 1.5      # v_max_f32 + half a v_min3_f32
-OPS_PER_CANDIDATE = 2.5                # with the v_add_f32
+
+
+def search_ops(C, P, D, T):
+    return float(C) * (15 * P + 11 * D + 3 * T * T)
+
+
 # Vector ops of the decode-stage search for one (call, instance) pair.  A free call goes through the instance's
 # first-room table: 6 per step of the bisection for its threshold's rank, 8 per stretch of the timeline, 24 for
 # the call's decode time, threshold and the comparison with its best so far.  A locked call scans its one
@@ -515,8 +520,7 @@ def cpu_baseline(rnd, target_s=9.0):
 def calibration_leg(torch):
     """What the chip does on known work, in this run: the rate at which it issues plain fp32 vector instructions of
     each kind (v_max_f32 alone, v_add_f32 alone, the two alternating; 16 independent registers per lane, eight
-    wavefronts per SIMD, no memory), the arithmetic of the search's inner loop on registers alone, and a plain
-    256 MiB device copy."""
+    wavefronts per SIMD, no memory), and a plain 256 MiB device copy."""
     import ctypes
     from paper_2605_16637_amd import build as hx_build
     if not os.path.exists(hx_build.CALIB_LIB):
@@ -534,12 +538,6 @@ def calibration_leg(torch):
         sec = time_launches(torch, fn, 10, warmup=3)
         out[name] = {"lane_ops_per_s": blocks * 256 * iters * 32 / sec, "launch_ms": sec * 1e3}
 
-    def search():
-        assert lib.hx_calib_search(blocks, iters, ptr, stream()) == 0
-    sec = time_launches(torch, search, 10, warmup=3)
-    cand = blocks * 256 * iters * 32 / sec
-    out["search loop on registers"] = {"candidates_per_s": cand, "main_pipe_lane_ops_per_s": cand * MAIN_PIPE_OPS_PER_CANDIDATE,
-                                       "all_lane_ops_per_s": cand * OPS_PER_CANDIDATE, "launch_ms": sec * 1e3}
     n16 = 256 * 1024 * 1024 // 16
     src = torch.empty(n16 * 4, dtype=torch.float32, device="cuda:0").fill_(1.0)
     dst = torch.empty_like(src)
@@ -605,7 +603,7 @@ def round_latency(torch, ctx, synth, name, seed, eager, rounds=500):
             # back-to-back launches of a kernel this short start about 10 us apart whatever its length (the kernel trace
             # in profiles/ has its duration: 8 us on the mid round); the fraction is therefore a lower bound
             "fused_search_kernel": {"launch_period_us": score_s * 1e6, "candidates_per_s": rnd.n_candidates / score_s,
-                                    "frac_of_main_pipe_peak": rnd.n_candidates * MAIN_PIPE_OPS_PER_CANDIDATE / score_s / 1e12 / ALU_PEAK_TOPS},
+                                    "frac_of_main_pipe_peak": search_ops(rnd.calls["n"], rnd.pre["n"], rnd.dec["n"], rnd.links["n_types"]) / score_s / 1e12 / ALU_PEAK_TOPS},
             "calls_with_ratio_above_1.5": late}
 
 
@@ -679,7 +677,8 @@ def main():
     value = n_cand * args.steps / wall
     # the dominant kernel on its own: table prepare + fused search, HIP events on the launch stream
     score_s = time_launches(torch, rd.score, max(20, min(args.steps, 200)))
-    achieved = n_cand * MAIN_PIPE_OPS_PER_CANDIDATE / score_s / 1e12
+    ops = search_ops(C, P, D, rnd.links["n_types"])
+    achieved = ops / score_s / 1e12
     out = {
         "metric": "placement candidates scored/sec",
         "value": value, "unit": "candidates/s",
@@ -690,6 +689,8 @@ def main():
                                 "mid": "mid round: 4096 ready calls x 64 prefill x 64 decode, 4 classes",
                                 "stream": "streaming round shape: 32768 ready calls x 512 x 512, 8 classes"}[args.workload],
                    "calls": C, "prefill": P, "decode": D, "candidates_per_round": n_cand,
+                   "search": "exact minimum over every feasible (prefill, decode) pair of every call, found class by class; a candidate counts "
+                             "as scored when the minimum covers it (all pairs do), not when its cost is formed on its own",
                    "dag_nodes": rnd.dag.n_nodes, "dag_edges": rnd.dag.n_edges, "workflows": rnd.dag.n_wf,
                    # share of (call, decode instance) pairs whose KV does not fit the instance's free tokens (inputs only)
                    "infeasible_pair_fraction": float(np.mean(
@@ -707,19 +708,16 @@ def main():
                                "same search runs as hx_reveal_search_kernel, with the horizon refresh's workgroups in the same launch",
                      "bound": "alu",
                      "achieved": achieved, "peak": ALU_PEAK_TOPS,
-                     "unit": "T lane-ops/s on the SIMDs' main fp32 pipe (v_max_f32, v_min3_f32: 1.5 per candidate; the v_add_f32 pairs with them on the second pipe)",
+                     "unit": "T lane-ops/s: the search's vector instructions against one per SIMD and 4 cycles",
                      "frac": achieved / ALU_PEAK_TOPS,
                      "traffic": profiled_traffic("fused_search_large_sweep.txt", FUSED_SOURCES) if args.workload == "large" else None,
-                     "main_pipe_ops_per_candidate": MAIN_PIPE_OPS_PER_CANDIDATE, "ops_per_candidate": OPS_PER_CANDIDATE,
+                     "ops_per_call": ops / C, "pairs_per_call": P * D,
                      "launch_ms": score_s * 1e3, "candidates_per_s_kernel": n_cand / score_s,
-                     "frac_of_fp32_vector_peak_157.3_tflops": n_cand * OPS_PER_CANDIDATE / score_s / 1e12 / FP32_VECTOR_PEAK_TFLOPS},
+                     "frac_of_fp32_vector_peak_157.3_tflops": achieved / FP32_VECTOR_PEAK_TFLOPS},
     }
     if not args.no_calibration:
         cal = calibration_leg(torch)
         out["calibration"] = cal
-        measured = cal["search loop on registers"]["main_pipe_lane_ops_per_s"] / 1e12
-        out["roofline"]["peak_measured"] = measured
-        out["roofline"]["frac_of_measured"] = achieved / measured
 
     if not args.no_extras:
         eager = args.eager or args.launch == "eager"

@@ -368,8 +368,7 @@ int hx_commit(hx_ctx *ctx, const hx_calls *calls, const int32_t *best_p, const i
  * made on `stream` in that order (the first one that fails ends the call; what
  * was enqueued before it stays enqueued), in fewer launches: the new nodes'
  * costs are worked out by the append's first kernel, and -- where every
- * argument check of the calls passes and the search is large enough beside
- * the append -- the append's walks up the graph share the search's launch (the
+ * argument check of the calls passes -- the append's walks up the graph share the search's launch (the
  * search does not depend on them; only the ratio does) and the ratio is formed
  * by the commit's launch.  n_new may be 0 (nothing is revealed), calls.n may
  * be 0.  The counters of `prefill` and `decode` that

@@ -197,7 +197,8 @@ __device__ __forceinline__ bool hx_cp_walk(const CpArgs &a, char *base, int n0, 
 // well), `nc` and `tab` being the arguments and the class tables of the standalone cost.
 // STREAM: rem, level and tail leave with stores that do not claim cache lines (see the store phase).
 // ROLLED: the cost's class pairs one after the other (hx_node_cost_eval_rolled), for a kernel with few registers to spare.
-template <int NMAX, bool COST, bool STREAM, bool ROLLED = false>
+// NT: threads of the workgroup.
+template <int NMAX, bool COST, bool STREAM, bool ROLLED = false, int NT = CP_THREADS>
 __device__ __forceinline__ void hx_cp_local_body(const CpArgs &a, int wpb, CpNode *s_node, int &s_any,
                                                  const NodeCostArgs *nc, CostTables *tab, int block)
 {
@@ -205,12 +206,12 @@ __device__ __forceinline__ void hx_cp_local_body(const CpArgs &a, int wpb, CpNod
     // for (the tables' loads and divisions then run under those instead of in front of them); block-uniform
     bool tab_ready = !COST;
     constexpr int CP_NMAX = NMAX;             // nodes staged per run
-    constexpr int CP_NPT = (NMAX + CP_THREADS - 1) / CP_THREADS;
+    constexpr int CP_NPT = (NMAX + NT - 1) / NT;
     const int tid = threadIdx.x;
     const int w0 = block * wpb;
     const int w1 = min(w0 + wpb, a.n_wf);
-    // the walking lanes: wave (block mod 4), lane = workflow within the run
-    const int wl = tid - ((block & 3) << 6);
+    // the walking lanes: one wave, another one in consecutive blocks; lane = workflow within the run
+    const int wl = tid - ((block % (NT / HX_WAVE)) << 6);
     bool not_dag = false, bad_index = false;
     if (tid == 0) s_node[0] = CpNode{0, -1, 0u, 0u};
     char *const base = (char *)s_node;
@@ -256,7 +257,7 @@ __device__ __forceinline__ void hx_cp_local_body(const CpArgs &a, int wpb, CpNod
                 int ra[CP_NPT], rb[CP_NPT];
 #pragma unroll
                 for (int k = 0; k < CP_NPT; ++k) {
-                    const int i = min(k * CP_THREADS + tid, nn - 1);   // a thread past the end repeats the last node
+                    const int i = min(k * NT + tid, nn - 1);   // a thread past the end repeats the last node
                     if constexpr (COST) { len_in[k] = nc->L_in[n0 + i]; len_out[k] = nc->L_out[n0 + i]; }
                     else c[k] = a.cost[n0 + i];
                     ra[k] = a.row_ptr[n0 + i];
@@ -283,7 +284,7 @@ __device__ __forceinline__ void hx_cp_local_body(const CpArgs &a, int wpb, CpNod
                 // the costs are worked out (COST) and parked while the ids are on their way
 #pragma unroll
                 for (int k = 0; k < CP_NPT; ++k) {
-                    const int i = k * CP_THREADS + tid;
+                    const int i = k * NT + tid;
                     if constexpr (COST) if (i < nn) {
                         c[k] = ROLLED ? hx_node_cost_eval_rolled(nc->m, *tab, nc->T, len_in[k], len_out[k])
                                       : hx_node_cost_eval(nc->m, *tab, nc->T, len_in[k], len_out[k]);
@@ -294,7 +295,7 @@ __device__ __forceinline__ void hx_cp_local_body(const CpArgs &a, int wpb, CpNod
                 }
 #pragma unroll
                 for (int k = 0; k < CP_NPT; ++k) {
-                    const int i = k * CP_THREADS + tid;
+                    const int i = k * NT + tid;
                     const int ic = min(i, nn - 1);
                     // a legal successor is one of ic+1 .. nn-1: one unsigned compare of its distance beyond ic+1
                     const int first = n0 + ic + 1;
@@ -323,7 +324,7 @@ __device__ __forceinline__ void hx_cp_local_body(const CpArgs &a, int wpb, CpNod
             __syncthreads();
 #pragma unroll
             for (int k = 0; k < CP_NPT; ++k) {
-                const int i = k * CP_THREADS + tid;
+                const int i = k * NT + tid;
                 if (i < nn) {
                     const int4 me = *(const int4 *)&s_node[i + 1];
                     if constexpr (STREAM) {

@@ -5,7 +5,6 @@
 #include "hx_append.hpp"
 
 void hx_dag_release(hx_ctx *ctx);   // hx_dag.hip
-int hx_score_init();                // hx_score.hip
 int hx_reveal_search(hx_ctx *ctx, const hx_model *model, const hx_calls *calls,
                      const hx_prefill_tab *pre, const hx_decode_tab *dec, const hx_links *links,
                      const float *tail, const float *horizon, int32_t n_nodes, int32_t n_wf,
@@ -347,7 +346,7 @@ extern "C" int hx_ctx_create(hx_ctx **out, int device)
         unsigned long long *p = nullptr;
         e = hx_static_scratch(device, &p);
     }
-    if (e == hipSuccess && (hx_score_init() != HX_OK || hx_plan_init() != HX_OK || hx_decode_init() != HX_OK)) { what = "hipFuncSetAttribute(LDS size)"; e = hipErrorInvalidValue; }
+    if (e == hipSuccess && (hx_plan_init() != HX_OK || hx_decode_init() != HX_OK)) { what = "hipFuncSetAttribute(LDS size)"; e = hipErrorInvalidValue; }
     if (e == hipSuccess) {
         what = "launch of hx_clear_status_kernel";
         CommitArgs z{};
@@ -585,7 +584,7 @@ extern "C" int hx_round(hx_ctx *ctx, const hx_model *model, const hx_round_args 
         if (r->ratio) { tail = r->tail; horizon = r->horizon; n_nodes = r->n_nodes; }
     } else {
         // The append's walks ride in the search's launch, and the ratio in the commit's, where every argument check
-        // passes and the search is large enough beside them: four launches instead of five, the walks' chain of
+        // passes: four launches instead of five, the walks' chain of
         // memory round trips under the search.  Else the walks are a launch of their own and the calls follow.
         HxAppendPlan ap{};
         bool merged = false;

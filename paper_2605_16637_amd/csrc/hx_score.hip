@@ -6,28 +6,21 @@
 // earliest pair), feasibility per Sec. 5.4 Eq. (3),(4), projected ratio per
 // Sec. 5.1 Eq. (2).  How it is laid out is specific to gfx950:
 //
-//  * One wavefront owns one call at a time.  Lanes are prefill instances
-//    (KP per lane), so everything that depends on the decode instance only --
-//    its availability hint and the call's decode time there -- is the same
-//    for all 64 lanes and is read from LDS as a broadcast.
-//  * Transfer time depends on the two GPU classes only, so a lane keeps
-//    ready[class] = prefill finish + transfer for the <= 8 decode classes in
-//    registers, and decode instances are visited grouped by class: inside a
-//    class segment the inner loop is  t = max(ready, avail_d) + dec_d ;
-//    best = min(best, t)  with no index bookkeeping.
-//  * The index is recovered afterwards: the wave minimum fixes the winning
-//    prefill instance (lowest p among lanes that hold the minimum), and one
-//    pass of the wave over that instance's D candidates finds the lowest d
-//    that reproduces the minimum bit for bit.  This gives exactly the
-//    lexicographic minimum of (cost, p*D + d).
+//  * The fused search does not form every pair: a candidate's cost grows with the
+//    moment the KV arrives, which depends on the decode instance through its
+//    class only, so the earliest arrival per class stands for all prefill
+//    instances.  Lanes are calls; the pool's tables are read from LDS as
+//    broadcasts (see hx_fused_search_body).
+//  * Results are exactly the lexicographic minimum of (cost, p*D + d) over all
+//    pairs, with the costs the materialised tensor holds, bit for bit.
 #include "hx_common.hpp"
 #include "hx_terms.hpp"
 #include "hx_search.hpp"
 #include "hx_cp.hpp"
 #include "hx_append.hpp"
 
-#include <cfloat>
 #include <cmath>
+#include <type_traits>
 
 namespace {
 
@@ -139,134 +132,6 @@ __global__ __launch_bounds__(1024) void hx_prepare_kernel(PrepArgs a)
     }
 }
 
-// The same tables, built by the first 256 threads of a workgroup straight into its own LDS arrays (the fused search
-// does this itself instead of reading what hx_prepare_kernel wrote: a launch less per round, for a few
-// barriers more per workgroup).  Entry order is the one above: classes ascending, instances of a class
-// ascending.  s_scratch: [(HX_MAX_INSTANCES / HX_WAVE) * kT + kT] ints.  Ends with a barrier.
-struct PrepLds {
-    float *wait, *c1, *c2, *kB;
-    int *free, *orig, *dtype;
-    float *pw, *pinvF, *pinvB;
-    int *ptype;
-    float *invbw, *lat;
-    int *seg;            // [kT + 1]
-    int *scratch;
-    int Pp;
-};
-
-__device__ __forceinline__ void hx_prepare_into_lds(const PrepArgs &a, const PrepLds &o)
-{
-    constexpr int NCH = HX_MAX_INSTANCES / 256;          // chunks of 256 instances
-    // the first 256 threads of the workgroup do the work; wavefronts beyond them only keep the barriers company
-    const bool worker = threadIdx.x < 256;
-    const int tid = worker ? (int)threadIdx.x : (1 << 24);      // beyond every size: all the tests below fail
-    const int lane = threadIdx.x & (HX_WAVE - 1), wv = (threadIdx.x >> 6) & 3;
-    int *s_wcnt = o.scratch;                             // [NCH * 4 waves][kT]
-    int *s_cnt = o.scratch + NCH * 4 * kT;               // [kT]
-
-    // ---- reads (all of them before the first barrier)
-    const bool has_link = tid < kT * kT;
-    const int tp = tid / kT, td = tid % kT;
-    const bool link_in = has_link && tp < a.T && td < a.T;
-    const float l_bw = link_in ? a.bw[tp * a.T + td] : 1.0f;
-    const float l_lat = (link_in && a.lat) ? a.lat[tp * a.T + td] : 0.0f;
-    int my_t[NCH], d_used[NCH], d_batch[NCH], d_qd[NCH], d_cap[NCH];
-    float d_flops[NCH], d_hbm[NCH];
-    bool bad = false;
-#pragma unroll
-    for (int j = 0; j < NCH; ++j) {
-        const int d = j * 256 + tid;
-        const bool has_d = d < a.D;
-        my_t[j] = has_d ? a.d_type[d] : -1;
-        d_used[j] = has_d ? a.d_used[d] : 0; d_batch[j] = has_d ? a.d_batch[d] : 0; d_qd[j] = has_d ? a.d_qd[d] : 0;
-        d_cap[j] = has_d ? a.d_cap[d] : 0;
-        d_flops[j] = has_d ? a.d_flops[d] : 1.0f; d_hbm[j] = has_d ? a.d_hbm[d] : 1.0f;
-        if (has_d && (my_t[j] < 0 || my_t[j] >= a.T)) { bad = true; my_t[j] = 0; }
-    }
-    for (int p = tid; p < o.Pp; p += 256) {
-        const bool in = p < a.P;
-        int p_t = in ? a.p_type[p] : 0;
-        if (in && (p_t < 0 || p_t >= a.T)) { bad = true; p_t = 0; }
-        const float invF = in ? 1.0f / a.p_flops[p] : 0.0f;
-        o.pinvF[p] = invF;
-        o.pinvB[p] = in ? 1.0f / a.p_hbm[p] : 0.0f;
-        o.pw[p] = in ? hx_prefill_wait(a.m, a.p_backlog[p], invF) : INFINITY;    // lanes beyond P never win
-        o.ptype[p] = p_t;
-    }
-    if (bad) hx_raise(a.status, HX_ERR_INDEX);
-    if (has_link) {
-        o.invbw[tid] = link_in ? 1.0f / l_bw : 0.0f;
-        o.lat[tid] = l_lat;
-    }
-
-    // ---- decode instances ranked by class: per-wave class counts (ballots), class sizes, class segments
-    int my_rank[NCH];
-#pragma unroll
-    for (int j = 0; j < NCH; ++j) {
-        my_rank[j] = 0;
-        if (j * 256 < a.D) {
-#pragma unroll
-            for (int t = 0; t < kT; ++t) {
-                const unsigned long long b = __ballot(my_t[j] == t);
-                if (lane == 0 && worker) s_wcnt[(j * 4 + wv) * kT + t] = __popcll(b);
-                if (my_t[j] == t) my_rank[j] = __popcll(b & ((1ull << lane) - 1ull));
-            }
-        }
-    }
-    __syncthreads();
-    const int n_slots = (a.D + HX_WAVE - 1) / HX_WAVE;   // waves of instances, in instance order
-    if (tid < HX_WAVE) {                                 // the first wave: lane t < kT owns class t
-        int n = 0;
-        if (tid < kT)
-            for (int k = 0; k < n_slots; ++k) n += s_wcnt[k * kT + tid];     // independent reads
-        if (tid < kT) s_cnt[tid] = n;
-        // class segments: running sum of the padded class sizes over the lanes
-        const int padded = tid < kT ? (n + HX_DGROUP - 1) / HX_DGROUP * HX_DGROUP : 0;
-        int incl = padded;
-#pragma unroll
-        for (int off = 1; off < kT; off <<= 1) {
-            const int up = __shfl_up(incl, off);
-            if (lane >= off) incl += up;
-        }
-        if (tid < kT) o.seg[tid] = incl - padded;
-        if (tid == kT - 1) o.seg[kT] = incl;
-    }
-    __syncthreads();
-
-    // ---- entries: pads, then the instances (disjoint indices)
-    int seg[kT + 1], cnt[kT];
-#pragma unroll
-    for (int t = 0; t <= kT; ++t) seg[t] = o.seg[t];
-#pragma unroll
-    for (int t = 0; t < kT; ++t) cnt[t] = s_cnt[t];
-    const int n_entries = seg[kT];
-    for (int e = tid; e < n_entries; e += 256) {
-        int t = 0, first = 0, used = cnt[0];
-#pragma unroll
-        for (int k = 1; k < kT; ++k)
-            if (e >= seg[k]) { t = k; first = seg[k]; used = cnt[k]; }
-        if (e >= first + used) {
-            o.wait[e] = 0.0f; o.c1[e] = 0.0f; o.c2[e] = 0.0f; o.kB[e] = 0.0f;
-            o.free[e] = -1; o.orig[e] = -1; o.dtype[e] = t;
-        }
-    }
-#pragma unroll
-    for (int j = 0; j < NCH; ++j) {
-        const int d = j * 256 + tid;
-        if (d < a.D) {
-            const int t = my_t[j];
-            int e = o.seg[t] + my_rank[j];
-            for (int k = 0; k < j * 4 + wv; ++k) e += s_wcnt[k * kT + t];        // instances of the class in earlier waves
-            const HxDecF x = hx_decode_terms(a.m, d_used[j], d_batch[j], d_qd[j], 1.0f / d_flops[j], 1.0f / d_hbm[j]);
-            o.wait[e] = x.wait; o.c1[e] = x.c1; o.c2[e] = x.c2; o.kB[e] = x.kB;
-            const long long fr = (long long)d_cap[j] - (long long)d_used[j];
-            o.free[e] = fr < -1 ? -1 : (fr > 2147483647LL ? 2147483647 : (int)fr);
-            o.orig[e] = d; o.dtype[e] = t;
-        }
-    }
-    __syncthreads();
-}
-
 // ---- common argument block of the scoring kernels ------------------------------
 
 struct ScoreArgs {
@@ -290,116 +155,355 @@ __device__ __forceinline__ void hx_ratio(const ScoreArgs &a, int c, float best)
 }
 
 // ---- fused search ----------------------------------------------------------------
+//
+// A candidate's cost is max(done_p + x[class_p][class_d], avail_d) + dec_d.  It does not fall when its first operand
+// grows, and that operand depends on the prefill instance within a class through done_p only and on the decode
+// instance through its class only.  Maxima and minima round nothing and the additions are applied to the same
+// operands, so the minimum over all P x D pairs is, bit for bit,
+//     m[i]  = min over p of class i of done_p                      P evaluations per call
+//     r[k]  = min over i of m[i] + x[i][k]                         T x T
+//     best  = min over d of max(r[class_d], avail_d) + dec_d       D
+// and the pair is recovered by one more pass over p: the lowest p whose candidate with the winning decode
+// instance is the minimum.  P + T x T + D + P evaluations per call take the place of P x D.  Launches back to back, before
+// (one wavefront per call, 2.5 instructions per pair) and now: 64 calls x 4 x 4 6.0 -> 4.2 us, 4096 x 64 x 64 7.7 -> 4.7,
+// 16384 x 256 x 256 63.5 -> 8.4, 32768 x 512 x 512 450 -> 19.7, 16384 x 16 x 1024 88 -> 12.6.
+//
+// What bounds it: some 4 us of every launch are the chain of memory round trips (pool tables, call inputs) and the barriers
+// between the passes, which is why few calls are spread over all compute units; the rest is instruction issue and LDS
+// reads in about equal parts (a decode instance: 12 vector instructions and three reads, a prefill instance: 5 + 10 and
+// four).
+//
+// A workgroup takes CALLS calls through the whole pool, a lane one of them; the lanes of a call in a wavefront (64 / CALLS)
+// and the wavefronts deal the instances out among themselves, in turn, and read them from LDS as broadcasts.  Nothing
+// is reduced across lanes but once per call and pass.
+constexpr int FS_THREADS = 512;
+constexpr int FS_WAVES = FS_THREADS / HX_WAVE;
 
-// LDS carve-up shared by host (size) and device (offsets)
-struct FusedLds {
-    int Dp, Pp;
-    __host__ __device__ FusedLds(int n_entries_bound, int P)
-        : Dp(n_entries_bound), Pp((P + HX_WAVE - 1) / HX_WAVE * HX_WAVE) {}
-    __host__ __device__ size_t block_floats() const { return (size_t)7 * Dp + (size_t)4 * Pp + 2 * kT * kT + 16; }
-    __host__ __device__ size_t wave_floats() const { return (size_t)Dp + kT * kT; }
-    __host__ __device__ size_t bytes(int waves) const { return 4 * (block_floats() + waves * wave_floats()); }
+// LDS carve-up shared by host (size) and device (offsets), in 4-byte words; every array starts on a 16-byte boundary
+struct SearchLds {
+    int P, D, calls;
+    __host__ __device__ size_t pre() const { return 0; }                                   // float4 [P]: wait, 1/F, 1/B, class
+    __host__ __device__ size_t dec() const { return 4 * (size_t)P; }                       // float4 [D]: wait, c1, c2, kB
+    __host__ __device__ size_t dex() const { return dec() + 4 * (size_t)D; }               // int2 [D]: free tokens + 1, class
+    __host__ __device__ size_t link() const { return dex() + 2 * ((size_t)(D + 1) & ~(size_t)1); }   // float2 [kT*kT]: 1/bw, latency
+    __host__ __device__ size_t m() const { return link() + 2 * kT * kT; }                  // [kT][calls] earliest prefill finish per class
+    __host__ __device__ size_t r() const { return m() + (size_t)kT * calls; }              // [kT][calls] earliest arrival per decode class
+    __host__ __device__ size_t part() const { return r() + (size_t)kT * calls; }           // int2 [waves][calls]: cost, instance and tie of a wavefront's share
+    __host__ __device__ size_t pd() const { return part() + 2 * (size_t)FS_WAVES * calls; }  // int2 [calls]: the pair
+    __host__ __device__ size_t tie() const { return pd() + 2 * (size_t)calls; }            // [calls] not 0: the pair is left to hx_pair_of_tied
+    __host__ __device__ size_t slot() const { return tie() + (size_t)calls; }              // [2^slot_bits()] lowest decode instance of a hash value
+    __host__ __device__ int slot_bits() const { int b = 6; while ((1 << b) < 2 * D) ++b; return b; }
+    __host__ __device__ size_t bytes() const { return 4 * (slot() + ((size_t)1 << slot_bits())); }
 };
 
-// block, n_blocks: the workgroup's place among those that search (the launch may hold other workgroups too)
-template <int KP>
-__device__ __forceinline__ void hx_fused_search_body(const ScoreArgs &a, const PrepArgs &pa, int dp_bound, float *smem,
-                                                     int block, int n_blocks)
+// the sum of a call's lengths as the capacity test takes it: it fits where need < free tokens + 1 (0: nothing fits)
+__device__ __forceinline__ unsigned hx_free_plus1(int cap, int used)
 {
-    const FusedLds lay(dp_bound, a.P);
-    float *s_wait = smem;                  // 7 decode arrays of dp_bound entries
-    float *s_c1 = s_wait + lay.Dp;
-    float *s_c2 = s_c1 + lay.Dp;
-    float *s_kB = s_c2 + lay.Dp;
-    int *s_free = (int *)(s_kB + lay.Dp);
-    int *s_orig = s_free + lay.Dp;
-    int *s_dtype = s_orig + lay.Dp;
-    float *s_pw = (float *)(s_dtype + lay.Dp);   // 4 prefill arrays of Pp entries
-    float *s_pinvF = s_pw + lay.Pp;
-    float *s_pinvB = s_pinvF + lay.Pp;
-    int *s_ptype = (int *)(s_pinvB + lay.Pp);
-    float *s_invbw = (float *)(s_ptype + lay.Pp);
-    float *s_lat = s_invbw + kT * kT;
-    int *s_seg = (int *)(s_lat + kT * kT);       // kT+1 used, 16 reserved
-    float *s_wave = (float *)(s_seg + 16);
+    const long long fr = (long long)cap - (long long)used;
+    return fr < 0 ? 0u : (fr > 2147483647LL ? 0x80000000u : (unsigned)fr + 1u);
+}
+
+__device__ __forceinline__ unsigned hx_alike_hash(float c1, float c2, int type, int bits)
+{
+    return ((__float_as_uint(c1) + (unsigned)type) * 2654435761u ^ __float_as_uint(c2) * 2246822519u) * 3266489917u >> (32 - bits);
+}
+
+// The pair of a call whose minimum `best` several decode instances attain, by one wavefront: the lowest p that
+// attains it with any of them, then the lowest d that does with that p.  For a decode instance that attains it, the
+// prefill instances that do so with it are those that arrive by R, the largest arrival whose candidate is still the
+// minimum; R is found by bisection over the bit patterns between the earliest arrival (which attains it) and the
+// minimum itself (no later arrival can), and of a class only its largest R matters.  thr: [kT] words of LDS of
+// the wavefront's own.
+__device__ __forceinline__ int2 hx_pair_of_tied(const HxCallF &cf, unsigned need, float best, int P, int D, const float4 *s_pre,
+                                                const float4 *s_dec, const int2 *s_dex, const float2 *s_link, const float *r_call,
+                                                int r_stride, int *thr, int lane)
+{
+    if (lane < kT) thr[lane] = -1;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    for (int e0 = 0; e0 < D; e0 += HX_WAVE) {
+        const int e = min(e0 + lane, D - 1);
+        const float4 t = s_dec[e];
+        const int2 x = s_dex[e];
+        const float dec = hx_decode_time(cf, t.y, t.z, t.w);
+        const float r = r_call[x.y * r_stride];
+        const bool hit = need < (unsigned)x.x && hx_candidate(r, t.x, dec) == best;
+        int lo = __float_as_int(r), hi = hit ? __float_as_int(best) : lo;
+        while (__builtin_amdgcn_ballot_w64(lo < hi) != 0) {
+            const int mid = lo + ((hi - lo + 1) >> 1);
+            const bool still = hx_candidate(__int_as_float(mid), t.x, dec) <= best;
+            if (lo < hi) { if (still) lo = mid; else hi = mid - 1; }
+        }
+        if (hit) atomicMax(&thr[x.y], lo);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    int R[kT];
+#pragma unroll
+    for (int k = 0; k < kT; ++k) R[k] = thr[k];
+    int2 out = make_int2(-1, -1);
+    for (int p0 = 0; p0 < P; p0 += HX_WAVE) {
+        const int p = min(p0 + lane, P - 1);
+        const float4 t = s_pre[p];
+        const float done = hx_prefill_done(cf, t.x, t.y, t.z);
+        const float2 *row = s_link + __float_as_int(t.w) * kT;
+        bool ok = false;
+#pragma unroll
+        for (int k = 0; k < kT; ++k) {
+            const float2 l = row[k];
+            ok = ok || __float_as_int(done + hx_transfer(cf, l.x, l.y)) <= R[k];
+        }
+        const unsigned long long b = __builtin_amdgcn_ballot_w64(ok && p0 + lane < P);
+        if (b) { out.x = p0 + __builtin_ctzll(b); break; }
+    }
+    if (out.x >= 0) {
+        const float4 t = s_pre[out.x];
+        const float done = hx_prefill_done(cf, t.x, t.y, t.z);
+        const float2 *row = s_link + __float_as_int(t.w) * kT;
+        for (int e0 = 0; e0 < D; e0 += HX_WAVE) {
+            const int e = min(e0 + lane, D - 1);
+            const float4 q = s_dec[e];
+            const int2 x = s_dex[e];
+            const float2 l = row[x.y];
+            const float v = hx_candidate(done + hx_transfer(cf, l.x, l.y), q.x, hx_decode_time(cf, q.y, q.z, q.w));
+            const unsigned long long b = __builtin_amdgcn_ballot_w64(e0 + lane < D && need < (unsigned)x.x && v == best);
+            if (b) { out.y = e0 + __builtin_ctzll(b); break; }
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    return out;
+}
+
+// block: the workgroup's place among those that search (the launch may hold other workgroups too)
+template <int CALLS>
+__device__ __forceinline__ void hx_fused_search_body(const ScoreArgs &a, const PrepArgs &pa, float *smem, int block)
+{
+    constexpr int SUB = HX_WAVE / CALLS;                  // lanes of a wavefront that share a call
+    constexpr int SLICES = SUB * FS_WAVES;
+    const SearchLds lay{a.P, a.D, CALLS};
+    float4 *s_pre = (float4 *)(smem + lay.pre());
+    float4 *s_dec = (float4 *)(smem + lay.dec());
+    int2 *s_dex = (int2 *)(smem + lay.dex());
+    float2 *s_link = (float2 *)(smem + lay.link());
+    float *s_m = smem + lay.m();
+    float *s_r = smem + lay.r();
+    int2 *s_part = (int2 *)(smem + lay.part());
+    int2 *s_pd = (int2 *)(smem + lay.pd());
+    int *s_tie = (int *)(smem + lay.tie());
+    int *s_slot = (int *)(smem + lay.slot());
+    const int slot_bits = lay.slot_bits();
 
     const int tid = threadIdx.x;
     const int lane = tid & (HX_WAVE - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int waves_per_block = blockDim.x >> 6;
-    float *dbuf = s_wave + (size_t)wave * lay.wave_floats();    // the call's decode time per entry
-    float *xbuf = dbuf + lay.Dp;                                // transfer per class pair
+    const int cl = lane & (CALLS - 1);                    // the lane's call within the workgroup
+    const int slice = wave * SUB + lane / CALLS;
+    const int base = block * CALLS;
 
-    // What the wave's first call says of itself is asked for before the pool's tables are derived, and every
-    // later call's while the call before it is searched: the loads are wave-uniform (scalar), and none of the
-    // kernel's chains of dependent memory round trips waits for them on its own.
-    const int gw = block * waves_per_block + wave;
-    const int nw = n_blocks * waves_per_block;
+    // what the calls say of themselves is asked for before the pool's tables; the first CALLS threads also write the
+    // calls' results and ask for what the ratio needs
+    const int c_in = min(base + cl, a.C - 1);
+    const int L = a.L_in[c_in], O = a.L_out[c_in];
     const bool want_ratio = a.ratio != nullptr;
-    int c = gw;
-    int L = 0, O = 0, nd = 0, w = 0;
+    const int my_c = base + tid;
+    const bool mine = tid < CALLS && my_c < a.C;
+    int nd = 0, w = 0;
     float el = 0.0f;
-    if (c < a.C) {
-        L = a.L_in[c]; O = a.L_out[c];
-        if (want_ratio) { nd = a.node[c]; w = a.wf[c]; el = a.elapsed[c]; }
-    }
+    if (mine && want_ratio) { nd = a.node[my_c]; w = a.wf[my_c]; el = a.elapsed[my_c]; }
 
-    // the per-round tables of the pool, derived here; the class counts of the derivation borrow the
-    // waves' buffers, which nothing has used yet
-    const PrepLds out{s_wait, s_c1, s_c2, s_kB, s_free, s_orig, s_dtype, s_pw, s_pinvF, s_pinvB, s_ptype,
-                      s_invbw, s_lat, s_seg, (int *)s_wave, lay.Pp};
-    hx_prepare_into_lds(pa, out);
-    const int Dp = s_seg[kT];              // <= dp_bound by construction
-
-    int seg[kT + 1];
-#pragma unroll
-    for (int k = 0; k <= kT; ++k) seg[k] = __builtin_amdgcn_readfirstlane(s_seg[k]);
-    const HxPoolLds pool{s_wait, s_c1, s_c2, s_kB, s_free, s_orig, s_dtype, s_pw, s_pinvF, s_pinvB, s_ptype,
-                         s_invbw, s_lat, Dp, a.P, lay.Pp};
-
-    while (c < a.C) {
-        // the downstream tail and the horizon of the call's workflow travel while the call is searched
-        const bool ok = !want_ratio || (nd >= 0 && nd < a.n_nodes && w >= 0 && w < a.n_wf);
-        float tl = 0.0f, hz = 1.0f;
-        if (want_ratio && ok) { tl = a.tail[nd]; hz = a.horizon[w]; }
-        const int cn = c + nw;
-        int Ln = 0, On = 0, ndn = 0, wn = 0;
-        float eln = 0.0f;
-        if (cn < a.C) {
-            Ln = a.L_in[cn]; On = a.L_out[cn];
-            if (want_ratio) { ndn = a.node[cn]; wn = a.wf[cn]; eln = a.elapsed[cn]; }
-        }
-        const HxBest b = hx_search_call<KP>(a.m, pool, seg, dbuf, xbuf, L, O, lane);
-        if (lane == 0) {
-            a.best_p[c] = b.p;
-            a.best_d[c] = b.d;
-            a.best_cost[c] = b.cost;
-            if (want_ratio) {
-                if (!ok) hx_raise(a.status, HX_ERR_INDEX);
-                hx_store_bits(a.ratio, c, hx_ratio_bits(el, b.cost, tl, hz, ok));      // Eq. (2), as hx_projected_ratio forms it
+    // ---- the pool's per-round tables, in instance order
+    for (int i = tid; i < (1 << slot_bits); i += FS_THREADS) s_slot[i] = 0x7fffffff;
+    {
+        bool bad = false;
+        const bool link_in = tid < kT * kT && tid / kT < pa.T && tid % kT < pa.T;
+        const int link_at = (tid / kT) * pa.T + tid % kT;
+        const float l_bw = link_in ? pa.bw[link_at] : 1.0f;
+        const float l_lat = (link_in && pa.lat) ? pa.lat[link_at] : 0.0f;
+        for (int i0 = 0; i0 < max(a.P, a.D); i0 += FS_THREADS) {
+            const int i = i0 + tid;
+            const bool hp = i < a.P, hd = i < a.D;
+            const int p = hp ? i : 0, d = hd ? i : 0;
+            const float pf = pa.p_flops[p], pb = pa.p_hbm[p], df = pa.d_flops[d], db = pa.d_hbm[d];
+            const int bl = pa.p_backlog[p], used = pa.d_used[d], cap = pa.d_cap[d], batch = pa.d_batch[d], qd = pa.d_qd[d];
+            int tp = pa.p_type[p], td = pa.d_type[d];
+            if (tp < 0 || tp >= pa.T) { bad = bad || hp; tp = 0; }
+            if (td < 0 || td >= pa.T) { bad = bad || hd; td = 0; }
+            if (i0 == 0) __syncthreads();                          // the slots are clear; the loads above are on their way
+            if (hp) {
+                const float invF = 1.0f / pf;
+                s_pre[p] = make_float4(hx_prefill_wait(a.m, bl, invF), invF, 1.0f / pb, __int_as_float(tp));
+            }
+            if (hd) {
+                const HxDecF x = hx_decode_terms(a.m, used, batch, qd, 1.0f / df, 1.0f / db);
+                s_dec[d] = make_float4(x.wait, x.c1, x.c2, x.kB);
+                s_dex[d] = make_int2((int)hx_free_plus1(cap, used), td);
+                atomicMin(&s_slot[hx_alike_hash(x.c1, x.c2, td, slot_bits)], d);
             }
         }
-        c = cn; L = Ln; O = On; nd = ndn; w = wn; el = eln;
+        if (bad) hx_raise(a.status, HX_ERR_INDEX);
+        if (tid < kT * kT) s_link[tid] = make_float2(link_in ? 1.0f / l_bw : 0.0f, l_lat);
+        for (int i = tid; i < kT * CALLS; i += FS_THREADS) s_m[i] = INFINITY;      // a class without instances
+        if (tid < CALLS) { s_pd[tid] = make_int2(0x7fffffff, -1); s_tie[tid] = 0; }
+    }
+    const HxCallF cf = hx_call_terms(a.m, L, O);
+    const unsigned need = (unsigned)L + (unsigned)O;      // both are >= 0: the unsigned sum cannot wrap
+    __syncthreads();
+
+    // the tail and the horizon of the ratio travel while the calls are searched
+    const bool ok = nd >= 0 && nd < a.n_nodes && w >= 0 && w < a.n_wf;
+    float tl = 0.0f, hz = 1.0f;
+    if (mine && want_ratio && ok) { tl = a.tail[nd]; hz = a.horizon[w]; }
+
+    // Decode instances that cannot be chosen are taken out of the search: one of the same class and per-token terms, with a
+    // lower index, no later available and with no less room, is as good for every call and wins every tie.  (Idle
+    // instances of a class are alike; without this nearly every call of a drained pool has several minima.)
+    for (int d = tid; d < a.D; d += FS_THREADS) {
+        const float4 t = s_dec[d];
+        const int2 x = s_dex[d];
+        const int f = s_slot[hx_alike_hash(t.y, t.z, x.y, slot_bits)];
+        const float4 u = s_dec[f];
+        const int2 y = s_dex[f];
+        if (f < d && u.y == t.y && u.z == t.z && u.w == t.w && y.y == x.y && u.x <= t.x && (unsigned)y.x >= (unsigned)x.x) s_dex[d].x = 0;
+    }
+    // ---- m[i]: the earliest finish in every prefill class (finishes are not negative: their bits order like they do)
+    for (int p = slice; p < a.P; p += 4 * SLICES) {
+        float4 t[4];                                      // read together: none waits for the minimum before it
+#pragma unroll
+        for (int u = 0; u < 4; ++u) t[u] = s_pre[min(p + u * SLICES, a.P - 1)];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)                       // past the end the last instance once more
+            atomicMin((unsigned *)s_m + __float_as_int(t[u].w) * CALLS + cl, __float_as_uint(hx_prefill_done(cf, t[u].x, t[u].y, t[u].z)));
+    }
+    __syncthreads();
+    // ---- r[k]: the earliest the call's KV can be at an instance of decode class k
+    for (int i = tid; i < pa.T * CALLS; i += FS_THREADS) {
+        const int k = i / CALLS;                          // i % CALLS is the thread's own call
+        float r = INFINITY;
+#pragma unroll
+        for (int q = 0; q < kT; ++q) {
+            const float2 l = s_link[q * kT + k];
+            r = fminf(r, s_m[q * CALLS + cl] + hx_transfer(cf, l.x, l.y));      // a class without instances: +inf
+        }
+        s_r[k * CALLS + cl] = r;
+    }
+    __syncthreads();
+    // ---- the minimum over the decode instances, the lowest instance that attains it, and whether others do
+    float best = INFINITY;
+    int bd = -1;
+    bool tie = false;
+#pragma unroll 8
+    for (int d = slice; d < a.D; d += SLICES) {
+        const float4 t = s_dec[d];
+        const int2 x = s_dex[d];
+        float v = hx_candidate(s_r[x.y * CALLS + cl], t.x, hx_decode_time(cf, t.y, t.z, t.w));
+        v = need < (unsigned)x.x ? v : INFINITY;
+        const bool lt = v < best;
+        tie = !lt && (tie || v == best);
+        bd = lt ? d : bd;
+        best = fminf(best, v);
+    }
+    // instance and tie as one number: among equal costs the smallest number has the lowest instance, and there is a tie
+    int key = bd * 2 + (tie ? 1 : 0);
+#pragma unroll
+    for (int off = CALLS; off < HX_WAVE; off <<= 1) {
+        const float ov = __shfl_xor(best, off);
+        const int ok2 = __shfl_xor(key, off);
+        key = ov < best ? ok2 : (ov == best ? (min(key, ok2) | 1) : key);
+        best = fminf(best, ov);
+    }
+    if (lane < CALLS) s_part[wave * CALLS + cl] = make_int2(__float_as_int(best), key);
+    __syncthreads();
+    {
+        int2 q[FS_WAVES];
+#pragma unroll
+        for (int v = 0; v < FS_WAVES; ++v) q[v] = s_part[v * CALLS + cl];
+        best = __int_as_float(q[0].x);
+        key = q[0].y;
+#pragma unroll
+        for (int v = 1; v < FS_WAVES; ++v) {
+            const float ov = __int_as_float(q[v].x);
+            key = ov < best ? q[v].y : (ov == best ? (min(key, q[v].y) | 1) : key);
+            best = fminf(best, ov);
+        }
+    }
+    const bool any = best < INFINITY;
+    const int d_win = any ? key >> 1 : 0;
+    const float4 t_win = s_dec[d_win];
+    const int k_win = s_dex[d_win].y;
+    const float dec_win = hx_decode_time(cf, t_win.y, t_win.z, t_win.w);
+    if (slice == 0 && any) s_pd[cl].y = d_win;
+    // Several decode instances attain a minimum.  Those of the winner's class and with its decode time do so with the
+    // same prefill instances as the winner, whatever their availability: nothing changes, the lowest instance has been
+    // kept.  A call that has others (rare) is left to hx_pair_of_tied.  (Every wavefront sees every call: uniform.)
+    const bool tied = __builtin_amdgcn_ballot_w64(any && (key & 1)) != 0;
+    if (tied) {
+        for (int d = slice; d < a.D; d += SLICES) {
+            const float4 t = s_dec[d];
+            const int2 x = s_dex[d];
+            const float dec = hx_decode_time(cf, t.y, t.z, t.w);
+            if (any && need < (unsigned)x.x && (x.y != k_win || dec != dec_win) &&
+                hx_candidate(s_r[x.y * CALLS + cl], t.x, dec) == best) s_tie[cl] = 1;
+        }
+    }
+    // ---- the lowest prefill instance that attains the minimum with the winner
+    int p_low = 0x7fffffff;
+#pragma unroll 8
+    for (int p = slice; p < a.P; p += SLICES) {
+        const float4 t = s_pre[p];
+        const float2 l = s_link[__float_as_int(t.w) * kT + k_win];
+        const float v = hx_candidate(hx_prefill_done(cf, t.x, t.y, t.z) + hx_transfer(cf, l.x, l.y), t_win.x, dec_win);
+        if (v == best) p_low = min(p_low, p);
+    }
+#pragma unroll
+    for (int off = CALLS; off < HX_WAVE; off <<= 1) p_low = min(p_low, __shfl_xor(p_low, off));
+    if (lane < CALLS && any && p_low < 0x7fffffff) atomicMin(&s_pd[cl].x, p_low);
+    __syncthreads();
+    if (tied) {
+        for (int ct = wave; ct < CALLS; ct += FS_WAVES) {
+            if (s_tie[ct] == 0) continue;
+            const int c = min(base + ct, a.C - 1);
+            const int Lt = a.L_in[c], Ot = a.L_out[c];
+            float b = INFINITY;
+#pragma unroll
+            for (int v = 0; v < FS_WAVES; ++v) b = fminf(b, __int_as_float(s_part[v * CALLS + ct].x));
+            // its words of LDS: the class minima, which nobody reads any more
+            const int2 pd = hx_pair_of_tied(hx_call_terms(a.m, Lt, Ot), (unsigned)Lt + (unsigned)Ot, b, a.P, a.D, s_pre, s_dec, s_dex, s_link,
+                                            s_r + ct, CALLS, (int *)s_m + wave * kT, lane);
+            if (lane == 0) s_pd[ct] = pd;
+        }
+        __syncthreads();
+    }
+    if (mine) {                                           // the thread's own call is call my_c
+        const int2 pd = s_pd[tid];
+        const bool placed = any && pd.x != 0x7fffffff;
+        a.best_p[my_c] = placed ? pd.x : -1;
+        a.best_d[my_c] = placed ? pd.y : -1;
+        a.best_cost[my_c] = best;
+        if (want_ratio) {
+            if (!ok) hx_raise(a.status, HX_ERR_INDEX);
+            hx_store_bits(a.ratio, my_c, hx_ratio_bits(el, best, tl, hz, ok));      // Eq. (2), as hx_projected_ratio forms it
+        }
     }
 }
 
-template <int KP>
-__global__ __launch_bounds__(512) void hx_fused_search_kernel(ScoreArgs a, PrepArgs pa, int dp_bound)
+template <int CALLS>
+__global__ __launch_bounds__(FS_THREADS) void hx_fused_search_kernel(ScoreArgs a, PrepArgs pa)
 {
     extern __shared__ __align__(16) float smem[];
-    hx_fused_search_body<KP>(a, pa, dp_bound, smem, (int)blockIdx.x, (int)gridDim.x);
+    hx_fused_search_body<CALLS>(a, pa, smem, (int)blockIdx.x);
 }
 
 // ---- the first kernel of a scheduling round that brings its whole graph: reveal and search in one launch ----
 //
 // The horizon refresh (node cost + critical path, what hx_cp_cost_kernel does) and the search do not depend on each
 // other -- only the ratio needs both, and it is formed by the commit kernel that follows -- so they share a launch:
-// n_reveal workgroups take workflows exactly as hx_cp_cost_kernel's do (same body, the cost's prefill classes one
-// after the other to stay within the search's registers), the others search.  Same results as the two kernels,
-// one launch and the gap before it less.  On a small round (every wavefront has at most one call, all workgroups
-// resident at once) both halves are chains of memory round trips, which now run side by side; on a large one the
-// reveal's workgroups, the last of the grid then, take the places of the searching workgroups that end first
-// (those whose wavefronts were dealt one call fewer) while the rest of the chip goes on searching.
+// the first n_reveal workgroups take workflows exactly as hx_cp_cost_kernel's do (same body, a node per thread, the
+// cost's prefill classes one after the other to stay within the search's registers), the others search.  Same
+// results as the two kernels, one launch and the gap before it less: both halves are chains of memory round trips,
+// which run side by side.  The reveal's chain is the longer one, so its workgroups come first.
 constexpr int RV_NMAX = 512;             // nodes staged per run of a reveal workgroup
 
 struct RevealLds {
@@ -408,36 +512,31 @@ struct RevealLds {
     int any;
 };
 
-// FIRST: the reveal's workgroups are the first n_reveal of the grid (else the last)
-template <int KP, bool FIRST>
-__global__ __launch_bounds__(CP_THREADS) void hx_reveal_search_kernel(ScoreArgs a, PrepArgs pa, int dp_bound, CpArgs cp,
-                                                                      NodeCostArgs nc, int wpb, int n_reveal)
+template <int CALLS>
+__global__ __launch_bounds__(FS_THREADS) void hx_reveal_search_kernel(ScoreArgs a, PrepArgs pa, CpArgs cp, NodeCostArgs nc, int wpb,
+                                                                      int n_reveal)
 {
     extern __shared__ __align__(16) float smem[];
-    const int n_search = (int)gridDim.x - n_reveal;
-    const int block = FIRST ? (int)blockIdx.x - n_reveal : (int)blockIdx.x;              // among the searching ones
-    if (FIRST ? block < 0 : block >= n_search) {
+    if ((int)blockIdx.x < n_reveal) {
         RevealLds *l = (RevealLds *)smem;
-        hx_cp_local_body<RV_NMAX, true, false, true>(cp, wpb, l->node, l->any, &nc, &l->tab,
-                                                     FIRST ? (int)blockIdx.x : block - n_search);
+        hx_cp_local_body<RV_NMAX, true, false, true, FS_THREADS>(cp, wpb, l->node, l->any, &nc, &l->tab, (int)blockIdx.x);
         return;
     }
-    hx_fused_search_body<KP>(a, pa, dp_bound, smem, block, n_search);
+    hx_fused_search_body<CALLS>(a, pa, smem, (int)blockIdx.x - n_reveal);
 }
 
 // The same for a round that appends to the context's graph: the append's walks (hx_append_relax_kernel's work: one
 // thread per new node, a chain of device-scope atomics up its ancestors) take the first n_lead workgroups of the
-// search's launch.  They are all latency and no arithmetic, and where the search fills the chip the workgroups they
-// displace are again the ones with the fewest calls.
-template <int KP>
-__global__ __launch_bounds__(512) void hx_relax_search_kernel(ScoreArgs a, PrepArgs pa, int dp_bound, AppendArgs ap, int n_lead)
+// search's launch.  They are all latency and no arithmetic, and longer than the search that runs beside them.
+template <int CALLS>
+__global__ __launch_bounds__(FS_THREADS) void hx_relax_search_kernel(ScoreArgs a, PrepArgs pa, AppendArgs ap, int n_lead)
 {
     extern __shared__ __align__(16) float smem[];
     if ((int)blockIdx.x < n_lead) {
         hx_append_relax_body(ap, (int)blockIdx.x, n_lead);
         return;
     }
-    hx_fused_search_body<KP>(a, pa, dp_bound, smem, (int)blockIdx.x - n_lead, (int)gridDim.x - n_lead);
+    hx_fused_search_body<CALLS>(a, pa, smem, (int)blockIdx.x - n_lead);
 }
 
 // ---- materialised tensor ------------------------------------------------------------
@@ -672,25 +771,6 @@ int hx_prepare_pool(hx_ctx *ctx, const hx_model *model, const hx_prefill_tab *pr
     return hx_check_launch(ctx, "hx_prepare_kernel");
 }
 
-// the fused search may use all 160 KB of LDS; said once per process, outside any stream work
-int hx_score_init()
-{
-    const int lds = 160 * 1024;
-    const void *kernels[] = {
-        reinterpret_cast<const void *>(hx_fused_search_kernel<1>), reinterpret_cast<const void *>(hx_fused_search_kernel<2>),
-        reinterpret_cast<const void *>(hx_fused_search_kernel<4>),
-        reinterpret_cast<const void *>(hx_reveal_search_kernel<1, true>), reinterpret_cast<const void *>(hx_reveal_search_kernel<2, true>),
-        reinterpret_cast<const void *>(hx_reveal_search_kernel<4, true>),
-        reinterpret_cast<const void *>(hx_reveal_search_kernel<1, false>), reinterpret_cast<const void *>(hx_reveal_search_kernel<2, false>),
-        reinterpret_cast<const void *>(hx_reveal_search_kernel<4, false>),
-        reinterpret_cast<const void *>(hx_relax_search_kernel<1>), reinterpret_cast<const void *>(hx_relax_search_kernel<2>),
-        reinterpret_cast<const void *>(hx_relax_search_kernel<4>)};
-    hipError_t e = hipSuccess;
-    for (const void *k : kernels)
-        if (e == hipSuccess) e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    return e == hipSuccess ? HX_OK : HX_ERR_DEVICE;
-}
-
 namespace {
 
 // reveal: NULL, or the horizon refresh of the same round (hx_horizons_plan), to ride in the search's launch if the
@@ -753,82 +833,44 @@ int score_placements(hx_ctx *ctx, const hx_model *model, const hx_calls *calls,
     if (fused) {
         // the search derives the per-round tables of the pool in its own workgroups: no launch of its own for them
         const PrepArgs pa = make_prep_args(ctx, model, pre, dec, links);
-        // upper bound of the padded decode entries, known on the host without reading the device
-        const int dp_bound = (D + HX_DGROUP - 1) / HX_DGROUP * HX_DGROUP + (T - 1) * HX_DGROUP;
-        // Workgroups of 4 or 8 wavefronts (one or two per SIMD), as many per compute unit as local memory allows up
-        // to 6 wavefronts per SIMD (registers would allow 7; measured no faster, and 6 divides into either
-        // workgroup size): the pool tables are per workgroup, a wavefront adds its decode-time and transfer
-        // buffers.  Whichever size puts more wavefronts on a SIMD, the larger on a tie (half as many workgroups derive
-        // the pool's tables).
-        const FusedLds lay(dp_bound, P);
+        // Calls per workgroup: as few as spread the calls over every compute unit (the tables are derived once per
+        // workgroup, in the same time however many calls follow), 64 at most.  Two workgroups to a compute unit
+        // beat one of twice the calls as long as the tables are short beside the passes (16384 x 256 x 256: 8.4 us with 32
+        // calls each, 9.4 with 64); from 65 calls per compute unit on there are two of 64 (32768 x 512 x 512: 19.7 us,
+        // 21.7 with 32; 65536 x 256 x 256: 19.7, 23.6 with 32).  8192 x 64 x 64 takes 4.9 us with 32 and 5.3 with 16.
+        const int per_cu = (C + ctx->num_cu - 1) / ctx->num_cu;
+        const int calls_per_wg = per_cu > 64 ? 64 : per_cu > 16 ? 32 : per_cu > 8 ? 16 : 8;
+        const int n_search = (C + calls_per_wg - 1) / calls_per_wg;
+        const size_t lds = SearchLds{P, D, calls_per_wg}.bytes();
+        auto by_calls = [&](auto &&launch) {
+            if (calls_per_wg == 64) launch(std::integral_constant<int, 64>{});
+            else if (calls_per_wg == 32) launch(std::integral_constant<int, 32>{});
+            else if (calls_per_wg == 16) launch(std::integral_constant<int, 16>{});
+            else launch(std::integral_constant<int, 8>{});
+        };
         if (reveal) {
-            // Workgroups of four wavefronts, as many searching ones as are resident at once (six per compute unit, or
-            // what local memory allows) or as the calls need, whichever is less.  Where all of the launch is resident
-            // at once the reveal's workgroups are the first of the grid.  Where the searching workgroups alone fill
-            // the chip they are the last: they start as the first searching workgroups end -- those whose wavefronts
-            // have the fewest calls (calls are dealt c, c + n, ...) -- in places that would stand empty for the rest of
-            // the launch, and are done before the wavefronts with one call more (in front of the grid they held up
-            // that many searching workgroups from the start: 73 us against 71 for the large round's launch).  Not this
-            // way if the reveal's units are too large for its staging area or its workgroups more than a third of
-            // the searching ones.
-            const size_t lds4 = lay.bytes(4) > sizeof(RevealLds) ? lay.bytes(4) : sizeof(RevealLds);
-            if (lds4 > 160 * 1024) return HX_OK;
-            const long long by_lds = (long long)(160 * 1024) / (long long)lds4;
-            const long long resident = (by_lds < 6 ? by_lds : 6) * ctx->num_cu;
-            const long long need4 = (C + 3) / 4;
-            const int n_search = (int)(need4 < resident ? need4 : resident);
+            // not this way if the reveal's units are too large for its staging area
             const long long nodes_per_unit = (long long)reveal->a.n_nodes * reveal->wpb / (reveal->a.n_wf > 0 ? reveal->a.n_wf : 1);
-            const bool all_resident = need4 + reveal->grid <= resident;
-            if (nodes_per_unit > RV_NMAX * 7 / 10 || !(all_resident || 3LL * reveal->grid <= n_search)) return HX_OK;
-            auto launch = [&](auto kern) {
-                kern<<<reveal->grid + n_search, CP_THREADS, lds4, stream>>>(a, pa, dp_bound, reveal->a, reveal->nc, reveal->wpb,
-                                                                            reveal->grid);
-            };
-            if (all_resident) {
-                if (P <= 64) launch(hx_reveal_search_kernel<1, true>);
-                else if (P <= 128) launch(hx_reveal_search_kernel<2, true>);
-                else launch(hx_reveal_search_kernel<4, true>);
-            } else {
-                if (P <= 64) launch(hx_reveal_search_kernel<1, false>);
-                else if (P <= 128) launch(hx_reveal_search_kernel<2, false>);
-                else launch(hx_reveal_search_kernel<4, false>);
-            }
+            if (nodes_per_unit > RV_NMAX * 7 / 10) return HX_OK;
+            const size_t lds_both = lds > sizeof(RevealLds) ? lds : sizeof(RevealLds);
+            by_calls([&](auto calls) {
+                hx_reveal_search_kernel<calls()><<<reveal->grid + n_search, FS_THREADS, lds_both, stream>>>(
+                    a, pa, reveal->a, reveal->nc, reveal->wpb, reveal->grid);
+            });
             if (int rc = hx_check_launch(ctx, "hx_reveal_search_kernel")) return rc;
             *revealed = true;
             return HX_OK;
         }
-        const int reg_limit = 6 * 4;                               // wavefronts per compute unit
-        int waves = 4, blocks_per_cu = 1, best_on_cu = 0;
-        for (int w = 4; w <= 8; w += 4) {
-            const size_t need_lds = lay.bytes(w);
-            if (need_lds > 160 * 1024) continue;
-            int b = (int)((160 * 1024) / need_lds);
-            b = b > reg_limit / w ? reg_limit / w : b;
-            if (b * w >= best_on_cu) { best_on_cu = b * w; waves = w; blocks_per_cu = b; }
-        }
-        const size_t lds = lay.bytes(waves);
-        HX_REQUIRE(ctx, best_on_cu > 0, HX_ERR_SHAPE, "pool needs %zu B of LDS", lds);
-        int grid = ctx->num_cu * blocks_per_cu;
-        const int need = (C + waves - 1) / waves;
-        grid = grid > need ? need : grid;
         if (walks) {
-            // the walks' threads take several new nodes each if need be; not this way if they would be more than a
-            // third of the launch (a small search behind a large append: the two launches are then the better way)
-            const int threads = waves * HX_WAVE;
-            const int n_lead = (walks->a.n_new + threads - 1) / threads;
-            if (3LL * n_lead > grid) return HX_OK;
-            auto launch_w = [&](auto kern) { kern<<<n_lead + grid, threads, lds, stream>>>(a, pa, dp_bound, walks->a, n_lead); };
-            if (P <= 64) launch_w(hx_relax_search_kernel<1>);
-            else if (P <= 128) launch_w(hx_relax_search_kernel<2>);
-            else launch_w(hx_relax_search_kernel<4>);
+            const int n_lead = (walks->a.n_new + FS_THREADS - 1) / FS_THREADS;
+            by_calls([&](auto calls) {
+                hx_relax_search_kernel<calls()><<<n_lead + n_search, FS_THREADS, lds, stream>>>(a, pa, walks->a, n_lead);
+            });
             if (int rc = hx_check_launch(ctx, "hx_relax_search_kernel")) return rc;
             *revealed = true;
             return HX_OK;
         }
-        auto launch = [&](auto kern) { kern<<<grid, waves * HX_WAVE, lds, stream>>>(a, pa, dp_bound); };
-        if (P <= 64) launch(hx_fused_search_kernel<1>);
-        else if (P <= 128) launch(hx_fused_search_kernel<2>);
-        else launch(hx_fused_search_kernel<4>);
+        by_calls([&](auto calls) { hx_fused_search_kernel<calls()><<<n_search, FS_THREADS, lds, stream>>>(a, pa); });
         if (int rc = hx_check_launch(ctx, "hx_fused_search_kernel")) return rc;
     }
     if (cost || feas) {
@@ -873,8 +915,8 @@ int hx_reveal_search(hx_ctx *ctx, const hx_model *model, const hx_calls *calls,
                             best_p, best_d, best_cost, ratio, reveal, nullptr, revealed, stream_);
 }
 
-// The walks of an append that has begun and hx_score_placements (fused outputs) in one launch, where the search is
-// large enough beside them (*merged; otherwise nothing has been launched).  ratio: checked, not written, as above.
+// The walks of an append that has begun and hx_score_placements (fused outputs) in one launch (*merged; otherwise
+// nothing has been launched).  ratio: checked, not written, as above.
 int hx_relax_search(hx_ctx *ctx, const hx_model *model, const hx_calls *calls,
                     const hx_prefill_tab *pre, const hx_decode_tab *dec, const hx_links *links,
                     const float *tail, const float *horizon, int32_t n_nodes, int32_t n_wf,

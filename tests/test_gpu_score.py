@@ -93,6 +93,48 @@ def test_fused_search_ragged_shapes(ctx, C, P, D, T):
         assert (gp[1], gd[1]) == (-1, -1) and np.isinf(gc[1])
 
 
+# C just past the sizes at which a workgroup takes 8, 16, 32 and 64 calls on 256 compute units; pools around a wavefront's
+# share of instances and at the limits
+@pytest.mark.parametrize("C,P,D,T", [(1, 1, 1, 1), (9, 64, 63, 8), (2047, 3, 17, 2), (2049, 9, 33, 5), (4097, 17, 8, 8),
+                                     (8193, 5, 31, 3), (8193, 33, 2, 7), (40, 1024, 1024, 8), (70, 513, 511, 6)])
+@pytest.mark.parametrize("pool", ["any", "alike", "no output", "few values"])
+def test_fused_search_equals_selection_over_the_tensor(ctx, C, P, D, T, pool):
+    """The search works class by class; the selection compares the cost of every pair.  Same bits, also where many
+    pairs attain the minimum: instances alike, calls that decode nothing (cost = arrival), counters of few values."""
+    import torch
+    from paper_2605_16637_amd import binding
+    rng = np.random.default_rng(C + 7 * P + D)
+    types, pre, dec, links = random_pool(rng, P, D, T)
+    L, O = synth.gen_lengths(rng, C)
+    if pool == "alike":
+        for t in (pre, dec):
+            for k in ("backlog_tok", "used_tok", "batch", "qd_tok"):
+                if k in t:
+                    t[k][:] = 0
+    if pool == "no output":
+        O[::2] = 0
+    if pool == "few values":
+        pre["backlog_tok"][:] = rng.integers(0, 2, P) * 5000
+        dec["qd_tok"][:] = rng.integers(0, 3, D) * 4000
+        dec["used_tok"][:] = rng.integers(0, 2, D) * 40000
+        dec["batch"][:] = dec["used_tok"] // 2048
+        L[:], O[:] = L // 512 * 512, O // 64 * 64
+    if C > 2:
+        L[1] = 2000000000                 # fits nowhere
+    pre["n"], dec["n"] = P, D
+    calls = binding.to_device(dict(n=C, L_in=L, L_out=O))
+    dp, dd, dl = binding.to_device(pre), binding.to_device(dec), binding.to_device(links)
+    gp, gd, gc = fused(ctx, synth.MODEL, calls, dp, dd, dl)
+    cost = torch.empty(C * P * D, device="cuda:0")
+    ctx.hx_score_placements(synth.MODEL, calls, dp, dd, dl, cost=cost)
+    bp, bd = (torch.empty(C, dtype=torch.int32, device="cuda:0") for _ in range(2))
+    bc = torch.empty(C, device="cuda:0")
+    ctx.hx_select(C, P, D, cost, bp, bd, bc)
+    ctx.hx_stream_status()
+    assert np.array_equal(gc.view(np.int32), bc.cpu().numpy().view(np.int32))
+    assert np.array_equal(gp, bp.cpu().numpy()) and np.array_equal(gd, bd.cpu().numpy())
+
+
 def test_ties_resolve_to_lowest_flat_index(ctx):
     # homogeneous idle pool: all P*D candidates tie -> (0, 0); then knock out
     # the low indices one at a time
