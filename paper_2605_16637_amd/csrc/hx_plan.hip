@@ -8,6 +8,7 @@
 #include "hx_search.hpp"
 
 #include <cmath>
+#include <type_traits>
 
 namespace {
 
@@ -195,19 +196,43 @@ __global__ __launch_bounds__(1024) void hx_rank_within_kernel(int32_t *rank, int
 }
 
 // ---- recomputing greedy -------------------------------------------------------------
-
-constexpr int GREEDY_THREADS = 1024;
-constexpr int GREEDY_WAVES = GREEDY_THREADS / HX_WAVE;
+//
+// One workgroup plans the whole queue: the pool tables, the simulated state and the per-call results live in LDS, there
+// is no launch between the picks, and nothing is written to memory before the last.
+//
+// Every remaining call's cost is recomputed after every pick, but not pair by pair.  A candidate's cost is
+// max(done_p + x[class_p][class_d], avail_d) + dec_d; it does not fall when its first operand grows, so
+//     m[i]  = min over the prefill instances p of class i of done_p
+//     r[k]  = min over i of m[i] + x[i][k]
+//     best  = min over d of max(r[class_d], avail_d) + dec_d
+// is the minimum over all pairs bit for bit (maxima and minima round nothing, the additions have the same operands).
+// Prefill instances of one class and the same rates differ by their queue alone, and the one with the shortest
+// finishes first for every call: they are one entry ("kind") of the search.  A pick changes one prefill instance
+// (its kind's shortest queue: m of one class) and one decode instance (one column of dec).  The pair itself is
+// only found for the call that is picked, by the first wavefront, which also adds it to the state.
+//
+// What bounds it: a pick is a chain (argmax, pair, commit, candidates of the calls that remain, argmax) of some eight
+// LDS round trips and a few hundred dependent instructions; 8 calls or 64 make no difference to it.  So every wavefront
+// makes the pick for itself from a copy of the pool in its registers -- handing it on would be another barrier and
+// two round trips -- and few wavefronts take part: a call is one lane, or several (G) once the remaining calls leave
+// lanes idle.  The decode times of the calls stay in LDS, where they fit; a pick rewrites one column.  Calls that were
+// picked leave holes: when half of a stage's calls are gone, the rest is dealt to the lanes anew.
+// Whole plans, before (every call whose pair a pick touched searched again, pair by pair, by one of 16 wavefronts) and now:
+// 64 calls on 8 + 8 instances 338 -> 85 us, 256 on 64 + 64 2500 -> 465, 256 on 256 + 256 3860 -> 1640, 1024 on 64 + 64
+// 20100 -> 6320, 1024 on 256 + 256 30600 -> 16900.  (256 on 64 + 64 with four wavefronts instead of eight: 500.)
+constexpr int GREEDY_THREADS = 8 * HX_WAVE;                  // two wavefronts per SIMD
+constexpr int GREEDY_MAX_THREADS = HX_GREEDY_MAX_CALLS;      // a lane per call at least
+constexpr int GREEDY_K = HX_GREEDY_MAX_INSTANCES / HX_WAVE;
+constexpr int GREEDY_MAX_G = 16;                             // lanes per call at most: a row of lanes (a power of two)
 
 struct GreedyArgs {
     HxModelF m;
-    int C, P, D;
+    int C, P, D, T;
     const int32_t *L_in, *L_out, *node, *wf;
     const float *elapsed, *tail, *horizon;
     int n_nodes, n_wf;
-    const HxPrepTables *prep;
-    const float *d_flops, *d_hbm;
-    const int32_t *p_backlog, *d_used, *d_cap, *d_batch, *d_qd;
+    const float *p_flops, *p_hbm, *d_flops, *d_hbm, *bw, *lat;
+    const int32_t *p_backlog, *p_type, *d_used, *d_cap, *d_batch, *d_qd, *d_type;
     int tokens_per_seq, max_batch;
     int32_t *best_p, *best_d, *rank;
     float *best_cost, *ratio;
@@ -215,231 +240,479 @@ struct GreedyArgs {
     int32_t *status;
 };
 
-// LDS carve-up shared by host (size) and device (offsets), in 4-byte words
-struct GreedyLds {
-    int Dp, Pp, C, P, D;      // lengths of the LDS arrays (not the problem sizes)
-    __host__ __device__ GreedyLds(int dp_bound, int P_, int D_, int C_)
-        : Dp(dp_bound), Pp((P_ + HX_WAVE - 1) / HX_WAVE * HX_WAVE),
-          C((C_ + 3) & ~3), P((P_ + 3) & ~3), D((D_ + 3) & ~3) {}      // array lengths, kept 16-byte aligned
-    __host__ __device__ size_t words() const
-    {
-        return (size_t)7 * Dp + 4 * Pp + 2 * kT * kT + 16     // pool view, as in the fused search
-             + P + 7 * (size_t)D                               // simulated state and what is needed to re-derive an entry
-             + 11 * (size_t)C                                  // per call: pair, cost, ratio, flags; lengths, elapsed, tail, horizon; the list of calls to score again
-             + 4 * GREEDY_WAVES                                // reduction scratch
-             + (size_t)GREEDY_WAVES * (Dp + kT * kT + kT);     // per-wave search buffers
-    }
+// decode entries: by class, each class padded to whole groups of four, their number to a whole group per lane
+constexpr int GREEDY_ENTRIES = HX_GREEDY_MAX_INSTANCES + 4 * kT + 4 * GREEDY_MAX_G;
+
+// the pool in LDS; its arrays lie at fixed places (their addresses cost no registers)
+struct __align__(16) GreedyPool {
+    float w[GREEDY_ENTRIES], c1[GREEDY_ENTRIES], c2[GREEDY_ENTRIES], kB[GREEDY_ENTRIES];      // decode entries: hint, per-token terms
+    int free[GREEDY_ENTRIES], orig[GREEDY_ENTRIES];                   // free tokens, instance (-1: pad)
+    int goff[GREEDY_ENTRIES / 4];                                     // of a group of four: where the arrivals at its class begin
+    int used[HX_GREEDY_MAX_INSTANCES], batch[HX_GREEDY_MAX_INSTANCES], qd[HX_GREEDY_MAX_INSTANCES];   // decode instances: simulated state
+    int cap[HX_GREEDY_MAX_INSTANCES], pos[HX_GREEDY_MAX_INSTANCES], dty[HX_GREEDY_MAX_INSTANCES];     // capacity, entry, class
+    float dF[HX_GREEDY_MAX_INSTANCES], dB[HX_GREEDY_MAX_INSTANCES];   // 1/rates
+    float pw[HX_GREEDY_MAX_INSTANCES], pF[HX_GREEDY_MAX_INSTANCES], pB[HX_GREEDY_MAX_INSTANCES];      // prefill instances: wait, 1/rates
+    int pty[HX_GREEDY_MAX_INSTANCES], kind[HX_GREEDY_MAX_INSTANCES], backlog[HX_GREEDY_MAX_INSTANCES];
+    float kw[HX_GREEDY_MAX_INSTANCES], kF[HX_GREEDY_MAX_INSTANCES], kB2[HX_GREEDY_MAX_INSTANCES];     // kinds, by class: shortest wait, 1/rates
+    int kfirst[HX_GREEDY_MAX_INSTANCES];                              // first prefill instance of an instance's kind
+    float2 link[kT * kT], link_to[kT * kT];                           // 1/bandwidth, latency: by (from, to) and by (to, from)
+    int4 red[2][2][GREEDY_MAX_THREADS / HX_WAVE];                     // a wavefront's most urgent call, picks in turn: key, slot, L, O; cost, ratio, call
+    int wcnt[GREEDY_MAX_THREADS / HX_WAVE];
+    int seg[kT + 1], kseg[kT + 1], cnt[kT], kcnt[kT];                 // entries and kinds of a class begin here; how many there are
 };
 
-enum : int { ALIVE = 1, DIRTY = 2 };
+// the calls in LDS: host (size) and device (offsets), in 4-byte words
+struct GreedyCalls {
+    int C4;                                                           // calls, rounded up to a multiple of four
+    __host__ __device__ explicit GreedyCalls(int C) : C4((C + 3) & ~3) {}
+    __host__ __device__ int rec() const { return 0; }                 // int4 per slot: call, L, O
+    __host__ __device__ int in() const { return 4 * C4; }             // float4 per call: elapsed, tail, horizon (-1: index out of range)
+    __host__ __device__ int out() const { return 8 * C4; }            // int4 per call: pair, cost, ratio
+    __host__ __device__ int rank() const { return 12 * C4; }          // per call, -1 until it is picked
+    __host__ __device__ int r() const { return 13 * C4; }             // [kT][C4] earliest arrival per decode class
+    __host__ __device__ int dec() const { return (13 + kT) * C4; }    // decode times of the calls, as many as there is room for
+};
 
-// One block plans the whole queue: the pool tables, the simulated state and the
-// per-call results live in LDS, there is no launch between iterations.  A call
-// is scored again only if its current pair touches an instance a commit just
-// changed and the pair's cost moved: while commits only add load they can only
-// raise costs, so every other call keeps its pair and cost exactly.  A commit
-// that lowers a term of its decode instance (a snapshot batch above the batch
-// rule's value) has every remaining call scored again.
-template <int KP>
-__global__ __launch_bounds__(GREEDY_THREADS) void hx_plan_greedy_kernel(GreedyArgs a, int dp_bound)
+// The minimum over the groups of G neighbouring lanes (G a power of two, at most a row of 16; other G: the next one), in each lane.
+__device__ __forceinline__ float hx_lanes_min(float x, int G)
+{
+#define HX_ROW_MIN(ctrl) x = fminf(x, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), ctrl, 0xf, 0xf, true)))
+    if (G > 1) HX_ROW_MIN(0xB1);           // quad_perm [1,0,3,2]
+    if (G > 2) HX_ROW_MIN(0x4E);           // quad_perm [2,3,0,1]
+    if (G > 4) HX_ROW_MIN(0x141);          // row_half_mirror
+    if (G > 8) HX_ROW_MIN(0x140);          // row_mirror
+#undef HX_ROW_MIN
+    return x;
+}
+
+// LDS written by some lanes of a wavefront and read by others of it
+__device__ __forceinline__ void hx_wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+__device__ __forceinline__ float hx_lane_value(float x, int lane) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), lane)); }
+
+// dec_words: LDS words behind lay.dec()
+// K: instances of either side per lane of a wavefront's copy of the pool; TT: classes, or more
+template <int K, int TT, int THREADS>
+__global__ __launch_bounds__(THREADS) void hx_plan_greedy_kernel(GreedyArgs a, int dec_words)
 {
     extern __shared__ __align__(16) float smem[];
-    const HxPrepTables *__restrict__ t = a.prep;
-    const int Dp = t->n_entries;
-    const GreedyLds lay(dp_bound, a.P, a.D, a.C);
-    float *s_wait = smem;
-    float *s_c1 = s_wait + lay.Dp;
-    float *s_c2 = s_c1 + lay.Dp;
-    float *s_kB = s_c2 + lay.Dp;
-    int *s_free = (int *)(s_kB + lay.Dp);
-    int *s_orig = s_free + lay.Dp;
-    int *s_dtype = s_orig + lay.Dp;
-    float *s_pw = (float *)(s_dtype + lay.Dp);
-    float *s_pinvF = s_pw + lay.Pp;
-    float *s_pinvB = s_pinvF + lay.Pp;
-    int *s_ptype = (int *)(s_pinvB + lay.Pp);
-    float *s_invbw = (float *)(s_ptype + lay.Pp);
-    float *s_lat = s_invbw + kT * kT;
-    int *s_seg = (int *)(s_lat + kT * kT);
-    int *s_backlog = s_seg + 16;                       // simulated state
-    int *s_used = s_backlog + lay.P;
-    int *s_batch = s_used + lay.D;
-    int *s_qd = s_batch + lay.D;
-    int *s_cap = s_qd + lay.D;
-    int *s_pos = s_cap + lay.D;                        // entry of decode instance d
-    float *s_dinvF = (float *)(s_pos + lay.D);
-    float *s_dinvB = s_dinvF + lay.D;
-    int *s_bp = (int *)(s_dinvB + lay.D);              // per call
-    int *s_bd = s_bp + lay.C;
-    float *s_bc = (float *)(s_bd + lay.C);
-    float *s_ratio = s_bc + lay.C;
-    int *s_flags = (int *)(s_ratio + lay.C);
-    int *s_L = s_flags + lay.C;                        // what the queue says of a call, read once
-    int *s_O = s_L + lay.C;
-    float *s_el = (float *)(s_O + lay.C);
-    float *s_tl = s_el + lay.C;                        // tail of its node, horizon of its workflow (-1: index out of range)
-    float *s_hz = s_tl + lay.C;
-    int *s_list = (int *)(s_hz + lay.C);               // the calls to score again, in any order: dealt to the wavefronts evenly
-    float *s_redv = (float *)(s_list + lay.C);         // reduction scratch, then the pick
-    int *s_redi = (int *)(s_redv + GREEDY_WAVES);
-    int *s_pick = s_redi + GREEDY_WAVES;               // [0] call, [1] p, [2] d
-    float *s_wave = (float *)(s_pick + 2 * GREEDY_WAVES);
+    __shared__ GreedyPool s;
+    const GreedyCalls lay(a.C);
+    int4 *const s_rec = (int4 *)(smem + lay.rec());
+    float4 *const s_in = (float4 *)(smem + lay.in());
+    int4 *const s_out = (int4 *)(smem + lay.out());
+    int *const s_rank = (int *)(smem + lay.rank());
+    float *const s_r = smem + lay.r();
+    float *const s_dec = smem + lay.dec();
 
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, NT = blockDim.x;
     const int lane = tid & (HX_WAVE - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    float *dbuf = s_wave + (size_t)wave * (lay.Dp + kT * kT + kT);
-    float *xbuf = dbuf + lay.Dp;
-    float *rbuf = xbuf + kT * kT;
 
-    for (int e = tid; e < Dp; e += GREEDY_THREADS) {
-        s_wait[e] = t->dec_wait[e]; s_c1[e] = t->dec_c1[e]; s_c2[e] = t->dec_c2[e]; s_kB[e] = t->dec_kB[e];
-        s_free[e] = t->dec_free[e]; s_orig[e] = t->dec_orig[e]; s_dtype[e] = t->dec_type[e];
-    }
-    for (int p = tid; p < lay.Pp; p += GREEDY_THREADS) {
-        const bool in = p < a.P;
-        s_pw[p] = in ? t->pre_wait[p] : INFINITY;
-        s_pinvF[p] = in ? t->pre_invF[p] : 0.0f;
-        s_pinvB[p] = in ? t->pre_invB[p] : 0.0f;
-        s_ptype[p] = in ? t->pre_type[p] : 0;
-        if (in) s_backlog[p] = a.p_backlog[p];
-    }
-    for (int d = tid; d < a.D; d += GREEDY_THREADS) {
-        s_used[d] = a.d_used[d]; s_batch[d] = a.d_batch[d]; s_qd[d] = a.d_qd[d]; s_cap[d] = a.d_cap[d];
-        s_pos[d] = t->dec_pos[d];
-        s_dinvF[d] = 1.0f / a.d_flops[d]; s_dinvB[d] = 1.0f / a.d_hbm[d];
-    }
-    if (tid < kT * kT) { s_invbw[tid] = t->link_invbw[tid]; s_lat[tid] = t->link_lat[tid]; }
-    if (tid <= kT) s_seg[tid] = t->seg[tid];
-    for (int c = tid; c < a.C; c += GREEDY_THREADS) {
-        s_flags[c] = ALIVE | DIRTY;
-        s_list[c] = c;
-        s_L[c] = a.L_in[c]; s_O[c] = a.L_out[c]; s_el[c] = a.elapsed[c];
+    // ---- what the queue and the pool say, read once
+    for (int c = tid; c < a.C; c += NT) {
+        s_rec[c] = make_int4(c, a.L_in[c], a.L_out[c], 0);
         const int nd = a.node[c], w = a.wf[c];
         const bool ok = nd >= 0 && nd < a.n_nodes && w >= 0 && w < a.n_wf;
         if (!ok) hx_raise(a.status, HX_ERR_INDEX);
-        s_tl[c] = ok ? a.tail[nd] : 0.0f;
-        s_hz[c] = ok ? fmaxf(a.horizon[w], 0.0f) : -1.0f;
+        s_in[c] = make_float4(a.elapsed[c], ok ? a.tail[nd] : 0.0f, ok ? fmaxf(a.horizon[w], 0.0f) : -1.0f, 0.0f);
+        s_rank[c] = -1;
+    }
+    for (int p = tid; p < a.P; p += NT) {
+        int t = a.p_type[p];
+        if (t < 0 || t >= a.T) { hx_raise(a.status, HX_ERR_INDEX); t = 0; }
+        const float invF = 1.0f / a.p_flops[p];
+        const int bl = a.p_backlog[p];
+        s.pF[p] = invF; s.pB[p] = 1.0f / a.p_hbm[p]; s.pty[p] = t; s.backlog[p] = bl; s.pw[p] = hx_prefill_wait(a.m, bl, invF);
+    }
+    for (int d = tid; d < a.D; d += NT) {
+        int t = a.d_type[d];
+        if (t < 0 || t >= a.T) { hx_raise(a.status, HX_ERR_INDEX); t = 0; }
+        s.used[d] = a.d_used[d]; s.batch[d] = a.d_batch[d]; s.qd[d] = a.d_qd[d]; s.cap[d] = a.d_cap[d];
+        s.dF[d] = 1.0f / a.d_flops[d]; s.dB[d] = 1.0f / a.d_hbm[d]; s.dty[d] = t;
+    }
+    for (int i = tid; i < kT * kT; i += NT) {
+        const bool in = i / kT < a.T && i % kT < a.T;
+        const int at = (i / kT) * a.T + i % kT;
+        const float2 l = make_float2(in ? 1.0f / a.bw[at] : 0.0f, in && a.lat ? a.lat[at] : 0.0f);
+        s.link[i] = l; s.link_to[(i % kT) * kT + i / kT] = l;
+    }
+    for (int e = tid; e < GREEDY_ENTRIES; e += NT) {                       // pads: no room for anything
+        s.w[e] = 0.0f; s.c1[e] = 0.0f; s.c2[e] = 0.0f; s.kB[e] = 0.0f; s.free[e] = -1; s.orig[e] = -1;
+        if ((e & 3) == 0) s.goff[e >> 2] = 0;
+    }
+    if (tid < kT) { s.cnt[tid] = 0; s.kcnt[tid] = 0; }
+    __syncthreads();
+    // the size of the decode classes; the first prefill instance of every kind
+    for (int d = tid; d < a.D; d += NT) atomicAdd(&s.cnt[s.dty[d]], 1);
+    for (int p = tid; p < a.P; p += NT) {
+        const int t = s.pty[p];
+        const float F = s.pF[p], B = s.pB[p];
+        int first = p;
+#pragma unroll 4
+        for (int q = p - 1; q >= 0; --q) first = s.pty[q] == t && s.pF[q] == F && s.pB[q] == B ? q : first;
+        s.kfirst[p] = first;
+        if (first == p) atomicAdd(&s.kcnt[t], 1);
     }
     __syncthreads();
-
-    int seg[kT + 1];
-#pragma unroll
-    for (int k = 0; k <= kT; ++k) seg[k] = __builtin_amdgcn_readfirstlane(s_seg[k]);
-    const HxPoolLds pool{s_wait, s_c1, s_c2, s_kB, s_free, s_orig, s_dtype, s_pw, s_pinvF, s_pinvB, s_ptype,
-                         s_invbw, s_lat, Dp, a.P, lay.Pp};
-
-    int n_dirty = a.C;                                 // every call at first (uniform; s_pick[4] carries it from step to step)
-    for (int k = 0; k < a.C; ++k) {
-        // (1) score the calls whose pair may have changed, on the simulated state: the list deals them to the
-        // wavefronts evenly (by call index, a wavefront could find all of its calls dirty and its neighbour none)
-        for (int i = wave; i < n_dirty; i += GREEDY_WAVES) {
-            const int c = s_list[i];
-            if (s_flags[c] != (ALIVE | DIRTY)) continue;           // wave-uniform: c depends on the wave only
-            // large pools: class by class (KP = 0); small ones: pair by pair, whose inner loop costs less than the
-            // class search's reductions up to about 64 x 64 pairs
-            HxBest b;
-            if constexpr (KP == 0) b = hx_search_call_by_class(a.m, pool, dbuf, xbuf, rbuf, s_L[c], s_O[c], lane);
-            else b = hx_search_call<KP>(a.m, pool, seg, dbuf, xbuf, s_L[c], s_O[c], lane);
-            if (lane == 0) {
-                s_bp[c] = b.p; s_bd[c] = b.d; s_bc[c] = b.cost;
-                hx_store_bits(s_ratio, c, hx_ratio_bits(s_el[c], b.cost, s_tl[c], s_hz[c], s_hz[c] >= 0.0f));       // Eq. (2)
-                s_flags[c] = ALIVE;
-            }
-        }
-        __syncthreads();
-        // (2) the most urgent remaining call: largest ratio, lowest index among equals
-        float bv = -INFINITY;
-        int bi = 0x7fffffff;
-        for (int c = tid; c < a.C; c += GREEDY_THREADS) {
-            if (s_flags[c] & ALIVE) {
-                const float r = hx_rank_key(s_ratio[c]);
-                if (bi == 0x7fffffff || r > bv) { bv = r; bi = c; }
-            }
-        }
-        hx_wave_argmax(bv, bi);
-        if (lane == 0) { s_redv[wave] = bv; s_redi[wave] = bi; }
-        __syncthreads();
-        // (3) the first two wavefronts take the best of the wavefronts' candidates (one per lane, the same rule); the
-        // first lane of one records the pick and adds it to the prefill side of the simulated state, the first lane
-        // of the other to the decode side (two chains of dependent LDS reads side by side)
-        if (wave < 2) {
-            bv = lane < GREEDY_WAVES ? s_redv[lane] : -INFINITY;
-            bi = lane < GREEDY_WAVES ? s_redi[lane] : 0x7fffffff;
-            hx_wave_argmax(bv, bi);
-        }
-        if (tid == 0) {
-            const int c = bi, p = s_bp[c], d = s_bd[c];
-            a.best_p[c] = p; a.best_d[c] = d; a.best_cost[c] = s_bc[c]; hx_store_bits(a.ratio, c, __float_as_uint(s_ratio[c])); a.rank[c] = k;
-            s_flags[c] = 0;
-            s_pick[0] = c; s_pick[1] = p; s_pick[2] = d;
-            s_pick[4] = 0;                                  // the next step's list starts empty
-            if (p >= 0) {
-                const int L = s_L[c];
-                long long bl = (long long)s_backlog[p] + L;
-                if (L < 0 || s_O[c] < 0) bl = s_backlog[p];            // raised by the other lane
-                if (bl > 2147483647LL) { hx_raise(a.status, HX_ERR_OVERFLOW); bl = 2147483647LL; }
-                s_backlog[p] = (int)bl;
-                // the derived table entry of the prefill instance, by the function the per-round prepare uses
-                s_pw[p] = hx_prefill_wait(a.m, s_backlog[p], s_pinvF[p]);
-            }
-        }
-        if (tid == HX_WAVE) {
-            const int c = bi, p = s_bp[c], d = s_bd[c];
-            s_pick[3] = 0;
-            if (p >= 0) {
-                const int L = s_L[c], O = s_O[c];
-                long long qd = (long long)s_qd[d] + O, us = (long long)s_used[d] + L + O;
-                if (L < 0 || O < 0) { hx_raise(a.status, HX_ERR_INDEX); qd = s_qd[d]; us = s_used[d]; }
-                if (qd > 2147483647LL || us > 2147483647LL) {
-                    hx_raise(a.status, HX_ERR_OVERFLOW);
-                    qd = min(qd, 2147483647LL); us = min(us, 2147483647LL);
-                }
-                s_qd[d] = (int)qd; s_used[d] = (int)us;
-                // us >= 0 and tokens_per_seq are below 2^31, their sum fits 32 unsigned bits: no 64-bit division
-                const long long nb = us >= 0 ? (long long)(((unsigned)us + (unsigned)a.tokens_per_seq - 1u) / (unsigned)a.tokens_per_seq)
-                                             : (us + a.tokens_per_seq - 1) / a.tokens_per_seq;
-                s_batch[d] = (int)(nb > a.max_batch ? a.max_batch : nb);
-                // the derived table entry of the decode instance, by the function the per-round prepare uses
-                const HxDecF x = hx_decode_terms(a.m, s_used[d], s_batch[d], s_qd[d], s_dinvF[d], s_dinvB[d]);
-                const int e = s_pos[d];
-                const long long fr = (long long)s_cap[d] - us;
-                const int nfree = fr < -1 ? -1 : (int)fr;
-                // A commit normally only adds load.  It lowers a term when the snapshot's batch stood above what
-                // the batch rule gives for the new occupancy (the caller's batch is only required to be >= 0):
-                // then pairs on d get cheaper and any call may prefer d now.
-                s_pick[3] = (x.wait < s_wait[e] || x.c1 < s_c1[e] || x.c2 < s_c2[e] || nfree > s_free[e]) ? 1 : 0;
-                s_wait[e] = x.wait; s_c1[e] = x.c1; s_c2[e] = x.c2; s_kB[e] = x.kB;
-                s_free[e] = nfree;
-            }
-        }
-        __syncthreads();
-        // (4) which calls are scored again
-        const int pp = s_pick[1], pd = s_pick[2];
-        if (pp >= 0 && s_pick[3]) {
-            // a term of the decode instance fell: nothing can be kept
-            for (int c = tid; c < a.C; c += GREEDY_THREADS)
-                if (s_flags[c] & ALIVE) { s_flags[c] = ALIVE | DIRTY; s_list[atomicAdd(&s_pick[4], 1)] = c; }
-        } else if (pp >= 0) {
-            // load was only added: every pair costs what it did or more, so only calls whose pair touches one of
-            // the two instances can lose their minimum -- and not even those if the cost of their pair came out
-            // the same (e.g. the decode instance's availability still dominates a longer prefill queue)
-            for (int c = tid; c < a.C; c += GREEDY_THREADS)
-                if ((s_flags[c] & ALIVE) && (s_bp[c] == pp || s_bd[c] == pd) &&
-                    hx_pair_cost(a.m, pool, s_L[c], s_O[c], s_bp[c], s_pos[s_bd[c]]) != s_bc[c]) {
-                    s_flags[c] = ALIVE | DIRTY;
-                    s_list[atomicAdd(&s_pick[4], 1)] = c;
-                }
-        }
-        __syncthreads();
-        n_dirty = s_pick[4];
+    if (tid <= kT) {
+        int e = 0, q = 0;
+        for (int t = 0; t < tid; ++t) { e += (s.cnt[t] + 3) & ~3; q += s.kcnt[t]; }
+        s.seg[tid] = e; s.kseg[tid] = q;
     }
-    // the simulated state the plan leaves
-    for (int p = tid; p < a.P; p += GREEDY_THREADS) if (a.backlog_out) a.backlog_out[p] = s_backlog[p];
-    for (int d = tid; d < a.D; d += GREEDY_THREADS) {
-        if (a.used_out) a.used_out[d] = s_used[d];
-        if (a.batch_out) a.batch_out[d] = s_batch[d];
-        if (a.qd_out) a.qd_out[d] = s_qd[d];
+    __syncthreads();
+    for (int d = tid; d < a.D; d += NT) {
+        const int t = s.dty[d];
+        int e = s.seg[t];
+#pragma unroll 4
+        for (int q = 0; q < d; ++q) e += s.dty[q] == t;
+        const HxDecF x = hx_decode_terms(a.m, s.used[d], s.batch[d], s.qd[d], s.dF[d], s.dB[d]);
+        const long long fr = (long long)s.cap[d] - (long long)s.used[d];
+        s.w[e] = x.wait; s.c1[e] = x.c1; s.c2[e] = x.c2; s.kB[e] = x.kB;
+        s.free[e] = fr < -1 ? -1 : (fr > 2147483647LL ? 2147483647 : (int)fr);
+        s.orig[e] = d; s.pos[d] = e;
+        s.goff[e >> 2] = t * lay.C4;
+    }
+    for (int p = tid; p < a.P; p += NT) {
+        const int t = s.pty[p], first = s.kfirst[p];
+        int q = s.kseg[t];
+#pragma unroll 4
+        for (int o = 0; o < first; ++o) q += s.pty[o] == t && s.kfirst[o] == o;
+        s.kind[p] = q;
+        if (first == p) {
+            float w = s.pw[p];
+#pragma unroll 4
+            for (int o = p + 1; o < a.P; ++o) w = s.kfirst[o] == p ? fminf(w, s.pw[o]) : w;
+            s.kw[q] = w; s.kF[q] = s.pF[p]; s.kB2[q] = s.pB[p];
+        }
+    }
+    __syncthreads();
+    const int n_groups = __builtin_amdgcn_readfirstlane(s.seg[kT]) >> 2;
+    // lanes per call at most: some four groups of entries for each (more lanes only add reductions)
+    int g_max = 1;
+    while (g_max < GREEDY_MAX_G && 4 * g_max < n_groups) g_max <<= 1;
+
+    // Every wavefront keeps the simulated pool in its registers, an instance of either side per lane (K of each), and makes
+    // every pick for itself: the same arithmetic everywhere, nothing to hand on, and one barrier a pick.
+    int d_ty[K], d_off[K], d_pos[K], d_cap[K], d_used[K], d_qd[K], d_batch[K], d_free[K];
+    float d_F[K], d_B[K], d_w[K], d_c1[K], d_c2[K], d_kB[K];
+    int p_ty[K], p_kind[K], p_bl[K];
+    float p_w[K], p_F[K], p_B[K], p_kw[K];                // p_kw: the shortest wait of the instance's kind
+#pragma unroll
+    for (int j = 0; j < K; ++j) {
+        const bool hd = j * HX_WAVE + lane < a.D, hp = j * HX_WAVE + lane < a.P;
+        const int d = hd ? j * HX_WAVE + lane : 0, p = hp ? j * HX_WAVE + lane : 0;
+        const int e = s.pos[d];
+        d_ty[j] = s.dty[d]; d_off[j] = s.dty[d] * lay.C4; d_pos[j] = e; d_cap[j] = s.cap[d]; d_used[j] = s.used[d]; d_qd[j] = s.qd[d]; d_batch[j] = s.batch[d];
+        d_F[j] = s.dF[d]; d_B[j] = s.dB[d]; d_w[j] = s.w[e]; d_c1[j] = s.c1[e]; d_c2[j] = s.c2[e]; d_kB[j] = s.kB[e];
+        d_free[j] = hd ? s.free[e] : -1;
+        p_ty[j] = s.pty[p]; p_kind[j] = hp ? s.kind[p] : -1; p_bl[j] = s.backlog[p];
+        p_w[j] = hp ? s.pw[p] : INFINITY; p_F[j] = s.pF[p]; p_B[j] = s.pB[p]; p_kw[j] = s.kw[s.kind[p]];
+    }
+
+    unsigned several = 0;                                 // classes with more than one kind
+    for (int i = 0; i < kT; ++i) several |= s.kseg[i + 1] - s.kseg[i] > 1 ? 1u << i : 0u;
+    several = __builtin_amdgcn_readfirstlane(several);
+    bool over = false, bad = false;                       // reported once, at the end
+
+    int n = a.C, lanes = NT;
+    for (int k = 0; k < a.C;) {
+        // ---- a stage: the remaining calls in increasing order, G lanes each
+        const int n_before = n;
+        n = a.C - k;
+        if (k > 0) {
+            const int4 mine = s_rec[tid < n_before ? tid : 0];
+            const bool stays = tid < n_before && s_rank[mine.x] < 0;
+            const unsigned long long b = __builtin_amdgcn_ballot_w64(stays);
+            if (lane == 0) s.wcnt[wave] = __popcll(b);
+            __syncthreads();
+            int at = __popcll(b & ((1ull << lane) - 1ull));
+            for (int v = 0; v < wave; ++v) at += s.wcnt[v];
+            if (stays) s_rec[at] = mine;
+            __syncthreads();
+        }
+        int lg = 0;
+        while ((2 << lg) <= g_max && (n << (lg + 1)) <= lanes) ++lg;
+        const int G = 1 << lg, n_lanes = n << lg, n_waves = (n_lanes + HX_WAVE - 1) / HX_WAVE;
+        lanes = n_waves * HX_WAVE;                            // a wavefront that sits a stage out loses track of the pool
+        const int last = n_waves > 1 ? a.C - n / 2 : a.C;     // the stage's picks end here
+        const int per_lane = (n_groups + G - 1) >> lg;
+        const bool keep = 4 * per_lane * n_waves * HX_WAVE <= dec_words;      // the decode times of the remaining calls fit
+        const int dec_row = 4 * n_waves * HX_WAVE;
+        const int slot = tid >> lg, sub = tid & (G - 1);
+        const bool has = slot < n;
+        bool alive = has;
+        const int at = has ? slot : 0;                        // lanes without a call go along with the first one's and write nothing
+        const int4 mine = s_rec[at];
+        const int L = mine.y, O = mine.z;
+        const float4 in = s_in[mine.x];                       // elapsed, tail, horizon
+        const HxCallF cf = hx_call_terms(a.m, L, O);
+        float *const my_r = s_r + at;                         // [k * C4]
+        float *const my_dec = s_dec + 4 * tid;                // [j * dec_row] four decode times of the lane's j-th group
+        const int *const my_goff = s.goff + sub;              // [j << lg] of that group
+        const float4 *const my_w = (const float4 *)s.w + sub;
+        float m[TT];
+        float best = INFINITY;
+        unsigned ratio_bits = 0;
+
+        // r[k] of the lane's call, its lanes a class each
+        auto arrivals = [&]() {
+            auto rows = [&](auto n_, int k0) {                // N classes of the lane together (more lanes than classes: some twice)
+                constexpr int N = decltype(n_)::value;
+                float r[N];
+#pragma unroll
+                for (int u = 0; u < N; ++u) {
+                    const float2 *l = s.link_to + ((k0 + (u << lg) + sub) & (kT - 1)) * kT;
+                    r[u] = INFINITY;
+#pragma unroll
+                    for (int i = 0; i < TT; i += 2) {         // a class without instances, or beyond T: +inf
+                        const float4 x = *(const float4 *)(l + i);
+                        r[u] = fminf(r[u], fminf(m[i] + hx_transfer(cf, x.x, x.y), m[i + 1] + hx_transfer(cf, x.z, x.w)));
+                    }
+                }
+                if (alive) {                                  // (a picked call's may be being read)
+#pragma unroll
+                    for (int u = 0; u < N; ++u) my_r[((k0 + (u << lg) + sub) & (kT - 1)) * lay.C4] = r[u];
+                }
+            };
+            if (a.T <= G) rows(std::integral_constant<int, 1>{}, 0);
+            else if (a.T <= 2 * G) rows(std::integral_constant<int, 2>{}, 0);
+            else for (int k0 = 0; k0 < a.T; k0 += 4 * G) rows(std::integral_constant<int, 4>{}, k0);
+            hx_wave_sync();
+        };
+        auto decode_time = [&](int fr, float c1, float c2, float kB) {
+            return hx_fits(L, O, fr) ? hx_decode_time(cf, c1, c2, kB) : INFINITY;
+        };
+        auto decode_times = [&](int g) {
+            const int4 fr = ((const int4 *)s.free)[g];
+            const float4 c1 = ((const float4 *)s.c1)[g], c2 = ((const float4 *)s.c2)[g], kB = ((const float4 *)s.kB)[g];
+            return make_float4(decode_time(fr.x, c1.x, c2.x, kB.x), decode_time(fr.y, c1.y, c2.y, kB.y),
+                               decode_time(fr.z, c1.z, c2.z, kB.z), decode_time(fr.w, c1.w, c2.w, kB.w));
+        };
+        // The lowest cost of the lane's call and its ratio, Eq. (2).  N of the lane's groups at a time, read together (past
+        // the last the lane's first once more).
+        auto search_by = [&](auto n_) {
+            constexpr int N = decltype(n_)::value;
+            float v = INFINITY;
+            for (int row = 0; row < per_lane; row += N) {
+                float r[N];
+                float4 w[N], t[N];
+                int off[N];
+#pragma unroll
+                for (int u = 0; u < N; ++u) {
+                    const int at_row = row + u < per_lane ? row + u : 0;
+                    off[u] = my_goff[at_row << lg];
+                    w[u] = my_w[at_row << lg];
+                    t[u] = N > 2 ? *(const float4 *)(my_dec + at_row * dec_row) : decode_times(sub + (at_row << lg));
+                }
+#pragma unroll
+                for (int u = 0; u < N; ++u) r[u] = my_r[off[u]];
+#pragma unroll
+                for (int u = 0; u < N; ++u)
+                    v = fminf(v, fminf(fminf(hx_candidate(r[u], w[u].x, t[u].x), hx_candidate(r[u], w[u].y, t[u].y)),
+                                       fminf(hx_candidate(r[u], w[u].z, t[u].z), hx_candidate(r[u], w[u].w, t[u].w))));
+            }
+            best = hx_lanes_min(v, G);
+            ratio_bits = hx_ratio_bits(in.x, best, in.y, in.z, in.z >= 0.0f);
+        };
+        auto search = [&]() {
+            if (!keep) search_by(std::integral_constant<int, 2>{});
+            else if (per_lane <= 4) search_by(std::integral_constant<int, 4>{});
+            else search_by(std::integral_constant<int, (THREADS > GREEDY_THREADS ? 4 : 8)>{});      // (as the registers allow)
+        };
+
+        if (wave < n_waves) {
+#pragma unroll
+            for (int i = 0; i < TT; ++i) {
+                m[i] = INFINITY;
+                if (i < a.T)
+                    for (int q = s.kseg[i]; q < s.kseg[i + 1]; ++q)
+                        m[i] = fminf(m[i], hx_prefill_done(cf, s.kw[q], s.kF[q], s.kB2[q]));
+            }
+            if (keep) {
+                float *q = my_dec;
+                for (int j = 0; j < per_lane; ++j, q += dec_row) *(float4 *)q = decode_times(sub + (j << lg));
+            }
+            arrivals();
+            search();
+        }
+
+        if (wave >= n_waves) {                                // no calls here any more
+            if (n_waves > 1)
+                for (int i = k; i < last; ++i) __syncthreads();
+            k = last;
+        }
+        for (; k < last; ++k) {
+            // (1) the most urgent remaining call: largest ratio, lowest index among equals (slots, and with them lanes and
+            // wavefronts, are in index order)
+            const float key = alive ? hx_rank_key(__uint_as_float(ratio_bits)) : -INFINITY;
+            const float top = hx_wave_max(key);
+            // (no lane with a call: lane 0 stands in; its -inf and "no slot" lose to every wavefront that has one)
+            const unsigned long long at_top = __builtin_amdgcn_ballot_w64(alive && key == top);
+            int from = at_top ? __builtin_ctzll(at_top) : 0;
+            int pick = at_top ? (wave * HX_WAVE + from) >> lg : 0x7fffffff;
+            int pL = __builtin_amdgcn_readlane(L, from), pO = __builtin_amdgcn_readlane(O, from);
+            float cost = hx_lane_value(best, from);
+            int p_ratio = __builtin_amdgcn_readlane((int)ratio_bits, from), call = __builtin_amdgcn_readlane(mine.x, from);
+            if (n_waves > 1) {
+                if (lane == 0) {
+                    s.red[k & 1][0][wave] = make_int4(__float_as_int(top), pick, pL, pO);
+                    s.red[k & 1][1][wave] = make_int4(__float_as_int(cost), p_ratio, call, 0);
+                }
+                __syncthreads();
+                const int v = min(lane, n_waves - 1);         // (n_waves is at most a row of lanes; lanes beyond repeat the last)
+                const int4 q = s.red[k & 1][0][v], q2 = s.red[k & 1][1][v];
+                const float all = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(-hx_lanes_min(-__int_as_float(q.x), n_waves))));
+                from = __builtin_ctzll(__builtin_amdgcn_ballot_w64(q.y != 0x7fffffff && __int_as_float(q.x) == all));
+                pick = __builtin_amdgcn_readlane(q.y, from);
+                pL = __builtin_amdgcn_readlane(q.z, from); pO = __builtin_amdgcn_readlane(q.w, from);
+                cost = __int_as_float(__builtin_amdgcn_readlane(q2.x, from)); p_ratio = __builtin_amdgcn_readlane(q2.y, from);
+                call = __builtin_amdgcn_readlane(q2.z, from);
+            }
+            // (2) its pair: for every decode instance that attains the minimum (nearly always one) the lowest prefill
+            // instance that does so with it; the lowest (p, d) of these
+            int p = -1, d = -1;
+            if (cost < INFINITY) {
+                const HxCallF pc = hx_call_terms(a.m, pL, pO);
+                float done[K], dt[K];
+                unsigned long long todo[K];
+#pragma unroll
+                for (int j = 0; j < K; ++j) {
+                    const float r = s_r[d_off[j] + pick];
+                    done[j] = hx_prefill_done(pc, p_w[j], p_F[j], p_B[j]);
+                    dt[j] = hx_fits(pL, pO, d_free[j]) ? hx_decode_time(pc, d_c1[j], d_c2[j], d_kB[j]) : INFINITY;
+                    todo[j] = __builtin_amdgcn_ballot_w64(hx_candidate(r, d_w[j], dt[j]) == cost);
+                }
+                int best_p = 0x7fffffff;
+#pragma unroll
+                for (int j = 0; j < K; ++j) {
+                    while (todo[j]) {
+                        const int ld = __builtin_ctzll(todo[j]);
+                        todo[j] &= todo[j] - 1;
+                        const float q_w = hx_lane_value(d_w[j], ld), q_dt = hx_lane_value(dt[j], ld);
+                        const int q_t = __builtin_amdgcn_readlane(d_ty[j], ld);
+                        int low = 0x7fffffff;
+#pragma unroll
+                        for (int i = K - 1; i >= 0; --i) {
+                            const float2 l = s.link[p_ty[i] * kT + q_t];
+                            const unsigned long long b = __builtin_amdgcn_ballot_w64(hx_candidate(done[i] + hx_transfer(pc, l.x, l.y), q_w, q_dt) == cost);
+                            low = b ? i * HX_WAVE + __builtin_ctzll(b) : low;
+                        }
+                        if (low < best_p) { best_p = low; d = j * HX_WAVE + ld; }      // decode instances come in order
+                    }
+                }
+                p = best_p != 0x7fffffff ? best_p : -1;
+            }
+            if (tid == 0) {
+                s_rank[call] = k; s_out[call] = make_int4(p, p < 0 ? -1 : d, __float_as_int(cost), p_ratio);
+            }
+            alive = alive && slot != pick;
+            if (p < 0) continue;                              // nothing changes
+            // (3) what it adds to the state: every lane works it out for its own instances, the pair's keep it
+            const bool valid = pL >= 0 && pO >= 0;
+            const int add_L = valid ? pL : 0, add_O = valid ? pO : 0;
+            bad = bad || !valid;
+            int e = 0, ic = 0, kind = 0, n_free = 0;
+            float was = 0.0f, kF = 0.0f, kB = 0.0f, n_c1 = 0.0f, n_c2 = 0.0f, n_kB = 0.0f;
+#pragma unroll
+            for (int j = 0; j < K; ++j) {
+                const int n_bl = __builtin_elementwise_add_sat(p_bl[j], add_L);
+                const float n_w = hx_prefill_wait(a.m, n_bl, p_F[j]);
+                if (K == 1 || (p >> 6) == j) {
+                    const int lp = p & (HX_WAVE - 1);
+                    ic = __builtin_amdgcn_readlane(p_ty[j], lp); kind = __builtin_amdgcn_readlane(p_kind[j], lp);
+                    was = hx_lane_value(p_kw[j], lp); kF = hx_lane_value(p_F[j], lp); kB = hx_lane_value(p_B[j], lp);
+                    if (lane == lp) {
+                        over = over || n_bl - p_bl[j] != add_L;
+                        p_bl[j] = n_bl; p_w[j] = n_w;
+                    }
+                }
+            }
+            float now = INFINITY;
+#pragma unroll
+            for (int j = 0; j < K; ++j) now = p_kind[j] == kind ? fminf(now, p_w[j]) : now;
+            now = hx_wave_min(now);
+#pragma unroll
+            for (int j = 0; j < K; ++j) p_kw[j] = p_kind[j] == kind ? now : p_kw[j];
+            if (lane == 0) s.kw[kind] = now;
+#pragma unroll
+            for (int j = 0; j < K; ++j) {
+                if (K == 1 || (d >> 6) == j) {
+                    const int n_qd = __builtin_elementwise_add_sat(d_qd[j], add_O);
+                    const int us = __builtin_elementwise_add_sat(d_used[j], add_L), n_us = __builtin_elementwise_add_sat(us, add_O);
+                    // ceil(us / tokens_per_seq), rounded towards 0: both numbers are below 2^31, so 32 unsigned bits do
+                    const int num = n_us < 0 ? n_us + (a.tokens_per_seq - 1) : 0;
+                    const unsigned top = n_us < 0 ? (unsigned)(num < 0 ? -num : num) : (unsigned)n_us + (unsigned)a.tokens_per_seq - 1u;
+                    const unsigned quot = top / (unsigned)a.tokens_per_seq;
+                    const int n_batch = num < 0 ? -(int)quot : (quot > (unsigned)a.max_batch ? a.max_batch : (int)quot);
+                    // the derived table entries, by the function that made them
+                    const HxDecF x = hx_decode_terms(a.m, n_us, n_batch, n_qd, d_F[j], d_B[j]);
+                    const int n_fr = max(__builtin_elementwise_sub_sat(d_cap[j], n_us), -1);
+                    const int ld = d & (HX_WAVE - 1);
+                    if (lane == ld) {
+                        over = over || n_qd - d_qd[j] != add_O || us - d_used[j] != add_L || n_us - us != add_O;
+                        d_qd[j] = n_qd; d_used[j] = n_us; d_batch[j] = n_batch;
+                        d_w[j] = x.wait; d_c1[j] = x.c1; d_c2[j] = x.c2; d_kB[j] = x.kB; d_free[j] = n_fr;
+                        s.w[d_pos[j]] = x.wait; s.c1[d_pos[j]] = x.c1; s.c2[d_pos[j]] = x.c2; s.kB[d_pos[j]] = x.kB;
+                        s.free[d_pos[j]] = d_free[j];
+                    }
+                    e = __builtin_amdgcn_readlane(d_pos[j], ld); n_free = __builtin_amdgcn_readlane(d_free[j], ld);
+                    n_c1 = hx_lane_value(d_c1[j], ld); n_c2 = hx_lane_value(d_c2[j], ld); n_kB = hx_lane_value(d_kB[j], ld);
+                }
+            }
+            hx_wave_sync();
+            // (4) the calls that remain, against the new state
+            if (__builtin_amdgcn_ballot_w64(alive) == 0) continue;
+            if (keep && sub == ((e >> 2) & (G - 1))) my_dec[(e >> (2 + lg)) * dec_row + (e & 3)] = decode_time(n_free, n_c1, n_c2, n_kB);
+            bool moved = now != was;
+            if (moved) {
+                // the kind's shortest queue has grown (or, with a strange model, shrunk): m of its class grows with it, or
+                // falls back to the class's next kind -- if this kind held the minimum
+                float v = hx_prefill_done(cf, now, kF, kB);
+                if ((several >> ic) & 1) {
+                    const float before = hx_prefill_done(cf, was, kF, kB);
+                    float mc = m[0];
+#pragma unroll
+                    for (int i = 1; i < TT; ++i) mc = i == ic ? m[i] : mc;
+                    moved = __builtin_amdgcn_ballot_w64(before == mc) != 0 || now < was;
+                    if (moved) {
+                        const int q_end = s.kseg[ic + 1];
+                        for (int q = s.kseg[ic] + sub; q < q_end; q += G) v = fminf(v, hx_prefill_done(cf, s.kw[q], s.kF[q], s.kB2[q]));
+                        v = hx_lanes_min(v, G);
+                    }
+                }
+                if (moved) {
+#pragma unroll
+                    for (int i = 0; i < TT; ++i) m[i] = i == ic ? v : m[i];
+                }
+            }
+            if (moved) arrivals();
+            search();
+        }
+        __syncthreads();
+    }
+    // ---- the plan, and the simulated state it leaves
+    for (int c = tid; c < a.C; c += NT) {
+        const int4 q = s_out[c];
+        a.best_p[c] = q.x; a.best_d[c] = q.y; a.best_cost[c] = __int_as_float(q.z); a.rank[c] = s_rank[c];
+        hx_store_bits(a.ratio, c, (unsigned)q.w);
+    }
+    if (wave == 0) {
+        if (bad) hx_raise(a.status, HX_ERR_INDEX);
+        if (over) hx_raise(a.status, HX_ERR_OVERFLOW);
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+            const int i = j * HX_WAVE + lane;
+            if (i < a.P && a.backlog_out) a.backlog_out[i] = p_bl[j];
+            if (i < a.D && a.used_out) a.used_out[i] = d_used[j];
+            if (i < a.D && a.batch_out) a.batch_out[i] = d_batch[j];
+            if (i < a.D && a.qd_out) a.qd_out[i] = d_qd[j];
+        }
     }
 }
 
@@ -461,20 +734,19 @@ __global__ __launch_bounds__(256) void hx_copy_i32_kernel(const int32_t *src, in
 }  // namespace
 
 // the planner kernel may use all of a CU's LDS; said once per process
+constexpr int GREEDY_LDS = 160 * 1024;
+static_assert(sizeof(GreedyPool) + 4 * (13 + kT) * (size_t)HX_GREEDY_MAX_CALLS <= GREEDY_LDS, "the longest queue fits");
 int hx_plan_init()
 {
-    const int lds = 160 * 1024;
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(hx_plan_greedy_kernel<0>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    if (e == hipSuccess)
-        e = hipFuncSetAttribute(reinterpret_cast<const void *>(hx_plan_greedy_kernel<1>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    if (e == hipSuccess)
-        e = hipFuncSetAttribute(reinterpret_cast<const void *>(hx_plan_greedy_kernel<2>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    if (e == hipSuccess)
-        e = hipFuncSetAttribute(reinterpret_cast<const void *>(hx_plan_greedy_kernel<4>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    const int most = GREEDY_LDS - (int)sizeof(GreedyPool);
+    hipError_t e = hipSuccess;
+    auto allow = [&](const void *kernel) {
+        if (e == hipSuccess) e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, most);
+    };
+    allow(reinterpret_cast<const void *>(hx_plan_greedy_kernel<1, 4, GREEDY_THREADS>));
+    allow(reinterpret_cast<const void *>(hx_plan_greedy_kernel<1, kT, GREEDY_THREADS>));
+    allow(reinterpret_cast<const void *>(hx_plan_greedy_kernel<GREEDY_K, kT, GREEDY_THREADS>));
+    allow(reinterpret_cast<const void *>(hx_plan_greedy_kernel<GREEDY_K, kT, GREEDY_MAX_THREADS>));
     return e == hipSuccess ? HX_OK : HX_ERR_DEVICE;
 }
 
@@ -550,8 +822,10 @@ extern "C" int hx_plan_greedy(hx_ctx *ctx, const hx_model *model, const hx_calls
     a.C = C; a.P = P; a.D = D;
     a.L_in = calls->L_in; a.L_out = calls->L_out; a.node = calls->node; a.wf = calls->wf; a.elapsed = calls->elapsed;
     a.tail = tail; a.horizon = horizon; a.n_nodes = n_nodes; a.n_wf = n_wf;
-    a.prep = ctx->d_prep; a.d_flops = dec->flops; a.d_hbm = dec->hbm_bw;
-    a.p_backlog = pre->backlog_tok; a.d_used = dec->used_tok; a.d_cap = dec->cap_tok; a.d_batch = dec->batch; a.d_qd = dec->qd_tok;
+    a.T = links->n_types; a.bw = links->bw; a.lat = links->latency;
+    a.p_flops = pre->flops; a.p_hbm = pre->hbm_bw; a.p_backlog = pre->backlog_tok; a.p_type = pre->type;
+    a.d_flops = dec->flops; a.d_hbm = dec->hbm_bw; a.d_used = dec->used_tok; a.d_cap = dec->cap_tok;
+    a.d_batch = dec->batch; a.d_qd = dec->qd_tok; a.d_type = dec->type;
     a.tokens_per_seq = tokens_per_seq; a.max_batch = max_batch;
     a.best_p = best_p; a.best_d = best_d; a.rank = rank; a.best_cost = best_cost; a.ratio = ratio;
     a.backlog_out = backlog_tok_out; a.used_out = used_tok_out; a.batch_out = batch_out; a.qd_out = qd_tok_out;
@@ -568,14 +842,26 @@ extern "C" int hx_plan_greedy(hx_ctx *ctx, const hx_model *model, const hx_calls
         if (D && qd_tok_out) hx_copy_i32_kernel<<<(D + 255) / 256, 256, 0, stream>>>(dec->qd_tok, qd_tok_out, D);
         return hx_check_launch(ctx, "hx_plan_no_pool_kernel");
     }
-    if (int rc = hx_prepare_pool(ctx, model, pre, dec, links, stream)) return rc;
-    const int dp_bound = (D + HX_DGROUP - 1) / HX_DGROUP * HX_DGROUP + (T - 1) * HX_DGROUP;
-    const GreedyLds lay(dp_bound, P, D, C);
-    const size_t lds = 4 * lay.words();
-    HX_REQUIRE(ctx, lds <= 160 * 1024, HX_ERR_SHAPE, "queue and pool need %zu B of LDS", lds);
-    if ((long long)P * D > 64 * 64) hx_plan_greedy_kernel<0><<<1, GREEDY_THREADS, lds, stream>>>(a, dp_bound);
-    else if (P <= 64) hx_plan_greedy_kernel<1><<<1, GREEDY_THREADS, lds, stream>>>(a, dp_bound);
-    else if (P <= 128) hx_plan_greedy_kernel<2><<<1, GREEDY_THREADS, lds, stream>>>(a, dp_bound);
-    else hx_plan_greedy_kernel<4><<<1, GREEDY_THREADS, lds, stream>>>(a, dp_bound);
+    if (int rc = hx_check_pool(ctx, model, pre, dec, links)) return rc;
+    // A lane per call where the pool is small (a wavefront that is alone has no barriers); otherwise a lane for every
+    // four groups of decode entries, as long as that leaves two wavefronts per SIMD (a lane for every two: 472 us
+    // instead of 465 for 256 calls on 64 + 64, and no difference for 64 on 8 + 8).
+    const int groups = (D + 3) / 4;
+    int threads = C;
+    while (threads < GREEDY_THREADS && threads < C * ((groups + 3) / 4)) threads *= 2;
+    threads = (threads + HX_WAVE - 1) / HX_WAVE * HX_WAVE;
+    if (threads < HX_WAVE) threads = HX_WAVE;
+    if (threads > GREEDY_THREADS && C <= GREEDY_THREADS) threads = GREEDY_THREADS;
+    const GreedyCalls lay(C);
+    // room for the decode times of every call, as far as the LDS goes (what does not fit is worked out at each pick)
+    const size_t room = GREEDY_LDS - sizeof(GreedyPool) - 4 * lay.dec();
+    size_t lds = (size_t)threads * 16 * (((size_t)groups + T) * C / threads + 2);
+    lds = 4 * lay.dec() + (lds < room ? lds : room);
+    const int dec_words = (int)(lds / 4) - lay.dec();
+    auto launch = [&](auto kernel) { kernel<<<1, threads, lds, stream>>>(a, dec_words); };
+    if (threads > GREEDY_THREADS) launch(hx_plan_greedy_kernel<GREEDY_K, kT, GREEDY_MAX_THREADS>);
+    else if (P > HX_WAVE || D > HX_WAVE) launch(hx_plan_greedy_kernel<GREEDY_K, kT, GREEDY_THREADS>);
+    else if (T > 4) launch(hx_plan_greedy_kernel<1, kT, GREEDY_THREADS>);
+    else launch(hx_plan_greedy_kernel<1, 4, GREEDY_THREADS>);
     return hx_check_launch(ctx, "hx_plan_greedy_kernel");
 }

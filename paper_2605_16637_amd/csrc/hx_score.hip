@@ -750,10 +750,8 @@ int check_ratio_inputs(hx_ctx *ctx, const hx_calls *calls, const float *tail, co
 
 }  // namespace
 
-// Validates the pool tables and enqueues the kernel that derives the per-round
-// tables (ctx->d_prep) from them.  Shared by every entry point that scores.
-int hx_prepare_pool(hx_ctx *ctx, const hx_model *model, const hx_prefill_tab *pre, const hx_decode_tab *dec,
-                    const hx_links *links, hipStream_t stream)
+// Validates the pool tables.
+int hx_check_pool(hx_ctx *ctx, const hx_model *model, const hx_prefill_tab *pre, const hx_decode_tab *dec, const hx_links *links)
 {
     HX_REQUIRE(ctx, model && pre && dec && links, HX_ERR_INVALID_ARG, "NULL table");
     const int P = pre->n, D = dec->n, T = links->n_types;
@@ -766,6 +764,15 @@ int hx_prepare_pool(hx_ctx *ctx, const hx_model *model, const hx_prefill_tab *pr
     HX_REQUIRE(ctx, D == 0 || (dec->flops && dec->hbm_bw && dec->used_tok && dec->cap_tok && dec->batch &&
                                dec->qd_tok && dec->type), HX_ERR_INVALID_ARG, "NULL member in decode table");
     HX_REQUIRE(ctx, links->bw, HX_ERR_INVALID_ARG, "links.bw is NULL");
+    return HX_OK;
+}
+
+// Validates the pool tables and enqueues the kernel that derives the per-round
+// tables (ctx->d_prep) from them.
+int hx_prepare_pool(hx_ctx *ctx, const hx_model *model, const hx_prefill_tab *pre, const hx_decode_tab *dec,
+                    const hx_links *links, hipStream_t stream)
+{
+    if (int rc = hx_check_pool(ctx, model, pre, dec, links)) return rc;
     const PrepArgs pa = make_prep_args(ctx, model, pre, dec, links);
     hx_prepare_kernel<<<1, 1024, 0, stream>>>(pa);
     return hx_check_launch(ctx, "hx_prepare_kernel");

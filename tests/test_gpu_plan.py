@@ -128,6 +128,26 @@ def test_greedy_plan_matches_oracle(ctx, C, P, D, T, seed):
         assert np.array_equal(got[5], want.backlog_tok) and np.array_equal(got[6], want.used_tok)
 
 
+# one call a lane up to the widest workgroup, the stages in which the remaining calls are dealt to the lanes anew, more than
+# 64 instances of one side, more than four classes, groups of four decode instances that are not full, and prefill
+# instances of one class with rates of their own (several entries of the search per class)
+@pytest.mark.parametrize("C,P,D,T,seed", [(1, 1, 1, 1, 1), (65, 3, 5, 5, 2), (257, 9, 66, 3, 3), (90, 65, 7, 8, 4), (513, 5, 6, 2, 5)])
+def test_greedy_plan_with_rates_of_every_instance(ctx, C, P, D, T, seed):
+    rng = np.random.default_rng(170 + seed)
+    types, pre, dec, links = random_pool(rng, P, D, T)
+    for side, n in ((pre, P), (dec, D)):
+        for k in ("flops", "hbm_bw"):
+            # a third of the instances keep the rates of their class
+            side[k] = (side[k] * np.where(rng.random(n) < 0.33, 1.0, rng.uniform(0.7, 1.4, n))).astype(np.float32)
+    dec["cap_tok"] = (dec["used_tok"] + rng.integers(2000, 90000, D)).astype(np.int32)
+    L, O = synth.gen_lengths(rng, C)
+    elapsed = rng.uniform(0, 20, C).astype(np.float32)
+    node = rng.permutation(C).astype(np.int32); wf = rng.integers(0, 3, C).astype(np.int32)
+    tail = rng.uniform(0, 5, C).astype(np.float32); hor = rng.uniform(5, 50, 3).astype(np.float32)
+    got = run_greedy(ctx, synth.MODEL, L, O, elapsed, node, wf, tail, hor, pre, dec, links)
+    check_plan_stepwise(synth.MODEL, L, O, elapsed, node, wf, tail, hor, pre, dec, links, got)
+
+
 def test_greedy_hand_worked_conflict_on_gpu(ctx):
     from helpers import ROUND_MODEL, read_kv
     G = read_kv("round_numbers.txt")
