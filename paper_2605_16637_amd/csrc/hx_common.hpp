@@ -58,6 +58,7 @@ struct hx_ctx {
     int32_t *h_status = nullptr;       // pinned copy
     HxPrepTables *d_prep = nullptr;
     int32_t *d_flags = nullptr;        // sweep "changed" flags, [HX_MAX_SWEEP_FLAGS]
+    int32_t *d_sync = nullptr;         // sweeps over the whole graph: what its workgroups share; 4 words, 0 between launches
     unsigned long long *d_acc = nullptr;   // commit accumulators, [3 * HX_MAX_INSTANCES]
     int32_t *d_ticket = nullptr;           // commit: workgroups that have delivered their sums; 0 between launches
     int32_t *d_dpart = nullptr;            // decode-stage free list and per-group partial results, dpart_cap words

@@ -339,6 +339,7 @@ extern "C" int hx_ctx_create(hx_ctx **out, int device)
     if (e == hipSuccess) { what = "hipHostMalloc(status)"; e = hipHostMalloc((void **)&ctx->h_status, sizeof(int32_t), hipHostMallocDefault); }
     if (e == hipSuccess) { what = "hipMalloc(tables)"; e = hipMalloc((void **)&ctx->d_prep, sizeof(HxPrepTables)); }
     if (e == hipSuccess) { what = "hipMalloc(flags)"; e = hipMalloc((void **)&ctx->d_flags, HX_MAX_SWEEP_FLAGS * sizeof(int32_t)); }
+    if (e == hipSuccess) { what = "hipMalloc(sync)"; e = hipMalloc((void **)&ctx->d_sync, 4 * sizeof(int32_t)); }
     if (e == hipSuccess) { what = "hipMalloc(ticket)"; e = hipMalloc((void **)&ctx->d_ticket, sizeof(int32_t)); }
     if (e == hipSuccess) { what = "hipMalloc(accumulators)"; e = hipMalloc((void **)&ctx->d_acc, 3 * HX_MAX_INSTANCES * sizeof(unsigned long long)); }
     if (e == hipSuccess && device < HX_MAX_DEVICES) {     // set-up for hx_commit_static on this device
@@ -354,6 +355,7 @@ extern "C" int hx_ctx_create(hx_ctx **out, int device)
         hx_commit_clear_kernel<<<(3 * HX_MAX_INSTANCES + 255) / 256, 256, 0, nullptr>>>(z);
         hx_clear_status_kernel<<<1, 1, 0, nullptr>>>(ctx->d_status);
         hx_clear_status_kernel<<<1, 1, 0, nullptr>>>(ctx->d_ticket);
+        for (int i = 0; i < 4; ++i) hx_clear_status_kernel<<<1, 1, 0, nullptr>>>(ctx->d_sync + i);
         e = hipGetLastError();
     }
     if (e == hipSuccess) { what = "hipStreamSynchronize"; e = hipStreamSynchronize(nullptr); }
@@ -374,6 +376,7 @@ extern "C" int hx_ctx_destroy(hx_ctx *ctx)
     if (ctx->h_status) (void)hipHostFree(ctx->h_status);
     if (ctx->d_prep) (void)hipFree(ctx->d_prep);
     if (ctx->d_flags) (void)hipFree(ctx->d_flags);
+    if (ctx->d_sync) (void)hipFree(ctx->d_sync);
     if (ctx->d_ticket) (void)hipFree(ctx->d_ticket);
     if (ctx->d_acc) (void)hipFree(ctx->d_acc);
     if (ctx->d_dpart) (void)hipFree(ctx->d_dpart);

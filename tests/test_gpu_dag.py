@@ -435,3 +435,39 @@ def test_commit_matches_oracle(ctx, C):
     with pytest.raises(binding.HxError) as e:
         ctx.hx_stream_status()
     assert e.value.code == -6
+
+
+# sweeps inside a workgroup's slice and over the whole graph: a workflow that fills a slice or does not fit one, more successors
+# than a node has slots, rows at the very end of the id array, an edge into another slice, nodes of no workflow, and
+# two graphs in a row (what the workgroups share has to be clear again)
+@pytest.mark.parametrize("kind", ["full slice", "too large", "many successors", "few edges", "across", "no workflow", "empty workflows"])
+def test_sweeps_by_slice_and_over_the_whole_graph(ctx, kind):
+    rng = np.random.default_rng(sum(map(ord, kind)))
+    sizes = {"full slice": [1024, 3, 1021], "too large": [700, 1025, 40], "many successors": [90, 64], "few edges": [3, 1],
+             "across": [30] * 900, "no workflow": [50, 50], "empty workflows": [0, 5, 0, 0, 7, 0]}[kind]
+    n = int(np.sum(sizes))
+    wf_ptr = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    succ = [[] for _ in range(n)]
+    for a, b in zip(wf_ptr[:-1], wf_ptr[1:]):
+        order = a + rng.permutation(b - a)                  # any numbering: edges go forward along `order`
+        for i in range(b - a):
+            later = order[i + 1:]
+            if later.size and rng.random() < 0.85:
+                many = 12 if kind == "many successors" else 3
+                near = later[:40]
+                succ[order[i]] = list(rng.choice(near, min(near.size, int(rng.integers(1, many + 1))), replace=False))
+    if kind == "few edges":
+        succ = [[2], [], [], []]
+    if kind == "across":
+        for k in range(5):                                   # whole workflows hang on later ones, wherever these are staged
+            succ[int(wf_ptr[10 * k + 1] - 1)].append(int(wf_ptr[600 + 7 * k]))
+    if kind == "no workflow":
+        wf_ptr = np.array([10, 50, 90], np.int32)            # the first and the last ten nodes belong to none
+    deg = np.array([len(x) for x in succ])
+    row = np.zeros(n + 1, np.int32); row[1:] = np.cumsum(deg)
+    col = np.array([u for x in succ for u in sorted(x)], np.int32)
+    cost32 = rng.uniform(0.1, 2.0, n).astype(np.float32)
+    want = o.critical_path(row, col, cost32.astype(np.float64), wf_ptr, round_f32=True)
+    for _ in range(2):
+        assert_cp_bit_exact(gpu_cp(ctx, row, col, cost32, wf_ptr, max_sweeps=int(want[2].max()) + 2), want)
+    assert_cp_bit_exact(gpu_cp(ctx, row, col, cost32, wf_ptr, max_sweeps=4000), want)
