@@ -209,7 +209,8 @@ int hx_horizons(hx_ctx *ctx, const hx_model *model, int32_t n_nodes, int32_t n_e
 /*
  * Incremental form for DAGs revealed at run time (Sec. 4.1, online reveal;
  * Sec. 5.1, the horizon is refreshed at every reveal).  The graph lives
- * in the context.  hx_dag_reserve sizes it (allocates; not for the hot loop)
+ * in the context.  hx_dag_reserve sizes it (allocates unless a store of
+ * that size, or up to twice it, is there already; not for the hot loop)
  * and empties it.  An append propagates with one walk per new node, of any
  * depth; only a walk that is cut short (more than 16 parents waiting at once,
  * or more than 1024 nodes visited) hands over to level-by-level sweeps, of

@@ -41,7 +41,8 @@ struct HxPrepTables {
 };
 
 struct HxDagStore {
-    int32_t cap_nodes = 0, cap_edges = 0, cap_wf = 0, max_depth = 0;
+    int32_t cap_nodes = 0, cap_edges = 0, cap_wf = 0, max_depth = 0;      // as reserved
+    int32_t room_nodes = 0, room_edges = 0, room_wf = 0;                  // as allocated
     int32_t n_nodes = 0, n_edges = 0;
     float *cost = nullptr, *rem = nullptr, *tail = nullptr, *horizon = nullptr;
     int32_t *level = nullptr, *wf = nullptr, *parent_row_ptr = nullptr, *parent_col = nullptr;

@@ -367,6 +367,26 @@ def test_append_errors(ctx):
     assert list(rem) == [6, 5, 4, 3, 2, 1] and list(level) == [5, 4, 3, 2, 1, 0] and list(hor) == [6]
 
 
+def test_a_reserve_of_a_similar_size_begins_an_empty_graph(ctx):
+    # 16 nodes, then 10 of the same store: as empty as a new one, and no larger than was asked for; then another store
+    from paper_2605_16637_amd import binding
+    for cap in (16, 10, 16, 40):
+        ctx.hx_dag_reserve(cap, cap, 2, 4)
+        with pytest.raises(binding.HxError) as e:
+            ctx.hx_dag_append(dev(np.zeros(cap + 2, np.int32)), dev(np.zeros(0, np.int32)), dev(np.ones(cap + 1, np.float32)),
+                              dev(np.zeros(cap + 1, np.int32)))
+        assert e.value.code == -4
+        cost = np.arange(1, 7, dtype=np.float32)
+        ctx.hx_dag_append(dev(np.array([0, 0, 1, 2, 3, 4, 5], np.int32)), dev(np.arange(5, dtype=np.int32)), dev(cost),
+                          dev(np.ones(6, np.int32)))
+        ctx.hx_stream_status()
+        rem, tail, level, hor = view(ctx, 6, 2)
+        assert list(rem) == list(np.cumsum(cost[::-1])[::-1]) and list(level) == [5, 4, 3, 2, 1, 0] and list(hor) == [0, 21]
+        ctx.hx_dag_set_cost(dev(np.array([5], np.int32)), dev(np.array([100.0], np.float32)))
+        ctx.hx_stream_status()
+        assert view(ctx, 6, 2)[3][1] == 115
+
+
 def chain_and_fan(n_chain, n_fan):
     """A chain 0 <- 1 <- ... and then one node whose parents are the last n_fan chain nodes."""
     rp = np.concatenate([[0], np.arange(n_chain), [n_chain - 1 + n_fan]]).astype(np.int32)       # node 0 has no parent
