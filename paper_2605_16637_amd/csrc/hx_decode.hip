@@ -77,13 +77,17 @@ __device__ __forceinline__ int hx_parts_sum(int r, int parts)
     return r;
 }
 
-// All threads of the workgroup call this.  cnt entries of one instance -> compact timeline in
-// `out`, its length in *n_out (LDS).  Ends the call with a barrier.
-template <bool COHERENT>
+// All threads of the workgroup (WAVE: all lanes of one wavefront) call this.  cnt entries of one instance -> compact
+// timeline in `out`, its length in *n_out (LDS).  Ends the call with a barrier.
+template <bool COHERENT, bool WAVE = false>
 __device__ void hx_build_timeline(int cnt, const float *st, const float *en, const int32_t *tk,
                                   TlScratch w, Tl out, int *n_out, int32_t *status)
 {
-    const int tid = threadIdx.x, nthreads = blockDim.x;
+    const int tid = WAVE ? threadIdx.x & (HX_WAVE - 1) : threadIdx.x, nthreads = WAVE ? HX_WAVE : blockDim.x;
+    auto sync = [] {
+        if constexpr (WAVE) hx_wave_sync();
+        else __syncthreads();
+    };
     const int n_ev = 2 * cnt + 1;
     for (int i = tid; i < n_ev; i += nthreads) {
         float time = 0.0f;
@@ -104,7 +108,7 @@ __device__ void hx_build_timeline(int cnt, const float *st, const float *en, con
         w.key[i] = ((u64)__float_as_uint(time) << 32) | ((u64)is_end << 31) | (unsigned)i;
         w.delta[i] = delta;
     }
-    __syncthreads();
+    sync();
     // position of every event = number of smaller keys (keys are unique); with threads to spare, the 2 or 4
     // neighbouring lanes of an event count a part of the keys each
     const int parts = hx_count_parts(n_ev, nthreads);
@@ -128,7 +132,7 @@ __device__ void hx_build_timeline(int cnt, const float *st, const float *en, con
             w.ds[r] = w.delta[i];
         }
     }
-    __syncthreads();
+    sync();
     // one wavefront: running occupancy, and one entry per distinct time (the last event of that time)
     if (tid < HX_WAVE) {
         const int per = (n_ev + HX_WAVE - 1) / HX_WAVE;
@@ -160,9 +164,9 @@ __device__ void hx_build_timeline(int cnt, const float *st, const float *en, con
         }
         if (tid == HX_WAVE - 1) *n_out = pos;
     }
-    __syncthreads();
+    sync();
     for (int i = *n_out + tid; i < hx_tl_len(n_ev); i += nthreads) out.e[i] = make_int2(0x7f800000, 0);
-    __syncthreads();
+    sync();
 }
 
 // ---- earliest capacity-feasible start, one lane per (call, instance) ------------------
@@ -182,7 +186,8 @@ struct HxSlot {
 // whose successor is "never" always has room: everything has ended by then).  Run starts only
 // grow along the timeline, so the earliest start is the minimum over all hits.  The loop ends when
 // every lane has its answer or has passed the end of its timeline.
-__device__ __forceinline__ HxSlot hx_earliest_start(const int2 *e, int n, int thr, float T, bool active)
+// begin: a multiple of eight, the lane's first entry (0, or a place no start can lie before).
+__device__ __forceinline__ HxSlot hx_earliest_start(const int2 *e, int n, int thr, float T, bool active, int begin = 0)
 {
     const bool open = active && thr >= 0;
     float rs = INFINITY, ans = INFINITY;
@@ -192,10 +197,10 @@ __device__ __forceinline__ HxSlot hx_earliest_start(const int2 *e, int n, int th
         ans = fminf(ans, __int_as_float(nxt_) >= rs + T ? rs : INFINITY);         \
     }
     // eight entries per step, the next eight already on their way (lanes that are through read entry 0 on)
-    const int4 *q = reinterpret_cast<const int4 *>(e);
+    const int4 *q = reinterpret_cast<const int4 *>(e) + (begin >> 1);
     int4 c0 = q[0], c1 = q[1], c2 = q[2], c3 = q[3];
     for (int i0 = 0;; i0 += 8) {
-        const bool going = open && i0 < n && !(ans < INFINITY);
+        const bool going = open && begin + i0 < n && !(ans < INFINITY);
         if (__builtin_amdgcn_ballot_w64(going) == 0) break;
         const int at = going ? (i0 >> 1) + 4 : 0;
         const int4 n0 = q[at], n1 = q[at + 1], n2 = q[at + 2], n3 = q[at + 3];
@@ -804,6 +809,10 @@ __global__ __launch_bounds__(64) void hx_decode_finish_kernel(DecodeFinishArgs a
 
 constexpr int DG_THREADS = 1024;
 constexpr int DG_WAVES = DG_THREADS / HX_WAVE;
+constexpr int DP_MAX_THREADS = HX_DECODE_GREEDY_MAX_CALLS;   // a lane per call at least
+constexpr int DP_THREADS = 512;
+constexpr int DP_MAX_G = 4;                                  // lanes per call at most
+constexpr int DP_FEW = 12;                                   // calls of a wavefront whose starts are found one after the other (24: 705 us)
 
 struct DGreedyArgs {
     HxModelF m;
@@ -832,21 +841,16 @@ struct DGreedyLds {
     __host__ __device__ size_t off_inst() const { return off_tl() + hx_align16((size_t)D * nt * 8); }
     __host__ __device__ size_t off_call() const { return off_inst() + (size_t)6 * D * 4; }
     __host__ __device__ size_t off_red() const { return off_call() + (size_t)11 * Q * 4; }
-    __host__ __device__ size_t off_mat() const { return hx_align16(off_red() + (size_t)(2 * DG_WAVES + 8) * 4); }
-    __host__ __device__ size_t bytes() const { return off_mat(); }
-    // with the start of every (instance, call) pair kept: [D][Q] floats more
-    __host__ __device__ size_t bytes_with_matrix() const { return off_mat() + (size_t)D * Q * 4; }
+    __host__ __device__ size_t bytes() const { return hx_align16(off_red() + (size_t)(2 * DG_WAVES + 8) * 4); }
 };
 
 enum : int { DG_ALIVE = 1, DG_DIRTY = 2 };
 
-// An added interval can only delay starts on the instance that received it; everything else stands.
-// keep_all (when LDS has room for the start of every (instance, call) pair): after a step only that
-// instance's column is computed again, one call per lane, all lanes on the same timeline; a call whose best
-// was there takes the minimum of its row again (start + the call's decode time on the instance, the sum its
-// finish was when the pair was scored); the start of the call that is picked is read from its row.  Otherwise: a call is scored again, on every instance, if its instance is the one that changed.
-// Both ways give the same plan: the same functions on the same timelines, the same (finish, instance) rule.
-__global__ __launch_bounds__(DG_THREADS) void hx_decode_plan_kernel(DGreedyArgs a, int keep_all)
+// The plan where LDS has no room for the start of every (instance, call) pair.  An added interval can only delay starts on
+// the instance that received it; everything else stands: a call is scored again, on every instance, if its instance
+// is the one that changed.  The same plan as the kernel below makes: the same functions on the same timelines, the
+// same (finish, instance) rule.
+__global__ __launch_bounds__(DG_THREADS) void hx_decode_plan_lean_kernel(DGreedyArgs a)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     const DGreedyLds lay(a.stride, a.D, a.Q);
@@ -872,7 +876,6 @@ __global__ __launch_bounds__(DG_THREADS) void hx_decode_plan_kernel(DGreedyArgs 
     float *s_redv = (float *)(smem + lay.off_red());
     int *s_redi = (int *)(s_redv + DG_WAVES);
     int *s_pick = s_redi + DG_WAVES;
-    float *s_mat = (float *)(smem + lay.off_mat());       // [lay.D][lay.Q] start of call c on instance d, +inf: none (keep_all)
 
     const int tid = threadIdx.x;
     const int lane = tid & (HX_WAVE - 1);
@@ -903,8 +906,8 @@ __global__ __launch_bounds__(DG_THREADS) void hx_decode_plan_kernel(DGreedyArgs 
     }
 
     for (int k = 0; k < a.Q; ++k) {
-        // (1) score the calls whose instance changed (keep_all: every call, once): one wavefront per call, lanes over instances
-        for (int c = wave; c < a.Q && (!keep_all || k == 0); c += DG_WAVES) {
+        // (1) score the calls whose instance changed: one wavefront per call, lanes over instances
+        for (int c = wave; c < a.Q; c += DG_WAVES) {
             if (s_flags[c] != (DG_ALIVE | DG_DIRTY)) continue;     // wave-uniform
             const int L = s_L[c], O = s_O[c];
             const int lk = s_lk[c];
@@ -920,7 +923,6 @@ __global__ __launch_bounds__(DG_THREADS) void hx_decode_plan_kernel(DGreedyArgs 
                 const HxSlot s = hx_earliest_start(s_tl + (size_t)dd * lay.nt, s_n[dd],
                                                    q.thr, q.T, in && q.legal);
                 const float v = s.S + q.T;
-                if (keep_all && in) s_mat[(size_t)d * lay.Q + c] = s.found ? s.S : INFINITY;
                 if (in && s.found && v < bv) { bv = v; bS = s.S; bd = d; }
             }
             const float best = hx_wave_min(bv);
@@ -957,8 +959,6 @@ __global__ __launch_bounds__(DG_THREADS) void hx_decode_plan_kernel(DGreedyArgs 
         }
         if (tid == 0) {
             const int c = ri, d = s_bd[c];
-            // its best may have moved since its start was last written: the start on the instance it has now
-            if (keep_all && d >= 0) s_bs[c] = s_mat[(size_t)d * lay.Q + c];
             a.best_d[c] = d; a.best_start[c] = s_bs[c]; a.best_cost[c] = s_bc[c]; hx_store_bits(a.ratio, c, __float_as_uint(s_ratio[c])); a.rank[c] = k;
             s_flags[c] = 0;
             int changed = -1;
@@ -1038,57 +1038,323 @@ __global__ __launch_bounds__(DG_THREADS) void hx_decode_plan_kernel(DGreedyArgs 
             } else {
                 hx_build_timeline<true>(s_cnt[pd], a.iv_start + at, a.iv_end + at, a.iv_tok + at, w, tl, &s_n[pd], a.status);
             }
-            if (!keep_all) {
-                for (int c = tid; c < a.Q; c += DG_THREADS)
-                    if ((s_flags[c] & DG_ALIVE) && s_bd[c] == pd) s_flags[c] = DG_ALIVE | DG_DIRTY;
-            } else {
-                HxDecF x;
-                x.wait = 0.0f; x.c1 = s_c1[pd]; x.c2 = s_c2[pd]; x.kB = s_kB[pd];
-                const int cap = s_cap[pd], n = s_n[pd];
-                for (int base = 0; base < a.Q; base += DG_THREADS) {
-                    const int c = base + tid;
-                    const bool live = c < a.Q && (s_flags[c] & DG_ALIVE);
-                    const int L = live ? s_L[c] : 0, O = live ? s_O[c] : 0;
-                    const int lk = live ? s_lk[c] : -1;
-                    const HxDecodeCand q = hx_decode_candidate(a.m, L, O, live ? lk : -1, pd, a.D, x, cap, a.status);
-                    const HxSlot s = hx_earliest_start(tl.e, n, q.thr, q.T, live && q.legal);
-                    if (live) {
-                        s_mat[(size_t)pd * lay.Q + c] = s.found ? s.S : INFINITY;
-                        if (s_bd[c] == pd) {
-                            // lowest instance among equal finishes: ascending, strictly smaller (the finish is the kept
-                            // start plus the call's decode time there, the same sum as when the pair was scored)
-                            const HxCallF cf = hx_call_terms(a.m, L, O);
-                            float bv = INFINITY;
-                            int bd = -1;
-                            int d = 0;
-                            for (; d + 8 <= a.D; d += 8) {                    // eight instances' reads in flight
-                                float S8[8], c1[8], c2[8], kB[8];
-#pragma unroll
-                                for (int u = 0; u < 8; ++u) {
-                                    S8[u] = s_mat[(size_t)(d + u) * lay.Q + c];
-                                    c1[u] = s_c1[d + u]; c2[u] = s_c2[d + u]; kB[u] = s_kB[d + u];
-                                }
-#pragma unroll
-                                for (int u = 0; u < 8; ++u) {
-                                    const float v = S8[u] + hx_decode_time(cf, c1[u], c2[u], kB[u]);
-                                    if (v < bv) { bv = v; bd = d + u; }
-                                }
-                            }
-                            for (; d < a.D; ++d) {
-                                const float v = s_mat[(size_t)d * lay.Q + c] + hx_decode_time(cf, s_c1[d], s_c2[d], s_kB[d]);
-                                if (v < bv) { bv = v; bd = d; }
-                            }
-                            s_bd[c] = bd;
-                            s_bc[c] = bv;
-                            hx_store_bits(s_ratio, c, hx_ratio_bits(s_el[c], bv, s_tail[c], s_hz[c], s_hz[c] >= 0.0f));   // Eq. (2)
-                        }
-                    }
-                }
-            }
+            for (int c = tid; c < a.Q; c += DG_THREADS)
+                if ((s_flags[c] & DG_ALIVE) && s_bd[c] == pd) s_flags[c] = DG_ALIVE | DG_DIRTY;
         }
         __syncthreads();
     }
     for (int d = tid; d < a.D; d += DG_THREADS) a.iv_count[d] = s_cnt[d];
+}
+
+// LDS carve-up shared by host (size) and device (offsets)
+struct DPlanLds {
+    int ne, nt, D, Q;      // events per instance, stored timeline length, padded sizes
+    __host__ __device__ DPlanLds(int stride, int D_, int Q_)
+        : ne(2 * stride + 1), nt(hx_tl_len(2 * stride + 1) + 2), D((D_ + 3) & ~3), Q((Q_ + 3) & ~3) {}
+    __host__ __device__ size_t off_red() const { return hx_align16((size_t)D * nt * 8); }                // int4 [2][2][wavefronts]
+    __host__ __device__ size_t off_inst() const { return off_red() + 4 * 16 * (DP_MAX_THREADS / HX_WAVE); }    // float4 per instance: c1, c2, kB, capacity
+    __host__ __device__ size_t off_n() const { return off_inst() + (size_t)16 * D; }                     // per instance: timeline entries, intervals
+    __host__ __device__ size_t off_list() const { return off_n() + (size_t)8 * D; }                      // per slot: its call
+    __host__ __device__ size_t off_call() const { return off_list() + (size_t)4 * Q; }                   // per call: L, O, lock, elapsed, tail, horizon, picked
+    __host__ __device__ size_t off_scratch() const { return hx_align16(off_call() + (size_t)28 * Q); }
+    __host__ __device__ size_t off_mat() const { return off_scratch() + hx_scratch_bytes(ne); }          // [D][Q] start of call c on instance d, +inf: none
+    __host__ __device__ size_t bytes() const { return off_mat() + (size_t)D * Q * 4; }
+};
+
+// The plan where LDS has room for the start of every (instance, call) pair.  An added interval can only delay starts on
+// the instance that received it, and there only those whose decode overlaps it: the calls of which this is true look
+// for their start again, from where it was; a call whose best was there and moved takes the minimum of its row
+// again (start + the call's decode time on the instance, the sum its finish was when the pair was scored).
+//
+// What bounds it: a pick is a chain of argmax, insertion into the timeline, scan and row minimum; a call is a lane, or
+// several once the remaining calls leave lanes idle (their row is then split), the results of a call stay in its
+// lanes' registers, every wavefront makes the pick for itself, the first one inserts.  Two barriers a pick.
+// 256 calls on 32 instances 1350 -> 660 us, 100 on 32 500 -> 262, 1000 on 8 4530 -> 2650, 8 on 2 33 -> 26 (before: all 16
+// wavefronts took part, one lane made the pick, every call looked again over the whole timeline).  Of 77 calls a pick that
+// the new interval touches, nine move; the test against the most tokens held under it leaves few others.
+// At most two lanes per call 687 us, four 662, eight 685; four wavefronts 737 instead of eight.
+__global__ __launch_bounds__(DP_MAX_THREADS) void hx_decode_plan_kernel(DGreedyArgs a)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    const DPlanLds lay(a.stride, a.D, a.Q);
+    int2 *const s_tl = (int2 *)smem;
+    int4 *const s_red = (int4 *)(smem + lay.off_red());
+    float4 *const s_inst = (float4 *)(smem + lay.off_inst());
+    int *const s_n = (int *)(smem + lay.off_n()), *const s_cnt = s_n + lay.D;
+    int *const s_list = (int *)(smem + lay.off_list());
+    int *const s_L = (int *)(smem + lay.off_call()), *const s_O = s_L + lay.Q, *const s_lk = s_O + lay.Q;
+    float *const s_el = (float *)(s_lk + lay.Q), *const s_tail = s_el + lay.Q, *const s_hz = s_tail + lay.Q;
+    int *const s_gone = (int *)(s_hz + lay.Q);
+    float *const s_mat = (float *)(smem + lay.off_mat());
+    __shared__ int s_wcnt[DP_MAX_THREADS / HX_WAVE], s_most;
+
+    const int tid = threadIdx.x, NT = blockDim.x;
+    const int lane = tid & (HX_WAVE - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+    for (int d = tid; d < a.D; d += NT) {
+        int cnt = a.iv_count[d];
+        if (cnt < 0 || cnt > a.stride) { hx_raise(a.status, HX_ERR_INDEX); cnt = cnt < 0 ? 0 : a.stride; }
+        s_cnt[d] = cnt;
+        const HxDecF x = hx_decode_terms(a.m, a.d_used[d], a.d_batch[d], 0, 1.0f / a.d_flops[d], 1.0f / a.d_hbm[d]);
+        s_inst[d] = make_float4(x.c1, x.c2, x.kB, __int_as_float(a.d_cap[d]));
+    }
+    for (int c = tid; c < a.Q; c += NT) {
+        const int L = a.L_in[c], O = a.L_out[c], lk = a.lock ? a.lock[c] : -1;
+        const bool fine = L >= 0 && O >= 0 && lk >= -1 && lk < a.D;      // otherwise the call has no place (lock -2)
+        const int nd = a.node[c], w = a.wf[c];
+        const bool ok = nd >= 0 && nd < a.n_nodes && w >= 0 && w < a.n_wf;
+        if (!fine || !ok) hx_raise(a.status, HX_ERR_INDEX);
+        s_L[c] = fine ? L : 0; s_O[c] = fine ? O : 0; s_lk[c] = fine ? lk : -2;
+        s_el[c] = a.elapsed[c];
+        s_tail[c] = ok ? a.tail[nd] : 0.0f;                    // tail of its node, horizon of its workflow (-1: index out of range)
+        s_hz[c] = ok ? fmaxf(a.horizon[w], 0.0f) : -1.0f;
+        s_gone[c] = 0;
+        s_list[c] = c;
+    }
+    __syncthreads();
+    // the timelines, an instance per wavefront; the builders' scratch is where the matrix will be, as far as it goes
+    {
+        const size_t one = hx_scratch_bytes(lay.ne);
+        const int builders = min(NT / HX_WAVE, (int)((lay.bytes() - lay.off_scratch()) / one));
+        for (int d = wave; d < a.D && wave < builders; d += builders) {
+            const size_t at = (size_t)d * a.stride;
+            hx_build_timeline<false, true>(s_cnt[d], a.iv_start + at, a.iv_end + at, a.iv_tok + at,
+                                           hx_carve_scratch(smem + lay.off_scratch() + wave * one, lay.ne),
+                                           Tl{s_tl + (size_t)d * lay.nt}, &s_n[d], a.status);
+        }
+    }
+    __syncthreads();
+    // tokens a call may find occupied on an instance, < 0: never fits, or has no place there
+    auto threshold = [&](int L, int O, int lk, int d, float cap) {
+        const long long room = (long long)__float_as_int(cap) - ((long long)L + (long long)O);
+        return (room < 0 || (lk != -1 && lk != d)) ? -1 : (room > (long long)INT_MAX ? INT_MAX : (int)room);
+    };
+    // every start: a wavefront takes 64 calls on one instance at a time, all its lanes on the same timeline
+    const int blocks = (a.Q + HX_WAVE - 1) / HX_WAVE;
+    for (int i = wave; i < blocks * a.D; i += NT / HX_WAVE) {
+        const int d = i / blocks, c = (i - d * blocks) * HX_WAVE + lane;
+        const bool in = c < a.Q;
+        const int L = in ? s_L[c] : 0, O = in ? s_O[c] : 0, lk = in ? s_lk[c] : -2;
+        const float4 x = s_inst[d];
+        const HxSlot got = hx_earliest_start(s_tl + (size_t)d * lay.nt, s_n[d], threshold(L, O, lk, d, x.w),
+                                             hx_decode_time(hx_call_terms(a.m, L, O), x.x, x.y, x.z), in);
+        if (in) s_mat[d * lay.Q + c] = got.S;
+    }
+    __syncthreads();
+
+    int n = a.Q, lanes = NT;
+    for (int k = 0; k < a.Q;) {
+        // ---- a stage: the remaining calls in increasing order, G lanes each; a wavefront per 64 lanes
+        const int n_before = n;
+        n = a.Q - k;
+        if (k > 0) {
+            const int c = s_list[tid < n_before ? tid : 0];
+            const bool stays = tid < n_before && s_gone[c] == 0;
+            const u64 b = __builtin_amdgcn_ballot_w64(stays);
+            if (lane == 0) s_wcnt[wave] = __popcll(b);
+            __syncthreads();
+            int at = __popcll(b & ((1ull << lane) - 1ull));
+            for (int v = 0; v < wave; ++v) at += s_wcnt[v];
+            if (stays) s_list[at] = c;
+            __syncthreads();
+        }
+        int lg = 0;
+        while ((2 << lg) <= DP_MAX_G && (n << (lg + 1)) <= lanes) ++lg;
+        const int G = 1 << lg, n_lanes = n << lg, n_waves = (n_lanes + HX_WAVE - 1) / HX_WAVE;
+        lanes = n_waves * HX_WAVE;
+        const int last = n_waves > 1 ? a.Q - n / 2 : a.Q;      // the stage's picks end here
+        const int slot = tid >> lg, sub = tid & (G - 1);
+        bool alive = slot < n;
+        const int c = s_list[alive ? slot : 0];                // lanes without a call go along with the first one's and write nothing
+        const int L = s_L[c], O = s_O[c], lk = s_lk[c];
+        const float el = s_el[c], tail = s_tail[c], hz = s_hz[c];
+        const HxCallF cf = hx_call_terms(a.m, L, O);
+        float best = INFINITY;
+        int best_d = INT_MAX;
+        unsigned ratio_bits = 0;
+        // the earliest finish of the lane's call, the lowest instance that has it, and its ratio, Eq. (2)
+        auto row = [&]() {
+            float v = INFINITY;
+            int at = INT_MAX;
+#pragma unroll 4
+            for (int d = sub; d < a.D; d += G) {               // ascending, strictly smaller
+                const float4 x = s_inst[d];
+                const float f = s_mat[d * lay.Q + c] + hx_decode_time(cf, x.x, x.y, x.z);
+                at = f < v ? d : at;
+                v = fminf(v, f);
+            }
+            best = hx_lanes_min(v, G);
+            best_d = hx_lanes_min(v == best ? at : INT_MAX, G);
+            ratio_bits = hx_ratio_bits(el, best, tail, hz, hz >= 0.0f);
+        };
+        if (wave < n_waves) row();
+        if (wave >= n_waves) {                                 // no calls here any more
+            if (n_waves > 1)
+                for (int i = k; i < last; ++i) { __syncthreads(); __syncthreads(); }
+            k = last;
+        }
+        for (; k < last; ++k) {
+            // (1) the most urgent remaining call: largest ratio, lowest index among equals (slots, and with them lanes and
+            // wavefronts, are in index order)
+            const float key = alive ? hx_rank_key(__uint_as_float(ratio_bits)) : -INFINITY;
+            const float top = hx_wave_max(key);
+            const u64 at_top = __builtin_amdgcn_ballot_w64(alive && key == top);
+            int from = at_top ? __builtin_ctzll(at_top) : 0;   // (no lane with a call: it loses to every wavefront that has one)
+            int pick = at_top ? (wave * HX_WAVE + from) >> lg : INT_MAX;
+            int pc = __builtin_amdgcn_readlane(c, from), pd = __builtin_amdgcn_readlane(best_d, from);
+            float E = hx_lane_value(best, from);
+            int p_ratio = __builtin_amdgcn_readlane((int)ratio_bits, from);
+            if (n_waves > 1) {
+                int4 *red = s_red + (k & 1) * 2 * (DP_MAX_THREADS / HX_WAVE);
+                if (lane == 0) {
+                    red[wave] = make_int4(__float_as_int(top), pick, pc, pd);
+                    red[DP_MAX_THREADS / HX_WAVE + wave] = make_int4(__float_as_int(E), p_ratio, 0, 0);
+                }
+                __syncthreads();
+                const int v = min(lane, n_waves - 1);          // (n_waves is at most a row of lanes; lanes beyond repeat the last)
+                const int4 q = red[v], q2 = red[DP_MAX_THREADS / HX_WAVE + v];
+                const float all = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(-hx_lanes_min(-__int_as_float(q.x), n_waves))));
+                from = __builtin_ctzll(__builtin_amdgcn_ballot_w64(q.y != INT_MAX && __int_as_float(q.x) == all));
+                pick = __builtin_amdgcn_readlane(q.y, from);
+                pc = __builtin_amdgcn_readlane(q.z, from); pd = __builtin_amdgcn_readlane(q.w, from);
+                E = __int_as_float(__builtin_amdgcn_readlane(q2.x, from)); p_ratio = __builtin_amdgcn_readlane(q2.y, from);
+            }
+            const bool placed = pd != INT_MAX;
+            const float S = placed ? s_mat[pd * lay.Q + pc] : INFINITY;
+            const int cnt = placed ? s_cnt[pd] : 0, n_old = placed ? s_n[pd] : 1;
+            const bool added = placed && cnt < a.stride;
+            const long long need = placed ? (long long)s_L[pc] + (long long)s_O[pc] : 0;
+            const int tok = need > (long long)INT_MAX ? INT_MAX : (int)need;
+            // The usual case -- the interval holds something, starts now or later and ends at a finite time -- is inserted
+            // into the timeline; anything else has the timeline built again from the instance's intervals.
+            const bool insert = S >= 0.0f && S < E && E < INFINITY && need > 0;
+            alive = alive && slot != pick;
+            int2 *const tl = s_tl + (added ? pd : 0) * lay.nt;
+            // (2) the first wavefront adds its interval (the last one records the pick)
+            const size_t at = (size_t)(added ? pd : 0) * a.stride + cnt;
+            if (wave == n_waves - 1 && lane == 0) {
+                a.best_d[pc] = placed ? pd : -1; a.best_start[pc] = S; a.best_cost[pc] = E; a.rank[pc] = k;
+                hx_store_bits(a.ratio, pc, (unsigned)p_ratio);
+                s_gone[pc] = 1;
+                if (placed && !added) hx_raise(a.status, HX_ERR_CAPACITY);
+                if (added && insert) { a.iv_start[at] = S; a.iv_end[at] = E; a.iv_tok[at] = tok; }
+            }
+            if (wave == 0) {
+                if (added && insert) {
+                    // The compact timeline is a function of the instance's events, so adding the two events of the new
+                    // interval (S, E, tok) to it gives what building it again would: entries from S up to E hold tok
+                    // more; S and E become entries of their own unless the timeline already has an entry at that time
+                    // (S: the occupancy before it plus tok; E: the occupancy that stood before E).
+                    int pos_s = 0, pos_e = 0;
+                    bool has_s = false, has_e = false;
+                    const int top0 = (n_old - 1) & ~(HX_WAVE - 1);
+                    int2 me;                                   // of the last 64 entries at the end
+                    for (int i0 = 0; i0 <= top0; i0 += HX_WAVE) {
+                        me = tl[min(i0 + lane, n_old - 1)];
+                        const float t = i0 + lane < n_old ? __int_as_float(me.x) : INFINITY;      // S and E are finite
+                        pos_s += __popcll(__builtin_amdgcn_ballot_w64(t < S)); pos_e += __popcll(__builtin_amdgcn_ballot_w64(t < E));
+                        has_s = has_s || __builtin_amdgcn_ballot_w64(t == S) != 0; has_e = has_e || __builtin_amdgcn_ballot_w64(t == E) != 0;
+                    }
+                    // pos_e >= 1: entry 0 is now, and E > 0
+                    const int before_s = max(pos_s - 1, 0), before_e = pos_e - 1;
+                    const int occ_before_s = top0 == 0 ? __builtin_amdgcn_readlane(me.y, before_s) : tl[before_s].y;
+                    const int occ_before_e = top0 == 0 ? __builtin_amdgcn_readlane(me.y, before_e) : tl[before_e].y;
+                    bool over = false;
+                    int most = 0;                              // tokens held at most from S up to E
+                    auto more = [&](int occ) {
+                        const int sum = __builtin_elementwise_add_sat(occ, tok);      // both are >= 0
+                        over = over || sum - occ != tok;
+                        most = max(most, sum);
+                        return sum;
+                    };
+                    // from the last 64 entries to the first: an entry moves by two places at most, towards the end
+                    for (int i0 = top0; i0 >= 0; i0 -= HX_WAVE) {
+                        const int i = i0 + lane;
+                        if (i0 != top0) me = tl[i];
+                        hx_wave_sync();
+                        if (i < n_old)
+                            tl[i + (!has_s && i >= pos_s) + (!has_e && i >= pos_e)] = make_int2(me.x, i >= pos_s && i < pos_e ? more(me.y) : me.y);
+                        hx_wave_sync();
+                    }
+                    const int n_new = n_old + !has_s + !has_e;
+                    if (lane == 0) {
+                        if (!has_s) tl[pos_s] = make_int2(__float_as_int(S > 0.0f ? S : 0.0f), more(occ_before_s));
+                        if (!has_e) tl[pos_e + !has_s] = make_int2(__float_as_int(E), occ_before_e);
+                        s_n[pd] = n_new;
+                    }
+                    most = -hx_wave_min(-most);
+                    if (lane == 0) s_most = most;
+                    if (over) hx_raise(a.status, HX_ERR_OVERFLOW);
+                    // the filler behind the entries reaches as far as a timeline of two more events may be read
+                    const int fill = hx_tl_len(2 * cnt + 1) + lane;
+                    if (fill < hx_tl_len(2 * cnt + 3) && fill >= n_new) tl[fill] = make_int2(0x7f800000, 0);
+                } else if (added) {
+                    if (lane == 0) { a.iv_start[at] = S; a.iv_end[at] = E; a.iv_tok[at] = tok; }
+                    __threadfence();                           // the other lanes are about to read the interval from memory
+                    const size_t at0 = (size_t)pd * a.stride;
+                    hx_build_timeline<true, true>(cnt + 1, a.iv_start + at0, a.iv_end + at0, a.iv_tok + at0,
+                                                  hx_carve_scratch(smem + lay.off_scratch(), lay.ne), Tl{tl}, &s_n[pd], a.status);
+                }
+                hx_wave_sync();
+            }
+            if (n_waves > 1) __syncthreads();
+            if (!added) continue;
+            if (tid == 0) s_cnt[pd] = cnt + 1;                 // (every wavefront has read it)
+            // (3) who has to look again: where the call may go at all, if its start with its decode time touches the new
+            // interval, and some moment of that leaves it no room
+            const float4 x = s_inst[pd];
+            const float T = hx_decode_time(cf, x.x, x.y, x.z);
+            const int thr = threshold(L, O, lk, pd, x.w);
+            const float old = s_mat[pd * lay.Q + c];
+            const bool touched = alive && sub == 0 && old < INFINITY && (!insert || (old < E && S < old + T && thr < s_most));
+            u64 todo = __builtin_amdgcn_ballot_w64(touched);
+            if (todo == 0) continue;
+            const int n_tl = s_n[pd];
+            float now = INFINITY;
+            if (n_tl <= HX_WAVE && __popcll(todo) <= DP_FEW) {
+                // Few calls on a timeline of few entries: one call after the other, a lane per entry.  An entry where
+                // a run of entries with room begins is a start if the run's end, the next entry without, is far enough.
+                const int2 me = tl[lane];                      // behind the last entry: never, empty
+                const float t = __int_as_float(me.x);
+                while (todo) {
+                    const int ld = __builtin_ctzll(todo);
+                    todo &= todo - 1;
+                    const u64 full = __builtin_amdgcn_ballot_w64(lane < n_tl && me.y > __builtin_amdgcn_readlane(thr, ld));
+                    const float T_ld = hx_lane_value(T, ld);
+                    u64 runs = ~full & ((full << 1) | 1);      // first entries of the runs
+                    float got = INFINITY;
+                    while (runs) {
+                        const int i = __builtin_ctzll(runs);
+                        const u64 end = full >> i;
+                        const float rs = hx_lane_value(t, i), re = end ? hx_lane_value(t, i + __builtin_ctzll(end)) : INFINITY;
+                        if (i >= n_tl) break;
+                        if (re >= rs + T_ld) { got = rs; break; }
+                        runs &= runs - 1;
+                    }
+                    now = lane == ld ? got : now;
+                }
+            } else {
+                // its start was the earliest, and load was only added: nothing before it can be one now
+                int begin = 0;
+                if (insert)
+                    for (int i0 = 8; i0 < n_tl; i0 += 64) {
+                        float t[8];
+#pragma unroll
+                        for (int u = 0; u < 8; ++u) t[u] = __int_as_float(tl[min(i0 + 8 * u, n_tl)].x);      // entry n: never
+#pragma unroll
+                        for (int u = 0; u < 8; ++u) begin += touched && t[u] <= old ? 8 : 0;
+                    }
+                now = hx_earliest_start(tl, n_tl, thr, T, touched, begin).S;
+            }
+            if (touched) s_mat[pd * lay.Q + c] = now;
+            const u64 moved = __builtin_amdgcn_ballot_w64(touched && best_d == pd && now != old);
+            hx_wave_sync();
+            if (moved) row();
+        }
+        __syncthreads();
+    }
+    for (int d = tid; d < a.D; d += NT) a.iv_count[d] = s_cnt[d];
 }
 
 __global__ __launch_bounds__(256) void hx_decode_no_instance_kernel(DGreedyArgs a)
@@ -1120,11 +1386,15 @@ int check_tables(hx_ctx *ctx, const hx_calls *q, const hx_decode_tab *dec, const
 
 }  // namespace
 
-// the decode planner may use all of a CU's LDS; said once per process
+// the decode planners may use all of a CU's LDS; said once per process
+constexpr size_t DP_LDS = 160 * 1024 - 128;                  // but for the first one's own counters
 int hx_decode_init()
 {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(hx_decode_plan_kernel),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, DP_LDS);
+    if (e == hipSuccess)
+        e = hipFuncSetAttribute(reinterpret_cast<const void *>(hx_decode_plan_lean_kernel),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     return e == hipSuccess ? HX_OK : HX_ERR_DEVICE;
 }
 
@@ -1263,8 +1533,9 @@ extern "C" int hx_decode_plan_greedy(hx_ctx *ctx, const hx_model *model, const h
     if (D == 0) {
         hx_decode_no_instance_kernel<<<(Q + 255) / 256, 256, 0, stream>>>(a);
     } else {
-        const bool keep_all = lay.bytes_with_matrix() <= (size_t)160 * 1024;
-        hx_decode_plan_kernel<<<1, DG_THREADS, keep_all ? lay.bytes_with_matrix() : lay.bytes(), stream>>>(a, keep_all ? 1 : 0);
+        const size_t lds = DPlanLds(iv->stride, D, Q).bytes();
+        if (lds <= DP_LDS) hx_decode_plan_kernel<<<1, Q > DP_THREADS ? DP_MAX_THREADS : DP_THREADS, lds, stream>>>(a);
+        else hx_decode_plan_lean_kernel<<<1, DG_THREADS, lay.bytes(), stream>>>(a);
     }
     return hx_check_launch(ctx, "hx_decode_plan_greedy kernel");
 }

@@ -273,28 +273,6 @@ struct GreedyCalls {
     __host__ __device__ int dec() const { return (13 + kT) * C4; }    // decode times of the calls, as many as there is room for
 };
 
-// The minimum over the groups of G neighbouring lanes (G a power of two, at most a row of 16; other G: the next one), in each lane.
-__device__ __forceinline__ float hx_lanes_min(float x, int G)
-{
-#define HX_ROW_MIN(ctrl) x = fminf(x, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), ctrl, 0xf, 0xf, true)))
-    if (G > 1) HX_ROW_MIN(0xB1);           // quad_perm [1,0,3,2]
-    if (G > 2) HX_ROW_MIN(0x4E);           // quad_perm [2,3,0,1]
-    if (G > 4) HX_ROW_MIN(0x141);          // row_half_mirror
-    if (G > 8) HX_ROW_MIN(0x140);          // row_mirror
-#undef HX_ROW_MIN
-    return x;
-}
-
-// LDS written by some lanes of a wavefront and read by others of it
-__device__ __forceinline__ void hx_wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-__device__ __forceinline__ float hx_lane_value(float x, int lane) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), lane)); }
-
 // dec_words: LDS words behind lay.dec()
 // K: instances of either side per lane of a wavefront's copy of the pool; TT: classes, or more
 template <int K, int TT, int THREADS>

@@ -54,6 +54,39 @@ __device__ __forceinline__ void hx_wave_argmax(float &v, int &i)
     v = top;
 }
 
+// The minimum over the groups of G neighbouring lanes (G a power of two, at most a row of 16; other G: the next one), in each lane.
+__device__ __forceinline__ float hx_lanes_min(float x, int G)
+{
+#define HX_ROW_MIN(ctrl) x = fminf(x, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), ctrl, 0xf, 0xf, true)))
+    if (G > 1) HX_ROW_MIN(0xB1);           // quad_perm [1,0,3,2]
+    if (G > 2) HX_ROW_MIN(0x4E);           // quad_perm [2,3,0,1]
+    if (G > 4) HX_ROW_MIN(0x141);          // row_half_mirror
+    if (G > 8) HX_ROW_MIN(0x140);          // row_mirror
+#undef HX_ROW_MIN
+    return x;
+}
+
+__device__ __forceinline__ int hx_lanes_min(int x, int G)
+{
+#define HX_ROW_MIN(ctrl) x = min(x, __builtin_amdgcn_mov_dpp(x, ctrl, 0xf, 0xf, true))
+    if (G > 1) HX_ROW_MIN(0xB1);
+    if (G > 2) HX_ROW_MIN(0x4E);
+    if (G > 4) HX_ROW_MIN(0x141);
+    if (G > 8) HX_ROW_MIN(0x140);
+#undef HX_ROW_MIN
+    return x;
+}
+
+// LDS written by some lanes of a wavefront and read by others of it
+__device__ __forceinline__ void hx_wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+__device__ __forceinline__ float hx_lane_value(float x, int lane) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), lane)); }
+
 // The library is built on the assumption that no arithmetic ever sees a NaN, so
 // the NaN that marks a bad index is chosen among integers and stored as bits.
 constexpr unsigned HX_QNAN_BITS = 0x7fc00000u;

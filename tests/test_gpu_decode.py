@@ -398,6 +398,23 @@ def test_decode_greedy_matches_oracle(ctx, Q, D, stride, res, plan, lockf, seed)
     assert (got["best_start"][got["best_d"] >= 0] > 0).any()
 
 
+# more than one wavefront of calls, dealt to the lanes anew as they go, on timelines of more than 64 entries; one instance;
+# more than 512 calls (a lane each in the widest workgroup)
+@pytest.mark.parametrize("Q,D,stride,res,plan,lockf,extra,seed", [(300, 3, 70, 50, 20, 0.3, 300, 6), (65, 1, 9, 6, 3, 0.0, 65, 7),
+                                                                   (520, 8, 10, 7, 3, 0.4, 300, 8)])
+def test_decode_greedy_of_longer_queues(ctx, Q, D, stride, res, plan, lockf, extra, seed):
+    r, lock, iv = synth.make_decode_round("decode_tiny", 20 + seed, n_wf=max(8, Q // 4), Q=Q, D=D, T=min(4, D), stride=stride,
+                                          n_resident=res, n_planned=plan, lock_fraction=lockf)
+    L, O = r.calls["L_in"], r.calls["L_out"]
+    rng = np.random.default_rng(seed)
+    node = rng.permutation(Q).astype(np.int32); wf = rng.integers(0, 4, Q).astype(np.int32)
+    elapsed = rng.uniform(0, 20, Q).astype(np.float32)
+    tail = rng.uniform(0, 5, Q).astype(np.float32); hor = rng.uniform(5, 50, 4).astype(np.float32)
+    big = widen(iv, D, extra)
+    got = run_plan(ctx, r.model, L, O, lock, node, wf, elapsed, tail, hor, r.dec, big)
+    check_plan_stepwise(r.model, L, O, lock, node, wf, elapsed, tail, hor, r.dec, big, got)
+
+
 @pytest.mark.parametrize("Q,D,stride,res,plan", [(40, 4, 16, 10, 3), (80, 64, 16, 10, 3)])      # finish of every pair kept; not kept
 def test_decode_greedy_with_workflows_without_horizon(ctx, Q, D, stride, res, plan):
     # a workflow whose horizon is 0 makes its calls infinitely urgent: they are planned first, lowest index first, and
