@@ -34,7 +34,34 @@ __device__ __forceinline__ unsigned long long hx_rank_key64(float r, int idx)
     return ((unsigned long long)b << 32) | (unsigned)(0xffffffffu - (unsigned)idx);
 }
 
-// rank[c] = number of calls ahead of c: larger ratio, or equal ratio and lower
+// rank[c] = number of calls ahead of c: larger ratio, or equal ratio and lower index.  Short queues: a workgroup ranks 64
+// calls, a lane each, its wavefronts comparing them with a share of the queue each; one launch, nothing to
+// clear (64 calls 6.5 -> 3.9 us; 2048 calls 6.4 -> 6.3, where two launches are as good).
+constexpr int RANK_THREADS = 1024;
+constexpr int RANK_DIRECT = 2048;
+
+__global__ __launch_bounds__(RANK_THREADS) void hx_rank_direct_kernel(const float *ratio, int32_t *rank, int C)
+{
+    __shared__ unsigned long long s_key[RANK_DIRECT];
+    __shared__ int s_ahead[HX_WAVE];
+    const int tid = threadIdx.x, lane = tid & (HX_WAVE - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c = blockIdx.x * HX_WAVE + lane;
+    for (int i = tid; i < C; i += RANK_THREADS) s_key[i] = hx_rank_key64(ratio[i], i);
+    if (tid < HX_WAVE) s_ahead[tid] = 0;
+    __syncthreads();
+    const unsigned long long mine = s_key[min(c, C - 1)];
+    const int share = (C + RANK_THREADS / HX_WAVE - 1) / (RANK_THREADS / HX_WAVE);
+    const int end = min((wave + 1) * share, C);
+    int ahead = 0;
+#pragma unroll 8
+    for (int i = wave * share; i < end; ++i) ahead += s_key[i] > mine;
+    if (ahead) atomicAdd(&s_ahead[lane], ahead);
+    __syncthreads();
+    if (tid < HX_WAVE && c < C) rank[c] = s_ahead[tid];
+}
+
+// Longer queues, up to RANK_SMALL: rank[c] = number of calls ahead of c: larger ratio, or equal ratio and lower
 // index.  Block (i, j) counts, for 256 calls, those ahead of them among the
 // `tile` calls of tile j; the partial counts are added up with integer atomics.
 __global__ __launch_bounds__(256) void hx_rank_count_kernel(const float *ratio, int32_t *rank, int C, int tile)
@@ -738,6 +765,10 @@ extern "C" int hx_rank(hx_ctx *ctx, int32_t C, const float *ratio, int32_t *rank
     HX_REQUIRE(ctx, guard.ok, HX_ERR_DEVICE, "cannot select device %d", ctx->device);
     hipStream_t stream = (hipStream_t)stream_;
     const int bx = (C + 255) / 256;
+    if (C <= RANK_DIRECT) {
+        hx_rank_direct_kernel<<<(C + HX_WAVE - 1) / HX_WAVE, RANK_THREADS, 0, stream>>>(ratio, rank, C);
+        return hx_check_launch(ctx, "hx_rank_direct_kernel");
+    }
     if (C <= RANK_SMALL) {
         // small queues: every call against every call, no scratch.  Tiles short enough for a few thousand
         // workgroups (a workgroup's time is its tile's length, whatever the queue's), long enough to be worth

@@ -42,6 +42,26 @@ def test_rank_matches_oracle(ctx, C):
     assert np.array_equal(got, want)
 
 
+# the ordering where its tiles can go wrong: the sizes around their limits, all ratios equal, all infinite, ratios over
+# many magnitudes and of either sign, a few values a rounding apart
+@pytest.mark.parametrize("C", [63, 64, 65, 1025, 2048, 2049, 8192, 8193, 16384])
+@pytest.mark.parametrize("kind", ["equal", "infinite", "magnitudes", "close"])
+def test_rank_of_unusual_ratios(ctx, C, kind):
+    import torch
+    rng = np.random.default_rng(C)
+    r = {"equal": np.full(C, 0.7), "infinite": np.full(C, np.inf),
+         "magnitudes": 10.0 ** rng.uniform(-37, 37, C) * rng.choice([-1, 1], C),
+         "close": np.float32(1.5) + rng.integers(0, 3, C) * np.finfo(np.float32).eps}[kind].astype(np.float32)
+    if kind == "magnitudes":
+        r[rng.integers(0, C, 5)] = [np.inf, -np.inf, 0.0, np.inf, np.float32(3.4e38)]
+    rank = torch.full((C,), -1, dtype=torch.int32, device="cuda:0")
+    ctx.hx_rank(dev(r), rank)
+    ctx.hx_stream_status()
+    order = np.argsort(-r.astype(np.float64), kind="stable")
+    want = np.empty(C, np.int64); want[order] = np.arange(C)
+    assert np.array_equal(rank.cpu().numpy(), want)
+
+
 def run_greedy(ctx, model, L, O, elapsed, node, wf, tail, hor, pre, dec, links):
     import torch
     from paper_2605_16637_amd import binding
