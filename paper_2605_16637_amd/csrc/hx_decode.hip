@@ -1302,12 +1302,13 @@ __global__ __launch_bounds__(DP_MAX_THREADS) void hx_decode_plan_kernel(DGreedyA
             if (!added) continue;
             if (tid == 0) s_cnt[pd] = cnt + 1;                 // (every wavefront has read it)
             // (3) who has to look again: where the call may go at all, if its start with its decode time touches the new
-            // interval, and some moment of that leaves it no room
+            // interval, and some moment of that leaves it no room.  A start needs room at its own moment, however short
+            // the decode time (0, or lost in the addition): S <= old stands beside the window's S < old + T.
             const float4 x = s_inst[pd];
             const float T = hx_decode_time(cf, x.x, x.y, x.z);
             const int thr = threshold(L, O, lk, pd, x.w);
             const float old = s_mat[pd * lay.Q + c];
-            const bool touched = alive && sub == 0 && old < INFINITY && (!insert || (old < E && S < old + T && thr < s_most));
+            const bool touched = alive && sub == 0 && old < INFINITY && (!insert || (old < E && (S <= old || S < old + T) && thr < s_most));
             u64 todo = __builtin_amdgcn_ballot_w64(touched);
             if (todo == 0) continue;
             const int n_tl = s_n[pd];

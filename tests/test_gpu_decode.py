@@ -459,6 +459,44 @@ def test_decode_greedy_with_calls_that_decode_nothing(ctx, Q, D, stride, res, pl
     assert np.array_equal(got["best_start"][placed & (O == 0)], got["best_cost"][placed & (O == 0)])
 
 
+def plan_with_calls_that_decode_nothing(ctx, seed, Q, D, stride, res, plan, extra):
+    r, lock, iv = synth.make_decode_round("decode_tiny", seed, n_wf=max(8, Q // 4), Q=Q, D=D, T=min(4, D), stride=stride,
+                                          n_resident=res, n_planned=plan, lock_fraction=0.2)
+    L, O = r.calls["L_in"], r.calls["L_out"].copy()
+    O[::3] = 0
+    rng = np.random.default_rng(seed)
+    node = rng.permutation(Q).astype(np.int32); wf = rng.integers(0, 4, Q).astype(np.int32)
+    elapsed = rng.uniform(0, 20, Q).astype(np.float32)
+    tail = rng.uniform(0, 5, Q).astype(np.float32); hor = rng.uniform(5, 50, 4).astype(np.float32)
+    big = widen(iv, D, extra)
+    got = run_plan(ctx, r.model, L, O, lock, node, wf, elapsed, tail, hor, r.dec, big)
+    check_plan_stepwise(r.model, L, O, lock, node, wf, elapsed, tail, hor, r.dec, big, got)
+
+
+# many seeds: whether a call without output tokens starts exactly where an interval is added hangs on the numbers
+@pytest.mark.parametrize("Q,D,stride,res,plan,extra,seeds", [(40, 4, 16, 10, 3, 40, range(1, 32)), (100, 3, 16, 10, 3, 100, range(40, 43))])
+def test_decode_greedy_moves_calls_that_decode_nothing(ctx, Q, D, stride, res, plan, extra, seeds):
+    for seed in seeds:
+        plan_with_calls_that_decode_nothing(ctx, seed, Q, D, stride, res, plan, extra)
+
+
+@pytest.mark.parametrize("at", [0.0, 1e6])
+def test_decode_greedy_start_needs_room_at_its_own_moment(ctx, at):
+    # One instance with room for one call.  A is urgent and decodes for about a second from `at` on (what is resident ends
+    # there); B's decode time is nothing, or is lost in the sum with `at`: it fits only after A all the same.
+    from helpers import ROUND_MODEL
+    dec = dict(flops=np.array([1e13], np.float32), hbm_bw=np.array([1e12], np.float32), used_tok=np.zeros(1, np.int32),
+               cap_tok=np.array([1500], np.int32), batch=np.zeros(1, np.int32), qd_tok=np.zeros(1, np.int32), type=np.zeros(1, np.int32))
+    iv = dict(stride=4, count=np.array([1 if at else 0], np.int32), start=np.zeros(4, np.float32), end=np.full(4, at, np.float32),
+              tok=np.full(4, 1500, np.int32))
+    L, O = np.array([1000, 1000]), np.array([100, 0 if at == 0 else 1])
+    g = run_plan(ctx, ROUND_MODEL, L, O, None, [0, 1], [0, 0], [5.0, 1.0], [0.0, 0.0], [10.0], dec, iv)
+    check_plan_stepwise(ROUND_MODEL, L, O, None, np.array([0, 1]), np.array([0, 0]), [5.0, 1.0], [0.0, 0.0], [10.0], dec, iv, g)
+    assert list(g["rank"]) == [0, 1] and list(g["best_d"]) == [0, 0]
+    assert g["best_start"][0] == np.float32(at) and g["best_cost"][0] > np.float32(at)
+    assert g["best_start"][1] == g["best_cost"][0] and g["best_cost"][1] == g["best_cost"][0]
+
+
 def test_decode_greedy_at_the_benchmarks_size(ctx):
     # the queue bench.py times: 256 calls x 32 instances, 24 resident + 4 planned entries each, lists of 140 entries
     Q, D = 256, 32
