@@ -865,7 +865,7 @@ __global__ __launch_bounds__(DG_THREADS) void hx_decode_plan_lean_kernel(DGreedy
     int *s_bd = (int *)(smem + lay.off_call());
     float *s_bs = (float *)(s_bd + lay.Q);
     float *s_bc = s_bs + lay.Q;
-    float *s_ratio = s_bc + lay.Q;
+    unsigned *s_ratio = (unsigned *)(s_bc + lay.Q);       // bits: it may be the NaN
     int *s_flags = (int *)(s_ratio + lay.Q);
     int *s_L = s_flags + lay.Q;                            // what the queue says of a call, read once
     int *s_O = s_L + lay.Q;
@@ -933,7 +933,7 @@ __global__ __launch_bounds__(DG_THREADS) void hx_decode_plan_lean_kernel(DGreedy
                 s_bd[c] = any ? best_d : -1;
                 s_bs[c] = any ? best_S : INFINITY;
                 s_bc[c] = any ? best : INFINITY;
-                hx_store_bits(s_ratio, c, hx_ratio_bits(s_el[c], any ? best : INFINITY, s_tail[c], s_hz[c], s_hz[c] >= 0.0f));   // Eq. (2)
+                s_ratio[c] = hx_ratio_bits(s_el[c], any ? best : INFINITY, s_tail[c], s_hz[c], s_hz[c] >= 0.0f);   // Eq. (2)
                 s_flags[c] = DG_ALIVE;
             }
         }
@@ -959,7 +959,7 @@ __global__ __launch_bounds__(DG_THREADS) void hx_decode_plan_lean_kernel(DGreedy
         }
         if (tid == 0) {
             const int c = ri, d = s_bd[c];
-            a.best_d[c] = d; a.best_start[c] = s_bs[c]; a.best_cost[c] = s_bc[c]; hx_store_bits(a.ratio, c, __float_as_uint(s_ratio[c])); a.rank[c] = k;
+            a.best_d[c] = d; a.best_start[c] = s_bs[c]; a.best_cost[c] = s_bc[c]; hx_store_bits(a.ratio, c, s_ratio[c]); a.rank[c] = k;
             s_flags[c] = 0;
             int changed = -1;
             if (d >= 0) {
@@ -1046,13 +1046,19 @@ __global__ __launch_bounds__(DG_THREADS) void hx_decode_plan_lean_kernel(DGreedy
     for (int d = tid; d < a.D; d += DG_THREADS) a.iv_count[d] = s_cnt[d];
 }
 
+// what a call has to know of an instance; the capacity stays an integer (as a float, some capacities are NaNs)
+struct __align__(16) DPlanInst {
+    float c1, c2, kB;
+    int cap;
+};
+
 // LDS carve-up shared by host (size) and device (offsets)
 struct DPlanLds {
     int ne, nt, D, Q;      // events per instance, stored timeline length, padded sizes
     __host__ __device__ DPlanLds(int stride, int D_, int Q_)
         : ne(2 * stride + 1), nt(hx_tl_len(2 * stride + 1) + 2), D((D_ + 3) & ~3), Q((Q_ + 3) & ~3) {}
     __host__ __device__ size_t off_red() const { return hx_align16((size_t)D * nt * 8); }                // int4 [2][2][wavefronts]
-    __host__ __device__ size_t off_inst() const { return off_red() + 4 * 16 * (DP_MAX_THREADS / HX_WAVE); }    // float4 per instance: c1, c2, kB, capacity
+    __host__ __device__ size_t off_inst() const { return off_red() + 4 * 16 * (DP_MAX_THREADS / HX_WAVE); }    // DPlanInst per instance
     __host__ __device__ size_t off_n() const { return off_inst() + (size_t)16 * D; }                     // per instance: timeline entries, intervals
     __host__ __device__ size_t off_list() const { return off_n() + (size_t)8 * D; }                      // per slot: its call
     __host__ __device__ size_t off_call() const { return off_list() + (size_t)4 * Q; }                   // per call: L, O, lock, elapsed, tail, horizon, picked
@@ -1079,7 +1085,7 @@ __global__ __launch_bounds__(DP_MAX_THREADS) void hx_decode_plan_kernel(DGreedyA
     const DPlanLds lay(a.stride, a.D, a.Q);
     int2 *const s_tl = (int2 *)smem;
     int4 *const s_red = (int4 *)(smem + lay.off_red());
-    float4 *const s_inst = (float4 *)(smem + lay.off_inst());
+    DPlanInst *const s_inst = (DPlanInst *)(smem + lay.off_inst());
     int *const s_n = (int *)(smem + lay.off_n()), *const s_cnt = s_n + lay.D;
     int *const s_list = (int *)(smem + lay.off_list());
     int *const s_L = (int *)(smem + lay.off_call()), *const s_O = s_L + lay.Q, *const s_lk = s_O + lay.Q;
@@ -1097,7 +1103,7 @@ __global__ __launch_bounds__(DP_MAX_THREADS) void hx_decode_plan_kernel(DGreedyA
         if (cnt < 0 || cnt > a.stride) { hx_raise(a.status, HX_ERR_INDEX); cnt = cnt < 0 ? 0 : a.stride; }
         s_cnt[d] = cnt;
         const HxDecF x = hx_decode_terms(a.m, a.d_used[d], a.d_batch[d], 0, 1.0f / a.d_flops[d], 1.0f / a.d_hbm[d]);
-        s_inst[d] = make_float4(x.c1, x.c2, x.kB, __int_as_float(a.d_cap[d]));
+        s_inst[d] = DPlanInst{x.c1, x.c2, x.kB, a.d_cap[d]};
     }
     for (int c = tid; c < a.Q; c += NT) {
         const int L = a.L_in[c], O = a.L_out[c], lk = a.lock ? a.lock[c] : -1;
@@ -1126,8 +1132,8 @@ __global__ __launch_bounds__(DP_MAX_THREADS) void hx_decode_plan_kernel(DGreedyA
     }
     __syncthreads();
     // tokens a call may find occupied on an instance, < 0: never fits, or has no place there
-    auto threshold = [&](int L, int O, int lk, int d, float cap) {
-        const long long room = (long long)__float_as_int(cap) - ((long long)L + (long long)O);
+    auto threshold = [&](int L, int O, int lk, int d, int cap) {
+        const long long room = (long long)cap - ((long long)L + (long long)O);
         return (room < 0 || (lk != -1 && lk != d)) ? -1 : (room > (long long)INT_MAX ? INT_MAX : (int)room);
     };
     // every start: a wavefront takes 64 calls on one instance at a time, all its lanes on the same timeline
@@ -1136,9 +1142,9 @@ __global__ __launch_bounds__(DP_MAX_THREADS) void hx_decode_plan_kernel(DGreedyA
         const int d = i / blocks, c = (i - d * blocks) * HX_WAVE + lane;
         const bool in = c < a.Q;
         const int L = in ? s_L[c] : 0, O = in ? s_O[c] : 0, lk = in ? s_lk[c] : -2;
-        const float4 x = s_inst[d];
-        const HxSlot got = hx_earliest_start(s_tl + (size_t)d * lay.nt, s_n[d], threshold(L, O, lk, d, x.w),
-                                             hx_decode_time(hx_call_terms(a.m, L, O), x.x, x.y, x.z), in);
+        const DPlanInst x = s_inst[d];
+        const HxSlot got = hx_earliest_start(s_tl + (size_t)d * lay.nt, s_n[d], threshold(L, O, lk, d, x.cap),
+                                             hx_decode_time(hx_call_terms(a.m, L, O), x.c1, x.c2, x.kB), in);
         if (in) s_mat[d * lay.Q + c] = got.S;
     }
     __syncthreads();
@@ -1179,8 +1185,8 @@ __global__ __launch_bounds__(DP_MAX_THREADS) void hx_decode_plan_kernel(DGreedyA
             int at = INT_MAX;
 #pragma unroll 4
             for (int d = sub; d < a.D; d += G) {               // ascending, strictly smaller
-                const float4 x = s_inst[d];
-                const float f = s_mat[d * lay.Q + c] + hx_decode_time(cf, x.x, x.y, x.z);
+                const DPlanInst x = s_inst[d];
+                const float f = s_mat[d * lay.Q + c] + hx_decode_time(cf, x.c1, x.c2, x.kB);
                 at = f < v ? d : at;
                 v = fminf(v, f);
             }
@@ -1197,7 +1203,7 @@ __global__ __launch_bounds__(DP_MAX_THREADS) void hx_decode_plan_kernel(DGreedyA
         for (; k < last; ++k) {
             // (1) the most urgent remaining call: largest ratio, lowest index among equals (slots, and with them lanes and
             // wavefronts, are in index order)
-            const float key = alive ? hx_rank_key(__uint_as_float(ratio_bits)) : -INFINITY;
+            const float key = alive ? hx_rank_key(ratio_bits) : -INFINITY;
             const float top = hx_wave_max(key);
             const u64 at_top = __builtin_amdgcn_ballot_w64(alive && key == top);
             int from = at_top ? __builtin_ctzll(at_top) : 0;   // (no lane with a call: it loses to every wavefront that has one)
@@ -1304,9 +1310,9 @@ __global__ __launch_bounds__(DP_MAX_THREADS) void hx_decode_plan_kernel(DGreedyA
             // (3) who has to look again: where the call may go at all, if its start with its decode time touches the new
             // interval, and some moment of that leaves it no room.  A start needs room at its own moment, however short
             // the decode time (0, or lost in the addition): S <= old stands beside the window's S < old + T.
-            const float4 x = s_inst[pd];
-            const float T = hx_decode_time(cf, x.x, x.y, x.z);
-            const int thr = threshold(L, O, lk, pd, x.w);
+            const DPlanInst x = s_inst[pd];
+            const float T = hx_decode_time(cf, x.c1, x.c2, x.kB);
+            const int thr = threshold(L, O, lk, pd, x.cap);
             const float old = s_mat[pd * lay.Q + c];
             const bool touched = alive && sub == 0 && old < INFINITY && (!insert || (old < E && (S <= old || S < old + T) && thr < s_most));
             u64 todo = __builtin_amdgcn_ballot_w64(touched);

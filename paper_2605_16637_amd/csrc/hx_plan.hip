@@ -27,9 +27,9 @@ __global__ __launch_bounds__(256) void hx_rank_zero_kernel(int32_t *rank, int C)
 
 // (ratio, index) as one unsigned 64-bit key that orders like "larger ratio first,
 // then lower index": the float bits made monotone, then the complemented index
-__device__ __forceinline__ unsigned long long hx_rank_key64(float r, int idx)
+__device__ __forceinline__ unsigned long long hx_rank_key64(unsigned bits, int idx)
 {
-    unsigned b = __float_as_uint(hx_rank_key(r));
+    unsigned b = __float_as_uint(hx_rank_key(bits));
     b ^= (b & 0x80000000u) ? 0xffffffffu : 0x80000000u;
     return ((unsigned long long)b << 32) | (unsigned)(0xffffffffu - (unsigned)idx);
 }
@@ -47,7 +47,7 @@ __global__ __launch_bounds__(RANK_THREADS) void hx_rank_direct_kernel(const floa
     const int tid = threadIdx.x, lane = tid & (HX_WAVE - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = blockIdx.x * HX_WAVE + lane;
-    for (int i = tid; i < C; i += RANK_THREADS) s_key[i] = hx_rank_key64(ratio[i], i);
+    for (int i = tid; i < C; i += RANK_THREADS) s_key[i] = hx_rank_key64(hx_load_bits(ratio, i), i);
     if (tid < HX_WAVE) s_ahead[tid] = 0;
     __syncthreads();
     const unsigned long long mine = s_key[min(c, C - 1)];
@@ -69,11 +69,11 @@ __global__ __launch_bounds__(256) void hx_rank_count_kernel(const float *ratio, 
     __shared__ unsigned long long s_key[RANK_TILE];
     const int k0 = blockIdx.y * tile;
     const int kn = min(tile, C - k0);
-    for (int i = threadIdx.x; i < kn; i += blockDim.x) s_key[i] = hx_rank_key64(ratio[k0 + i], k0 + i);
+    for (int i = threadIdx.x; i < kn; i += blockDim.x) s_key[i] = hx_rank_key64(hx_load_bits(ratio, k0 + i), k0 + i);
     __syncthreads();
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= C) return;
-    const unsigned long long mine = hx_rank_key64(ratio[c], c);
+    const unsigned long long mine = hx_rank_key64(hx_load_bits(ratio, c), c);
     int ahead = 0;
 #pragma unroll 8
     for (int i = 0; i < kn; ++i) ahead += s_key[i] > mine;
@@ -101,7 +101,7 @@ __global__ __launch_bounds__(RANK_SPLIT) void hx_rank_splitters_kernel(const flo
     __shared__ unsigned long long s[RANK_SPLIT];
     const int t = threadIdx.x;
     const int c = (int)(((long long)t * C) / RANK_SPLIT);
-    s[t] = hx_rank_key64(ratio[c], c);
+    s[t] = hx_rank_key64(hx_load_bits(ratio, c), c);
     w.hist[t] = 0;
     if (t == 0) w.hist[RANK_SPLIT] = 0;
     __syncthreads();
@@ -144,7 +144,7 @@ __global__ __launch_bounds__(1024) void hx_rank_slot_kernel(const float *ratio, 
     const int c = blockIdx.x * blockDim.x + t;
     int b = 0, local = 0;
     if (c < C) {
-        b = hx_rank_bucket(s_split, hx_rank_key64(ratio[c], c));
+        b = hx_rank_bucket(s_split, hx_rank_key64(hx_load_bits(ratio, c), c));
         local = atomicAdd(&s_cnt[b], 1);
     }
     __syncthreads();
@@ -185,7 +185,7 @@ __global__ __launch_bounds__(256) void hx_rank_scatter_kernel(const float *ratio
     hx_rank_starts(w.hist, s_start);
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= C) return;
-    const unsigned long long key = hx_rank_key64(ratio[c], c);
+    const unsigned long long key = hx_rank_key64(hx_load_bits(ratio, c), c);
     w.bkey[s_start[hx_rank_bucket(s_split, key)] + rank[c]] = key;
 }
 
@@ -555,7 +555,7 @@ __global__ __launch_bounds__(THREADS) void hx_plan_greedy_kernel(GreedyArgs a, i
         for (; k < last; ++k) {
             // (1) the most urgent remaining call: largest ratio, lowest index among equals (slots, and with them lanes and
             // wavefronts, are in index order)
-            const float key = alive ? hx_rank_key(__uint_as_float(ratio_bits)) : -INFINITY;
+            const float key = alive ? hx_rank_key(ratio_bits) : -INFINITY;
             const float top = hx_wave_max(key);
             // (no lane with a call: lane 0 stands in; its -inf and "no slot" lose to every wavefront that has one)
             const unsigned long long at_top = __builtin_amdgcn_ballot_w64(alive && key == top);

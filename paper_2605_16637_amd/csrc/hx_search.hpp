@@ -114,9 +114,11 @@ __device__ __forceinline__ void hx_projected_ratio(const int32_t *node, const in
     hx_store_bits(ratio, c, hx_ratio_bits(elapsed[c], best, ok ? tail[nd] : 0.0f, ok ? horizon[w] : 1.0f, ok));
 }
 
-// ordering key of a ratio: a NaN (raised elsewhere as a bad index) sorts with +inf
-__device__ __forceinline__ float hx_rank_key(float r)
+// a ratio as it is stored: it may be the NaN, and a float that may be one is not so much as handed to a function
+__device__ __forceinline__ unsigned hx_load_bits(const float *in, int i) { return ((const unsigned *)in)[i]; }
+
+// ordering key of a ratio's bits: the NaN (raised elsewhere as a bad index) sorts with +inf
+__device__ __forceinline__ float hx_rank_key(unsigned b)
 {
-    const unsigned b = __float_as_uint(r);                       // chosen among integers: r may be the NaN
     return __uint_as_float((b & 0x7fffffffu) > 0x7f800000u ? 0x7f800000u : b);
 }

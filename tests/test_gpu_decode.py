@@ -497,6 +497,25 @@ def test_decode_greedy_start_needs_room_at_its_own_moment(ctx, at):
     assert g["best_start"][1] == g["best_cost"][0] and g["best_cost"][1] == g["best_cost"][0]
 
 
+def test_decode_greedy_with_capacities_that_are_no_numbers_as_floats(ctx):
+    # INT_MAX ("no limit") and -1 ("nothing fits") are NaNs if their bits are taken for a float's
+    Q, D = 48, 4
+    r, lock, iv = synth.make_decode_round("decode_tiny", 41, n_wf=12, Q=Q, D=D, T=4, stride=16, n_resident=10, n_planned=3,
+                                          lock_fraction=0.3)
+    dec = dict(r.dec); dec["cap_tok"] = dec["cap_tok"].copy()
+    dec["cap_tok"][:3] = [2**31 - 1, -1, 0x7fc00001]
+    L, O = r.calls["L_in"], r.calls["L_out"]
+    rng = np.random.default_rng(41)
+    node = rng.permutation(Q).astype(np.int32); wf = rng.integers(0, 4, Q).astype(np.int32)
+    elapsed = rng.uniform(0, 20, Q).astype(np.float32)
+    tail = rng.uniform(0, 5, Q).astype(np.float32); hor = rng.uniform(5, 50, 4).astype(np.float32)
+    big = widen(iv, D, Q)
+    got = run_plan(ctx, r.model, L, O, lock, node, wf, elapsed, tail, hor, dec, big)
+    check_plan_stepwise(r.model, L, O, lock, node, wf, elapsed, tail, hor, dec, big, got)
+    assert (got["best_d"] != 1).all() and (got["best_start"][(got["best_d"] == 0) | (got["best_d"] == 2)] == 0).all()
+    assert (got["best_d"][lock == 1] == -1).all() and (lock == 1).any()
+
+
 def test_decode_greedy_at_the_benchmarks_size(ctx):
     # the queue bench.py times: 256 calls x 32 instances, 24 resident + 4 planned entries each, lists of 140 entries
     Q, D = 256, 32

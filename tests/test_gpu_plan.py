@@ -62,6 +62,21 @@ def test_rank_of_unusual_ratios(ctx, C, kind):
     assert np.array_equal(rank.cpu().numpy(), want)
 
 
+@pytest.mark.parametrize("C", [40, 3000, 20000])      # one launch; all pairs; by buckets
+def test_rank_puts_a_ratio_that_is_no_number_with_the_infinite(ctx, C):
+    import torch
+    rng = np.random.default_rng(C)
+    r = rng.uniform(0.1, 5.0, C).astype(np.float32)
+    odd = rng.choice(C, 9, replace=False)
+    r[odd[:5]] = np.nan; r[odd[5:]] = np.inf
+    rank = torch.full((C,), -1, dtype=torch.int32, device="cuda:0")
+    ctx.hx_rank(dev(r), rank)
+    ctx.hx_stream_status()
+    order = np.argsort(-np.where(np.isnan(r), np.inf, r), kind="stable")
+    want = np.empty(C, np.int64); want[order] = np.arange(C)
+    assert np.array_equal(rank.cpu().numpy(), want)
+
+
 def run_greedy(ctx, model, L, O, elapsed, node, wf, tail, hor, pre, dec, links):
     import torch
     from paper_2605_16637_amd import binding
