@@ -58,8 +58,8 @@ struct hx_ctx {
     int32_t *d_status = nullptr;       // sticky device status word
     int32_t *h_status = nullptr;       // pinned copy
     HxPrepTables *d_prep = nullptr;
-    int32_t *d_flags = nullptr;        // sweep "changed" flags, [HX_MAX_SWEEP_FLAGS]
-    int32_t *d_sync = nullptr;         // sweeps over the whole graph: what its workgroups share; 4 words, 0 between launches
+    int32_t *d_report = nullptr;       // counts of hx_validate_round, [HX_VALIDATE_FIELDS]
+    int32_t *d_sync = nullptr;         // sweeps: what the workgroups share, [HX_SYNC_WORDS], 0 between launches
     unsigned long long *d_acc = nullptr;   // commit accumulators, [3 * HX_MAX_INSTANCES]
     int32_t *d_ticket = nullptr;           // commit: workgroups that have delivered their sums; 0 between launches
     int32_t *d_dpart = nullptr;            // decode-stage free list and per-group partial results, dpart_cap words
@@ -74,7 +74,8 @@ struct hx_ctx {
     HxDagStore dag;
 };
 
-constexpr int HX_MAX_SWEEP_FLAGS = 4096;
+constexpr int HX_SWEEP_LIMIT = 4096;      // max_sweeps is below it
+constexpr int HX_SYNC_WORDS = 66;
 
 inline int hx_fail(hx_ctx *ctx, int code, const char *fmt, ...)
 {

@@ -28,7 +28,7 @@ int create_fail(const char *what, hipError_t e)
     return HX_ERR_DEVICE;
 }
 
-__global__ void hx_clear_status_kernel(int32_t *status) { *status = 0; }
+__global__ void hx_clear_status_kernel(int32_t *status) { status[threadIdx.x] = 0; }      // a thread per word
 
 struct CommitArgs {
     int C, P, D;
@@ -338,8 +338,8 @@ extern "C" int hx_ctx_create(hx_ctx **out, int device)
     e = hipMalloc((void **)&ctx->d_status, sizeof(int32_t));
     if (e == hipSuccess) { what = "hipHostMalloc(status)"; e = hipHostMalloc((void **)&ctx->h_status, sizeof(int32_t), hipHostMallocDefault); }
     if (e == hipSuccess) { what = "hipMalloc(tables)"; e = hipMalloc((void **)&ctx->d_prep, sizeof(HxPrepTables)); }
-    if (e == hipSuccess) { what = "hipMalloc(flags)"; e = hipMalloc((void **)&ctx->d_flags, HX_MAX_SWEEP_FLAGS * sizeof(int32_t)); }
-    if (e == hipSuccess) { what = "hipMalloc(sync)"; e = hipMalloc((void **)&ctx->d_sync, 4 * sizeof(int32_t)); }
+    if (e == hipSuccess) { what = "hipMalloc(report)"; e = hipMalloc((void **)&ctx->d_report, HX_VALIDATE_FIELDS * sizeof(int32_t)); }
+    if (e == hipSuccess) { what = "hipMalloc(sync)"; e = hipMalloc((void **)&ctx->d_sync, HX_SYNC_WORDS * sizeof(int32_t)); }
     if (e == hipSuccess) { what = "hipMalloc(ticket)"; e = hipMalloc((void **)&ctx->d_ticket, sizeof(int32_t)); }
     if (e == hipSuccess) { what = "hipMalloc(accumulators)"; e = hipMalloc((void **)&ctx->d_acc, 3 * HX_MAX_INSTANCES * sizeof(unsigned long long)); }
     if (e == hipSuccess && device < HX_MAX_DEVICES) {     // set-up for hx_commit_static on this device
@@ -355,7 +355,7 @@ extern "C" int hx_ctx_create(hx_ctx **out, int device)
         hx_commit_clear_kernel<<<(3 * HX_MAX_INSTANCES + 255) / 256, 256, 0, nullptr>>>(z);
         hx_clear_status_kernel<<<1, 1, 0, nullptr>>>(ctx->d_status);
         hx_clear_status_kernel<<<1, 1, 0, nullptr>>>(ctx->d_ticket);
-        for (int i = 0; i < 4; ++i) hx_clear_status_kernel<<<1, 1, 0, nullptr>>>(ctx->d_sync + i);
+        hx_clear_status_kernel<<<1, HX_SYNC_WORDS, 0, nullptr>>>(ctx->d_sync);
         e = hipGetLastError();
     }
     if (e == hipSuccess) { what = "hipStreamSynchronize"; e = hipStreamSynchronize(nullptr); }
@@ -375,7 +375,7 @@ extern "C" int hx_ctx_destroy(hx_ctx *ctx)
     if (ctx->d_status) (void)hipFree(ctx->d_status);
     if (ctx->h_status) (void)hipHostFree(ctx->h_status);
     if (ctx->d_prep) (void)hipFree(ctx->d_prep);
-    if (ctx->d_flags) (void)hipFree(ctx->d_flags);
+    if (ctx->d_report) (void)hipFree(ctx->d_report);
     if (ctx->d_sync) (void)hipFree(ctx->d_sync);
     if (ctx->d_ticket) (void)hipFree(ctx->d_ticket);
     if (ctx->d_acc) (void)hipFree(ctx->d_acc);
@@ -527,16 +527,16 @@ extern "C" int hx_validate_round(hx_ctx *ctx, const hx_calls *calls, const hx_pr
     ValidateArgs a{C, P, D, T, n_nodes, n_wf, calls->L_in, calls->L_out, calls->node, calls->wf, calls->elapsed,
                    pre->flops, pre->hbm_bw, pre->backlog_tok, pre->type,
                    dec->flops, dec->hbm_bw, dec->used_tok, dec->cap_tok, dec->batch, dec->qd_tok, dec->type,
-                   links->bw, links->latency, ctx->d_flags};
+                   links->bw, links->latency, ctx->d_report};
     int n = C > P ? C : P;
     n = n > D ? n : D;
     n = n > T * T ? n : T * T;
     int grid = (n + 255) / 256;
     grid = grid > ctx->num_cu * 4 ? ctx->num_cu * 4 : grid;
-    hx_validate_clear_kernel<<<1, 256, 0, stream>>>(ctx->d_flags);
+    hx_validate_clear_kernel<<<1, 256, 0, stream>>>(ctx->d_report);
     hx_validate_kernel<<<grid, 256, 0, stream>>>(a);
     if (int rc = hx_check_launch(ctx, "hx_validate_kernel")) return rc;
-    HX_HIP(ctx, hipMemcpyAsync(report, ctx->d_flags, HX_VALIDATE_FIELDS * sizeof(int32_t), hipMemcpyDeviceToHost, stream));
+    HX_HIP(ctx, hipMemcpyAsync(report, ctx->d_report, HX_VALIDATE_FIELDS * sizeof(int32_t), hipMemcpyDeviceToHost, stream));
     HX_HIP(ctx, hipStreamSynchronize(stream));
     static const char *const what[HX_VALIDATE_FIELDS] = {
         "negative L_in", "negative L_out", "node outside 0..n_nodes-1", "wf outside 0..n_wf-1", "elapsed negative or not finite",

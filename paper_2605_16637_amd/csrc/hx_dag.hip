@@ -68,33 +68,39 @@ void hx_cp_cost_kernel(CpArgs a, NodeCostArgs nc, int wpb)
 // ---- critical path, level-synchronous sweeps ------------------------------------------
 //
 // Successors may be anywhere, but in nearly every graph they lie in their node's workflow, or near it.  A workgroup takes a
-// slice of whole workflows into LDS and sweeps there, a barrier a sweep, until nothing changes.  Whatever it cannot
-// finish by itself -- an edge out of the slice, a workflow that does not fit, a malformed row, a cycle, the limit -- makes
-// it raise `again`, and the kernel that follows then does the whole graph over, grid-wide, a sweep at a time.  Both
-// reach the one fixed point there is (values only grow towards it), the same bits.  20000 nodes in 1000 workflows of depth
-// 12, 14 sweeps allowed, with the node costs: 73 -> 27 us (a launch a sweep before); 1.8 million in 90000: 280 -> 53.
+// slice of whole workflows into LDS and sweeps there, a barrier a sweep, until nothing changes.  Where that does not
+// finish the graph a second kernel sweeps it as a whole, from the values the slices left if only edges between them (or
+// malformed rows) are missing, from the beginning if some nodes have no value yet (a workflow that does not fit, nodes of
+// no workflow) or a slice was still changing at the limit (a cycle, or too small a limit).  Values only grow, towards
+// the one fixed point there is, so both ways and every order give the same bits.
+// Against a launch a sweep, 14 sweeps allowed: 20000 nodes in 1000 workflows of depth 12 64 -> 21 us, 1.8 million in
+// 90000 276 -> 42; with one edge into another slice 64 -> 26 (20000 nodes) and 96 -> 36 (400000); every successor
+// anywhere in the graph 79 -> 71 and 173 -> 177.
 constexpr int CS_THREADS = 256;
 constexpr int CS_NMAX = 1024;         // nodes of a slice
 constexpr int CS_NPT = CS_NMAX / CS_THREADS;
 
-__global__ __launch_bounds__(CS_THREADS) void hx_cp_sweep_slices_kernel(CpArgs a, int wpb, int max_sweeps, int32_t *again)
+// words of the context's d_sync, all 0 between launches; the counter of arrivals and the word that is polled have cache
+// lines of their own (polls would hold the arrivals up)
+enum : int { SY_AGAIN = 0, SY_OVER = 1, SY_LEFT = 2, SY_STUCK = 3, SY_COUNT = 32, SY_GO = 64 };
+static_assert(SY_GO + 2 == HX_SYNC_WORDS, "two words each for the last two");
+
+__global__ __launch_bounds__(CS_THREADS) void hx_cp_sweep_slices_kernel(CpArgs a, int wpb, int max_sweeps, int32_t *sync)
 {
     __shared__ int2 s_val[CS_NMAX + 1];                    // (rem, level) of node n0 + i at i + 1; 0: the empty successor
     __shared__ int s_changed[3];
     const int tid = threadIdx.x;
     const int w1 = min(((int)blockIdx.x + 1) * wpb, a.n_wf);
-    bool odd = false;
-    if (tid == 0) {
-        s_val[0] = make_int2(0, -1);
-        // nodes that belong to no workflow are swept too
-        if (blockIdx.x == 0) odd = a.wf_ptr[0] != 0 || a.wf_ptr[a.n_wf] != a.n_nodes;
-    }
+    bool odd = false, over = false;                        // over: not every node has been given a value
+    if (tid == 0) s_val[0] = make_int2(0, -1);
+    // nodes that belong to no workflow are swept too
+    if (blockIdx.x == 0) over = a.wf_ptr[0] != 0 || a.wf_ptr[a.n_wf] != a.n_nodes;
     for (int wa = (int)blockIdx.x * wpb; wa < w1;) {
         // the run [wa, wb): as many of the slice's workflows as fit
         int wb = w1;
         const int n0 = a.wf_ptr[wa];
         int n1 = a.wf_ptr[wb];
-        if (n0 < 0 || n1 < n0 || n1 > a.n_nodes) { odd = true; break; }
+        if (n0 < 0 || n1 < n0 || n1 > a.n_nodes) { over = true; break; }
         if (n1 - n0 > CS_NMAX) {
             int lo = wa, hi = wb;
             while (hi - lo > 1) {
@@ -104,7 +110,7 @@ __global__ __launch_bounds__(CS_THREADS) void hx_cp_sweep_slices_kernel(CpArgs a
             }
             wb = max(lo, wa + 1);
             n1 = a.wf_ptr[wb];
-            if (n1 < n0 || n1 > a.n_nodes || n1 - n0 > CS_NMAX) { odd = true; break; }
+            if (n1 < n0 || n1 > a.n_nodes || n1 - n0 > CS_NMAX) { over = true; break; }
         }
         const int nn = n1 - n0;
         float c[CS_NPT];
@@ -138,8 +144,9 @@ __global__ __launch_bounds__(CS_THREADS) void hx_cp_sweep_slices_kernel(CpArgs a
         __syncthreads();
         // Values another wavefront writes meanwhile may or may not be seen: they only grow, and a sweep in which nothing
         // was written has read final values.
+        const int limit = min(max_sweeps, nn + 1);         // (only a cycle takes more than nn + 1)
         int s = 1;
-        for (; s <= max_sweeps; ++s) {
+        for (; s <= limit; ++s) {
             bool changed = false;
 #pragma unroll
             for (int k = 0; k < CS_NPT; ++k) {
@@ -163,7 +170,7 @@ __global__ __launch_bounds__(CS_THREADS) void hx_cp_sweep_slices_kernel(CpArgs a
             __syncthreads();
             if (s_changed[s % 3] == 0) break;
         }
-        if (s > max_sweeps) odd = true;                    // still changing: a cycle, or the limit is too small
+        if (s > limit) over = true;                        // still changing: a cycle, or the limit is too small
 #pragma unroll
         for (int k = 0; k < CS_NPT; ++k) {
             const int i = k * CS_THREADS + tid;
@@ -182,122 +189,208 @@ __global__ __launch_bounds__(CS_THREADS) void hx_cp_sweep_slices_kernel(CpArgs a
         __syncthreads();                                   // the next run stages over these values
         wa = wb;
     }
-    if (odd) __hip_atomic_store(again, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // one store a workgroup (one a wavefront: 130 us with 590 workgroups)
+    over = __syncthreads_or(over);
+    odd = __syncthreads_or(odd);
+    if (tid == 0 && over) sync[SY_OVER] = 1;
+    if (tid == 0 && (over || odd)) sync[SY_AGAIN] = 1;
 }
 
-// one sweep over the nodes first, first + step, ..: every node pulls from its successors
-__device__ __forceinline__ bool hx_cp_sweep(const CpArgs &a, int first, int step)
+// Grid-wide sweeps: every node pulls from its successors.  What bounds them is latency, a chain of memory round trips a sweep:
+// a thread takes CG_NPT nodes together, a step between them, and keeps their rows, successors and values in registers
+// from sweep to sweep where that covers the graph, so that a sweep is the successors' values and no more.
+constexpr int CG_THREADS = 512;
+constexpr int CG_NPT = 4;
+
+struct CgNodes {
+    float c[CG_NPT], tail[CG_NPT];
+    int lvl[CG_NPT], ra[CG_NPT], rb[CG_NPT], id[CG_NPT][CP_DEG];      // id: -1 where there is no successor
+    bool left[CG_NPT];                                  // more successors than places, or a row at the very end of the id array
+};
+
+// the nodes v0, v0 + step, ..: rows and successors; tail and level as they were stored, or 0 (fresh)
+__device__ __forceinline__ void hx_cp_nodes_load(const CpArgs &a, CgNodes &q, int v0, int step, bool fresh)
+{
+    bool bad = false;
+#pragma unroll
+    for (int k = 0; k < CG_NPT; ++k) {
+        const long long at = v0 + (long long)k * step;
+        const bool in = at < a.n_nodes;
+        const int v = in ? (int)at : 0;
+        q.c[k] = in ? a.cost[v] : 0.0f;
+        q.ra[k] = in ? a.row_ptr[v] : 0; q.rb[k] = in ? a.row_ptr[v + 1] : 0;
+        q.tail[k] = in && !fresh ? __hip_atomic_load(&a.tail[v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.0f;
+        q.lvl[k] = in && !fresh ? __hip_atomic_load(&a.level[v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+    }
+#pragma unroll
+    for (int k = 0; k < CG_NPT; ++k) {
+        if (q.ra[k] < 0 || q.rb[k] > a.n_edges || q.ra[k] > q.rb[k]) { bad = true; q.ra[k] = q.rb[k] = 0; }
+        const int deg = q.rb[k] - q.ra[k];
+        q.left[k] = deg > CP_DEG || (deg > 0 && q.ra[k] > a.n_edges - CP_DEG);
+        int id[CP_DEG] = {0, 0, 0, 0};
+        if (a.n_edges >= CP_DEG) __builtin_memcpy(id, a.col + min(q.ra[k], a.n_edges - CP_DEG), sizeof id);
+#pragma unroll
+        for (int j = 0; j < CP_DEG; ++j) {
+            const bool own = !q.left[k] && j < deg, fine = (unsigned)id[j] < (unsigned)a.n_nodes;
+            bad = bad || (own && !fine);
+            q.id[k][j] = own && fine ? id[j] : -1;
+        }
+    }
+    if (bad) hx_raise(a.status, HX_ERR_INDEX);
+}
+
+// One sweep over those nodes.  All that is written, and all that is read of what another thread writes, goes by device-scope
+// atomics (also what no other workgroup reads in passing: nothing may lie in an XCD's cache when the last one redoes it).
+__device__ __forceinline__ bool hx_cp_nodes_sweep(const CpArgs &a, CgNodes &q, int v0, int step)
 {
     bool changed = false, bad = false;
-    for (int v = first; v < a.n_nodes; v += step) {
-        int r0 = a.row_ptr[v], r1 = a.row_ptr[v + 1];
-        if (r0 < 0 || r1 > a.n_edges || r0 > r1) { bad = true; continue; }
-        float tl = 0.0f;
-        int lv = 0;
-        for (int e = r0; e < r1; ++e) {
-            int u = a.col[e];
+    float r[CG_NPT][CP_DEG];
+    int l[CG_NPT][CP_DEG];
+#pragma unroll
+    for (int k = 0; k < CG_NPT; ++k) {
+#pragma unroll
+        for (int j = 0; j < CP_DEG; ++j) {
+            const int u = q.id[k][j];
+            r[k][j] = 0.0f; l[k][j] = -1;
+            if (u >= 0) {
+                r[k][j] = __hip_atomic_load(&a.rem[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                l[k][j] = __hip_atomic_load(&a.level[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < CG_NPT; ++k) {
+        float tl = fmaxf(fmaxf(fmaxf(r[k][0], r[k][1]), fmaxf(r[k][2], r[k][3])), 0.0f);
+        int lv = max(max(l[k][0], l[k][1]), max(l[k][2], l[k][3])) + 1;
+        if (q.left[k]) for (int e = q.ra[k]; e < q.rb[k]; ++e) {
+            const int u = a.col[e];
             if (u < 0 || u >= a.n_nodes) { bad = true; continue; }
             tl = fmaxf(tl, __hip_atomic_load(&a.rem[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
             lv = max(lv, __hip_atomic_load(&a.level[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1);
         }
-        // a level beyond the node count can only come from a cycle: stop growing
-        lv = min(lv, a.n_nodes);
-        if (tl != a.tail[v] || lv != __hip_atomic_load(&a.level[v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
+        lv = min(lv, a.n_nodes);                        // a level beyond the node count can only come from a cycle: stop growing
+        if (tl != q.tail[k] || lv != q.lvl[k]) {        // (never without a node: it has no successors)
+            const int v = v0 + k * step;
             changed = true;
-            a.tail[v] = tl;
+            q.tail[k] = tl; q.lvl[k] = lv;
+            __hip_atomic_store(&a.tail[v], tl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __hip_atomic_store(&a.level[v], lv, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(&a.rem[v], a.cost[v] + tl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(&a.rem[v], q.c[k] + tl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
     if (bad) hx_raise(a.status, HX_ERR_INDEX);
     return changed;
 }
 
+// sweep s (1, 2, ..) over the thread's nodes of the whole graph; over: the first begins with nothing but the costs
+__device__ __forceinline__ bool hx_cp_sweep(const CpArgs &a, CgNodes &q, int first, int step, int s, bool over)
+{
+    const bool kept = a.n_nodes <= (long long)step * CG_NPT;      // all of them are in q from the first sweep on
+    bool changed = false;
+    for (long long v0 = first; v0 < a.n_nodes; v0 += (long long)step * CG_NPT) {
+        if (!kept || s == 1) hx_cp_nodes_load(a, q, (int)v0, step, s == 1 && over);
+        changed = hx_cp_nodes_sweep(a, q, (int)v0, step) || changed;
+    }
+    return changed;
+}
+
 __device__ __forceinline__ void hx_cp_sweep_init(const CpArgs &a, int first, int step)
 {
     for (int v = first; v < a.n_nodes; v += step) {
-        a.tail[v] = 0.0f;
+        __hip_atomic_store(&a.tail[v], 0.0f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __hip_atomic_store(&a.rem[v], a.cost[v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __hip_atomic_store(&a.level[v], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 
-// a wavefront per workflow: thread `first` of `step`, both multiples of whole wavefronts but for the lane
+// A workflow's horizon by 16 lanes, or by a wavefront where workflows are large: thread `first` of `step`, both multiples
+// of whole wavefronts but for the lane.
 __device__ __forceinline__ void hx_cp_sweep_horizons(const CpArgs &a, int first, int step)
 {
-    const int lane = first & (HX_WAVE - 1);
-    for (int w = first / HX_WAVE; w < a.n_wf; w += step / HX_WAVE) {
-        const int s = a.wf_ptr[w], e = a.wf_ptr[w + 1];
+    const bool large = a.n_nodes > 64LL * a.n_wf;
+    const int G = large ? HX_WAVE : 16, sub = first & (G - 1);
+    // (whole wavefronts go round together: the reductions take every lane)
+    for (int w0 = (first & ~(HX_WAVE - 1)) / G; w0 < a.n_wf; w0 += step / G) {
+        const int w = w0 + (first & (HX_WAVE - 1)) / G;
+        const int s = w < a.n_wf ? a.wf_ptr[w] : 0, e = w < a.n_wf ? a.wf_ptr[w + 1] : 0;
         float h = 0.0f;
         if (s < 0 || e > a.n_nodes || s > e) hx_raise(a.status, HX_ERR_INDEX);
         else {
 #pragma unroll 4
-            for (int v = s + lane; v < e; v += HX_WAVE) h = fmaxf(h, __hip_atomic_load(&a.rem[v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+            for (int v = s + sub; v < e; v += G) h = fmaxf(h, __hip_atomic_load(&a.rem[v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
         }
-        h = hx_wave_max(h);
-        if (lane == 0) a.horizon[w] = h;
+        h = large ? hx_wave_max(h) : -hx_lanes_min(-h, 16);
+        if (sub == 0 && w < a.n_wf) __hip_atomic_store(&a.horizon[w], h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 
-// words of the context's d_sync, all 0 between launches
-enum : int { SY_AGAIN = 0, SY_COUNT = 1, SY_STUCK = 2, SY_LEFT = 3 };
-
-constexpr int CG_THREADS = 1024;
 constexpr int CG_POLLS = 1 << 18;     // some 0.2 s
 
-// All workgroups have arrived `target / gridDim` times.  The wait is bounded: workgroups that are not on the chip yet
-// (it may be full of other work) are waited for a while, then everybody gives up (false).
-__device__ __forceinline__ bool hx_grid_wait(int32_t *sync, int target)
+// All workgroups meet; *any: one of them came with `mark`.  target: arrivals so far, theirs included; seen: what the
+// last meeting left (0 before the first).  The wait is bounded: workgroups that are not on the chip yet (it may be full
+// of other work) are waited for a while, then everybody gives up (false).
+//
+// Arrivals and marks are counted in the halves of one word; whoever completes the count passes it on to those who wait.
+// No cache is written back or invalidated here (by every wavefront 60 us a meeting of 256 workgroups, by one wavefront
+// of each 7): what passes from one workgroup to another inside the kernel -- rem, level and these words -- is stored and
+// loaded by device-scope atomics alone, which the caches of an XCD do not hold back, and a store has arrived when
+// its wavefront has waited for it.
+__device__ __forceinline__ bool hx_grid_wait(int32_t *sync, unsigned target, bool mark, bool *any, unsigned long long *seen)
 {
-    __shared__ int s_ok;
-    __threadfence();                                       // every wavefront's own stores are on their way out before it arrives
-    __syncthreads();
+    __shared__ unsigned long long s_go;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // every wavefront's own stores have arrived
+    mark = __syncthreads_or(mark);
+    if (gridDim.x == 1) { *any = mark; return true; }
     if (threadIdx.x == 0) {
-        atomicAdd(&sync[SY_COUNT], 1);
-        int ok = 1;
-        for (int i = 0; __hip_atomic_load(&sync[SY_COUNT], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target; ++i) {
-            if (i >= CG_POLLS || __hip_atomic_load(&sync[SY_STUCK], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
-                __hip_atomic_store(&sync[SY_STUCK], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                ok = 0;
-                break;
+        unsigned long long *const count = (unsigned long long *)(sync + SY_COUNT), *const go = (unsigned long long *)(sync + SY_GO);
+        const unsigned long long mine = 1ull + ((unsigned long long)mark << 32);
+        unsigned long long now = __hip_atomic_fetch_add(count, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + mine;
+        if ((unsigned)now == target) __hip_atomic_store(go, now, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        else
+            for (int i = 0; (unsigned)(now = __hip_atomic_load(go, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) != target; ++i) {
+                if (i >= CG_POLLS || ((i & 15) == 15 && __hip_atomic_load(&sync[SY_STUCK], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)) {
+                    __hip_atomic_store(&sync[SY_STUCK], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    now = 0;
+                    break;
+                }
+                __builtin_amdgcn_s_sleep(2);
             }
-            __builtin_amdgcn_s_sleep(2);
-        }
-        __threadfence();
-        s_ok = ok;
+        s_go = now;
     }
     __syncthreads();
-    return s_ok != 0;
+    const unsigned long long now = s_go;
+    *any = (now >> 32) != (*seen >> 32);
+    *seen = now;
+    return now != 0;
 }
 
-// The whole graph, if a slice could not be finished by itself: at most one workgroup per compute unit, a grid-wide wait a
-// sweep (a launch per sweep cost as much as the sweep, also for graphs that need none).  Should the workgroups not come
-// together, the last one to leave does everything alone.
-__global__ __launch_bounds__(CG_THREADS) void hx_cp_sweep_all_kernel(CpArgs a, int max_sweeps, int32_t *flags, int32_t *sync)
+// The whole graph, where the slices could not finish it: at most one workgroup per compute unit, a meeting of all of them a
+// sweep (2 us with 40 workgroups, 3 with 256; a launch per sweep costs more than that also for graphs that need none).
+// Should the workgroups not come together, the last one to leave does everything alone.
+__global__ __launch_bounds__(CG_THREADS) void hx_cp_sweep_all_kernel(CpArgs a, int max_sweeps, int32_t *sync)
 {
-    __shared__ int s_last, s_changed;
-    if (__hip_atomic_load(&sync[SY_AGAIN], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0) return;
+    __shared__ int s_last;
+    if (sync[SY_AGAIN] == 0) return;
     const int first = blockIdx.x * CG_THREADS + threadIdx.x, step = gridDim.x * CG_THREADS;
-    for (int i = first; i <= max_sweeps; i += step) __hip_atomic_store(&flags[i], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    hx_cp_sweep_init(a, first, step);
-    bool here = hx_grid_wait(sync, gridDim.x), more = true;
-    int arrived = gridDim.x;
-    for (int s = 1; here && more && s <= max_sweeps; ++s) {
-        if (hx_cp_sweep(a, first, step)) __hip_atomic_store(&flags[s], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        arrived += gridDim.x;
-        here = hx_grid_wait(sync, arrived);
-        more = __hip_atomic_load(&flags[s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+    const bool over = sync[SY_OVER] != 0;
+    CgNodes q;
+    bool here = true, more = true;
+    unsigned arrived = 0;
+    unsigned long long seen = 0;
+    if (over) {
+        hx_cp_sweep_init(a, first, step);
+        here = hx_grid_wait(sync, arrived += gridDim.x, false, &more, &seen);
+        more = true;
     }
+    for (int s = 1; here && more && s <= max_sweeps; ++s)
+        here = hx_grid_wait(sync, arrived += gridDim.x, hx_cp_sweep(a, q, first, step, s, over), &more, &seen);
     if (here) {
         hx_cp_sweep_horizons(a, first, step);
         if (more && first == 0) hx_raise(a.status, HX_ERR_NOT_DAG);
     }
-    __threadfence();
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    if (threadIdx.x == 0) {
-        s_last = atomicAdd(&sync[SY_LEFT], 1) == (int)gridDim.x - 1;
-        __threadfence();
-    }
+    if (threadIdx.x == 0) s_last = __hip_atomic_fetch_add(&sync[SY_LEFT], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1;
     __syncthreads();
     if (!s_last) return;
     if (__hip_atomic_load(&sync[SY_STUCK], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
@@ -306,19 +399,15 @@ __global__ __launch_bounds__(CG_THREADS) void hx_cp_sweep_all_kernel(CpArgs a, i
         for (int s = 1; more && s <= max_sweeps; ++s) {
             __threadfence();
             __syncthreads();
-            if (threadIdx.x == 0) s_changed = 0;
-            __syncthreads();
-            if (hx_cp_sweep(a, threadIdx.x, CG_THREADS)) s_changed = 1;
-            __threadfence();
-            __syncthreads();
-            more = s_changed != 0;
+            more = __syncthreads_or(hx_cp_sweep(a, q, threadIdx.x, CG_THREADS, s, true));
         }
+        __threadfence();
         __syncthreads();
         hx_cp_sweep_horizons(a, threadIdx.x, CG_THREADS);
         if (more && threadIdx.x == 0) hx_raise(a.status, HX_ERR_NOT_DAG);
     }
     __syncthreads();
-    if (threadIdx.x < 4) __hip_atomic_store(&sync[threadIdx.x], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (threadIdx.x < HX_SYNC_WORDS) __hip_atomic_store(&sync[threadIdx.x], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // ---- incremental append ------------------------------------------------------------------
@@ -514,7 +603,7 @@ extern "C" int hx_critical_path(hx_ctx *ctx, int32_t n_nodes, int32_t n_edges,
 {
     if (!ctx) return HX_ERR_INVALID_ARG;
     HX_REQUIRE(ctx, n_nodes >= 0 && n_edges >= 0 && n_wf >= 0 && max_sweeps >= 0, HX_ERR_INVALID_ARG, "negative size");
-    HX_REQUIRE(ctx, max_sweeps < HX_MAX_SWEEP_FLAGS, HX_ERR_SHAPE, "max_sweeps beyond %d", HX_MAX_SWEEP_FLAGS - 1);
+    HX_REQUIRE(ctx, max_sweeps < HX_SWEEP_LIMIT, HX_ERR_SHAPE, "max_sweeps beyond %d", HX_SWEEP_LIMIT - 1);
     HX_REQUIRE(ctx, succ_row_ptr && wf_ptr, HX_ERR_INVALID_ARG, "NULL row_ptr or wf_ptr");
     HX_REQUIRE(ctx, n_edges == 0 || succ_col_idx, HX_ERR_INVALID_ARG, "NULL col_idx");
     HX_REQUIRE(ctx, n_nodes == 0 || (node_cost && rem && tail && level), HX_ERR_INVALID_ARG, "NULL node array");
@@ -541,13 +630,12 @@ extern "C" int hx_critical_path(hx_ctx *ctx, int32_t n_nodes, int32_t n_edges,
     const long long spread = (n_wf + ctx->num_cu - 1) / ctx->num_cu;
     fit = fit > spread ? spread : fit;
     const int wpb = (int)(fit < 1 ? 1 : fit);
-    if (n_wf > 0) hx_cp_sweep_slices_kernel<<<(n_wf + wpb - 1) / wpb, CS_THREADS, 0, stream>>>(a, wpb, max_sweeps, ctx->d_sync + SY_AGAIN);
-    else hx_fill_i32_kernel<<<1, 64, 0, stream>>>(ctx->d_sync + SY_AGAIN, 1, 1);
+    hx_cp_sweep_slices_kernel<<<n_wf > 0 ? (n_wf + wpb - 1) / wpb : 1, CS_THREADS, 0, stream>>>(a, wpb, max_sweeps, ctx->d_sync);
     if (int rc = hx_check_launch(ctx, "hx_cp_sweep_slices_kernel")) return rc;
     const long long most = n_nodes > n_wf ? n_nodes : n_wf;      // (workflows may be empty)
     int grid = (int)((most + CG_THREADS - 1) / CG_THREADS);
     grid = grid > ctx->num_cu ? ctx->num_cu : (grid < 1 ? 1 : grid);
-    hx_cp_sweep_all_kernel<<<grid, CG_THREADS, 0, stream>>>(a, max_sweeps, ctx->d_flags, ctx->d_sync);
+    hx_cp_sweep_all_kernel<<<grid, CG_THREADS, 0, stream>>>(a, max_sweeps, ctx->d_sync);
     return hx_check_launch(ctx, "hx_cp_sweep_all_kernel");
 }
 

@@ -491,3 +491,58 @@ def test_sweeps_by_slice_and_over_the_whole_graph(ctx, kind):
     for _ in range(2):
         assert_cp_bit_exact(gpu_cp(ctx, row, col, cost32, wf_ptr, max_sweeps=int(want[2].max()) + 2), want)
     assert_cp_bit_exact(gpu_cp(ctx, row, col, cost32, wf_ptr, max_sweeps=4000), want)
+
+
+# the sweeps over the whole graph at the sizes where they change: one workgroup or several, nodes kept in registers from sweep
+# to sweep or read again (more than 4 per thread of 256 workgroups of 512), horizons by 16 lanes or by a wavefront;
+# successors anywhere, or a chain of workflows each of which hangs on the next
+@pytest.mark.parametrize("n_wf,size", [(7, 3), (25, 20), (26, 20), (300, 20), (60, 200), (26300, 20)])
+@pytest.mark.parametrize("kind", ["anywhere", "chain of workflows", "one workflow beside"])
+def test_sweeps_over_the_whole_graph_at_its_sizes(ctx, n_wf, size, kind):
+    rng = np.random.default_rng(n_wf + size)
+    n = n_wf * size
+    if kind == "one workflow beside":                        # a workflow that fits no slice: everything from the beginning
+        n += 1100
+    wf_ptr = np.append(np.arange(n_wf) * size, [n_wf * size, n][n > n_wf * size:]).astype(np.int32)
+    at = rng.permutation(n) if kind == "anywhere" else np.arange(n)
+    i = np.arange(n - 1)
+    deg = rng.integers(0, 4, n - 1)                          # up to three successors, later along `at`
+    src = np.repeat(i, deg)
+    dst = src + (rng.integers(n // 12 + 1, n // 6 + 2, src.size) if kind == "anywhere" else rng.integers(1, 4, src.size))
+    keep = dst < n
+    if kind != "anywhere":
+        keep &= np.minimum(src // size, n_wf) == np.minimum(dst // size, n_wf)      # inside a workflow
+    src, dst = src[keep], dst[keep]
+    if kind == "chain of workflows":
+        last = np.arange(1, min(n_wf, 12)) * size - 1
+        src, dst = np.append(src, last), np.append(dst, last + 1)
+    edges = np.unique(np.stack([at[src], at[dst]], 1), axis=0)
+    row = np.zeros(n + 1, np.int32); row[1:] = np.cumsum(np.bincount(edges[:, 0], minlength=n))
+    col = edges[:, 1].astype(np.int32)
+    cost32 = rng.uniform(0.1, 2.0, n).astype(np.float32)
+    want = o.critical_path(row, col, cost32.astype(np.float64), wf_ptr, round_f32=True)
+    limit = int(want[2].max()) + 2
+    assert 2 < limit < 2000
+    for _ in range(2):
+        assert_cp_bit_exact(gpu_cp(ctx, row, col, cost32, wf_ptr, max_sweeps=limit), want)
+
+
+def test_sweeps_report_a_cycle_between_slices(ctx):
+    from paper_2605_16637_amd import binding
+    n_wf, size = 400, 5
+    n = n_wf * size
+    # every workflow a chain; the first hangs on the last and the last on the first
+    succ = [[v + 1] if (v + 1) % size else [] for v in range(n)]
+    succ[size - 1], succ[n - 1] = [n - size], [0]
+    row = np.zeros(n + 1, np.int32); row[1:] = np.cumsum([len(x) for x in succ])
+    col = np.array([u for x in succ for u in x], np.int32)
+    cost32 = np.ones(n, np.float32)
+    gpu_cp(ctx, row, col, cost32, np.arange(n_wf + 1) * size, max_sweeps=50, check=False)
+    with pytest.raises(binding.HxError) as e:
+        ctx.hx_stream_status()
+    assert e.value.code == -3
+    # without the way back it is a graph of depth 9
+    row[n:] -= 1
+    want = o.critical_path(row, col[:-1], cost32.astype(np.float64), np.arange(n_wf + 1) * size, round_f32=True)
+    assert want[2].max() == 2 * size - 1
+    assert_cp_bit_exact(gpu_cp(ctx, row, col[:-1], cost32, np.arange(n_wf + 1) * size, max_sweeps=2 * size + 1), want)
