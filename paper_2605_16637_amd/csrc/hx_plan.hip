@@ -36,9 +36,10 @@ __device__ __forceinline__ unsigned long long hx_rank_key64(unsigned bits, int i
 
 // rank[c] = number of calls ahead of c: larger ratio, or equal ratio and lower index.  Short queues: a workgroup ranks 64
 // calls, a lane each, its wavefronts comparing them with a share of the queue each; one launch, nothing to
-// clear (64 calls 6.5 -> 3.9 us; 2048 calls 6.4 -> 6.3, where two launches are as good).
+// clear.  Launches back to back, two of them before and one now: 64 calls 4.7 -> 3.1 us, 1024 5.3 -> 4.8; 1200 5.2 either
+// way, 2048 would be 7.1 instead of 5.6.
 constexpr int RANK_THREADS = 1024;
-constexpr int RANK_DIRECT = 2048;
+constexpr int RANK_DIRECT = 1024;
 
 __global__ __launch_bounds__(RANK_THREADS) void hx_rank_direct_kernel(const float *ratio, int32_t *rank, int C)
 {

@@ -62,7 +62,7 @@ def test_rank_of_unusual_ratios(ctx, C, kind):
     assert np.array_equal(rank.cpu().numpy(), want)
 
 
-@pytest.mark.parametrize("C", [40, 3000, 20000])      # one launch; all pairs; by buckets
+@pytest.mark.parametrize("C", [40, 1024, 3000, 20000])      # one launch, at most; all pairs; by buckets
 def test_rank_puts_a_ratio_that_is_no_number_with_the_infinite(ctx, C):
     import torch
     rng = np.random.default_rng(C)
