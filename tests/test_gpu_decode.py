@@ -462,8 +462,10 @@ def test_decode_greedy_with_calls_that_decode_nothing(ctx, Q, D, stride, res, pl
 def plan_with_calls_that_decode_nothing(ctx, seed, Q, D, stride, res, plan, extra):
     r, lock, iv = synth.make_decode_round("decode_tiny", seed, n_wf=max(8, Q // 4), Q=Q, D=D, T=min(4, D), stride=stride,
                                           n_resident=res, n_planned=plan, lock_fraction=0.2)
-    L, O = r.calls["L_in"], r.calls["L_out"].copy()
+    L, O = r.calls["L_in"].copy(), r.calls["L_out"].copy()
     O[::3] = 0
+    if seed % 2:
+        L[::6] = 0                           # no tokens at all
     rng = np.random.default_rng(seed)
     node = rng.permutation(Q).astype(np.int32); wf = rng.integers(0, 4, Q).astype(np.int32)
     elapsed = rng.uniform(0, 20, Q).astype(np.float32)
