@@ -93,6 +93,54 @@ def test_fused_search_ragged_shapes(ctx, C, P, D, T):
         assert (gp[1], gd[1]) == (-1, -1) and np.isinf(gc[1])
 
 
+def assert_search_equals_selection(ctx, C, P, D, L, O, pre, dec, links):
+    import torch
+    from paper_2605_16637_amd import binding
+    calls = binding.to_device(dict(n=C, L_in=L, L_out=O))
+    dp, dd, dl = binding.to_device(dict(pre, n=P)), binding.to_device(dict(dec, n=D)), binding.to_device(links)
+    gp, gd, gc = fused(ctx, synth.MODEL, calls, dp, dd, dl)
+    cost = torch.empty(C * P * D, device="cuda:0")
+    ctx.hx_score_placements(synth.MODEL, calls, dp, dd, dl, cost=cost)
+    bp, bd = (torch.empty(C, dtype=torch.int32, device="cuda:0") for _ in range(2))
+    bc = torch.empty(C, device="cuda:0")
+    ctx.hx_select(C, P, D, cost, bp, bd, bc)
+    ctx.hx_stream_status()
+    assert np.array_equal(gc, bc.cpu().numpy()) and np.array_equal(gp, bp.cpu().numpy()) and np.array_equal(gd, bd.cpu().numpy())
+
+
+# Ties between classes: all classes the same hardware behind the same links, classes the same two by two, and the same hardware
+# behind links of their own; 64 calls a workgroup (beyond 64 per compute unit), 32 and 8.
+@pytest.mark.parametrize("C,P,D,T", [(16500, 13, 9, 4), (33000, 5, 8, 8), (9000, 24, 17, 3), (70, 513, 511, 6), (33, 8, 8, 8)])
+@pytest.mark.parametrize("pool", ["classes alike", "alike by twos", "links of their own", "any", "few values"])
+def test_fused_search_with_ties_between_classes(ctx, C, P, D, T, pool):
+    rng = np.random.default_rng(C + 3 * P + D)
+    types, pre, dec, links = random_pool(rng, P, D, T)
+    L, O = synth.gen_lengths(rng, C)
+    O[::5] = 0
+    same = {"classes alike": np.zeros(T, int), "alike by twos": np.arange(T) // 2, "links of their own": np.zeros(T, int)}.get(pool)
+    if same is not None:
+        for t in (pre, dec):
+            for k in ("flops", "hbm_bw"):
+                t[k] = types[k][same[t["type"]]]
+            for k in ("backlog_tok", "used_tok", "batch", "qd_tok"):
+                if k in t:
+                    t[k][:] = 0
+        dec["cap_tok"][:] = 400000
+        if pool == "links of their own":
+            # the same hardware everywhere, two bandwidths: a tie between classes need not be one for every prefill instance
+            links["bw"] = np.where(rng.random((T, T)) < 0.5, 1e10, 4e10).astype(np.float32)
+            links["latency"] = None
+        else:
+            links["bw"] = links["bw"][same][:, same].copy()
+            links["latency"] = links["latency"][same][:, same].copy()
+    if pool == "few values":
+        pre["backlog_tok"][:] = rng.integers(0, 2, P) * 5000
+        dec["qd_tok"][:] = rng.integers(0, 3, D) * 4000
+        dec["used_tok"][:] = rng.integers(0, 2, D) * 40000
+        dec["batch"][:] = dec["used_tok"] // 2048
+    assert_search_equals_selection(ctx, C, P, D, L, O, pre, dec, links)
+
+
 # C just past the sizes at which a workgroup takes 8, 16, 32 and 64 calls on 256 compute units; pools around a wavefront's
 # share of instances and at the limits
 @pytest.mark.parametrize("C,P,D,T", [(1, 1, 1, 1), (9, 64, 63, 8), (2047, 3, 17, 2), (2049, 9, 33, 5), (4097, 17, 8, 8),
