@@ -212,8 +212,10 @@ __device__ __forceinline__ unsigned hx_alike_hash(float c1, float c2, int type, 
 // attains it with any of them, then the lowest d that does with that p.  For a decode instance that attains it, the
 // prefill instances that do so with it are those that arrive by R, the largest arrival whose candidate is still the
 // minimum; R is found by bisection over the bit patterns between the earliest arrival (which attains it) and the
-// minimum itself (no later arrival can), and of a class only its largest R matters.  thr: [kT] words of LDS of
-// the wavefront's own.
+// minimum itself (no later arrival can), begun close to where it must be, and of a class only its largest R matters.
+// (4096 calls on 64 + 64 idle instances, alike in four classes with faster links inside a class, so that this is every
+// call: 9.0 us; from end to end of that range, with the call read again from memory, 11.8; pair by pair 8.8.)
+// thr: [kT] words of LDS of the wavefront's own.
 __device__ __forceinline__ int2 hx_pair_of_tied(const HxCallF &cf, unsigned need, float best, int P, int D, const float4 *s_pre,
                                                 const float4 *s_dec, const int2 *s_dex, const float2 *s_link, const float *r_call,
                                                 int r_stride, int *thr, int lane)
@@ -230,9 +232,15 @@ __device__ __forceinline__ int2 hx_pair_of_tied(const HxCallF &cf, unsigned need
         const float r = r_call[x.y * r_stride];
         const bool hit = need < (unsigned)x.x && hx_candidate(r, t.x, dec) == best;
         int lo = __float_as_int(r), hi = hit ? __float_as_int(best) : lo;
+        auto attains = [&](int arrival) { return hx_candidate(__int_as_float(arrival), t.x, dec) <= best; };
+        // it is best - dec, give or take a rounding of the result: where both ends of that hold, a few steps remain of thirty
+        const float about = fmaxf(best - dec, 0.0f);
+        const int from = __float_as_int(about) - 2, to = __float_as_int(about + (__int_as_float(__float_as_int(best) + 1) - best)) + 2;
+        if (hit && from > lo && attains(from)) lo = from;
+        if (hit && to < hi && to > lo && !attains(to)) hi = to - 1;
         while (__builtin_amdgcn_ballot_w64(lo < hi) != 0) {
             const int mid = lo + ((hi - lo + 1) >> 1);
-            const bool still = hx_candidate(__int_as_float(mid), t.x, dec) <= best;
+            const bool still = attains(mid);
             if (lo < hi) { if (still) lo = mid; else hi = mid - 1; }
         }
         if (hit) atomicMax(&thr[x.y], lo);
@@ -438,7 +446,7 @@ __device__ __forceinline__ void hx_fused_search_body(const ScoreArgs &a, const P
     // Several decode instances attain a minimum.  Those of the winner's class, or of one with the same links to it, and with
     // its decode time do so with the same prefill instances as the winner, whatever their availability: nothing
     // changes, the lowest instance has been kept.  (Classes with the same links: 4096 calls on an idle pool of 64 + 64
-    // alike instances in four classes 11.4 -> 7.1 us.)  A call that has others (rare) is left to hx_pair_of_tied.
+    // alike instances in four classes 11.4 -> 6.8 us.)  A call that has others (rare) is left to hx_pair_of_tied.
     // (Every wavefront sees every call: uniform.)
     const bool tied = __builtin_amdgcn_ballot_w64(any && (key & 1)) != 0;
     if (tied) {
@@ -449,7 +457,7 @@ __device__ __forceinline__ void hx_fused_search_body(const ScoreArgs &a, const P
             if (any && need < (unsigned)x.x && (x.y != k_win || dec != dec_win) &&
                 hx_candidate(s_r[x.y * CALLS + cl], t.x, dec) == best) {
                 bool alike = dec == dec_win;
-                for (int q = 0; q < kT; ++q) {
+                for (int q = 0; q < pa.T; ++q) {
                     const float2 u = s_link[q * kT + x.y], v = s_link[q * kT + k_win];
                     alike = alike && u.x == v.x && u.y == v.y;
                 }
@@ -473,11 +481,8 @@ __device__ __forceinline__ void hx_fused_search_body(const ScoreArgs &a, const P
     if (tied) {
         for (int ct = wave; ct < CALLS; ct += FS_WAVES) {
             if (s_tie[ct] == 0) continue;
-            const int c = min(base + ct, a.C - 1);
-            const int Lt = a.L_in[c], Ot = a.L_out[c];
-            float b = INFINITY;
-#pragma unroll
-            for (int v = 0; v < FS_WAVES; ++v) b = fminf(b, __int_as_float(s_part[v * CALLS + ct].x));
+            const int Lt = __builtin_amdgcn_readlane(L, ct), Ot = __builtin_amdgcn_readlane(O, ct);      // lane ct's call is call ct
+            const float b = hx_lane_value(best, ct);
             // its words of LDS: the class minima, which nobody reads any more
             const int2 pd = hx_pair_of_tied(hx_call_terms(a.m, Lt, Ot), (unsigned)Lt + (unsigned)Ot, b, a.P, a.D, s_pre, s_dec, s_dex, s_link,
                                             s_r + ct, CALLS, (int *)s_m + wave * kT, lane);
