@@ -702,8 +702,6 @@ extern "C" int hx_dag_reserve(hx_ctx *ctx, int32_t max_nodes, int32_t max_edges,
     HxDeviceGuard guard(ctx->device);
     HX_REQUIRE(ctx, guard.ok, HX_ERR_DEVICE, "cannot select device %d", ctx->device);
     hipStream_t stream = (hipStream_t)stream_;
-    // whatever is still at work on the old graph, on any stream, is waited for
-    HX_HIP(ctx, hipDeviceSynchronize());
     HxDagStore &g = ctx->dag;
     int rc = HX_OK;
     const size_t N = (size_t)max_nodes, E = (size_t)max_edges, W = (size_t)max_wf;
@@ -711,7 +709,13 @@ extern "C" int hx_dag_reserve(hx_ctx *ctx, int32_t max_nodes, int32_t max_edges,
     // arrays costs some 350 us, a third of a session of eight rounds (1120 -> 786 us).
     auto keeps = [](int32_t have, size_t want) { return (size_t)have >= want && (size_t)have <= 2 * want; };
     const bool keep = g.cost && keeps(g.room_nodes, N) && keeps(g.room_edges, E) && keeps(g.room_wf, W);
-    if (!keep) dag_free(g);
+    // Whatever is still at work on the old graph, on any stream, is waited for: by the device where its arrays stay, as
+    // freeing them does otherwise; nothing but this stream where there are none.
+    if (keep) HX_HIP(ctx, hipDeviceSynchronize());
+    else {
+        HX_HIP(ctx, hipStreamSynchronize(stream));
+        dag_free(g);
+    }
     if (!keep && ((rc = dev_alloc(ctx, &g.cost, N)) || (rc = dev_alloc(ctx, &g.rem, N)) || (rc = dev_alloc(ctx, &g.tail, N)) ||
         (rc = dev_alloc(ctx, &g.horizon, W)) || (rc = dev_alloc(ctx, &g.level, N)) || (rc = dev_alloc(ctx, &g.wf, N)) ||
         (rc = dev_alloc(ctx, &g.parent_row_ptr, N + 1)) || (rc = dev_alloc(ctx, &g.parent_col, E)) ||

@@ -387,6 +387,26 @@ def test_a_reserve_of_a_similar_size_begins_an_empty_graph(ctx):
         assert view(ctx, 6, 2)[3][1] == 115
 
 
+def test_a_first_reserve_does_not_wait_for_other_streams():
+    import torch
+    from paper_2605_16637_amd import binding
+    c = binding.Context(0)
+    side, mine = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    done = torch.cuda.Event()
+    with torch.cuda.stream(side):
+        torch.cuda._sleep(400_000_000)               # some 0.2 s
+        done.record()
+    with torch.cuda.stream(mine):
+        c.hx_dag_reserve(1000, 1000, 10, 8)
+        first = done.query()
+        c.hx_dag_reserve(900, 900, 10, 8)            # the same arrays again: nothing may be at work on them
+        second = done.query()
+    assert not first and second
+    c.hx_stream_status()
+    c.close()
+
+
 def chain_and_fan(n_chain, n_fan):
     """A chain 0 <- 1 <- ... and then one node whose parents are the last n_fan chain nodes."""
     rp = np.concatenate([[0], np.arange(n_chain), [n_chain - 1 + n_fan]]).astype(np.int32)       # node 0 has no parent
