@@ -52,6 +52,10 @@ struct HxDagStore {
     uint32_t epoch = 0;
 };
 
+constexpr int HX_SWEEP_LIMIT = 4096;      // max_sweeps is below it
+constexpr int HX_SYNC_WORDS = 66;
+constexpr int HX_SWEEP_POLLS = 1 << 18;   // a workgroup waits for the others some 0.2 s
+
 struct hx_ctx {
     int device = 0;
     char err[256] = "no error";
@@ -60,6 +64,7 @@ struct hx_ctx {
     HxPrepTables *d_prep = nullptr;
     int32_t *d_report = nullptr;       // counts of hx_validate_round, [HX_VALIDATE_FIELDS]
     int32_t *d_sync = nullptr;         // sweeps: what the workgroups share, [HX_SYNC_WORDS], 0 between launches
+    int sweep_polls = HX_SWEEP_POLLS;
     unsigned long long *d_acc = nullptr;   // commit accumulators, [3 * HX_MAX_INSTANCES]
     int32_t *d_ticket = nullptr;           // commit: workgroups that have delivered their sums; 0 between launches
     int32_t *d_dpart = nullptr;            // decode-stage free list and per-group partial results, dpart_cap words
@@ -73,9 +78,6 @@ struct hx_ctx {
     int num_cu = 256;
     HxDagStore dag;
 };
-
-constexpr int HX_SWEEP_LIMIT = 4096;      // max_sweeps is below it
-constexpr int HX_SYNC_WORDS = 66;
 
 inline int hx_fail(hx_ctx *ctx, int code, const char *fmt, ...)
 {

@@ -324,10 +324,8 @@ __device__ __forceinline__ void hx_cp_sweep_horizons(const CpArgs &a, int first,
     }
 }
 
-constexpr int CG_POLLS = 1 << 18;     // some 0.2 s
-
 // All workgroups meet; *any: one of them came with `mark`.  target: arrivals so far, theirs included; seen: what the
-// last meeting left (0 before the first).  The wait is bounded: workgroups that are not on the chip yet (it may be full
+// last meeting left (0 before the first).  The wait is bounded by `polls`: workgroups that are not on the chip yet (it may be full
 // of other work) are waited for a while, then everybody gives up (false).
 //
 // Arrivals and marks are counted in the halves of one word; whoever completes the count passes it on to those who wait.
@@ -335,7 +333,7 @@ constexpr int CG_POLLS = 1 << 18;     // some 0.2 s
 // of each 7): what passes from one workgroup to another inside the kernel -- rem, level and these words -- is stored and
 // loaded by device-scope atomics alone, which the caches of an XCD do not hold back, and a store has arrived when
 // its wavefront has waited for it.
-__device__ __forceinline__ bool hx_grid_wait(int32_t *sync, unsigned target, bool mark, bool *any, unsigned long long *seen)
+__device__ __forceinline__ bool hx_grid_wait(int32_t *sync, int polls, unsigned target, bool mark, bool *any, unsigned long long *seen)
 {
     __shared__ unsigned long long s_go;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // every wavefront's own stores have arrived
@@ -348,7 +346,7 @@ __device__ __forceinline__ bool hx_grid_wait(int32_t *sync, unsigned target, boo
         if ((unsigned)now == target) __hip_atomic_store(go, now, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         else
             for (int i = 0; (unsigned)(now = __hip_atomic_load(go, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) != target; ++i) {
-                if (i >= CG_POLLS || ((i & 15) == 15 && __hip_atomic_load(&sync[SY_STUCK], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)) {
+                if (i >= polls || ((i & 15) == 15 && __hip_atomic_load(&sync[SY_STUCK], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)) {
                     __hip_atomic_store(&sync[SY_STUCK], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     now = 0;
                     break;
@@ -367,7 +365,7 @@ __device__ __forceinline__ bool hx_grid_wait(int32_t *sync, unsigned target, boo
 // The whole graph, where the slices could not finish it: at most one workgroup per compute unit, a meeting of all of them a
 // sweep (2 us with 40 workgroups, 3 with 256; a launch per sweep costs more than that also for graphs that need none).
 // Should the workgroups not come together, the last one to leave does everything alone.
-__global__ __launch_bounds__(CG_THREADS) void hx_cp_sweep_all_kernel(CpArgs a, int max_sweeps, int32_t *sync)
+__global__ __launch_bounds__(CG_THREADS) void hx_cp_sweep_all_kernel(CpArgs a, int max_sweeps, int polls, int32_t *sync)
 {
     __shared__ int s_last;
     if (sync[SY_AGAIN] == 0) return;
@@ -379,11 +377,11 @@ __global__ __launch_bounds__(CG_THREADS) void hx_cp_sweep_all_kernel(CpArgs a, i
     unsigned long long seen = 0;
     if (over) {
         hx_cp_sweep_init(a, first, step);
-        here = hx_grid_wait(sync, arrived += gridDim.x, false, &more, &seen);
+        here = hx_grid_wait(sync, polls, arrived += gridDim.x, false, &more, &seen);
         more = true;
     }
     for (int s = 1; here && more && s <= max_sweeps; ++s)
-        here = hx_grid_wait(sync, arrived += gridDim.x, hx_cp_sweep(a, q, first, step, s, over), &more, &seen);
+        here = hx_grid_wait(sync, polls, arrived += gridDim.x, hx_cp_sweep(a, q, first, step, s, over), &more, &seen);
     if (here) {
         hx_cp_sweep_horizons(a, first, step);
         if (more && first == 0) hx_raise(a.status, HX_ERR_NOT_DAG);
@@ -635,8 +633,16 @@ extern "C" int hx_critical_path(hx_ctx *ctx, int32_t n_nodes, int32_t n_edges,
     const long long most = n_nodes > n_wf ? n_nodes : n_wf;      // (workflows may be empty)
     int grid = (int)((most + CG_THREADS - 1) / CG_THREADS);
     grid = grid > ctx->num_cu ? ctx->num_cu : (grid < 1 ? 1 : grid);
-    hx_cp_sweep_all_kernel<<<grid, CG_THREADS, 0, stream>>>(a, max_sweeps, ctx->d_sync);
+    hx_cp_sweep_all_kernel<<<grid, CG_THREADS, 0, stream>>>(a, max_sweeps, ctx->sweep_polls, ctx->d_sync);
     return hx_check_launch(ctx, "hx_cp_sweep_all_kernel");
+}
+
+// for tests: how long a workgroup of the sweeps waits for the others (0: all but the last to arrive give up at once)
+extern "C" int hx_test_sweep_polls(hx_ctx *ctx, int polls)
+{
+    if (!ctx || polls < 0) return HX_ERR_INVALID_ARG;
+    ctx->sweep_polls = polls;
+    return HX_OK;
 }
 
 int hx_horizons_plan(hx_ctx *ctx, const hx_model *model, int32_t n_nodes, int32_t n_edges,

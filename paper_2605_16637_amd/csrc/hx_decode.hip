@@ -1506,6 +1506,9 @@ extern "C" int hx_decode_score(hx_ctx *ctx, const hx_model *model, const hx_call
     return hx_check_launch(ctx, "hx_decode_score kernels");
 }
 
+// whether a shape's plan is made without the start of every pair (tests ask too)
+extern "C" int hx_test_decode_plan_lean(int stride, int D, int Q) { return DPlanLds(stride, D, Q).bytes() > DP_LDS; }
+
 extern "C" int hx_decode_plan_greedy(hx_ctx *ctx, const hx_model *model, const hx_calls *queue, const int32_t *lock,
                                      const hx_decode_tab *dec, const hx_intervals *iv,
                                      const float *tail, const float *horizon, int32_t n_nodes, int32_t n_wf,
@@ -1542,7 +1545,7 @@ extern "C" int hx_decode_plan_greedy(hx_ctx *ctx, const hx_model *model, const h
         hx_decode_no_instance_kernel<<<(Q + 255) / 256, 256, 0, stream>>>(a);
     } else {
         const size_t lds = DPlanLds(iv->stride, D, Q).bytes();
-        if (lds <= DP_LDS) hx_decode_plan_kernel<<<1, Q > DP_THREADS ? DP_MAX_THREADS : DP_THREADS, lds, stream>>>(a);
+        if (!hx_test_decode_plan_lean(iv->stride, D, Q)) hx_decode_plan_kernel<<<1, Q > DP_THREADS ? DP_MAX_THREADS : DP_THREADS, lds, stream>>>(a);
         else hx_decode_plan_lean_kernel<<<1, DG_THREADS, lay.bytes(), stream>>>(a);
     }
     return hx_check_launch(ctx, "hx_decode_plan_greedy kernel");

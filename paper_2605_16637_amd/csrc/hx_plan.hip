@@ -301,6 +301,25 @@ struct GreedyCalls {
     __host__ __device__ int dec() const { return (13 + kT) * C4; }    // decode times of the calls, as many as there is room for
 };
 
+// how the remaining n calls of a stage are dealt to the lanes the stage before left
+struct GreedyStage {
+    int lg, n_waves, per_lane;      // 2^lg lanes a call, wavefronts, groups of four decode entries a lane
+    bool keep;                      // the decode times of the remaining calls fit the words for them
+};
+
+__host__ __device__ inline GreedyStage greedy_stage(int n, int lanes, int n_groups, int dec_words)
+{
+    // lanes per call at most: some four groups of entries for each (more lanes only add reductions)
+    int g_max = 1, lg = 0;
+    while (g_max < GREEDY_MAX_G && 4 * g_max < n_groups) g_max <<= 1;
+    while ((2 << lg) <= g_max && (n << (lg + 1)) <= lanes) ++lg;
+    const int n_waves = ((n << lg) + HX_WAVE - 1) / HX_WAVE, per_lane = (n_groups + (1 << lg) - 1) >> lg;
+    return {lg, n_waves, per_lane, 4 * per_lane * n_waves * HX_WAVE <= dec_words};
+}
+
+// the calls with which the next stage begins: half of them picked, or none left
+__host__ __device__ inline int greedy_next(int n, int n_waves) { return n_waves > 1 ? n / 2 : 0; }
+
 // dec_words: LDS words behind lay.dec()
 // K: instances of either side per lane of a wavefront's copy of the pool; TT: classes, or more
 template <int K, int TT, int THREADS>
@@ -399,9 +418,6 @@ __global__ __launch_bounds__(THREADS) void hx_plan_greedy_kernel(GreedyArgs a, i
     }
     __syncthreads();
     const int n_groups = __builtin_amdgcn_readfirstlane(s.seg[kT]) >> 2;
-    // lanes per call at most: some four groups of entries for each (more lanes only add reductions)
-    int g_max = 1;
-    while (g_max < GREEDY_MAX_G && 4 * g_max < n_groups) g_max <<= 1;
 
     // Every wavefront keeps the simulated pool in its registers, an instance of either side per lane (K of each), and makes
     // every pick for itself: the same arithmetic everywhere, nothing to hand on, and one barrier a pick.
@@ -442,13 +458,11 @@ __global__ __launch_bounds__(THREADS) void hx_plan_greedy_kernel(GreedyArgs a, i
             if (stays) s_rec[at] = mine;
             __syncthreads();
         }
-        int lg = 0;
-        while ((2 << lg) <= g_max && (n << (lg + 1)) <= lanes) ++lg;
-        const int G = 1 << lg, n_lanes = n << lg, n_waves = (n_lanes + HX_WAVE - 1) / HX_WAVE;
+        const GreedyStage st = greedy_stage(n, lanes, n_groups, dec_words);
+        const int lg = st.lg, G = 1 << lg, n_waves = st.n_waves, per_lane = st.per_lane;
+        const bool keep = st.keep;
         lanes = n_waves * HX_WAVE;                            // a wavefront that sits a stage out loses track of the pool
-        const int last = n_waves > 1 ? a.C - n / 2 : a.C;     // the stage's picks end here
-        const int per_lane = (n_groups + G - 1) >> lg;
-        const bool keep = 4 * per_lane * n_waves * HX_WAVE <= dec_words;      // the decode times of the remaining calls fit
+        const int last = a.C - greedy_next(n, n_waves);       // the stage's picks end here
         const int dec_row = 4 * n_waves * HX_WAVE;
         const int slot = tid >> lg, sub = tid & (G - 1);
         const bool has = slot < n;
@@ -801,6 +815,47 @@ extern "C" int hx_rank(hx_ctx *ctx, int32_t C, const float *ratio, int32_t *rank
     return hx_check_launch(ctx, "hx_rank kernels");
 }
 
+struct GreedyLaunch {
+    int threads;
+    size_t lds;
+    int dec_words;
+};
+
+static GreedyLaunch greedy_launch(int C, int D, int T)
+{
+    // A lane per call where the pool is small (a wavefront that is alone has no barriers); otherwise a lane for every
+    // four groups of decode entries, as long as that leaves two wavefronts per SIMD (a lane for every two: 472 us
+    // instead of 465 for 256 calls on 64 + 64, and no difference for 64 on 8 + 8).
+    const int groups = (D + 3) / 4;
+    int threads = C;
+    while (threads < GREEDY_THREADS && threads < C * ((groups + 3) / 4)) threads *= 2;
+    threads = (threads + HX_WAVE - 1) / HX_WAVE * HX_WAVE;
+    if (threads < HX_WAVE) threads = HX_WAVE;
+    if (threads > GREEDY_THREADS && C <= GREEDY_THREADS) threads = GREEDY_THREADS;
+    const GreedyCalls lay(C);
+    // room for the decode times of every call, as far as the LDS goes (what does not fit is worked out at each pick)
+    const size_t room = GREEDY_LDS - sizeof(GreedyPool) - 4 * lay.dec();
+    size_t lds = (size_t)threads * 16 * (((size_t)groups + T) * C / threads + 2);
+    lds = 4 * lay.dec() + (lds < room ? lds : room);
+    return {threads, lds, (int)(lds / 4) - lay.dec()};
+}
+
+// for tests: of a plan's stages, with n_groups groups of four decode entries, is there one whose decode times are kept (1), one
+// whose are not (2), both (3)
+extern "C" int hx_test_plan_stages(int C, int D, int T, int n_groups)
+{
+    if (C < 1 || C > HX_GREEDY_MAX_CALLS || D < 1 || D > HX_GREEDY_MAX_INSTANCES || T < 1 || T > HX_MAX_TYPES) return HX_ERR_SHAPE;
+    const GreedyLaunch g = greedy_launch(C, D, T);
+    int seen = 0;
+    for (int n = C, lanes = g.threads; n > 0;) {
+        const GreedyStage st = greedy_stage(n, lanes, n_groups, g.dec_words);
+        seen |= st.keep ? 1 : 2;
+        lanes = st.n_waves * HX_WAVE;
+        n = greedy_next(n, st.n_waves);
+    }
+    return seen;
+}
+
 extern "C" int hx_plan_greedy(hx_ctx *ctx, const hx_model *model, const hx_calls *calls,
                               const hx_prefill_tab *pre, const hx_decode_tab *dec, const hx_links *links,
                               const float *tail, const float *horizon, int32_t n_nodes, int32_t n_wf,
@@ -853,23 +908,9 @@ extern "C" int hx_plan_greedy(hx_ctx *ctx, const hx_model *model, const hx_calls
         return hx_check_launch(ctx, "hx_plan_no_pool_kernel");
     }
     if (int rc = hx_check_pool(ctx, model, pre, dec, links)) return rc;
-    // A lane per call where the pool is small (a wavefront that is alone has no barriers); otherwise a lane for every
-    // four groups of decode entries, as long as that leaves two wavefronts per SIMD (a lane for every two: 472 us
-    // instead of 465 for 256 calls on 64 + 64, and no difference for 64 on 8 + 8).
-    const int groups = (D + 3) / 4;
-    int threads = C;
-    while (threads < GREEDY_THREADS && threads < C * ((groups + 3) / 4)) threads *= 2;
-    threads = (threads + HX_WAVE - 1) / HX_WAVE * HX_WAVE;
-    if (threads < HX_WAVE) threads = HX_WAVE;
-    if (threads > GREEDY_THREADS && C <= GREEDY_THREADS) threads = GREEDY_THREADS;
-    const GreedyCalls lay(C);
-    // room for the decode times of every call, as far as the LDS goes (what does not fit is worked out at each pick)
-    const size_t room = GREEDY_LDS - sizeof(GreedyPool) - 4 * lay.dec();
-    size_t lds = (size_t)threads * 16 * (((size_t)groups + T) * C / threads + 2);
-    lds = 4 * lay.dec() + (lds < room ? lds : room);
-    const int dec_words = (int)(lds / 4) - lay.dec();
-    auto launch = [&](auto kernel) { kernel<<<1, threads, lds, stream>>>(a, dec_words); };
-    if (threads > GREEDY_THREADS) launch(hx_plan_greedy_kernel<GREEDY_K, kT, GREEDY_MAX_THREADS>);
+    const GreedyLaunch g = greedy_launch(C, D, T);
+    auto launch = [&](auto kernel) { kernel<<<1, g.threads, g.lds, stream>>>(a, g.dec_words); };
+    if (g.threads > GREEDY_THREADS) launch(hx_plan_greedy_kernel<GREEDY_K, kT, GREEDY_MAX_THREADS>);
     else if (P > HX_WAVE || D > HX_WAVE) launch(hx_plan_greedy_kernel<GREEDY_K, kT, GREEDY_THREADS>);
     else if (T > 4) launch(hx_plan_greedy_kernel<1, kT, GREEDY_THREADS>);
     else launch(hx_plan_greedy_kernel<1, 4, GREEDY_THREADS>);

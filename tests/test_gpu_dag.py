@@ -566,3 +566,56 @@ def test_sweeps_report_a_cycle_between_slices(ctx):
     want = o.critical_path(row, col[:-1], cost32.astype(np.float64), np.arange(n_wf + 1) * size, round_f32=True)
     assert want[2].max() == 2 * size - 1
     assert_cp_bit_exact(gpu_cp(ctx, row, col[:-1], cost32, np.arange(n_wf + 1) * size, max_sweeps=2 * size + 1), want)
+
+
+# The workgroups of the sweeps over the whole graph do not come together: with no polls all but the last to arrive give up at
+# once, and the last to leave does the graph alone.  Afterwards the shared words are clear: the next graph, with the usual
+# patience, comes out right, and so does one that the slices finish.
+@pytest.mark.parametrize("kind", ["anywhere", "chain of workflows", "one workflow beside", "no workflows", "cycle"])
+def test_sweeps_whose_workgroups_do_not_meet(kind):
+    from paper_2605_16637_amd import binding
+    c = binding.Context(0)
+    assert c.lib.hx_test_sweep_polls(c._ctx, -1) == -1
+    rng = np.random.default_rng(len(kind))
+    n_wf, size = 200, 30
+    n = n_wf * size
+    if kind == "one workflow beside":
+        n += 1500
+    wf_ptr = np.append(np.arange(n_wf) * size, [n_wf * size, n][n > n_wf * size:]).astype(np.int32)
+    at = rng.permutation(n) if kind == "anywhere" else np.arange(n)
+    src = np.repeat(np.arange(n - 1), rng.integers(0, 4, n - 1))
+    dst = src + (rng.integers(n // 12 + 1, n // 6 + 2, src.size) if kind == "anywhere" else rng.integers(1, 4, src.size))
+    keep = dst < n
+    if kind != "anywhere":
+        keep &= np.minimum(src // size, n_wf) == np.minimum(dst // size, n_wf)
+    src, dst = src[keep], dst[keep]
+    inside = src.size
+    if kind in ("chain of workflows", "cycle"):              # the first eight workflows, first node to first node
+        src, dst = np.append(src, np.arange(7) * size), np.append(dst, np.arange(1, 8) * size)
+
+    def graph(src, dst):
+        edges = np.unique(np.stack([at[src], at[dst]], 1), axis=0)
+        row = np.zeros(n + 1, np.int32); row[1:] = np.cumsum(np.bincount(edges[:, 0], minlength=n))
+        return row, edges[:, 1].astype(np.int32)
+
+    row, col = graph(src, dst)
+    if kind == "no workflows":
+        wf_ptr = np.zeros(1, np.int32)
+    cost32 = rng.uniform(0.1, 2.0, n).astype(np.float32)
+    if kind == "cycle":
+        c.lib.hx_test_sweep_polls(c._ctx, 0)
+        looped = graph(np.append(src, 7 * size), np.append(dst, 0))      # and back again: reported, also by the last one alone
+        gpu_cp(c, *looped, cost32, wf_ptr, max_sweeps=60, check=False)
+        with pytest.raises(binding.HxError) as e:
+            c.hx_stream_status()
+        assert e.value.code == -3
+    want = o.critical_path(row, col, cost32.astype(np.float64), wf_ptr, round_f32=True)
+    limit = int(want[2].max()) + 2
+    for polls in (0, 0, 1 << 18, 3, 1 << 18):
+        assert c.lib.hx_test_sweep_polls(c._ctx, polls) == 0
+        assert_cp_bit_exact(gpu_cp(c, row, col, cost32, wf_ptr, max_sweeps=limit), want)
+    if kind == "chain of workflows":
+        row, col = graph(src[:inside], dst[:inside])
+        want = o.critical_path(row, col, cost32.astype(np.float64), wf_ptr, round_f32=True)
+        assert_cp_bit_exact(gpu_cp(c, row, col, cost32, wf_ptr, max_sweeps=limit), want)
+    c.close()

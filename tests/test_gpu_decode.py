@@ -374,8 +374,7 @@ def check_plan_stepwise(model, L, O, lock, node, wf, elapsed, tail, hor, dec, iv
 
 
 @pytest.mark.parametrize("Q,D,stride,res,plan,lockf,seed", [(3, 2, 4, 2, 1, 0.5, 1), (40, 4, 16, 10, 3, 0.5, 2), (64, 8, 20, 12, 4, 0.0, 3),
-                                                              # (80 x 64 with 96 entries each leaves no local memory for the finish of
-                                                              # every pair: the planner then rescans the calls of the changed instance)
+                                                              # many instances with long lists
                                                               (100, 16, 30, 20, 6, 1.0, 4), (80, 64, 16, 10, 3, 0.3, 5),
                                                               # two instances and long chains of appended intervals: exact ties of start + decode time
                                                               (69, 2, 2, 1, 1, 0.3726785374341105, 760292)])
@@ -415,7 +414,7 @@ def test_decode_greedy_of_longer_queues(ctx, Q, D, stride, res, plan, lockf, ext
     check_plan_stepwise(r.model, L, O, lock, node, wf, elapsed, tail, hor, r.dec, big, got)
 
 
-@pytest.mark.parametrize("Q,D,stride,res,plan", [(40, 4, 16, 10, 3), (80, 64, 16, 10, 3)])      # finish of every pair kept; not kept
+@pytest.mark.parametrize("Q,D,stride,res,plan", [(40, 4, 16, 10, 3), (80, 64, 16, 10, 3)])      # few instances; many
 def test_decode_greedy_with_workflows_without_horizon(ctx, Q, D, stride, res, plan):
     # a workflow whose horizon is 0 makes its calls infinitely urgent: they are planned first, lowest index first, and
     # placed like any other call; their ratio stays +inf when their best instance moves
@@ -438,7 +437,7 @@ def test_decode_greedy_with_workflows_without_horizon(ctx, Q, D, stride, res, pl
     assert (got["best_d"][urgent] >= 0).any()
 
 
-@pytest.mark.parametrize("Q,D,stride,res,plan", [(40, 4, 16, 10, 3), (80, 64, 16, 10, 3)])      # finish of every pair kept; not kept
+@pytest.mark.parametrize("Q,D,stride,res,plan", [(40, 4, 16, 10, 3), (80, 64, 16, 10, 3)])      # few instances; many
 def test_decode_greedy_with_calls_that_decode_nothing(ctx, Q, D, stride, res, plan):
     # a call without output tokens finishes when it starts: its interval holds nothing and the instance's timeline
     # stays as it is (the planner then builds the timeline again instead of inserting the interval)
@@ -516,6 +515,32 @@ def test_decode_greedy_with_capacities_that_are_no_numbers_as_floats(ctx):
     check_plan_stepwise(r.model, L, O, lock, node, wf, elapsed, tail, hor, dec, big, got)
     assert (got["best_d"] != 1).all() and (got["best_start"][(got["best_d"] == 0) | (got["best_d"] == 2)] == 0).all()
     assert (got["best_d"][lock == 1] == -1).all() and (lock == 1).any()
+
+
+# Where local memory has no room for the start of every pair the plan is made by a kernel of its own: as above, with a workflow
+# without horizon and with calls that decode nothing; and a queue just short of it
+@pytest.mark.parametrize("Q,extra,lean", [(150, 104, True), (150, 80, False), (100, 104, True)])
+@pytest.mark.parametrize("kind", ["plain", "no horizon", "decode nothing"])
+def test_decode_greedy_without_room_for_every_pair(ctx, Q, extra, lean, kind):
+    D = 64
+    r, lock, iv = synth.make_decode_round("decode_tiny", 50 + Q, n_wf=Q // 4, Q=Q, D=D, T=4, stride=16, n_resident=10, n_planned=3,
+                                          lock_fraction=0.2)
+    L, O = r.calls["L_in"], r.calls["L_out"].copy()
+    rng = np.random.default_rng(Q)
+    node = rng.permutation(Q).astype(np.int32); wf = rng.integers(0, 4, Q).astype(np.int32)
+    elapsed = rng.uniform(0, 20, Q).astype(np.float32)
+    tail = rng.uniform(0, 5, Q).astype(np.float32); hor = rng.uniform(5, 50, 4).astype(np.float32)
+    if kind == "no horizon":
+        hor[1] = 0.0
+    if kind == "decode nothing":
+        O[::3] = 0
+    big = widen(iv, D, extra)
+    assert ctx.lib.hx_test_decode_plan_lean(big["stride"], D, Q) == int(lean)
+    got = run_plan(ctx, r.model, L, O, lock, node, wf, elapsed, tail, hor, r.dec, big)
+    check_plan_stepwise(r.model, L, O, lock, node, wf, elapsed, tail, hor, r.dec, big, got)
+    if kind == "no horizon":
+        urgent = np.nonzero(wf == 1)[0]
+        assert np.array_equal(np.argsort(got["rank"][urgent]), np.arange(urgent.size)) and got["rank"][urgent].max() < urgent.size
 
 
 def test_decode_greedy_at_the_benchmarks_size(ctx):

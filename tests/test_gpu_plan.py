@@ -183,6 +183,24 @@ def test_greedy_plan_with_rates_of_every_instance(ctx, C, P, D, T, seed):
     check_plan_stepwise(synth.MODEL, L, O, elapsed, node, wf, tail, hor, pre, dec, links, got)
 
 
+# Plans that begin with more decode times than the workgroup's memory keeps and end with few enough: up to 512 calls with small
+# and large pools, and more
+@pytest.mark.parametrize("C,P,D,T,seed", [(512, 8, 64, 8, 1), (400, 66, 90, 4, 2), (1024, 4, 18, 3, 3)])
+def test_greedy_plan_whose_decode_times_are_not_kept_at_first(ctx, C, P, D, T, seed):
+    rng = np.random.default_rng(270 + seed)
+    types, pre, dec, links = random_pool(rng, P, D, T)
+    groups = int(sum(-(-int((dec["type"] == t).sum()) // 4) for t in range(T)))
+    assert ctx.lib.hx_test_plan_stages(C, D, T, groups) == 3              # some stages keep them, some do not
+    dec["cap_tok"] = (dec["used_tok"] + rng.integers(20000, 300000, D)).astype(np.int32)
+    L, O = synth.gen_lengths(rng, C)
+    elapsed = rng.uniform(0, 20, C).astype(np.float32)
+    node = rng.permutation(C).astype(np.int32); wf = rng.integers(0, 3, C).astype(np.int32)
+    tail = rng.uniform(0, 5, C).astype(np.float32); hor = rng.uniform(5, 50, 3).astype(np.float32)
+    got = run_greedy(ctx, synth.MODEL, L, O, elapsed, node, wf, tail, hor, pre, dec, links)
+    check_plan_stepwise(synth.MODEL, L, O, elapsed, node, wf, tail, hor, pre, dec, links, got)
+    assert (got[0] >= 0).sum() > C // 2
+
+
 def test_greedy_hand_worked_conflict_on_gpu(ctx):
     from helpers import ROUND_MODEL, read_kv
     G = read_kv("round_numbers.txt")
