@@ -449,7 +449,7 @@ __device__ __forceinline__ void hx_fused_search_body(const ScoreArgs &a, const P
     // alike instances in four classes 11.4 -> 6.8 us.)  A call that has others (rare) is left to hx_pair_of_tied.
     // (Every wavefront sees every call: uniform.)
     const bool tied = __builtin_amdgcn_ballot_w64(any && (key & 1)) != 0;
-    if (__builtin_expect(tied, false)) {
+    if (tied) {
         for (int d = slice; d < a.D; d += SLICES) {
             const float4 t = s_dec[d];
             const int2 x = s_dex[d];
@@ -478,7 +478,7 @@ __device__ __forceinline__ void hx_fused_search_body(const ScoreArgs &a, const P
     for (int off = CALLS; off < HX_WAVE; off <<= 1) p_low = min(p_low, __shfl_xor(p_low, off));
     if (lane < CALLS && any && p_low < 0x7fffffff) atomicMin(&s_pd[cl].x, p_low);
     __syncthreads();
-    if (__builtin_expect(tied, false)) {
+    if (tied) {
         for (int ct = wave; ct < CALLS; ct += FS_WAVES) {
             if (s_tie[ct] == 0) continue;
             const int Lt = __builtin_amdgcn_readlane(L, ct), Ot = __builtin_amdgcn_readlane(O, ct);      // lane ct's call is call ct
