@@ -12,32 +12,24 @@
 #include "../../include/hx.h"
 
 constexpr int HX_WAVE = 64;
-// decode entries are grouped by GPU class and each class segment is padded to
-// a multiple of this many entries, so the inner search loop needs no tail
-constexpr int HX_DGROUP = 8;
-constexpr int HX_DPAD = HX_MAX_INSTANCES + HX_MAX_TYPES * HX_DGROUP;   // padded decode entries, upper bound
 
-// Per-round tables the prepare kernel derives from the raw snapshots; one copy
-// lives in the context's scratch and every scoring kernel stages it into LDS.
+// What hx_prepare_kernel derives from the raw snapshots for the kernel that writes the cost tensor; one copy lives in the
+// context's scratch.
 struct HxPrepTables {
-    // prefill side, by instance
+    // prefill instances
     float pre_wait[HX_MAX_INSTANCES];   // backlog_tok * phi / F
     float pre_invF[HX_MAX_INSTANCES];
     float pre_invB[HX_MAX_INSTANCES];
     int32_t pre_type[HX_MAX_INSTANCES];
-    // decode side, by entry (grouped by class, padded); pads have orig = -1, free = -1
-    float dec_wait[HX_DPAD];            // decode availability hint
-    float dec_c1[HX_DPAD];              // phi * (batch + 1) / F
-    float dec_c2[HX_DPAD];              // (omega + kappa * used) / B
-    float dec_kB[HX_DPAD];              // kappa / B
-    int32_t dec_free[HX_DPAD];          // cap_tok - used_tok
-    int32_t dec_orig[HX_DPAD];          // instance index of the entry
-    int32_t dec_type[HX_DPAD];          // class of the entry
-    int32_t dec_pos[HX_MAX_INSTANCES];  // entry of instance d
-    int32_t seg[HX_MAX_TYPES + 1];      // class t owns entries seg[t] .. seg[t+1]-1
+    // decode instances
+    float dec_wait[HX_MAX_INSTANCES];   // availability hint
+    float dec_c1[HX_MAX_INSTANCES];     // phi * (batch + 1) / F
+    float dec_c2[HX_MAX_INSTANCES];     // (omega + kappa * used) / B
+    float dec_kB[HX_MAX_INSTANCES];     // kappa / B
+    int32_t dec_free[HX_MAX_INSTANCES]; // cap_tok - used_tok
+    int32_t dec_type[HX_MAX_INSTANCES];
     float link_invbw[HX_MAX_TYPES * HX_MAX_TYPES];
     float link_lat[HX_MAX_TYPES * HX_MAX_TYPES];
-    int32_t n_entries;                  // seg[T]
 };
 
 struct HxDagStore {

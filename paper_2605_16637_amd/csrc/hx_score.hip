@@ -38,18 +38,13 @@ struct PrepArgs {
     int32_t *status;
 };
 
-// One workgroup of 1024 threads, one thread per instance of either side (at most HX_MAX_INSTANCES each).
-// Everything is read at the top and written at the bottom: the three barriers in between (class counts,
-// class segments) then wait for neither loads nor stores.
+// The pool's tables for hx_materialise_kernel (the search derives its own): one workgroup of 1024 threads, one thread per
+// instance of either side (at most HX_MAX_INSTANCES each).
 __global__ __launch_bounds__(1024) void hx_prepare_kernel(PrepArgs a)
 {
-    __shared__ int s_cnt[kT], s_seg[kT + 1];
-    __shared__ int s_wcnt[HX_MAX_INSTANCES / HX_WAVE][kT];
     const int tid = threadIdx.x;
-    const int lane = tid & (HX_WAVE - 1), wv = tid >> 6;
     HxPrepTables *o = a.out;
-
-    // ---- reads
+    // everything is read before anything is written
     const bool has_link = tid < kT * kT;
     const int tp = tid / kT, td = tid % kT;
     const bool link_in = has_link && tp < a.T && td < a.T;
@@ -60,44 +55,12 @@ __global__ __launch_bounds__(1024) void hx_prepare_kernel(PrepArgs a)
     const float p_flops = has_p ? a.p_flops[tid] : 1.0f, p_hbm = has_p ? a.p_hbm[tid] : 1.0f;
     const int p_backlog = has_p ? a.p_backlog[tid] : 0;
     const bool has_d = tid < a.D;
-    int my_t = has_d ? a.d_type[tid] : -1;
+    int d_t = has_d ? a.d_type[tid] : 0;
     const int d_used = has_d ? a.d_used[tid] : 0, d_batch = has_d ? a.d_batch[tid] : 0, d_qd = has_d ? a.d_qd[tid] : 0;
     const int d_cap = has_d ? a.d_cap[tid] : 0;
     const float d_flops = has_d ? a.d_flops[tid] : 1.0f, d_hbm = has_d ? a.d_hbm[tid] : 1.0f;
-    if (has_p && (p_t < 0 || p_t >= a.T)) { hx_raise(a.status, HX_ERR_INDEX); p_t = 0; }
-    if (has_d && (my_t < 0 || my_t >= a.T)) { hx_raise(a.status, HX_ERR_INDEX); my_t = 0; }
-
-    // ---- decode instances ranked by class: per-wave class counts (ballots), class sizes, class segments
-    int my_rank = 0;                     // instances of my class before me in my wave
-#pragma unroll
-    for (int t = 0; t < kT; ++t) {
-        unsigned long long b = __ballot(my_t == t);
-        if (lane == 0) s_wcnt[wv][t] = __popcll(b);
-        if (my_t == t) my_rank = __popcll(b & ((1ull << lane) - 1ull));
-    }
-    __syncthreads();
-    // class sizes: one thread per class adds up the waves' counts, then one thread lays out the segments
-    if (tid < kT) {
-        int n = 0;
-        for (int k = 0; k < (a.D + HX_WAVE - 1) / HX_WAVE; ++k) {
-            const int here = s_wcnt[k][tid];
-            s_wcnt[k][tid] = n;                      // instances of the class in earlier waves
-            n += here;
-        }
-        s_cnt[tid] = n;
-    }
-    __syncthreads();
-    if (tid == 0) {
-        int e = 0;
-        for (int t = 0; t < kT; ++t) {
-            s_seg[t] = e;
-            e += (s_cnt[t] + HX_DGROUP - 1) / HX_DGROUP * HX_DGROUP;
-        }
-        s_seg[kT] = e;
-    }
-    __syncthreads();
-
-    // ---- writes
+    if (p_t < 0 || p_t >= a.T) { hx_raise(a.status, HX_ERR_INDEX); p_t = 0; }
+    if (d_t < 0 || d_t >= a.T) { hx_raise(a.status, HX_ERR_INDEX); d_t = 0; }
     if (has_link) {
         o->link_invbw[tid] = link_in ? 1.0f / l_bw : 0.0f;
         o->link_lat[tid] = l_lat;
@@ -109,26 +72,12 @@ __global__ __launch_bounds__(1024) void hx_prepare_kernel(PrepArgs a)
         o->pre_wait[tid] = hx_prefill_wait(a.m, p_backlog, invF);
         o->pre_type[tid] = p_t;
     }
-    if (tid <= kT) o->seg[tid] = s_seg[tid];
-    const int n_entries = s_seg[kT];
-    if (tid == 0) o->n_entries = n_entries;
-    // pads (real entries below: disjoint indices)
-    for (int e = tid; e < n_entries; e += blockDim.x) {
-        int t = 0;
-        while (t + 1 < kT && e >= s_seg[t + 1]) ++t;
-        if (e >= s_seg[t] + s_cnt[t]) {
-            o->dec_wait[e] = 0.0f; o->dec_c1[e] = 0.0f; o->dec_c2[e] = 0.0f; o->dec_kB[e] = 0.0f;
-            o->dec_free[e] = -1; o->dec_orig[e] = -1; o->dec_type[e] = t;
-        }
-    }
     if (has_d) {
-        const int d = tid, t = my_t;
-        int e = s_seg[t] + s_wcnt[wv][t] + my_rank;
-        HxDecF x = hx_decode_terms(a.m, d_used, d_batch, d_qd, 1.0f / d_flops, 1.0f / d_hbm);
-        o->dec_wait[e] = x.wait; o->dec_c1[e] = x.c1; o->dec_c2[e] = x.c2; o->dec_kB[e] = x.kB;
-        long long fr = (long long)d_cap - (long long)d_used;
-        o->dec_free[e] = fr < -1 ? -1 : (fr > 2147483647LL ? 2147483647 : (int)fr);
-        o->dec_orig[e] = d; o->dec_type[e] = t; o->dec_pos[d] = e;
+        const HxDecF x = hx_decode_terms(a.m, d_used, d_batch, d_qd, 1.0f / d_flops, 1.0f / d_hbm);
+        o->dec_wait[tid] = x.wait; o->dec_c1[tid] = x.c1; o->dec_c2[tid] = x.c2; o->dec_kB[tid] = x.kB;
+        const long long fr = (long long)d_cap - (long long)d_used;
+        o->dec_free[tid] = fr < -1 ? -1 : (fr > 2147483647LL ? 2147483647 : (int)fr);
+        o->dec_type[tid] = d_t;
     }
 }
 
@@ -559,7 +508,7 @@ __global__ __launch_bounds__(FS_THREADS) void hx_relax_search_kernel(ScoreArgs a
 // KB and the barriers and the per-call tables would otherwise cost as much as the stores; 1 on large ones).
 // LDS: per call of the batch the prefill finish per instance, the decode time per instance and the class-pair
 // transfer times, each worked out by 256 / nc threads; beside them what does not depend on the call (waits,
-// per-token terms, classes; original instance order), staged once per workgroup.
+// per-token terms, classes), staged once per workgroup.
 __global__ __launch_bounds__(256) void hx_materialise_kernel(ScoreArgs a, int nc)
 {
     extern __shared__ __align__(16) float smem[];
@@ -587,9 +536,8 @@ __global__ __launch_bounds__(256) void hx_materialise_kernel(ScoreArgs a, int nc
         s_pw[p] = t->pre_wait[p]; s_pF[p] = t->pre_invF[p]; s_pB[p] = t->pre_invB[p]; s_ptype[p] = t->pre_type[p];
     }
     for (int d = tid; d < a.D; d += blockDim.x) {
-        const int e = t->dec_pos[d];
-        s_c1[d] = t->dec_c1[e]; s_c2[d] = t->dec_c2[e]; s_kB[d] = t->dec_kB[e]; s_free[d] = t->dec_free[e];
-        s_wait[d] = t->dec_wait[e]; s_dtype[d] = t->dec_type[e];
+        s_c1[d] = t->dec_c1[d]; s_c2[d] = t->dec_c2[d]; s_kB[d] = t->dec_kB[d]; s_free[d] = t->dec_free[d];
+        s_wait[d] = t->dec_wait[d]; s_dtype[d] = t->dec_type[d];
     }
     if (tid < kT * kT) { s_lbw[tid] = t->link_invbw[tid]; s_llat[tid] = t->link_lat[tid]; }
     // the part of the workgroup that works out the tables of one call of the batch
