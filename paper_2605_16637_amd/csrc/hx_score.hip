@@ -165,6 +165,7 @@ __device__ __forceinline__ unsigned hx_alike_hash(float c1, float c2, int type, 
 // (4096 calls on 64 + 64 idle instances, alike in four classes with faster links inside a class, so that this is every
 // call: 9.0 us; from end to end of that range, with the call read again from memory, 11.8; pair by pair 8.8.)
 // thr: [kT] words of LDS of the wavefront's own.
+// (Its loops and those of the tied pass are not unrolled: 500 bytes less code in every search, 64 calls on 4 + 4 9.62 -> 9.50 us.)
 __device__ __forceinline__ int2 hx_pair_of_tied(const HxCallF &cf, unsigned need, float best, int P, int D, const float4 *s_pre,
                                                 const float4 *s_dec, const int2 *s_dex, const float2 *s_link, const float *r_call,
                                                 int r_stride, int *thr, int lane)
@@ -173,6 +174,7 @@ __device__ __forceinline__ int2 hx_pair_of_tied(const HxCallF &cf, unsigned need
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll 1
     for (int e0 = 0; e0 < D; e0 += HX_WAVE) {
         const int e = min(e0 + lane, D - 1);
         const float4 t = s_dec[e];
@@ -187,6 +189,7 @@ __device__ __forceinline__ int2 hx_pair_of_tied(const HxCallF &cf, unsigned need
         const int from = __float_as_int(about) - 2, to = __float_as_int(about + (__int_as_float(__float_as_int(best) + 1) - best)) + 2;
         if (hit && from > lo && attains(from)) lo = from;
         if (hit && to < hi && to > lo && !attains(to)) hi = to - 1;
+#pragma unroll 1
         while (__builtin_amdgcn_ballot_w64(lo < hi) != 0) {
             const int mid = lo + ((hi - lo + 1) >> 1);
             const bool still = attains(mid);
@@ -201,6 +204,7 @@ __device__ __forceinline__ int2 hx_pair_of_tied(const HxCallF &cf, unsigned need
 #pragma unroll
     for (int k = 0; k < kT; ++k) R[k] = thr[k];
     int2 out = make_int2(-1, -1);
+#pragma unroll 1
     for (int p0 = 0; p0 < P; p0 += HX_WAVE) {
         const int p = min(p0 + lane, P - 1);
         const float4 t = s_pre[p];
@@ -219,7 +223,8 @@ __device__ __forceinline__ int2 hx_pair_of_tied(const HxCallF &cf, unsigned need
         const float4 t = s_pre[out.x];
         const float done = hx_prefill_done(cf, t.x, t.y, t.z);
         const float2 *row = s_link + __float_as_int(t.w) * kT;
-        for (int e0 = 0; e0 < D; e0 += HX_WAVE) {
+    #pragma unroll 1
+    for (int e0 = 0; e0 < D; e0 += HX_WAVE) {
             const int e = min(e0 + lane, D - 1);
             const float4 q = s_dec[e];
             const int2 x = s_dex[e];
@@ -399,6 +404,7 @@ __device__ __forceinline__ void hx_fused_search_body(const ScoreArgs &a, const P
     // (Every wavefront sees every call: uniform.)
     const bool tied = __builtin_amdgcn_ballot_w64(any && (key & 1)) != 0;
     if (tied) {
+#pragma unroll 1
         for (int d = slice; d < a.D; d += SLICES) {
             const float4 t = s_dec[d];
             const int2 x = s_dex[d];
@@ -406,6 +412,7 @@ __device__ __forceinline__ void hx_fused_search_body(const ScoreArgs &a, const P
             if (any && need < (unsigned)x.x && (x.y != k_win || dec != dec_win) &&
                 hx_candidate(s_r[x.y * CALLS + cl], t.x, dec) == best) {
                 bool alike = dec == dec_win;
+#pragma unroll 1
                 for (int q = 0; q < pa.T; ++q) {
                     const float2 u = s_link[q * kT + x.y], v = s_link[q * kT + k_win];
                     alike = alike && u.x == v.x && u.y == v.y;
@@ -428,6 +435,7 @@ __device__ __forceinline__ void hx_fused_search_body(const ScoreArgs &a, const P
     if (lane < CALLS && any && p_low < 0x7fffffff) atomicMin(&s_pd[cl].x, p_low);
     __syncthreads();
     if (tied) {
+#pragma unroll 1
         for (int ct = wave; ct < CALLS; ct += FS_WAVES) {
             if (s_tie[ct] == 0) continue;
             const int Lt = __builtin_amdgcn_readlane(L, ct), Ot = __builtin_amdgcn_readlane(O, ct);      // lane ct's call is call ct
