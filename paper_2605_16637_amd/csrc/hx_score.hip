@@ -119,8 +119,8 @@ __device__ __forceinline__ void hx_ratio(const ScoreArgs &a, int c, float best)
 //
 // What bounds it: some 4 us of every launch are the chain of memory round trips (pool tables, call inputs) and the barriers
 // between the passes, which is why few calls are spread over all compute units; the rest is instruction issue and LDS
-// reads in about equal parts (a decode instance: 12 vector instructions and three reads, a prefill instance: 5 + 10 and
-// four).
+// reads (a decode instance: 13.5 vector instructions and 2.5 reads, a prefill instance: 8 + 13 and two reads in each
+// pass).
 //
 // A workgroup takes CALLS calls through the whole pool, a lane one of them; the lanes of a call in a wavefront (64 / CALLS)
 // and the wavefronts deal the instances out among themselves, in turn, and read them from LDS as broadcasts.  Nothing
