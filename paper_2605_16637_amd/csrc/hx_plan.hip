@@ -301,24 +301,24 @@ struct GreedyCalls {
     __host__ __device__ int dec() const { return (13 + kT) * C4; }    // decode times of the calls, as many as there is room for
 };
 
-// how the remaining n calls of a stage are dealt to the lanes the stage before left
-struct GreedyStage {
-    int lg, n_waves, per_lane;      // 2^lg lanes a call, wavefronts, groups of four decode entries a lane
-    bool keep;                      // the decode times of the remaining calls fit the words for them
-};
-
-__host__ __device__ inline GreedyStage greedy_stage(int n, int lanes, int n_groups, int dec_words)
+// lanes per call at most: some four groups of entries for each (more lanes only add reductions)
+__host__ __device__ inline int greedy_g_max(int n_groups)
 {
-    // lanes per call at most: some four groups of entries for each (more lanes only add reductions)
-    int g_max = 1, lg = 0;
+    int g_max = 1;
     while (g_max < GREEDY_MAX_G && 4 * g_max < n_groups) g_max <<= 1;
-    while ((2 << lg) <= g_max && (n << (lg + 1)) <= lanes) ++lg;
-    const int n_waves = ((n << lg) + HX_WAVE - 1) / HX_WAVE, per_lane = (n_groups + (1 << lg) - 1) >> lg;
-    return {lg, n_waves, per_lane, 4 * per_lane * n_waves * HX_WAVE <= dec_words};
+    return g_max;
 }
 
-// the calls with which the next stage begins: half of them picked, or none left
-__host__ __device__ inline int greedy_next(int n, int n_waves) { return n_waves > 1 ? n / 2 : 0; }
+// log2 of the lanes per call for the n calls of a stage, on the lanes the stage before left
+__host__ __device__ inline int greedy_lg(int n, int lanes, int g_max)
+{
+    int lg = 0;
+    while ((2 << lg) <= g_max && (n << (lg + 1)) <= lanes) ++lg;
+    return lg;
+}
+
+// the decode times of a stage's calls fit the words for them
+__host__ __device__ inline bool greedy_keeps(int per_lane, int n_waves, int dec_words) { return 4 * per_lane * n_waves * HX_WAVE <= dec_words; }
 
 // dec_words: LDS words behind lay.dec()
 // K: instances of either side per lane of a wavefront's copy of the pool; TT: classes, or more
@@ -417,7 +417,7 @@ __global__ __launch_bounds__(THREADS) void hx_plan_greedy_kernel(GreedyArgs a, i
         }
     }
     __syncthreads();
-    const int n_groups = __builtin_amdgcn_readfirstlane(s.seg[kT]) >> 2;
+    const int n_groups = __builtin_amdgcn_readfirstlane(s.seg[kT]) >> 2, g_max = greedy_g_max(n_groups);
 
     // Every wavefront keeps the simulated pool in its registers, an instance of either side per lane (K of each), and makes
     // every pick for itself: the same arithmetic everywhere, nothing to hand on, and one barrier a pick.
@@ -458,11 +458,12 @@ __global__ __launch_bounds__(THREADS) void hx_plan_greedy_kernel(GreedyArgs a, i
             if (stays) s_rec[at] = mine;
             __syncthreads();
         }
-        const GreedyStage st = greedy_stage(n, lanes, n_groups, dec_words);
-        const int lg = st.lg, G = 1 << lg, n_waves = st.n_waves, per_lane = st.per_lane;
-        const bool keep = st.keep;
+        const int lg = greedy_lg(n, lanes, g_max);
+        const int G = 1 << lg, n_lanes = n << lg, n_waves = (n_lanes + HX_WAVE - 1) / HX_WAVE;
         lanes = n_waves * HX_WAVE;                            // a wavefront that sits a stage out loses track of the pool
-        const int last = a.C - greedy_next(n, n_waves);       // the stage's picks end here
+        const int last = n_waves > 1 ? a.C - n / 2 : a.C;     // the stage's picks end here
+        const int per_lane = (n_groups + G - 1) >> lg;
+        const bool keep = greedy_keeps(per_lane, n_waves, dec_words);
         const int dec_row = 4 * n_waves * HX_WAVE;
         const int slot = tid >> lg, sub = tid & (G - 1);
         const bool has = slot < n;
@@ -848,10 +849,10 @@ extern "C" int hx_test_plan_stages(int C, int D, int T, int n_groups)
     const GreedyLaunch g = greedy_launch(C, D, T);
     int seen = 0;
     for (int n = C, lanes = g.threads; n > 0;) {
-        const GreedyStage st = greedy_stage(n, lanes, n_groups, g.dec_words);
-        seen |= st.keep ? 1 : 2;
-        lanes = st.n_waves * HX_WAVE;
-        n = greedy_next(n, st.n_waves);
+        const int lg = greedy_lg(n, lanes, greedy_g_max(n_groups)), n_waves = ((n << lg) + HX_WAVE - 1) / HX_WAVE;
+        seen |= greedy_keeps((n_groups + (1 << lg) - 1) >> lg, n_waves, g.dec_words) ? 1 : 2;
+        lanes = n_waves * HX_WAVE;
+        n = n_waves > 1 ? n / 2 : 0;
     }
     return seen;
 }
