@@ -163,9 +163,10 @@ __device__ __forceinline__ unsigned hx_alike_hash(float c1, float c2, int type, 
 // minimum; R is found by bisection over the bit patterns between the earliest arrival (which attains it) and the
 // minimum itself (no later arrival can), begun close to where it must be, and of a class only its largest R matters.
 // (4096 calls on 64 + 64 idle instances, alike in four classes with faster links inside a class, so that this is every
-// call: 9.0 us; from end to end of that range, with the call read again from memory, 11.8; pair by pair 8.8.)
+// call: 9.6 us; from end to end of that range, with the call read again from memory, 11.8; pair by pair 8.8.)
+// Every search carries this code, so it is kept small, its loops not unrolled: the classes one after the other instead of
+// all eight side by side cost such calls 0.6 us and save every other search of a small round 0.1.
 // thr: [kT] words of LDS of the wavefront's own.
-// (Its loops and those of the tied pass are not unrolled: 500 bytes less code in every search, 64 calls on 4 + 4 9.62 -> 9.50 us.)
 __device__ __forceinline__ int2 hx_pair_of_tied(const HxCallF &cf, unsigned need, float best, int P, int D, const float4 *s_pre,
                                                 const float4 *s_dec, const int2 *s_dex, const float2 *s_link, const float *r_call,
                                                 int r_stride, int *thr, int lane)
@@ -200,9 +201,8 @@ __device__ __forceinline__ int2 hx_pair_of_tied(const HxCallF &cf, unsigned need
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    int R[kT];
-#pragma unroll
-    for (int k = 0; k < kT; ++k) R[k] = thr[k];
+    const int R_of = thr[lane & (kT - 1)];                // lane k: of class k
+    const unsigned classes = (unsigned)__builtin_amdgcn_ballot_w64(lane < kT && R_of >= 0);
     int2 out = make_int2(-1, -1);
 #pragma unroll 1
     for (int p0 = 0; p0 < P; p0 += HX_WAVE) {
@@ -211,10 +211,11 @@ __device__ __forceinline__ int2 hx_pair_of_tied(const HxCallF &cf, unsigned need
         const float done = hx_prefill_done(cf, t.x, t.y, t.z);
         const float2 *row = s_link + __float_as_int(t.w) * kT;
         bool ok = false;
-#pragma unroll
-        for (int k = 0; k < kT; ++k) {
+#pragma unroll 1
+        for (unsigned left = classes; left; left &= left - 1) {
+            const int k = __builtin_ctz(left);
             const float2 l = row[k];
-            ok = ok || __float_as_int(done + hx_transfer(cf, l.x, l.y)) <= R[k];
+            ok = ok || __float_as_int(done + hx_transfer(cf, l.x, l.y)) <= __builtin_amdgcn_readlane(R_of, k);
         }
         const unsigned long long b = __builtin_amdgcn_ballot_w64(ok && p0 + lane < P);
         if (b) { out.x = p0 + __builtin_ctzll(b); break; }
