@@ -177,8 +177,9 @@ int hx_node_cost(hx_ctx *ctx, const hx_model *model, int32_t n,
  *   workflow size and any number of successors per node are accepted; the
  *   pass is fastest when a node has at most 4.
  * max_sweeps  > 0: level-synchronous relaxation for any numbering; successors
- *   may be anywhere.  Sweeps until nothing changes, at most max_sweeps times
- *   (a DAG of depth L needs L+2); still changing then -> HX_ERR_NOT_DAG in the
+ *   may be anywhere.  Sweeps until nothing changes, inside parts of the graph
+ *   and then, where that does not finish it, over the whole, at most max_sweeps
+ *   times each (a DAG of depth L needs L+2); still changing then -> HX_ERR_NOT_DAG in the
  *   stream status (a cycle, or the limit was too small).
  * Both give bit-identical results on inputs both accept.
  */
