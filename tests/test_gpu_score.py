@@ -141,8 +141,8 @@ def test_fused_search_with_ties_between_classes(ctx, C, P, D, T, pool):
     assert_search_equals_selection(ctx, C, P, D, L, O, pre, dec, links)
 
 
-# C just past the sizes at which a workgroup takes 8, 16, 32 and 64 calls on 256 compute units; pools around a wavefront's
-# share of instances and at the limits
+# C just past the sizes at which a workgroup takes 8, 16 and 32 calls on 256 compute units (64: above); pools around a
+# wavefront's share of instances and at the limits
 @pytest.mark.parametrize("C,P,D,T", [(1, 1, 1, 1), (9, 64, 63, 8), (2047, 3, 17, 2), (2049, 9, 33, 5), (4097, 17, 8, 8),
                                      (8193, 5, 31, 3), (8193, 33, 2, 7), (40, 1024, 1024, 8), (70, 513, 511, 6)])
 @pytest.mark.parametrize("pool", ["any", "alike", "no output", "few values"])
