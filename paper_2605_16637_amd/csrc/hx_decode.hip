@@ -812,6 +812,7 @@ constexpr int DG_WAVES = DG_THREADS / HX_WAVE;
 constexpr int DP_MAX_THREADS = HX_DECODE_GREEDY_MAX_CALLS;   // a lane per call at least
 constexpr int DP_THREADS = 512;
 constexpr int DP_MAX_G = 4;                                  // lanes per call at most
+constexpr int DP_TOGETHER = 60;                              // comparisons a lane that a timeline built by all wavefronts has to save
 constexpr int DP_FEW = 12;                                   // calls of a wavefront whose starts are found one after the other (24: 705 us)
 
 struct DGreedyArgs {
@@ -1119,10 +1120,24 @@ __global__ __launch_bounds__(DP_MAX_THREADS) void hx_decode_plan_kernel(DGreedyA
         s_list[c] = c;
     }
     __syncthreads();
-    // the timelines, an instance per wavefront; the builders' scratch is where the matrix will be, as far as it goes
-    {
-        const size_t one = hx_scratch_bytes(lay.ne);
-        const int builders = min(NT / HX_WAVE, (int)((lay.bytes() - lay.off_scratch()) / one));
+    // the timelines; the builders' scratch is where the matrix will be, as far as it goes
+    const size_t one = hx_scratch_bytes(lay.ne);
+    const int builders = min(NT / HX_WAVE, (int)((lay.bytes() - lay.off_scratch()) / one));
+    int most = 0;
+    for (int d = lane; d < a.D; d += HX_WAVE) most = max(most, s_cnt[d]);
+    most = -hx_wave_min(-most);
+    // An instance per wavefront, unless that leaves wavefronts without work (few instances, or scratch for few builders) over
+    // lists that are long enough (an event is compared with every other): then one after the other by all of them.  Two
+    // calls on 8 instances: lists of 10 23 us either way, 50 48 -> 30, 400 1235 -> 249; 256 calls on 32 with lists of 28 566
+    // by a wavefront each and 620 by all.
+    const long long n_ev = 2 * most + 1, rounds = (a.D + builders - 1) / builders;
+    if (n_ev * n_ev * (rounds * NT - (long long)HX_WAVE * a.D) > (long long)DP_TOGETHER * a.D * HX_WAVE * NT) {
+        for (int d = 0; d < a.D; ++d) {
+            const size_t at = (size_t)d * a.stride;
+            hx_build_timeline<false>(s_cnt[d], a.iv_start + at, a.iv_end + at, a.iv_tok + at,
+                                     hx_carve_scratch(smem + lay.off_scratch(), lay.ne), Tl{s_tl + (size_t)d * lay.nt}, &s_n[d], a.status);
+        }
+    } else {
         for (int d = wave; d < a.D && wave < builders; d += builders) {
             const size_t at = (size_t)d * a.stride;
             hx_build_timeline<false, true>(s_cnt[d], a.iv_start + at, a.iv_end + at, a.iv_tok + at,

@@ -543,6 +543,23 @@ def test_decode_greedy_without_room_for_every_pair(ctx, Q, extra, lean, kind):
         assert np.array_equal(np.argsort(got["rank"][urgent]), np.arange(urgent.size)) and got["rank"][urgent].max() < urgent.size
 
 
+# timelines built by a wavefront each or by all of them together: few instances and long lists, eight and nine instances, short
+# lists; the longest lists the planner takes
+@pytest.mark.parametrize("Q,D,res,plan,extra", [(3, 1, 480, 20, 3), (12, 2, 120, 10, 12), (20, 5, 40, 8, 20), (9, 8, 60, 5, 9), (200, 9, 9, 3, 200), (6, 8, 3, 1, 6)])
+def test_decode_greedy_builds_timelines_of_any_length(ctx, Q, D, res, plan, extra):
+    r, lock, iv = synth.make_decode_round("decode_tiny", 60 + Q, n_wf=max(8, Q // 4), Q=Q, D=D, T=min(4, D), stride=res + plan,
+                                          n_resident=res, n_planned=plan, lock_fraction=0.2)
+    L, O = r.calls["L_in"], r.calls["L_out"]
+    rng = np.random.default_rng(Q + D)
+    node = rng.permutation(Q).astype(np.int32); wf = rng.integers(0, 4, Q).astype(np.int32)
+    elapsed = rng.uniform(0, 20, Q).astype(np.float32)
+    tail = rng.uniform(0, 5, Q).astype(np.float32); hor = rng.uniform(5, 50, 4).astype(np.float32)
+    big = widen(iv, D, extra)
+    assert ctx.lib.hx_test_decode_plan_lean(big["stride"], D, Q) == 0
+    got = run_plan(ctx, r.model, L, O, lock, node, wf, elapsed, tail, hor, r.dec, big)
+    check_plan_stepwise(r.model, L, O, lock, node, wf, elapsed, tail, hor, r.dec, big, got)
+
+
 def test_decode_greedy_at_the_benchmarks_size(ctx):
     # the queue bench.py times: 256 calls x 32 instances, 24 resident + 4 planned entries each, lists of 140 entries
     Q, D = 256, 32
