@@ -1277,13 +1277,26 @@ __global__ __launch_bounds__(DP_MAX_THREADS) void hx_decode_plan_kernel(DGreedyA
                     int pos_s = 0, pos_e = 0;
                     bool has_s = false, has_e = false;
                     const int top0 = (n_old - 1) & ~(HX_WAVE - 1);
-                    int2 me;                                   // of the last 64 entries at the end
-                    for (int i0 = 0; i0 <= top0; i0 += HX_WAVE) {
-                        me = tl[min(i0 + lane, n_old - 1)];
-                        const float t = i0 + lane < n_old ? __int_as_float(me.x) : INFINITY;      // S and E are finite
-                        pos_s += __popcll(__builtin_amdgcn_ballot_w64(t < S)); pos_e += __popcll(__builtin_amdgcn_ballot_w64(t < E));
-                        has_s = has_s || __builtin_amdgcn_ballot_w64(t == S) != 0; has_e = has_e || __builtin_amdgcn_ballot_w64(t == E) != 0;
+                    const int2 tail_me = tl[min(top0 + lane, n_old - 1)];      // of the last 64 entries
+                    if (top0 == 0) {
+                        const float t = lane < n_old ? __int_as_float(tail_me.x) : INFINITY;      // S and E are finite
+                        pos_s = __popcll(__builtin_amdgcn_ballot_w64(t < S)); pos_e = __popcll(__builtin_amdgcn_ballot_w64(t < E));
+                        has_s = __builtin_amdgcn_ballot_w64(t == S) != 0; has_e = __builtin_amdgcn_ballot_w64(t == E) != 0;
+                    } else {
+                        // more than 64 entries: every seg-th first, then the seg of them (at most 16) that lead up to the place, by
+                        // half a wavefront for S and the other for E
+                        const int seg = (n_old + HX_WAVE - 1) / HX_WAVE;
+                        const float t = lane * seg < n_old ? __int_as_float(tl[lane * seg].x) : INFINITY;
+                        const int from_s = max((int)__popcll(__builtin_amdgcn_ballot_w64(t < S)) - 1, 0) * seg;
+                        const int from_e = max((int)__popcll(__builtin_amdgcn_ballot_w64(t < E)) - 1, 0) * seg;
+                        const int i = (lane < 32 ? from_s : from_e) + (lane & 31);
+                        const bool in = (lane & 31) <= seg && i < n_old;      // (one more: the entry at the place itself)
+                        const float u = in ? __int_as_float(tl[i].x) : INFINITY, mine = lane < 32 ? S : E;
+                        const u64 before = __builtin_amdgcn_ballot_w64(u < mine), same = __builtin_amdgcn_ballot_w64(u == mine);
+                        pos_s = from_s + (int)__popc((unsigned)before); pos_e = from_e + (int)__popc((unsigned)(before >> 32));
+                        has_s = (unsigned)same != 0; has_e = (unsigned)(same >> 32) != 0;
                     }
+                    int2 me = tail_me;
                     // pos_e >= 1: entry 0 is now, and E > 0
                     const int before_s = max(pos_s - 1, 0), before_e = pos_e - 1;
                     const int occ_before_s = top0 == 0 ? __builtin_amdgcn_readlane(me.y, before_s) : tl[before_s].y;
@@ -1296,8 +1309,8 @@ __global__ __launch_bounds__(DP_MAX_THREADS) void hx_decode_plan_kernel(DGreedyA
                         most = max(most, sum);
                         return sum;
                     };
-                    // from the last 64 entries to the first: an entry moves by two places at most, towards the end
-                    for (int i0 = top0; i0 >= 0; i0 -= HX_WAVE) {
+                    // from the last 64 entries to those at S: an entry moves by two places at most, towards the end
+                    for (int i0 = top0; i0 >= 0 && i0 + HX_WAVE > pos_s; i0 -= HX_WAVE) {
                         const int i = i0 + lane;
                         if (i0 != top0) me = tl[i];
                         hx_wave_sync();
