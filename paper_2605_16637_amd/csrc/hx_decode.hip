@@ -1573,7 +1573,11 @@ extern "C" int hx_decode_plan_greedy(hx_ctx *ctx, const hx_model *model, const h
         hx_decode_no_instance_kernel<<<(Q + 255) / 256, 256, 0, stream>>>(a);
     } else {
         const size_t lds = DPlanLds(iv->stride, D, Q).bytes();
-        if (!hx_test_decode_plan_lean(iv->stride, D, Q)) hx_decode_plan_kernel<<<1, Q > DP_THREADS ? DP_MAX_THREADS : DP_THREADS, lds, stream>>>(a);
+        // The widest workgroup also where few calls meet long lists: the calls need no more lanes, but the timelines are built by all
+        // of them (64 calls on 8 instances with lists of 310: 592 -> 532 us; 200 calls, which would be dealt to more lanes: 1452 ->
+        // 1577; lists of 128 and fewer: no difference).
+        const bool wide = Q > DP_THREADS || (Q * DP_MAX_G <= DP_THREADS && iv->stride >= 256);
+        if (!hx_test_decode_plan_lean(iv->stride, D, Q)) hx_decode_plan_kernel<<<1, wide ? DP_MAX_THREADS : DP_THREADS, lds, stream>>>(a);
         else hx_decode_plan_lean_kernel<<<1, DG_THREADS, lay.bytes(), stream>>>(a);
     }
     return hx_check_launch(ctx, "hx_decode_plan_greedy kernel");
