@@ -20,12 +20,12 @@ struct NodeCostArgs {
     float *cost;
 };
 
-// Per-class tables of the standalone cost, padded to kT x kT (a pair with a class
-// that does not exist has infinite transfer latency), so that the pair loop
-// unrolls completely and its table reads are LDS broadcasts.
+// Per-class tables of the standalone cost, padded to kT x kT (a pair with a class that does not exist has infinite
+// transfer latency and loses).  link[td * kT + tp]: (1 / bandwidth, latency) from prefill class tp to decode class td, two
+// prefill classes to a 16-byte read, an LDS broadcast.
 struct CostTables {
     float invF[kT], invB[kT], c1[kT], c2[kT], kB[kT];
-    float invbw[kT * kT], lat[kT * kT];
+    alignas(16) float2 link[kT * kT];
 };
 
 // filled by the first kT * kT threads of the block; a barrier follows at the caller's
@@ -40,61 +40,63 @@ __device__ __forceinline__ void hx_cost_tables_fill(CostTables &t, const NodeCos
         t.c1[tid] = in ? d.c1 : 0.0f; t.c2[tid] = in ? d.c2 : 0.0f; t.kB[tid] = in ? d.kB : 0.0f;
     }
     if (tid < kT * kT) {
-        const int tp = tid / kT, td = tid % kT;
+        const int td = tid / kT, tp = tid % kT;
         const bool in = tp < a.T && td < a.T;
-        t.invbw[tid] = in ? 1.0f / a.bw[tp * a.T + td] : 0.0f;
-        t.lat[tid] = in ? (a.lat ? a.lat[tp * a.T + td] : 0.0f) : INFINITY;
+        t.link[tid] = make_float2(in ? 1.0f / a.bw[tp * a.T + td] : 0.0f,
+                                  in ? (a.lat ? a.lat[tp * a.T + td] : 0.0f) : INFINITY);
     }
 }
 
-// min over class pairs of prefill + transfer + decode on an idle pool.  T: classes in use (wave-uniform); the
-// pairs beyond them would lose anyway (infinite latency in the padded tables) and are not evaluated.
-__device__ __forceinline__ float hx_node_cost_eval(const HxModelF &m, const CostTables &t, int T, int L, int O)
+// Min over class pairs of prefill + transfer + decode on an idle pool, for NN nodes together.  T: classes in use
+// (wave-uniform), TT >= T: classes with room in registers.  The earliest arrival at a decode class stands for all prefill
+// classes: a candidate does not fall when its arrival grows, and minima round nothing.  The decode classes are taken one after
+// the other, so a node holds TT finishes and a handful of other values.  Bound: instruction issue, some 3 instructions a pair;
+// the tables' LDS reads are shared by the NN nodes.  2.0 M nodes, 4 classes, on their own: 20.5 us with all pairs unrolled at
+// once (186 registers, two wavefronts on a SIMD), 9.4 us so (57 registers, four nodes a thread).
+template <int NN, int TT>
+__device__ __forceinline__ void hx_node_cost_eval(const HxModelF &m, const CostTables &t, int T, const int (&L)[NN], const int (&O)[NN],
+                                                  float (&out)[NN])
 {
-    const HxCallF cf = hx_call_terms(m, L, O);
-    float done[kT];
+    float kvL[NN], ctx[NN], Of[NN], done[NN][TT];
 #pragma unroll
-    for (int tp = 0; tp < kT; ++tp) done[tp] = tp < T ? hx_prefill_done(cf, 0.0f, t.invF[tp], t.invB[tp]) : INFINITY;
-    float best = INFINITY;
+    for (int n = 0; n < NN; ++n) {
+        const HxCallF cf = hx_call_terms(m, L[n], O[n]);
+        kvL[n] = cf.kvL; ctx[n] = cf.ctx; Of[n] = cf.O;
+        // (classes beyond T: finite, excluded by their links)
 #pragma unroll
-    for (int td = 0; td < kT; ++td) {
-        if (td < T) {
-            // the earliest arrival stands for all prefill classes: a candidate does not fall when its arrival grows, and
-            // minima round nothing (the maximum with the wait and the decode time once per decode class, not per pair: 2.0 M
-            // nodes, 4 classes, with the critical path after it 33.0 -> 32.7 us)
-            float r = INFINITY;
-#pragma unroll
-            for (int tp = 0; tp < kT; ++tp)
-                if (tp < T) r = fminf(r, done[tp] + hx_transfer(cf, t.invbw[tp * kT + td], t.lat[tp * kT + td]));
-            best = fminf(best, hx_candidate(r, 0.0f, hx_decode_time(cf, t.c1[td], t.c2[td], t.kB[td])));
-        }
+        for (int tp = 0; tp < TT; ++tp) done[n][tp] = hx_prefill_done(cf, 0.0f, t.invF[tp], t.invB[tp]);
+        out[n] = INFINITY;
     }
-    return best;
-}
-
-
-// The same minimum with the prefill classes taken one after the other instead of all pairs at once: some twenty
-// registers instead of two hundred, for kernels whose other work sets the register budget.  Every pair's cost is
-// formed here; the minimum is the same bits either way.
-__device__ __forceinline__ float hx_node_cost_eval_rolled(const HxModelF &m, const CostTables &t, int T, int L, int O)
-{
-    const HxCallF cf = hx_call_terms(m, L, O);
-    float dec[kT];
-#pragma unroll
-    for (int td = 0; td < kT; ++td) dec[td] = td < T ? hx_decode_time(cf, t.c1[td], t.c2[td], t.kB[td]) : INFINITY;
-    float best = INFINITY;
 #pragma unroll 1
-    for (int tp = 0; tp < T; ++tp) {
-        const float done = hx_prefill_done(cf, 0.0f, t.invF[tp], t.invB[tp]);
+    for (int td = 0; td < T; ++td) {
+        float r[NN];
 #pragma unroll
-        for (int td = 0; td < kT; ++td) {
-            if (td < T) {
-                const float x = hx_transfer(cf, t.invbw[tp * kT + td], t.lat[tp * kT + td]);
-                best = fminf(best, hx_candidate(done + x, 0.0f, dec[td]));
-            }
+        for (int n = 0; n < NN; ++n) r[n] = INFINITY;
+#pragma unroll
+        for (int tp = 0; tp < TT; tp += 2) {
+            if (TT > 4 && tp >= T) break;
+            const float4 x = *(const float4 *)&t.link[td * kT + tp];
+#pragma unroll
+            for (int n = 0; n < NN; ++n)
+                r[n] = fminf(r[n], fminf(done[n][tp] + fmaf(kvL[n], x.x, x.y), done[n][tp + 1] + fmaf(kvL[n], x.z, x.w)));
+        }
+        const float c1 = t.c1[td], c2 = t.c2[td], kB = t.kB[td];
+#pragma unroll
+        for (int n = 0; n < NN; ++n) {
+            HxCallF cf;
+            cf.ctx = ctx[n]; cf.O = Of[n];
+            out[n] = fminf(out[n], hx_candidate(r[n], 0.0f, hx_decode_time(cf, c1, c2, kB)));
         }
     }
-    return best;
+}
+
+// one node, any number of classes
+__device__ __forceinline__ float hx_node_cost_one(const HxModelF &m, const CostTables &t, int T, int L, int O)
+{
+    const int Ls[1] = {L}, Os[1] = {O};
+    float out[1];
+    hx_node_cost_eval<1, kT>(m, t, T, Ls, Os, out);
+    return out[0];
 }
 
 // ---- critical path, single pass ---------------------------------------------------
@@ -196,9 +198,8 @@ __device__ __forceinline__ bool hx_cp_walk(const CpArgs &a, char *base, int n0, 
 // COST: the node costs are not read but worked out here from the nodes' lengths (and written out as
 // well), `nc` and `tab` being the arguments and the class tables of the standalone cost.
 // STREAM: rem, level and tail leave with stores that do not claim cache lines (see the store phase).
-// ROLLED: the cost's class pairs one after the other (hx_node_cost_eval_rolled), for a kernel with few registers to spare.
 // NT: threads of the workgroup.
-template <int NMAX, bool COST, bool STREAM, bool ROLLED = false, int NT = CP_THREADS>
+template <int NMAX, bool COST, bool STREAM, int NT = CP_THREADS>
 __device__ __forceinline__ void hx_cp_local_body(const CpArgs &a, int wpb, CpNode *s_node, int &s_any,
                                                  const NodeCostArgs *nc, CostTables *tab, int block)
 {
@@ -286,8 +287,7 @@ __device__ __forceinline__ void hx_cp_local_body(const CpArgs &a, int wpb, CpNod
                 for (int k = 0; k < CP_NPT; ++k) {
                     const int i = k * NT + tid;
                     if constexpr (COST) if (i < nn) {
-                        c[k] = ROLLED ? hx_node_cost_eval_rolled(nc->m, *tab, nc->T, len_in[k], len_out[k])
-                                      : hx_node_cost_eval(nc->m, *tab, nc->T, len_in[k], len_out[k]);
+                        c[k] = hx_node_cost_one(nc->m, *tab, nc->T, len_in[k], len_out[k]);
                         nc->cost[n0 + i] = c[k];
                     }
                     if (i < nn) *(int2 *)&s_node[i + 1] = make_int2(__float_as_int(c[k]), deg[k] < 0);
@@ -363,8 +363,7 @@ __device__ __forceinline__ void hx_cp_local_body(const CpArgs &a, int wpb, CpNod
                 }
                 float cv;
                 if constexpr (COST) {
-                    cv = ROLLED ? hx_node_cost_eval_rolled(nc->m, *tab, nc->T, nc->L_in[v], nc->L_out[v])
-                                : hx_node_cost_eval(nc->m, *tab, nc->T, nc->L_in[v], nc->L_out[v]);
+                    cv = hx_node_cost_one(nc->m, *tab, nc->T, nc->L_in[v], nc->L_out[v]);
                     nc->cost[v] = cv;
                 }
                 else cv = a.cost[v];

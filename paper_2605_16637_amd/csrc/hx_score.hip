@@ -491,7 +491,7 @@ __global__ __launch_bounds__(FS_THREADS) void hx_reveal_search_kernel(ScoreArgs 
     extern __shared__ __align__(16) float smem[];
     if ((int)blockIdx.x < n_reveal) {
         RevealLds *l = (RevealLds *)smem;
-        hx_cp_local_body<RV_NMAX, true, false, true, FS_THREADS>(cp, wpb, l->node, l->any, &nc, &l->tab, (int)blockIdx.x);
+        hx_cp_local_body<RV_NMAX, true, false, FS_THREADS>(cp, wpb, l->node, l->any, &nc, &l->tab, (int)blockIdx.x);
         return;
     }
     hx_fused_search_body<CALLS>(a, pa, smem, (int)blockIdx.x - n_reveal);

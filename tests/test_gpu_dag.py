@@ -69,6 +69,34 @@ def test_node_cost_and_critical_path(ctx, name, seed):
     assert_costs_close(got2[0], want64[0], "rem, GPU cost"); assert_costs_close(got2[3], want64[3], "horizon, GPU cost")
 
 
+@pytest.mark.parametrize("T", [1, 3, 4, 5, 8])
+def test_node_cost_of_many_nodes(ctx, T):
+    # From 262144 nodes on (256 compute units) a thread takes four; beyond 2097152 it comes back for more.  Any part of the
+    # array on its own, short enough for a node a thread, has the same bits, and nothing is written past the end.
+    import torch
+    from paper_2605_16637_amd import binding
+    rng = np.random.default_rng(T)
+    types = dict(flops=rng.uniform(1e14, 3e15, T).astype(np.float32), hbm_bw=rng.uniform(1e12, 8e12, T).astype(np.float32))
+    links = dict(n_types=T, bw=rng.uniform(1e10, 1e11, T * T).astype(np.float32),
+                 latency=rng.uniform(0, 0.01, T * T).astype(np.float32) if T % 2 else None)
+    most = 2097152 + 1025
+    L, O = rng.integers(0, 32769, most).astype(np.int32), rng.integers(0, 4097, most).astype(np.int32)
+    dL, dO, tF, tB, dl = dev(L), dev(O), dev(types["flops"]), dev(types["hbm_bw"]), binding.to_device(links)
+
+    def cost(i, n):
+        out = torch.full((n + 64,), -7.0, device="cuda:0")
+        ctx.hx_node_cost(synth.MODEL, dL[i:i + n], dO[i:i + n], tF, tB, dl, out[:n])
+        ctx.hx_stream_status()
+        assert bool((out[n:] == -7.0).all())
+        return out[:n].cpu().numpy()
+
+    parts = np.concatenate([cost(i, min(200000, most - i)) for i in range(0, most, 200000)])
+    for n in (262144, 262145, 524287, most):
+        assert np.array_equal(cost(0, n), parts[:n])
+    some = rng.choice(most, 2000, replace=False)
+    assert_costs_close(parts[some], o.node_cost(synth.MODEL, L[some], O[some], types, links), "node cost")
+
+
 def test_critical_path_stress_full_size(ctx):
     # 100 000 workflows, 2.0 M nodes, ~3.4 M edges, depth up to 32
     rnd = synth.make_round("cp", 1)
