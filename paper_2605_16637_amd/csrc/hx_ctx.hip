@@ -56,36 +56,6 @@ __global__ __launch_bounds__(256) void hx_commit_clear_kernel(CommitArgs a)
     if (i < a.P + 2 * a.D) a.acc[i] = 0ull;
 }
 
-// sum of x over the lanes of `members` (all lanes of the wave take part)
-__device__ __forceinline__ unsigned long long hx_wave_sum(unsigned long long x)
-{
-#pragma unroll
-    for (int off = HX_WAVE / 2; off > 0; off >>= 1) x += __shfl_xor(x, off);
-    return x;
-}
-
-// Adds, per distinct key among the lanes of the wave, the lanes' values into
-// acc[key] with one LDS atomic per key (chosen placements concentrate on a few
-// instances: 64 atomics on one address would serialise).
-__device__ __forceinline__ void hx_add_by_key(unsigned long long *acc, bool valid, int key,
-                                              unsigned long long v0, unsigned long long *acc1, unsigned long long v1)
-{
-    unsigned long long todo = __ballot(valid);
-    const int lane = threadIdx.x & (HX_WAVE - 1);
-    while (todo) {
-        const int leader = __ffsll((long long)todo) - 1;
-        const int k = __shfl(key, leader);
-        const bool mine = valid && key == k;
-        const unsigned long long s0 = hx_wave_sum(mine ? v0 : 0ull);
-        const unsigned long long s1 = acc1 ? hx_wave_sum(mine ? v1 : 0ull) : 0ull;
-        if (lane == leader) {
-            atomicAdd(&acc[k], s0);
-            if (acc1) atomicAdd(&acc1[k], s1);
-        }
-        todo &= ~__ballot(mine);
-    }
-}
-
 __device__ __forceinline__ int hx_add_sat_drain(int cur, unsigned long long add, int drain, int32_t *status)
 {
     unsigned long long total = (unsigned long long)(cur < 0 ? 0 : cur) + add;
@@ -94,30 +64,117 @@ __device__ __forceinline__ int hx_add_sat_drain(int cur, unsigned long long add,
     return left < 0 ? 0 : (left > 2147483647LL ? 2147483647 : (int)left);
 }
 
-// The state update of Algorithm 1 for all calls of the round at once: integer
-// additions commute, so the result does not depend on call order.  Every wave
-// first combines its calls per instance, every block sums into an LDS copy of
-// the counters, and only the non-zero sums reach the global accumulators.
-__global__ __launch_bounds__(256) void hx_commit_add_kernel(CommitArgs a, RatioArgs rt)
+// sum over the wavefront; all lanes take part, all have the result
+__device__ __forceinline__ unsigned hx_wave_sum(unsigned x)
 {
+    x += (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false);      // row_shr 1, 2, 4, 8
+    x += (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false);
+    x += (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false);
+    x += (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false);
+    x += (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false);      // row_bcast 15, 31
+    x += (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false);
+    return (unsigned)__builtin_amdgcn_readlane((int)x, HX_WAVE - 1);
+}
+
+// of values below 2^31, in 64 bits: by halves, 64 of which fit 32 bits
+__device__ __forceinline__ unsigned long long hx_wave_sum_i31(int x)
+{
+    return (unsigned long long)hx_wave_sum((unsigned)x & 0xffffu) + ((unsigned long long)hx_wave_sum((unsigned)x >> 16) << 16);
+}
+
+// One call a lane into the workgroup's counters, by LDS atomics; all lanes of the wavefront take part.  Lanes that meet on a
+// counter are serialised there, and scored on one snapshot most calls of a round choose the same instance: where all of
+// a wavefront do, one lane adds their sum (16384 calls on 256 + 256 as part of a round 20.6 -> 18.9 us).  False: a pair or a length out of range.
+__device__ __forceinline__ bool hx_commit_call(const CommitArgs &a, unsigned long long *acc, int p, int d, int L, int O)
+{
+    bool valid = p >= 0 && d >= 0;                          // otherwise the call stays queued
+    const bool bad = valid && (p >= a.P || d >= a.D || L < 0 || O < 0);
+    valid = valid && !bad;
+    const unsigned long long m = __builtin_amdgcn_ballot_w64(valid);
+    if (m == 0) return !bad;
+    const int lead = __builtin_ctzll(m), lane = threadIdx.x & (HX_WAVE - 1);
+    const bool one_p = __builtin_amdgcn_ballot_w64(valid && p != __builtin_amdgcn_readlane(p, lead)) == 0;
+    const bool one_d = __builtin_amdgcn_ballot_w64(valid && d != __builtin_amdgcn_readlane(d, lead)) == 0;
+    const unsigned long long all_L = one_p || one_d ? hx_wave_sum_i31(valid ? L : 0) : 0ull;
+    if (one_p ? lane == lead : valid) atomicAdd(&acc[p], one_p ? all_L : (unsigned long long)L);
+    if (one_d) {
+        const unsigned long long all_O = hx_wave_sum_i31(valid ? O : 0);
+        if (lane == lead) { atomicAdd(&acc[a.P + d], all_L + all_O); atomicAdd(&acc[a.P + a.D + d], all_O); }
+    } else if (valid) {
+        atomicAdd(&acc[a.P + d], (unsigned long long)L + (unsigned long long)O);
+        atomicAdd(&acc[a.P + a.D + d], (unsigned long long)O);
+    }
+    return !bad;
+}
+
+// An instance's counters and drains (the prefill and the decode instance of one index), asked for together and, where the
+// caller can, before the sums are there.  A thread without an instance reads the status word instead: conditional loads
+// are waited for one after the other (64 calls in one workgroup 2.75 -> 2.6 us, 16384 in several 5.3 -> 4.9).
+struct InstanceState {
+    int backlog, drain_p, qd, drain_q, used, release;
+    __device__ __forceinline__ void load(const CommitArgs &a, int i)
+    {
+        const bool p = i < a.P, d = i < a.D;
+        backlog = *(p ? a.backlog + i : a.status); drain_p = *(p && a.drain_p ? a.drain_p + i : a.status);
+        qd = *(d ? a.qd + i : a.status); drain_q = *(d && a.drain_q ? a.drain_q + i : a.status);
+        used = *(d ? a.used + i : a.status); release = *(d && a.release ? a.release + i : a.status);
+    }
+    // the round's additions, then the drains
+    __device__ __forceinline__ void apply(const CommitArgs &a, int i, unsigned long long prompt, unsigned long long held, unsigned long long queued) const
+    {
+        if (i < a.P) a.backlog[i] = hx_add_sat_drain(backlog, prompt, a.drain_p ? drain_p : 0, a.status);
+        if (i < a.D) {
+            a.qd[i] = hx_add_sat_drain(qd, queued, a.drain_q ? drain_q : 0, a.status);
+            const int left = hx_add_sat_drain(used, held, a.release ? release : 0, a.status);
+            a.used[i] = left;
+            const long long b = ((long long)left + a.tokens_per_seq - 1) / a.tokens_per_seq;
+            a.batch[i] = (int)(b > a.max_batch ? a.max_batch : b);
+        }
+    }
+};
+
+// The state update of Algorithm 1 for all calls of the round at once: integer
+// additions commute, so the result does not depend on call order.  Every
+// workgroup adds into an LDS copy of the counters, and only the non-zero sums
+// reach the global accumulators.  Bound: the chain calls -> LDS -> device atomics and
+// their answers -> ticket -> drains, about 5 us, and the device atomics on the
+// counters the workgroups share, which is why many calls are given to few
+// workgroups.  64 lanes that meet on one counter cost some 80 cycles; combining
+// them in the wavefront first (a loop over its distinct instances, shuffles in
+// each turn) cost far more wherever they are many.  Launches back to back, that
+// form and this one (us; placements spread, all on one instance):
+//   4096 calls on 64 + 64       40.8 -> 4.9     5.9 -> 4.7
+//   16384 on 256 + 256          56.1 -> 5.2     7.3 -> 5.2
+//   32768 on 512 + 512          61.5 -> 6.0     9.6 -> 5.8
+// Workgroups of 256, 512 or 1024 threads took 5.1, 5.1, 5.1 for the first of these, spread, and 11.5, 7.1, 6.2 for the last.
+constexpr int CA_THREADS = 1024;          // most threads; rounds of up to CA_FEW_CALLS calls are launched with CA_FEW
+constexpr int CA_FEW = 512;
+constexpr int CA_FEW_CALLS = 8192;
+// The ratios are formed by workgroups of their own after the first n_add, CA_FOLD calls each: their gathers are random reads,
+// which many compute units do sooner than few.
+constexpr int CA_FOLD = 256;
+__global__ __launch_bounds__(CA_THREADS) void hx_commit_add_kernel(CommitArgs a, RatioArgs rt, int n_add)
+{
+    if ((int)blockIdx.x >= n_add) {
+        const int step = ((int)gridDim.x - n_add) * CA_FOLD;
+        if (threadIdx.x >= CA_FOLD) return;
+        for (long long c = ((long long)blockIdx.x - n_add) * CA_FOLD + threadIdx.x; c < a.C; c += step)
+            hx_projected_ratio(rt.node, rt.wf, rt.elapsed, rt.tail, rt.horizon, rt.n_nodes, rt.n_wf, (int)c, rt.best_cost[c], a.status, rt.ratio);
+        return;
+    }
     __shared__ unsigned long long s_acc[3 * HX_MAX_INSTANCES];
     const int n_acc = a.P + 2 * a.D;
+    InstanceState own;
+    own.load(a, threadIdx.x);
     for (int i = threadIdx.x; i < n_acc; i += blockDim.x) s_acc[i] = 0ull;
     __syncthreads();
     bool bad = false;
-    const int stride = gridDim.x * blockDim.x;
-    const int rounds = (a.C + stride - 1) / stride;          // the same trip count for every lane of a wave
-    for (int it = 0; it < rounds; ++it) {
-        const int c = it * stride + blockIdx.x * blockDim.x + threadIdx.x;
+    const int stride = n_add * blockDim.x;
+    for (long long at = blockIdx.x * blockDim.x; at < a.C; at += stride) {       // the same for all lanes
+        const long long c = at + threadIdx.x;
         int p = -1, d = -1, L = 0, O = 0;
         if (c < a.C) { p = a.best_p[c]; d = a.best_d[c]; L = a.L_in[c]; O = a.L_out[c]; }
-        if (rt.ratio && c < a.C)
-            hx_projected_ratio(rt.node, rt.wf, rt.elapsed, rt.tail, rt.horizon, rt.n_nodes, rt.n_wf, c, rt.best_cost[c], a.status, rt.ratio);
-        bool valid = p >= 0 && d >= 0;                      // otherwise the call stays queued
-        if (valid && (p >= a.P || d >= a.D || L < 0 || O < 0)) { bad = true; valid = false; }
-        hx_add_by_key(s_acc, valid, p, (unsigned long long)L, nullptr, 0ull);
-        hx_add_by_key(s_acc + a.P, valid, d, (unsigned long long)L + (unsigned long long)O,
-                      s_acc + a.P + a.D, (unsigned long long)O);
+        if (!hx_commit_call(a, s_acc, p, d, L, O)) bad = true;
     }
     if (bad) hx_raise(a.status, HX_ERR_INDEX);
     __syncthreads();
@@ -135,35 +192,37 @@ __global__ __launch_bounds__(256) void hx_commit_add_kernel(CommitArgs a, RatioA
     __syncthreads();
     if (threadIdx.x == 0) {
         const int t = atomicAdd(a.ticket, 1);
-        s_last = t == (int)gridDim.x - 1;
+        s_last = t == n_add - 1;
         if (s_last) __hip_atomic_store(a.ticket, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __syncthreads();
     if (!s_last) return;
-    for (int i = threadIdx.x; i < (a.P > a.D ? a.P : a.D); i += blockDim.x) {
-        if (i < a.P) a.backlog[i] = hx_add_sat_drain(a.backlog[i], atomicExch(&a.acc[i], 0ull), a.drain_p ? a.drain_p[i] : 0, a.status);
-        if (i < a.D) {
-            a.qd[i] = hx_add_sat_drain(a.qd[i], atomicExch(&a.acc[a.P + a.D + i], 0ull), a.drain_q ? a.drain_q[i] : 0, a.status);
-            const int used = hx_add_sat_drain(a.used[i], atomicExch(&a.acc[a.P + i], 0ull), a.release ? a.release[i] : 0, a.status);
-            a.used[i] = used;
-            long long b = ((long long)used + a.tokens_per_seq - 1) / a.tokens_per_seq;
-            a.batch[i] = (int)(b > a.max_batch ? a.max_batch : b);
-        }
+    const int n_inst = a.P > a.D ? a.P : a.D;
+    for (int i = threadIdx.x; i < n_inst; i += blockDim.x) {
+        if (i >= (int)blockDim.x) own.load(a, i);
+        const unsigned long long prompt = i < a.P ? atomicExch(&a.acc[i], 0ull) : 0ull;
+        const unsigned long long held = i < a.D ? atomicExch(&a.acc[a.P + i], 0ull) : 0ull;
+        const unsigned long long queued = i < a.D ? atomicExch(&a.acc[a.P + a.D + i], 0ull) : 0ull;
+        own.apply(a, i, prompt, held, queued);
     }
 }
+
+int commit_threads(int C) { return C <= CA_FEW_CALLS ? CA_FEW : CA_THREADS; }
 
 // Both steps in one workgroup, for rounds small enough that one compute unit adds them up as fast as a launch
 // takes: the additions go into the workgroup's LDS counters with LDS atomics, and the same threads then apply
 // the drains -- no global accumulators, one launch instead of two.  Same integer results.
 constexpr int COMMIT_ONE_THREADS = 1024;
-// rounds of at most this many calls are committed by the one-workgroup kernel: a launch saved (3-4 us of a small
-// round).  Measured: 4096 calls already take it 2 us longer than the two launches (chosen placements concentrate
-// on few instances, and lanes that meet on a counter wait for each other), 16384 calls 30 us longer.
-constexpr int HX_COMMIT_ONE_LAUNCH = 1024;
+// Rounds of at most this many calls are committed by the one-workgroup kernel: no device atomics and their answers, but the
+// lanes of all calls meet in one compute unit's LDS.  One workgroup and several (us; placements spread, all on three
+// instances): 1537 calls 3.3, 4.5 and 4.2, 4.8; 2048 3.4, 5.0 and 4.6, 5.0; 4096 4.5, 7.4 and 4.6, 5.0.
+constexpr int HX_COMMIT_ONE_LAUNCH = 2048;
 __global__ __launch_bounds__(COMMIT_ONE_THREADS) void hx_commit_one_kernel(CommitArgs a, RatioArgs rt)
 {
     __shared__ unsigned long long s_acc[3 * HX_MAX_INSTANCES];
     const int n_acc = a.P + 2 * a.D;
+    InstanceState own;
+    own.load(a, threadIdx.x);
     for (int i = threadIdx.x; i < n_acc; i += COMMIT_ONE_THREADS) s_acc[i] = 0ull;
     __syncthreads();
     bool bad = false;
@@ -174,44 +233,23 @@ __global__ __launch_bounds__(COMMIT_ONE_THREADS) void hx_commit_one_kernel(Commi
         if (c < a.C) { p = a.best_p[c]; d = a.best_d[c]; L = a.L_in[c]; O = a.L_out[c]; }
         if (rt.ratio && c < a.C)
             hx_projected_ratio(rt.node, rt.wf, rt.elapsed, rt.tail, rt.horizon, rt.n_nodes, rt.n_wf, c, rt.best_cost[c], a.status, rt.ratio);
-        bool valid = p >= 0 && d >= 0;
-        if (valid && (p >= a.P || d >= a.D || L < 0 || O < 0)) { bad = true; valid = false; }
-        if (valid) {       // LDS atomics: lanes that meet on a counter are serialised there, nowhere else
-            atomicAdd(&s_acc[p], (unsigned long long)L);
-            atomicAdd(&s_acc[a.P + d], (unsigned long long)L + (unsigned long long)O);
-            atomicAdd(&s_acc[a.P + a.D + d], (unsigned long long)O);
-        }
+        if (!hx_commit_call(a, s_acc, p, d, L, O)) bad = true;
     }
     if (bad) hx_raise(a.status, HX_ERR_INDEX);
     __syncthreads();
     const int i = threadIdx.x;
-    if (i < a.P) a.backlog[i] = hx_add_sat_drain(a.backlog[i], s_acc[i], a.drain_p ? a.drain_p[i] : 0, a.status);
-    if (i < a.D) {
-        a.qd[i] = hx_add_sat_drain(a.qd[i], s_acc[a.P + a.D + i], a.drain_q ? a.drain_q[i] : 0, a.status);
-        const int used = hx_add_sat_drain(a.used[i], s_acc[a.P + i], a.release ? a.release[i] : 0, a.status);
-        a.used[i] = used;
-        long long b = ((long long)used + a.tokens_per_seq - 1) / a.tokens_per_seq;
-        a.batch[i] = (int)(b > a.max_batch ? a.max_batch : b);
-    }
+    own.apply(a, i, i < a.P ? s_acc[i] : 0ull, i < a.D ? s_acc[a.P + i] : 0ull, i < a.D ? s_acc[a.P + a.D + i] : 0ull);
 }
 
 __global__ __launch_bounds__(256) void hx_commit_drain_kernel(CommitArgs a)
 {
     // the accumulators are left at zero for the next round
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < a.P) {
-        a.backlog[i] = hx_add_sat_drain(a.backlog[i], a.acc[i], a.drain_p ? a.drain_p[i] : 0, a.status);
-        a.acc[i] = 0ull;
-    }
-    if (i < a.D) {
-        a.qd[i] = hx_add_sat_drain(a.qd[i], a.acc[a.P + a.D + i], a.drain_q ? a.drain_q[i] : 0, a.status);
-        const int used = hx_add_sat_drain(a.used[i], a.acc[a.P + i], a.release ? a.release[i] : 0, a.status);
-        a.used[i] = used;
-        a.acc[a.P + i] = 0ull;
-        a.acc[a.P + a.D + i] = 0ull;
-        long long b = ((long long)used + a.tokens_per_seq - 1) / a.tokens_per_seq;
-        a.batch[i] = (int)(b > a.max_batch ? a.max_batch : b);
-    }
+    InstanceState own;
+    own.load(a, i);
+    own.apply(a, i, i < a.P ? a.acc[i] : 0ull, i < a.D ? a.acc[a.P + i] : 0ull, i < a.D ? a.acc[a.P + a.D + i] : 0ull);
+    if (i < a.P) a.acc[i] = 0ull;
+    if (i < a.D) { a.acc[a.P + i] = 0ull; a.acc[a.P + a.D + i] = 0ull; }
 }
 
 // ---- element-by-element check of a round's inputs (debug entry point) ----
@@ -442,10 +480,13 @@ int commit_round(hx_ctx *ctx, const hx_calls *calls, const int32_t *best_p, cons
         hx_commit_one_kernel<<<1, COMMIT_ONE_THREADS, 0, stream>>>(a, rt);
         return hx_check_launch(ctx, "hx_commit_one_kernel");
     }
-    int grid = (C + 255) / 256;
+    const int threads = commit_threads(C);
+    int grid = C / threads + (C % threads != 0);
     grid = grid > ctx->num_cu ? ctx->num_cu : grid;
     a.ticket = ctx->d_ticket;                  // the workgroup that finishes last applies the drains
-    hx_commit_add_kernel<<<grid, 256, 0, stream>>>(a, rt);
+    int fold = rt.ratio ? C / CA_FOLD + (C % CA_FOLD != 0) : 0;
+    fold = fold > ctx->num_cu ? ctx->num_cu : fold;
+    hx_commit_add_kernel<<<grid + fold, threads, 0, stream>>>(a, rt, grid);
     return hx_check_launch(ctx, "hx_commit_add_kernel");
 }
 
@@ -496,9 +537,10 @@ extern "C" int hx_commit_static(const hx_calls *calls, const int32_t *best_p, co
     // (a fill kernel, so that the call can be captured in a graph)
     hx_commit_clear_kernel<<<(P + 2 * D + 255) / 256, 256, 0, stream>>>(a);
     if (C > 0) {
-        int grid = (C + 255) / 256;
+        const int threads = commit_threads(C);
+        int grid = C / threads + (C % threads != 0);
         grid = grid > 256 ? 256 : grid;
-        hx_commit_add_kernel<<<grid, 256, 0, stream>>>(a, RatioArgs{});
+        hx_commit_add_kernel<<<grid, threads, 0, stream>>>(a, RatioArgs{}, grid);
     }
     const int n_inst = P > D ? P : D;
     hx_commit_drain_kernel<<<(n_inst + 255) / 256, 256, 0, stream>>>(a);

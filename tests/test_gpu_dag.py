@@ -505,6 +505,29 @@ def test_commit_matches_oracle(ctx, C):
     assert e.value.code == -6
 
 
+# where the commit's kernel or its workgroups change (2048 and 8192 calls), more instances on one side than a workgroup has
+# threads, and placements that all meet on few instances (hot) or none
+@pytest.mark.parametrize("C,P,D,hot", [(1, 1, 1, 0), (2048, 5, 1024, 0), (2049, 1024, 3, 0), (2049, 4, 4, 1), (8192, 600, 513, 0),
+                                       (8193, 64, 64, 1), (8193, 1024, 1024, 0), (0, 600, 700, 0)])
+def test_commit_at_the_lines_between_its_kernels(ctx, C, P, D, hot):
+    from paper_2605_16637_amd import binding
+    rng = np.random.default_rng(C + P)
+    L, O = synth.gen_lengths(rng, C)
+    bp = rng.integers(-1, min(P, 2) if hot else P, C).astype(np.int32)
+    bd = rng.integers(-1, min(D, 2) if hot else D, C).astype(np.int32)         # one side alone keeps a call queued
+    st = [rng.integers(0, 20000, P).astype(np.int32), rng.integers(0, 300000, D).astype(np.int32),
+          rng.integers(0, 200, D).astype(np.int32), rng.integers(0, 20000, D).astype(np.int32)]
+    for dr in ([rng.integers(0, 80 * C + 9, n).astype(np.int32) for n in (P, D, D)], [np.zeros(n, np.int32) for n in (P, D, D)]):
+        want = o.commit(L, O, bp, bd, *st, *dr)
+        assert want[4] == 0
+        g = [dev(x.copy()) for x in st]
+        drains = [dev(x) for x in dr] if dr[0].any() else [None] * 3          # no drains: NULL
+        ctx.hx_commit(binding.to_device(dict(n=C, L_in=L, L_out=O)), dev(bp), dev(bd), *g, *drains)
+        ctx.hx_stream_status()
+        for got, w in zip(g, want[:4]):
+            assert np.array_equal(got.cpu().numpy(), w)
+
+
 # sweeps inside a workgroup's slice and over the whole graph: a workflow that fills a slice or does not fit one, more successors
 # than a node has slots, rows at the very end of the id array, an edge into another slice, nodes of no workflow, and
 # two graphs in a row (what the workgroups share has to be clear again)
