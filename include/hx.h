@@ -38,7 +38,7 @@
  *    but the status word, which kernels update atomically).  A context is not
  *    thread-safe.
  *  - Device memory is allocated by hx_ctx_create and hx_dag_reserve, and by
- *    hx_decode_score and hx_rank (beyond 16384 calls) the first time they meet
+ *    hx_decode_score and hx_rank (beyond 28672 calls) the first time they meet
  *    a larger problem than before; every other call only launches kernels and
  *    can be captured in a HIP graph (hx_validate_round and hx_stream_status
  *    wait for the stream and cannot).
@@ -474,8 +474,9 @@ int hx_urgency(hx_ctx *ctx, const hx_calls *calls, const float *best_cost,
  * same risk score): rank[c] = position of call c when the calls are sorted by
  * decreasing ratio, equal ratios by increasing call index (0 = most urgent).
  * ratio [C] device in (as written by hx_score_placements or hx_select; +inf =
- * nothing feasible, ranked first), rank [C] device out.  Up to 16384 calls every
- * call is compared with every call (no scratch).  Beyond that the calls are
+ * nothing feasible, ranked first), rank [C] device out.  Up to 10240 calls every
+ * call is compared with every call, up to 28672 with those that lie between the
+ * same two of 255 sampled ones (no scratch).  Beyond that the calls are
  * split into 257 buckets by 256 sampled splitters and compared within their
  * bucket; the library then keeps 8 bytes of scratch per call, and a call with a
  * larger C than any before it allocates, after waiting for the device, and is

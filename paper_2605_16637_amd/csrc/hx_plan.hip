@@ -17,7 +17,7 @@ constexpr int kT = HX_MAX_TYPES;
 // ---- one-pass ordering -----------------------------------------------------------
 
 constexpr int RANK_TILE = 2048;      // calls compared against per block, at most
-constexpr int RANK_SMALL = 16384;    // queues up to this size are ranked by all-pairs counting
+constexpr int RANK_PAIRS = 10 * 1024;     // queues up to this size are ranked by all-pairs counting
 
 __global__ __launch_bounds__(256) void hx_rank_zero_kernel(int32_t *rank, int C)
 {
@@ -62,7 +62,7 @@ __global__ __launch_bounds__(RANK_THREADS) void hx_rank_direct_kernel(const floa
     if (tid < HX_WAVE && c < C) rank[c] = s_ahead[tid];
 }
 
-// Longer queues, up to RANK_SMALL: rank[c] = number of calls ahead of c: larger ratio, or equal ratio and lower
+// Longer queues, up to RANK_PAIRS: rank[c] = number of calls ahead of c: larger ratio, or equal ratio and lower
 // index.  Block (i, j) counts, for 256 calls, those ahead of them among the
 // `tile` calls of tile j; the partial counts are added up with integer atomics.
 __global__ __launch_bounds__(256) void hx_rank_count_kernel(const float *ratio, int32_t *rank, int C, int tile)
@@ -79,6 +79,112 @@ __global__ __launch_bounds__(256) void hx_rank_count_kernel(const float *ratio, 
 #pragma unroll 8
     for (int i = 0; i < kn; ++i) ahead += s_key[i] > mine;
     if (ahead) atomicAdd(&rank[c], ahead);
+}
+
+// Beyond RANK_PAIRS calls, up to RANK_CUT: one launch of a workgroup per bucket.  RANK_CUTS calls, one from each of as
+// many stretches of the queue and anywhere in it, are ordered by counting; workgroup b takes the calls between the b-th of
+// them and the next.  It reads the whole queue, counts the calls ahead of its bucket, gathers the bucket's members in LDS and counts among those.  Keys
+// are unique (they end in the call index), so the buckets stay balanced however many ratios are equal; should one
+// outgrow the LDS all the same, its members are counted against the whole queue instead.
+// Bound: two round trips and the ordering of the cuts (7 us together), then the pass over the queue and the largest bucket,
+// some six times the others, by pairs.  Launches back to back, all pairs of calls / cuts / the sample sort below: 8192
+// calls 8.9 / 9.3 / -, 12000 14.0 / 12.5 / -, 16384 21.3 / 13.4 / -, 24000 - / 20.0 / 26.8, 32768 - / 34.0 / 33.4.
+// (Cuts compared as 32-bit words with the ties by index, four at a time: 1.5 us more; workgroups of 512 threads: 0.5
+// less on 2048 calls, 3 more on 16384.)
+constexpr int RANK_CUT = 28 * 1024;
+constexpr int RANK_CUTS = 255;                   // buckets 0 .. RANK_CUTS
+constexpr int RANK_MEMBERS = 4096;               // members of a bucket that LDS holds
+constexpr int RANK_READ = 8;                     // calls a thread has in flight
+
+__global__ __launch_bounds__(RANK_THREADS) void hx_rank_cut_kernel(const float *ratio, int32_t *rank, int C)
+{
+    __shared__ unsigned long long s_cut[RANK_CUTS + 1], s_key[RANK_MEMBERS], s_low, s_high;
+    __shared__ int s_place[RANK_CUTS + 1], s_higher, s_n, s_ahead[HX_WAVE];
+    const int tid = threadIdx.x, lane = tid & (HX_WAVE - 1), b = blockIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    constexpr int WAVES = RANK_THREADS / HX_WAVE;
+    if (tid <= RANK_CUTS) {
+        // call of stretch tid (a multiplicative hash says where in it; the queue holds more calls than there are stretches)
+        const long long begin = (long long)tid * C / (RANK_CUTS + 1), size = (long long)(tid + 1) * C / (RANK_CUTS + 1) - begin;
+        const int c = (int)(begin + (((unsigned)tid * 2654435761u >> 8) * (unsigned long long)size >> 24));
+        s_cut[tid] = tid < RANK_CUTS ? hx_rank_key64(hx_load_bits(ratio, c), c) : 0ull;
+        s_place[tid] = 0;
+    }
+    if (tid < HX_WAVE) s_ahead[tid] = 0;
+    if (tid == 0) { s_higher = 0; s_n = 0; s_low = 0ull; s_high = ~0ull; }
+    unsigned bits[RANK_READ];                    // the first calls are on their way while the cuts are ordered
+    auto load = [&](int base) {
+#pragma unroll
+        for (int u = 0; u < RANK_READ; ++u) bits[u] = hx_load_bits(ratio, min(base + u * RANK_THREADS + tid, C - 1));
+    };
+    load(0);
+    __syncthreads();
+    {
+        const int i = tid & RANK_CUTS, from = (tid / (RANK_CUTS + 1)) * ((RANK_CUTS + 1) / 4);
+        const unsigned long long mine = s_cut[i];
+        int ahead = 0;
+#pragma unroll 8
+        for (int k = 0; k < (RANK_CUTS + 1) / 4; ++k) ahead += s_cut[from + k] > mine;
+        if (ahead) atomicAdd(&s_place[i], ahead);
+    }
+    __syncthreads();
+    if (tid < RANK_CUTS) {
+        if (s_place[tid] == b) s_low = s_cut[tid];
+        if (s_place[tid] == b - 1) s_high = s_cut[tid];
+    }
+    __syncthreads();
+    // the bucket: low <= key < high (the first has no upper end, the last no lower one)
+    const unsigned long long low = s_low, high = s_high;
+    int higher = 0;
+    for (int base = 0; base < C;) {
+        unsigned now[RANK_READ];
+#pragma unroll
+        for (int u = 0; u < RANK_READ; ++u) now[u] = bits[u];
+        const int at = base;
+        base += RANK_READ * RANK_THREADS;
+        if (base < C) load(base);
+#pragma unroll
+        for (int u = 0; u < RANK_READ; ++u) {
+            const int c = at + u * RANK_THREADS + tid;
+            const unsigned long long key = hx_rank_key64(now[u], c);
+            const bool in = c < C;
+            higher += in && key >= high;
+            if (in && key >= low && key < high) {
+                const int slot = atomicAdd(&s_n, 1);
+                if (slot < RANK_MEMBERS) s_key[slot] = key;
+            }
+        }
+    }
+    if (higher) atomicAdd(&s_higher, higher);
+    __syncthreads();
+    const int n = s_n;
+    higher = s_higher;
+    if (n > RANK_MEMBERS) {
+        for (int c = tid; c < C; c += RANK_THREADS) {
+            const unsigned long long mine = hx_rank_key64(hx_load_bits(ratio, c), c);
+            if (mine < low || mine >= high) continue;
+            int ahead = 0;
+#pragma unroll 8
+            for (int k = 0; k < C; ++k) ahead += hx_rank_key64(hx_load_bits(ratio, k), k) > mine;
+            rank[c] = ahead;
+        }
+        return;
+    }
+    // 64 members at a time, a lane each, against a share of the bucket per wavefront
+    const int share = (n + WAVES - 1) / WAVES, end = min((wave + 1) * share, n);
+    for (int m0 = 0; m0 < n; m0 += HX_WAVE) {
+        const unsigned long long mine = s_key[min(m0 + lane, n - 1)];
+        int ahead = 0;
+#pragma unroll 4
+        for (int k = wave * share; k < end; ++k) ahead += s_key[k] > mine;
+        if (ahead) atomicAdd(&s_ahead[lane], ahead);
+        __syncthreads();
+        if (wave == 0) {
+            if (m0 + lane < n) rank[0xffffffffu - (unsigned)(mine & 0xffffffffull)] = higher + s_ahead[lane];
+            s_ahead[lane] = 0;
+        }
+        __syncthreads();
+    }
 }
 
 // Larger queues: sample sort.  256 evenly spaced calls are sorted and serve as splitters; every call
@@ -785,7 +891,7 @@ extern "C" int hx_rank(hx_ctx *ctx, int32_t C, const float *ratio, int32_t *rank
         hx_rank_direct_kernel<<<(C + HX_WAVE - 1) / HX_WAVE, RANK_THREADS, 0, stream>>>(ratio, rank, C);
         return hx_check_launch(ctx, "hx_rank_direct_kernel");
     }
-    if (C <= RANK_SMALL) {
+    if (C <= RANK_PAIRS) {
         // small queues: every call against every call, no scratch.  Tiles short enough for a few thousand
         // workgroups (a workgroup's time is its tile's length, whatever the queue's), long enough to be worth
         // their atomics.
@@ -796,6 +902,10 @@ extern "C" int hx_rank(hx_ctx *ctx, int32_t C, const float *ratio, int32_t *rank
         hx_rank_zero_kernel<<<bx, 256, 0, stream>>>(rank, C);
         hx_rank_count_kernel<<<dim3(bx, by), 256, 0, stream>>>(ratio, rank, C, tile);
         return hx_check_launch(ctx, "hx_rank kernels");
+    }
+    if (C <= RANK_CUT) {
+        hx_rank_cut_kernel<<<RANK_CUTS + 1, RANK_THREADS, 0, stream>>>(ratio, rank, C);
+        return hx_check_launch(ctx, "hx_rank_cut_kernel");
     }
     const size_t need = (size_t)C + RANK_SPLIT + (RANK_BUCKETS + 1) / 2 + 8;      // keys, splitters, bucket sizes (two ints per word)
     if (need > ctx->rkey_cap) {

@@ -77,6 +77,34 @@ def test_rank_puts_a_ratio_that_is_no_number_with_the_infinite(ctx, C):
     assert np.array_equal(rank.cpu().numpy(), want)
 
 
+# the lines between the ways of ordering (10240 and 28672 calls), and queues whose calls mostly fall between two of the
+# calls that divide it: more in one bucket than a workgroup holds of it
+@pytest.mark.parametrize("C", [10240, 10241, 28672, 28673])
+@pytest.mark.parametrize("kind", ["spread", "sorted", "few values", "one bucket"])
+def test_rank_between_cuts(ctx, C, kind):
+    import torch
+    rng = np.random.default_rng(C)
+    r = rng.lognormal(0, 1, C)
+    if kind == "sorted":
+        r = np.sort(r)
+    elif kind == "few values":
+        r = rng.choice([0.5, 1.5, -2.0, np.inf, -np.inf], C)
+    elif kind == "one bucket":
+        # the call that each of 255 stretches gives as a divider is larger than all others
+        t = np.arange(255, dtype=np.int64)
+        begin = t * C // 256
+        size = (t + 1) * C // 256 - begin
+        hashed = (t * 2654435761 % 2 ** 32) >> 8
+        r[begin + (hashed * size >> 24)] += 1e6
+    r = r.astype(np.float32)
+    rank = torch.full((C + 64,), -1, dtype=torch.int32, device="cuda:0")
+    ctx.hx_rank(dev(r), rank[:C])
+    ctx.hx_stream_status()
+    order = np.argsort(-r.astype(np.float64), kind="stable")
+    want = np.empty(C, np.int64); want[order] = np.arange(C)
+    assert np.array_equal(rank[:C].cpu().numpy(), want) and bool((rank[C:] == -1).all())
+
+
 def run_greedy(ctx, model, L, O, elapsed, node, wf, tail, hor, pre, dec, links):
     import torch
     from paper_2605_16637_amd import binding
