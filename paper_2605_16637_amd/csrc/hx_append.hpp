@@ -5,12 +5,20 @@
 
 #include "hx_common.hpp"
 
+// A node of the graph store, 16 bytes: cost (bits), workflow (-1: none), second parent (-1: none), flags.
+constexpr int HX_NODE_TOP = 1;    // no first parent, or one of another workflow: nothing above it stands for it in its workflow's horizon
+constexpr int HX_NODE_MANY = 2;   // more than two parents: the others are read from its row of the parent lists
+
+// The first parents above a node (its own, that one's, ...; -1 beyond the last), kept beside it: 16 bytes.
+constexpr int HX_CHAIN = 4;
+
 struct AppendArgs {
     int n_old, n_new, e_old, n_new_edges, cap_wf;
     const int32_t *new_row_ptr, *new_col, *new_wf;
     const float *new_cost;
-    float *cost, *rem, *tail, *horizon;
-    int32_t *level, *wf, *prow, *pcol, *parent0, *mark;
+    int4 *rec, *chain;
+    float *rem, *tail, *horizon;
+    int32_t *level, *prow, *pcol, *mark;
     int32_t *list_in, *list_out;
     int32_t *counters;      // [0..2] rotating list sizes
     int cin, cout, czero;   // which counter is read, appended to, cleared
@@ -18,11 +26,19 @@ struct AppendArgs {
     int32_t *status;
 };
 
+__device__ __forceinline__ float hx_node_rec_cost(const int4 &rec) { return __int_as_float(rec.x); }
+
 // non-negative fp32 values order like their bit patterns
 __device__ __forceinline__ bool hx_raise_max_f32(float *addr, float v)
 {
     unsigned old = atomicMax((unsigned *)addr, __float_as_uint(v));
     return __float_as_uint(v) > old;
+}
+
+// A tail as signed bits: costs have none below zero, and -1, less than any, marks a tail that a refresh has yet to reach.
+__device__ __forceinline__ bool hx_raise_tail(const AppendArgs &a, int u, float v)
+{
+    return __float_as_int(v) > atomicMax((int *)&a.tail[u], __float_as_int(v));
 }
 
 // push the (new) rem and level of node v to its parent u; enqueue u if it grew.  The lanes of a
@@ -33,7 +49,7 @@ __device__ __forceinline__ bool hx_raise_max_f32(float *addr, float v)
 template <bool SCOPED>
 __device__ __forceinline__ void hx_push_parent_t(const AppendArgs &a, int u, float rem_v, int level_v)
 {
-    bool grew = hx_raise_max_f32(&a.tail[u], rem_v);
+    bool grew = hx_raise_tail(a, u, rem_v);
     int old = atomicMax(&a.level[u], level_v + 1);
     grew = grew || (level_v + 1 > old);
     const bool want = grew && (uint32_t)atomicExch(&a.mark[u], (int)a.epoch) != a.epoch;
@@ -67,87 +83,123 @@ __device__ __forceinline__ void hx_push_parent_scoped(const AppendArgs &a, int u
 }
 
 // Second phase of an append (a kernel boundary after init, so that a new node whose parent is
-// also new finds that parent initialised).  Asynchronous propagation: every new node walks up from itself, one thread per new node.  A visit
-// of node u recomputes rem[u] from the tail u has now, raises its workflow's horizon, and raises the
-// tail and level of u's parents; a parent that grew is visited next (further grown parents wait on a
-// small stack).  Whoever raises a node visits it afterwards with a tail at least as large as the one it left there, so
-// every increase is carried upwards by someone, and a thread whose value did not raise anything
-// stops: the fixed point is the same as that of the level-by-level sweeps, maxima are exact, and no
-// launch or barrier separates the levels.  A walk that outgrows its stack or its step budget hands
-// the remaining nodes to the worklist, which the sweeps after this kernel finish.
+// also new finds that parent initialised).  Asynchronous propagation: one thread per new node carries the length of
+// its own path upwards.  At every node it reaches it raises tail, level and rem, and at the top of a workflow the
+// horizon; where it raises nothing it stops, since whoever left the larger values there carries them further.  Maxima
+// are exact and rounding is monotone, so the fixed point is that of the level-by-level sweeps bit for bit, and no
+// launch or barrier separates the levels.  Further parents that grew wait on a small stack; a walk that outgrows it or
+// its step budget hands the remaining nodes to the worklist, which the sweeps after this kernel finish.
 //
-// A walk is a chain of memory round trips, and most of it goes up through first parents.  One round trip per
-// level on that path: a node's first parent is kept beside its row of parents, so it is known when the node is
-// reached; the two atomics that raise the parent return what it held before, which together with the raised value
-// is what it holds now; and everything else the visit of the parent needs (cost, workflow, its own row and first
-// parent -- nothing an append changes) is asked for together with those atomics.  Further parents, and nodes
-// taken from the stack, pay the extra trips.
+// What bounds it is the longest chain of memory round trips in any wavefront, and each compute unit's address unit, which
+// takes one lane's scattered access at a time.  Hence first parents are known four at a time: one round trip brings four
+// nodes, what they hold and the next four first parents; the raises ask for no answer, because what a walk
+// carries is its own path and not what it finds (only further parents wait for theirs); and the wavefronts are spread
+// over the compute units.  72 K new nodes beside a search of 23 us: 40 us with a round trip of device atomics a level, each
+// answer part of the next raise, and a horizon raised at every visit; now 30 (on their own 33 -> 27).  The refresh of 812 K
+// nodes, where every node walked and raised four values: 157 us, now 44.  (Eight first parents at a time: 42 and 60, most of
+// what they ask for lies above the point where a walk stops; two: as four.  Further parents queued in LDS for any idle lane
+// of the wavefront: 30 and 59, three times the code.)
+//
+// REFRESH: all costs new, levels as they are.  Only the nodes without children walk -- their walks reach every other
+// node, whose tail's mark of -1 the first to come raises -- and raise tails alone; rem and the horizons follow from
+// those in a pass of their own.
 constexpr int RELAX_STACK = 16;
 constexpr int RELAX_STEPS = 1024;
 
-struct HxVisit {
-    float cost, tl;
-    int lv, w, e0, e1, q0;
-};
-
-// what a visit needs of node u that no append changes
-__device__ __forceinline__ void hx_visit_fixed(const AppendArgs &a, int u, HxVisit &x)
-{
-    x.cost = a.cost[u]; x.w = a.wf[u]; x.e0 = a.prow[u]; x.e1 = a.prow[u + 1]; x.q0 = a.parent0[u];
-}
-
 // block, n_blocks: the workgroup's place among those that walk (the launch may hold other workgroups too)
+template <bool REFRESH>
 __device__ __forceinline__ void hx_append_relax_body(const AppendArgs &a, int block, int n_blocks)
 {
-    for (int i = block * (int)blockDim.x + (int)threadIdx.x; i < a.n_new; i += n_blocks * (int)blockDim.x) {
+    // the first wavefronts of all workgroups, then the second ones
+    const int lane = (int)(threadIdx.x & (HX_WAVE - 1)), wave = (int)(threadIdx.x / HX_WAVE);
+    for (int i = (wave * n_blocks + block) * HX_WAVE + lane; i < a.n_new; i += n_blocks * (int)blockDim.x) {
         int stack[RELAX_STACK];
         int sp = 0, steps = 0;
-        int u = a.n_old + i;
-        HxVisit x;
-        bool have = false;                   // x already describes u (reached through its child's first-parent slot)
-        while (u >= 0) {
-            if (!have) {
-                x.tl = __hip_atomic_load(&a.tail[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                x.lv = __hip_atomic_load(&a.level[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                hx_visit_fixed(a, u, x);
+        int v = a.n_old + i;
+        if (REFRESH && a.level[v] != 0) continue;
+        int4 me = a.rec[v], above = a.chain[v];
+        float r = hx_node_rec_cost(me) + 0.0f;               // rem of v as far as this walk knows
+        int lv = 0;
+        for (;;) {
+            const int up[HX_CHAIN] = {above.x, above.y, above.z, above.w};
+            int4 rec[HX_CHAIN];
+            int tl[HX_CHAIN], lvl[HX_CHAIN];
+#pragma unroll
+            for (int k = 0; k < HX_CHAIN; ++k) {
+                if (up[k] < 0) continue;
+                rec[k] = a.rec[up[k]];
+                tl[k] = __hip_atomic_load((const int *)&a.tail[up[k]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (!REFRESH) lvl[k] = __hip_atomic_load(&a.level[up[k]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
-            const float r = x.cost + x.tl;
-            const int lv = x.lv;
-            hx_raise_max_f32(&a.rem[u], r);
-            if (x.w >= 0) hx_raise_max_f32(&a.horizon[x.w], r);
-            ++steps;
-            int next = -1;
-            have = false;
-            const int e0 = x.e0, e1 = x.e1, q0 = x.q0;
-            if (e1 > e0 && q0 >= 0) {
-                // the first parent: raised, and its own visit prepared, in one round trip
-                const unsigned old_t = atomicMax((unsigned *)&a.tail[q0], __float_as_uint(r));
-                const int old_l = atomicMax(&a.level[q0], lv + 1);
-                HxVisit y;
-                hx_visit_fixed(a, q0, y);
-                if (__float_as_uint(r) > old_t || lv + 1 > old_l) {
-                    if (steps >= RELAX_STEPS) {
-                        hx_enqueue(a, q0);
-                    } else {
-                        y.tl = __uint_as_float(max(old_t, __float_as_uint(r)));
-                        y.lv = max(old_l, lv + 1);
-                        x = y; next = q0; have = true;
+            if (up[HX_CHAIN - 1] >= 0) above = a.chain[up[HX_CHAIN - 1]];
+            // up the chain: source k is v or up[k - 1], its first parent up[k]
+            int q[HX_CHAIN], src_lv[HX_CHAIN];
+            float src_r[HX_CHAIN];
+            bool live = true, tail_up = true;
+            unsigned many = 0;
+#pragma unroll
+            for (int k = 0; k < HX_CHAIN; ++k) {
+                const int4 src = k ? rec[k ? k - 1 : 0] : me;
+                q[k] = live ? src.z : -1; src_r[k] = r; src_lv[k] = lv;
+                many |= live && (src.w & HX_NODE_MANY) ? 1u << k : 0u;
+                if (!REFRESH && tail_up && (src.w & HX_NODE_TOP) && src.y >= 0) hx_raise_max_f32(&a.horizon[src.y], r);
+                const int t = up[k];
+                live = live && t >= 0;
+                tail_up = live && __float_as_int(r) > tl[k];
+                const bool level_up = !REFRESH && live && lv + 1 > lvl[k];
+                if (tail_up) atomicMax((int *)&a.tail[t], __float_as_int(r));
+                if (level_up) atomicMax(&a.level[t], lv + 1);
+                r = hx_node_rec_cost(rec[k]) + r;
+                lv += 1;
+                if (!REFRESH && tail_up) hx_raise_max_f32(&a.rem[t], r);
+                live = tail_up || level_up;
+                steps += live;
+            }
+            // second parents, then the others of nodes with more
+            int old_t[HX_CHAIN], old_l[HX_CHAIN];
+#pragma unroll
+            for (int k = 0; k < HX_CHAIN; ++k)
+                if (q[k] >= 0) {
+                    old_t[k] = atomicMax((int *)&a.tail[q[k]], __float_as_int(src_r[k]));
+                    if (!REFRESH) old_l[k] = atomicMax(&a.level[q[k]], src_lv[k] + 1);
+                }
+            auto wait = [&](int node) {
+                if (steps >= RELAX_STEPS || sp >= RELAX_STACK) hx_enqueue(a, node);
+                else stack[sp++] = node;
+            };
+#pragma unroll
+            for (int k = 0; k < HX_CHAIN; ++k)
+                if (q[k] >= 0 && (__float_as_int(src_r[k]) > old_t[k] || (!REFRESH && src_lv[k] + 1 > old_l[k]))) wait(q[k]);
+            if (many) {
+#pragma unroll
+                for (int k = 0; k < HX_CHAIN; ++k) {
+                    if (!((many >> k) & 1)) continue;
+                    const int s = k ? up[k ? k - 1 : 0] : v;
+                    const int e1 = a.prow[s + 1];
+                    for (int e = a.prow[s] + 2; e < e1; ++e) {
+                        const int p = a.pcol[e];
+                        if (p < 0) continue;
+                        bool grew = hx_raise_tail(a, p, src_r[k]);
+                        if (!REFRESH) grew = src_lv[k] + 1 > atomicMax(&a.level[p], src_lv[k] + 1) || grew;
+                        if (grew) wait(p);
                     }
                 }
             }
-            for (int e = e0 + 1; e < e1; ++e) {
-                const int q = a.pcol[e];
-                if (q < 0) continue;
-                bool grew = hx_raise_max_f32(&a.tail[q], r);
-                const int old = atomicMax(&a.level[q], lv + 1);
-                grew = grew || (lv + 1 > old);
-                if (!grew) continue;
-                if (steps >= RELAX_STEPS) hx_enqueue(a, q);
-                else if (next < 0) next = q;
-                else if (sp < RELAX_STACK) stack[sp++] = q;
-                else hx_enqueue(a, q);
+            if (live) {
+                v = up[HX_CHAIN - 1];
+                if (steps < RELAX_STEPS) { me = rec[HX_CHAIN - 1]; continue; }
+                hx_enqueue(a, v);
             }
-            u = next >= 0 ? next : (sp > 0 ? stack[--sp] : -1);
+            if (sp == 0) break;
+            // a further parent, with what it holds by now
+            v = stack[--sp];
+            ++steps;
+            me = a.rec[v]; above = a.chain[v];
+            r = hx_node_rec_cost(me) + __hip_atomic_load(&a.tail[v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (!REFRESH) {
+                lv = __hip_atomic_load(&a.level[v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                hx_raise_max_f32(&a.rem[v], r);
+            }
         }
     }
 }

@@ -36,9 +36,10 @@ struct HxDagStore {
     int32_t cap_nodes = 0, cap_edges = 0, cap_wf = 0, max_depth = 0;      // as reserved
     int32_t room_nodes = 0, room_edges = 0, room_wf = 0;                  // as allocated
     int32_t n_nodes = 0, n_edges = 0;
-    float *cost = nullptr, *rem = nullptr, *tail = nullptr, *horizon = nullptr;
-    int32_t *level = nullptr, *wf = nullptr, *parent_row_ptr = nullptr, *parent_col = nullptr;
-    int32_t *parent0 = nullptr;        // [cap_nodes] a node's first parent (-1: none), beside its row of parent_col
+    int4 *rec = nullptr;               // [cap_nodes] cost, workflow, second parent, flags (hx_append.hpp)
+    int4 *chain = nullptr;             // [cap_nodes] the first parents above a node
+    float *rem = nullptr, *tail = nullptr, *horizon = nullptr;
+    int32_t *level = nullptr, *parent_row_ptr = nullptr, *parent_col = nullptr;
     int32_t *mark = nullptr, *list[2] = {nullptr, nullptr};
     int32_t *counters = nullptr;       // [4]: list sizes (3, rotating) + epoch
     uint32_t epoch = 0;

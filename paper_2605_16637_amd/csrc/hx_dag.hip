@@ -423,9 +423,26 @@ __global__ __launch_bounds__(CG_THREADS) void hx_cp_sweep_all_kernel(CpArgs a, i
 
 // ---- incremental append ------------------------------------------------------------------
 
+// workflow of a new node (-1: out of range)
+__device__ __forceinline__ int hx_append_wf(const AppendArgs &a, int i)
+{
+    const int w = a.new_wf[i];
+    return w >= 0 && w < a.cap_wf ? w : -1;
+}
+
+// first parent of the new node v (-1: none, or not a valid one)
+__device__ __forceinline__ int hx_append_first_parent(const AppendArgs &a, int v)
+{
+    const int r0 = a.new_row_ptr[v - a.n_old], r1 = a.new_row_ptr[v - a.n_old + 1];
+    if (r0 < 0 || r1 > a.n_new_edges || r0 >= r1) return -1;
+    const int u = a.new_col[r0];
+    return u >= 0 && u < v ? u : -1;
+}
+
 // First phase of an append: the new nodes' own entries.  The two list counters the append needs at zero (the
 // one the walks append to, the one the first sweep after them clears) are cleared here: the walks are a launch
 // of their own after this one, so no launch is spent on the counters.
+// The horizons are raised by the walks, at the top of each workflow.
 // COST: the nodes' standalone costs are not read but worked out here from their lengths, exactly as
 // hx_node_cost_kernel does, and written to the caller's array as well (one launch less in front of the walks, where
 // every launch of a round still waits for the host).
@@ -447,28 +464,45 @@ __global__ __launch_bounds__(256) void hx_append_init_kernel(AppendArgs a, NodeC
         } else {
             c = a.new_cost[i];
         }
-        int w = a.new_wf[i];
         int r0 = a.new_row_ptr[i], r1 = a.new_row_ptr[i + 1];
+        const int w = hx_append_wf(a, i);
+        if (w < 0) hx_raise(a.status, HX_ERR_INDEX);
         if (r0 < 0 || r1 > a.n_new_edges || r0 > r1) { hx_raise(a.status, HX_ERR_INDEX); r0 = r1 = min(max(r0, 0), a.n_new_edges); }
-        a.cost[v] = c; a.rem[v] = c; a.tail[v] = 0.0f; a.level[v] = 0; a.mark[v] = 0;
+        a.rem[v] = c; a.tail[v] = 0.0f; a.level[v] = 0; a.mark[v] = 0;
         a.prow[v + 1] = a.e_old + r1;
-        if (w < 0 || w >= a.cap_wf) { hx_raise(a.status, HX_ERR_INDEX); w = -1; }
-        a.wf[v] = w;
-        if (w >= 0) hx_raise_max_f32(&a.horizon[w], c);
-        int first = -1;
+        int up[HX_CHAIN], second = -1;
+        up[0] = -1;
         for (int e = r0; e < r1; ++e) {
             int u = a.new_col[e];
             if (u < 0 || u >= v) { hx_raise(a.status, HX_ERR_NOT_DAG); u = -1; }
             a.pcol[a.e_old + e] = u;
-            if (e == r0) first = u;
+            if (e == r0) up[0] = u;
+            if (e == r0 + 1) second = u;
         }
-        a.parent0[v] = first;
+        // the first parents above: those of the nearest one that is not new lie beside it
+        const int wf0 = up[0] < 0 ? -1 : up[0] < a.n_old ? a.rec[up[0]].y : hx_append_wf(a, up[0] - a.n_old);
+        bool old = false;
+#pragma unroll
+        for (int k = 1; k < HX_CHAIN; ++k) {
+            if (old) continue;
+            const int p = up[k - 1];
+            if (p >= a.n_old) { up[k] = hx_append_first_parent(a, p); continue; }
+            int4 x = make_int4(-1, -1, -1, -1);
+            if (p >= 0) x = a.chain[p];
+            const int above[HX_CHAIN] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+            for (int j = k; j < HX_CHAIN; ++j) up[j] = above[j - k];
+            old = true;
+        }
+        a.chain[v] = make_int4(up[0], up[1], up[2], up[3]);
+        a.rec[v] = make_int4(__float_as_int(c), w, second, (up[0] < 0 || wf0 != w ? HX_NODE_TOP : 0) | (r1 - r0 > 2 ? HX_NODE_MANY : 0));
     }
 }
 
+template <bool REFRESH>
 __global__ __launch_bounds__(256) void hx_append_relax_kernel(AppendArgs a)
 {
-    hx_append_relax_body(a, (int)blockIdx.x, (int)gridDim.x);
+    hx_append_relax_body<REFRESH>(a, (int)blockIdx.x, (int)gridDim.x);
 }
 
 __global__ void hx_append_finish_kernel(AppendArgs a)
@@ -501,10 +535,10 @@ __global__ __launch_bounds__(1024) void hx_append_tail_kernel(AppendArgs a, int3
             const int u = __hip_atomic_load(&a.list_in[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             const float tl = __hip_atomic_load(&a.tail[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             const int lv = __hip_atomic_load(&a.level[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const float r = a.cost[u] + tl;
+            const int4 me = a.rec[u];
+            const float r = hx_node_rec_cost(me) + tl;
             a.rem[u] = r;
-            const int w = a.wf[u];
-            if (w >= 0) hx_raise_max_f32(&a.horizon[w], r);
+            if (me.y >= 0) hx_raise_max_f32(&a.horizon[me.y], r);
             for (int e = a.prow[u]; e < a.prow[u + 1]; ++e) {
                 int q = a.pcol[e];
                 if (q >= 0) hx_push_parent_scoped(a, q, r, lv);
@@ -521,24 +555,32 @@ __global__ __launch_bounds__(1024) void hx_append_tail_kernel(AppendArgs a, int3
     }
 }
 
-// cost of existing nodes replaced by observed values (an id outside the graph is skipped and reported)
-__global__ __launch_bounds__(256) void hx_set_cost_kernel(int n, const int32_t *ids, const float *value, float *cost, int n_nodes,
-                                                          int32_t *status)
+// Cost of existing nodes replaced by observed values (an id outside the graph is skipped and reported), and what the costs
+// determine back to its starting point: no horizons, no tails, those of nodes with children marked as not reached.
+__global__ __launch_bounds__(256) void hx_refresh_begin_kernel(AppendArgs a, int n, const int32_t *ids, const float *value, int n_wf)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int v = ids[i];
-    if (v < 0 || v >= n_nodes) { hx_raise(status, HX_ERR_INDEX); return; }
-    cost[v] = value[i];
-}
-
-// everything the costs determine back to its starting point: rem = cost, no tail, no horizon
-__global__ __launch_bounds__(256) void hx_refresh_reset_kernel(AppendArgs a, int n_wf)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < a.n_new) { a.rem[i] = a.cost[i]; a.tail[i] = 0.0f; }
+    if (i < n) {
+        const int v = ids[i];
+        if (v < 0 || v >= a.n_new) hx_raise(a.status, HX_ERR_INDEX);
+        else a.rec[v].x = __float_as_int(value[i]);
+    }
+    if (i < a.n_new) ((int *)a.tail)[i] = a.level[i] > 0 ? -1 : 0;
     if (i < n_wf) a.horizon[i] = 0.0f;
     if (i < 3) a.counters[i] = 0;
+}
+
+// rem from the tails, and the horizons from the tops of the workflows
+__global__ __launch_bounds__(256) void hx_refresh_end_kernel(AppendArgs a)
+{
+    const int v = blockIdx.x * blockDim.x + threadIdx.x;
+    if (v >= a.n_new) return;
+    const int4 me = a.rec[v];
+    const int t = ((const int *)a.tail)[v];
+    if (t < 0) a.tail[v] = 0.0f;                          // (never reached: the sweeps have run out and said so)
+    const float r = hx_node_rec_cost(me) + __int_as_float(max(t, 0));
+    a.rem[v] = r;
+    if ((me.w & HX_NODE_TOP) && me.y >= 0) hx_raise_max_f32(&a.horizon[me.y], r);
 }
 
 __global__ __launch_bounds__(256) void hx_fill_i32_kernel(int32_t *p, size_t n, int32_t v)
@@ -556,7 +598,7 @@ int dev_alloc(hx_ctx *ctx, T **p, size_t n)
 
 void dag_free(HxDagStore &g)
 {
-    void *ptrs[] = {g.cost, g.rem, g.tail, g.horizon, g.level, g.wf, g.parent_row_ptr, g.parent_col, g.parent0,
+    void *ptrs[] = {g.rec, g.chain, g.rem, g.tail, g.horizon, g.level, g.parent_row_ptr, g.parent_col,
                     g.mark, g.list[0], g.list[1], g.counters};
     for (void *p : ptrs) if (p) (void)hipFree(p);
     g = HxDagStore{};
@@ -730,10 +772,10 @@ extern "C" int hx_dag_reserve(hx_ctx *ctx, int32_t max_nodes, int32_t max_edges,
     HxDagStore &g = ctx->dag;
     int rc = HX_OK;
     const size_t N = (size_t)max_nodes, E = (size_t)max_edges, W = (size_t)max_wf;
-    // A store that is large enough and not more than twice as large as asked for is kept: freeing and allocating its 13
+    // A store that is large enough and not more than twice as large as asked for is kept: freeing and allocating its 12
     // arrays costs some 350 us, a third of a session of eight rounds (1120 -> 786 us).
     auto keeps = [](int32_t have, size_t want) { return (size_t)have >= want && (size_t)have <= 2 * want; };
-    const bool keep = g.cost && keeps(g.room_nodes, N) && keeps(g.room_edges, E) && keeps(g.room_wf, W);
+    const bool keep = g.rec && keeps(g.room_nodes, N) && keeps(g.room_edges, E) && keeps(g.room_wf, W);
     // Whatever is still at work on the old graph, on any stream, is waited for: by the device where its arrays stay, as
     // freeing them does otherwise; nothing but this stream where there are none.
     if (keep) HX_HIP(ctx, hipDeviceSynchronize());
@@ -741,10 +783,10 @@ extern "C" int hx_dag_reserve(hx_ctx *ctx, int32_t max_nodes, int32_t max_edges,
         HX_HIP(ctx, hipStreamSynchronize(stream));
         dag_free(g);
     }
-    if (!keep && ((rc = dev_alloc(ctx, &g.cost, N)) || (rc = dev_alloc(ctx, &g.rem, N)) || (rc = dev_alloc(ctx, &g.tail, N)) ||
-        (rc = dev_alloc(ctx, &g.horizon, W)) || (rc = dev_alloc(ctx, &g.level, N)) || (rc = dev_alloc(ctx, &g.wf, N)) ||
+    if (!keep && ((rc = dev_alloc(ctx, &g.rec, N)) || (rc = dev_alloc(ctx, &g.chain, N)) || (rc = dev_alloc(ctx, &g.rem, N)) || (rc = dev_alloc(ctx, &g.tail, N)) ||
+        (rc = dev_alloc(ctx, &g.horizon, W)) || (rc = dev_alloc(ctx, &g.level, N)) ||
         (rc = dev_alloc(ctx, &g.parent_row_ptr, N + 1)) || (rc = dev_alloc(ctx, &g.parent_col, E)) ||
-        (rc = dev_alloc(ctx, &g.parent0, N)) || (rc = dev_alloc(ctx, &g.mark, N)) || (rc = dev_alloc(ctx, &g.list[0], N)) ||
+        (rc = dev_alloc(ctx, &g.mark, N)) || (rc = dev_alloc(ctx, &g.list[0], N)) ||
         (rc = dev_alloc(ctx, &g.list[1], N)) || (rc = dev_alloc(ctx, &g.counters, (size_t)4)))) {
         dag_free(g);
         return rc;
@@ -768,7 +810,7 @@ int dag_append_begin(hx_ctx *ctx, int32_t n_new, int32_t n_new_edges, const int3
 {
     *plan = HxAppendPlan{};
     HxDagStore &g = ctx->dag;
-    HX_REQUIRE(ctx, g.cost, HX_ERR_INVALID_ARG, "hx_dag_reserve has not been called");
+    HX_REQUIRE(ctx, g.rec, HX_ERR_INVALID_ARG, "hx_dag_reserve has not been called");
     HX_REQUIRE(ctx, n_new >= 0 && n_new_edges >= 0, HX_ERR_INVALID_ARG, "negative size");
     HX_REQUIRE(ctx, n_new == 0 || (parent_row_ptr && new_cost && new_wf), HX_ERR_INVALID_ARG, "NULL array");
     HX_REQUIRE(ctx, n_new_edges == 0 || parent_col_idx, HX_ERR_INVALID_ARG, "NULL parent_col_idx");
@@ -783,8 +825,8 @@ int dag_append_begin(hx_ctx *ctx, int32_t n_new, int32_t n_new_edges, const int3
     AppendArgs a{};
     a.n_old = g.n_nodes; a.n_new = n_new; a.e_old = g.n_edges; a.n_new_edges = n_new_edges; a.cap_wf = g.cap_wf;
     a.new_row_ptr = parent_row_ptr; a.new_col = parent_col_idx; a.new_wf = new_wf; a.new_cost = new_cost;
-    a.cost = g.cost; a.rem = g.rem; a.tail = g.tail; a.horizon = g.horizon;
-    a.level = g.level; a.wf = g.wf; a.prow = g.parent_row_ptr; a.pcol = g.parent_col; a.parent0 = g.parent0; a.mark = g.mark;
+    a.rec = g.rec; a.chain = g.chain; a.rem = g.rem; a.tail = g.tail; a.horizon = g.horizon;
+    a.level = g.level; a.prow = g.parent_row_ptr; a.pcol = g.parent_col; a.mark = g.mark;
     a.counters = g.counters; a.status = ctx->d_status;
 
     int grid = (n_new + 255) / 256;
@@ -815,7 +857,7 @@ int hx_dag_append_walks(hx_ctx *ctx, const HxAppendPlan *plan, void *stream)
 {
     HxDeviceGuard guard(ctx->device);
     HX_REQUIRE(ctx, guard.ok, HX_ERR_DEVICE, "cannot select device %d", ctx->device);
-    hx_append_relax_kernel<<<plan->grid, 256, 0, (hipStream_t)stream>>>(plan->a);
+    hx_append_relax_kernel<false><<<plan->grid, 256, 0, (hipStream_t)stream>>>(plan->a);
     return hx_check_launch(ctx, "hx_append_relax_kernel");
 }
 
@@ -870,28 +912,27 @@ extern "C" int hx_dag_set_cost(hx_ctx *ctx, int32_t n, const int32_t *node_ids, 
 {
     if (!ctx) return HX_ERR_INVALID_ARG;
     HxDagStore &g = ctx->dag;
-    HX_REQUIRE(ctx, g.cost, HX_ERR_INVALID_ARG, "hx_dag_reserve has not been called");
+    HX_REQUIRE(ctx, g.rec, HX_ERR_INVALID_ARG, "hx_dag_reserve has not been called");
     HX_REQUIRE(ctx, n >= 0, HX_ERR_INVALID_ARG, "negative size");
     HX_REQUIRE(ctx, n == 0 || (node_ids && cost), HX_ERR_INVALID_ARG, "NULL array");
     if (n == 0 || g.n_nodes == 0) return HX_OK;
     HxDeviceGuard guard(ctx->device);
     HX_REQUIRE(ctx, guard.ok, HX_ERR_DEVICE, "cannot select device %d", ctx->device);
     hipStream_t stream = (hipStream_t)stream_;
-    hx_set_cost_kernel<<<(n + 255) / 256, 256, 0, stream>>>(n, node_ids, cost, g.cost, g.n_nodes, ctx->d_status);
-    // a cost may have gone down, so nothing can be kept: every node starts again from rem = cost and walks up
-    // (levels do not depend on costs and stay)
+    // a cost may have gone down, so nothing can be kept (levels do not depend on costs and stay)
     AppendArgs a{};
     a.n_old = 0; a.n_new = g.n_nodes; a.cap_wf = g.cap_wf;
-    a.cost = g.cost; a.rem = g.rem; a.tail = g.tail; a.horizon = g.horizon;
-    a.level = g.level; a.wf = g.wf; a.prow = g.parent_row_ptr; a.pcol = g.parent_col; a.parent0 = g.parent0; a.mark = g.mark;
+    a.rec = g.rec; a.chain = g.chain; a.rem = g.rem; a.tail = g.tail; a.horizon = g.horizon;
+    a.level = g.level; a.prow = g.parent_row_ptr; a.pcol = g.parent_col; a.mark = g.mark;
     a.counters = g.counters; a.status = ctx->d_status;
     a.cin = 0; a.cout = 1; a.czero = 2; a.epoch = ++g.epoch;
     a.list_in = g.list[1]; a.list_out = g.list[0];
-    const int m = g.n_nodes > g.cap_wf ? g.n_nodes : g.cap_wf;
-    hx_refresh_reset_kernel<<<(m + 255) / 256, 256, 0, stream>>>(a, g.cap_wf);
+    int m = g.n_nodes > g.cap_wf ? g.n_nodes : g.cap_wf;
+    m = m > n ? m : n;
+    hx_refresh_begin_kernel<<<(int)(((long long)m + 255) / 256), 256, 0, stream>>>(a, n, node_ids, cost, g.cap_wf);
     int grid = (g.n_nodes + 255) / 256;
     grid = grid > ctx->num_cu * 8 ? ctx->num_cu * 8 : grid;
-    hx_append_relax_kernel<<<grid, 256, 0, stream>>>(a);
+    hx_append_relax_kernel<true><<<grid, 256, 0, stream>>>(a);
     if (g.max_depth > 0) {
         a.epoch = g.epoch;
         hx_append_tail_kernel<<<1, 1024, 0, stream>>>(a, g.list[0], g.list[1], 0, g.max_depth);
@@ -900,6 +941,7 @@ extern "C" int hx_dag_set_cost(hx_ctx *ctx, int32_t n, const int32_t *node_ids, 
         a.cin = 1;
         hx_append_finish_kernel<<<1, 64, 0, stream>>>(a);
     }
+    hx_refresh_end_kernel<<<(int)(((long long)g.n_nodes + 255) / 256), 256, 0, stream>>>(a);
     return hx_check_launch(ctx, "hx_dag_set_cost kernels");
 }
 
@@ -908,7 +950,7 @@ extern "C" int hx_dag_view(hx_ctx *ctx, const float **rem, const float **tail, c
 {
     if (!ctx) return HX_ERR_INVALID_ARG;
     HxDagStore &g = ctx->dag;
-    HX_REQUIRE(ctx, g.cost, HX_ERR_INVALID_ARG, "hx_dag_reserve has not been called");
+    HX_REQUIRE(ctx, g.rec, HX_ERR_INVALID_ARG, "hx_dag_reserve has not been called");
     if (rem) *rem = g.rem;
     if (tail) *tail = g.tail;
     if (level) *level = g.level;

@@ -505,7 +505,7 @@ __global__ __launch_bounds__(FS_THREADS) void hx_relax_search_kernel(ScoreArgs a
 {
     extern __shared__ __align__(16) float smem[];
     if ((int)blockIdx.x < n_lead) {
-        hx_append_relax_body(ap, (int)blockIdx.x, n_lead);
+        hx_append_relax_body<false>(ap, (int)blockIdx.x, n_lead);
         return;
     }
     hx_fused_search_body<CALLS>(a, pa, smem, (int)blockIdx.x - n_lead);
@@ -840,7 +840,9 @@ int score_placements(hx_ctx *ctx, const hx_model *model, const hx_calls *calls,
             return HX_OK;
         }
         if (walks) {
-            const int n_lead = (walks->a.n_new + FS_THREADS - 1) / FS_THREADS;
+            // a workgroup of walks to every compute unit, as far as there are wavefronts of them
+            const int most = (walks->a.n_new + HX_WAVE - 1) / HX_WAVE, least = (walks->a.n_new + FS_THREADS - 1) / FS_THREADS;
+            const int n_lead = least > ctx->num_cu ? least : (most < ctx->num_cu ? most : ctx->num_cu);
             by_calls([&](auto calls) {
                 hx_relax_search_kernel<calls()><<<n_lead + n_search, FS_THREADS, lds, stream>>>(a, pa, walks->a, n_lead);
             });

@@ -373,6 +373,46 @@ def test_observed_costs_replace_estimates(ctx):
     assert e.value.code == -6
 
 
+@pytest.mark.parametrize("reach,most,cross", [(1, 1, 0.0), (3, 2, 0.3), (9, 6, 0.1), (400, 3, 1.0)])
+def test_append_of_any_graph(ctx, reach, most, cross):
+    """Parents of the same batch (the first parents above a node are followed through them), up to `most` parents,
+    also of other workflows, nodes that cost nothing; then other costs for some of them.  Batches of one node to some
+    workgroups full."""
+    rng = np.random.default_rng(reach)
+    ctx.hx_dag_reserve(6000, 40000, 64, 1500)
+    prow, pcol = [0], []
+    wf = np.zeros(0, np.int32); cost = np.zeros(0, np.float32)
+
+    def check():
+        want = o.critical_path_by_parents(np.array(prow, np.int32), np.array(pcol, np.int32), cost.astype(np.float64), wf, 64, round_f32=True)
+        got = view(ctx, cost.size, 64)
+        assert np.array_equal(got[2], want[2])
+        for k in (0, 1, 3):
+            assert np.array_equal(got[k].astype(np.float64), want[k]), k
+
+    for n_new in (1, 7, 64, 300, 1, 900):
+        n0, e0 = cost.size, len(pcol)
+        row = [0]
+        for v in range(n0, n0 + n_new):
+            k = min(v, int(rng.integers(0 if rng.random() < 0.02 else 1, most + 1)))
+            pcol.extend(rng.choice(np.arange(max(0, v - reach), v), min(k, reach, v), replace=False).tolist())
+            row.append(len(pcol) - e0)
+        prow.extend((e0 + np.array(row[1:])).tolist())
+        w = rng.integers(0, 64, n_new).astype(np.int32)
+        same = rng.random(n_new) >= cross
+        wf = np.concatenate([wf, np.where(same, 5, w).astype(np.int32)])
+        c = np.where(rng.random(n_new) < 0.3, 0.0, rng.uniform(0.1, 3.0, n_new)).astype(np.float32)
+        cost = np.concatenate([cost, c])
+        ctx.hx_dag_append(dev(np.array(row, np.int32)), dev(np.array(pcol[e0:], np.int32)), dev(c), dev(wf[n0:]))
+        ctx.hx_stream_status()
+        check()
+        ids = rng.choice(cost.size, max(1, cost.size // 3), replace=False).astype(np.int32)
+        cost[ids] = np.where(rng.random(ids.size) < 0.5, 0.0, rng.uniform(0.1, 3.0, ids.size)).astype(np.float32)
+        ctx.hx_dag_set_cost(dev(ids), dev(cost[ids]))
+        ctx.hx_stream_status()
+        check()
+
+
 def test_append_errors(ctx):
     from paper_2605_16637_amd import binding
     ctx.hx_dag_reserve(8, 8, 2, 4)
