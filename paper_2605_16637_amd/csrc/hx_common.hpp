@@ -13,25 +13,6 @@
 
 constexpr int HX_WAVE = 64;
 
-// What hx_prepare_kernel derives from the raw snapshots for the kernel that writes the cost tensor; one copy lives in the
-// context's scratch.
-struct HxPrepTables {
-    // prefill instances
-    float pre_wait[HX_MAX_INSTANCES];   // backlog_tok * phi / F
-    float pre_invF[HX_MAX_INSTANCES];
-    float pre_invB[HX_MAX_INSTANCES];
-    int32_t pre_type[HX_MAX_INSTANCES];
-    // decode instances
-    float dec_wait[HX_MAX_INSTANCES];   // availability hint
-    float dec_c1[HX_MAX_INSTANCES];     // phi * (batch + 1) / F
-    float dec_c2[HX_MAX_INSTANCES];     // (omega + kappa * used) / B
-    float dec_kB[HX_MAX_INSTANCES];     // kappa / B
-    int32_t dec_free[HX_MAX_INSTANCES]; // cap_tok - used_tok
-    int32_t dec_type[HX_MAX_INSTANCES];
-    float link_invbw[HX_MAX_TYPES * HX_MAX_TYPES];
-    float link_lat[HX_MAX_TYPES * HX_MAX_TYPES];
-};
-
 struct HxDagStore {
     int32_t cap_nodes = 0, cap_edges = 0, cap_wf = 0, max_depth = 0;      // as reserved
     int32_t room_nodes = 0, room_edges = 0, room_wf = 0;                  // as allocated
@@ -54,7 +35,6 @@ struct hx_ctx {
     char err[256] = "no error";
     int32_t *d_status = nullptr;       // sticky device status word
     int32_t *h_status = nullptr;       // pinned copy
-    HxPrepTables *d_prep = nullptr;
     int32_t *d_report = nullptr;       // counts of hx_validate_round, [HX_VALIDATE_FIELDS]
     int32_t *d_sync = nullptr;         // sweeps: what the workgroups share, [HX_SYNC_WORDS], 0 between launches
     int sweep_polls = HX_SWEEP_POLLS;
@@ -109,10 +89,8 @@ inline int hx_check_launch(hx_ctx *ctx, const char *what)
     return HX_OK;
 }
 
-// hx_score.hip: validate the pool tables; validate them and enqueue the per-round table kernel (fills ctx->d_prep)
+// hx_score.hip: validate the pool tables
 int hx_check_pool(hx_ctx *ctx, const hx_model *model, const hx_prefill_tab *pre, const hx_decode_tab *dec, const hx_links *links);
-int hx_prepare_pool(hx_ctx *ctx, const hx_model *model, const hx_prefill_tab *pre, const hx_decode_tab *dec,
-                    const hx_links *links, hipStream_t stream);
 
 // set the device of the context for the duration of a call
 struct HxDeviceGuard {

@@ -375,7 +375,6 @@ extern "C" int hx_ctx_create(hx_ctx **out, int device)
     const char *what = "hipMalloc(status)";
     e = hipMalloc((void **)&ctx->d_status, sizeof(int32_t));
     if (e == hipSuccess) { what = "hipHostMalloc(status)"; e = hipHostMalloc((void **)&ctx->h_status, sizeof(int32_t), hipHostMallocDefault); }
-    if (e == hipSuccess) { what = "hipMalloc(tables)"; e = hipMalloc((void **)&ctx->d_prep, sizeof(HxPrepTables)); }
     if (e == hipSuccess) { what = "hipMalloc(report)"; e = hipMalloc((void **)&ctx->d_report, HX_VALIDATE_FIELDS * sizeof(int32_t)); }
     if (e == hipSuccess) { what = "hipMalloc(sync)"; e = hipMalloc((void **)&ctx->d_sync, HX_SYNC_WORDS * sizeof(int32_t)); }
     if (e == hipSuccess) { what = "hipMalloc(ticket)"; e = hipMalloc((void **)&ctx->d_ticket, sizeof(int32_t)); }
@@ -412,7 +411,6 @@ extern "C" int hx_ctx_destroy(hx_ctx *ctx)
     hx_dag_release(ctx);
     if (ctx->d_status) (void)hipFree(ctx->d_status);
     if (ctx->h_status) (void)hipHostFree(ctx->h_status);
-    if (ctx->d_prep) (void)hipFree(ctx->d_prep);
     if (ctx->d_report) (void)hipFree(ctx->d_report);
     if (ctx->d_sync) (void)hipFree(ctx->d_sync);
     if (ctx->d_ticket) (void)hipFree(ctx->d_ticket);

@@ -1,4 +1,4 @@
-// Scoring of placement candidates: prepare (per-round tables), fused search
+// Scoring of placement candidates: fused search
 // (score + per-call argmin, no tensor written), materialised tensor, select.
 //
 // What is computed: Sec. 5.3 of the paper (enumerate prefill x decode
@@ -24,7 +24,7 @@
 
 namespace {
 
-// ---- prepare ------------------------------------------------------------------
+// ---- the pool as the kernels read it ---------------------------------------------
 
 struct PrepArgs {
     HxModelF m;
@@ -34,52 +34,8 @@ struct PrepArgs {
     const float *d_flops, *d_hbm;
     const int32_t *d_used, *d_cap, *d_batch, *d_qd, *d_type;
     const float *bw, *lat;
-    HxPrepTables *out;
     int32_t *status;
 };
-
-// The pool's tables for hx_materialise_kernel (the search derives its own): one workgroup of 1024 threads, one thread per
-// instance of either side (at most HX_MAX_INSTANCES each).
-__global__ __launch_bounds__(1024) void hx_prepare_kernel(PrepArgs a)
-{
-    const int tid = threadIdx.x;
-    HxPrepTables *o = a.out;
-    // everything is read before anything is written
-    const bool has_link = tid < kT * kT;
-    const int tp = tid / kT, td = tid % kT;
-    const bool link_in = has_link && tp < a.T && td < a.T;
-    const float l_bw = link_in ? a.bw[tp * a.T + td] : 1.0f;
-    const float l_lat = (link_in && a.lat) ? a.lat[tp * a.T + td] : 0.0f;
-    const bool has_p = tid < a.P;
-    int p_t = has_p ? a.p_type[tid] : 0;
-    const float p_flops = has_p ? a.p_flops[tid] : 1.0f, p_hbm = has_p ? a.p_hbm[tid] : 1.0f;
-    const int p_backlog = has_p ? a.p_backlog[tid] : 0;
-    const bool has_d = tid < a.D;
-    int d_t = has_d ? a.d_type[tid] : 0;
-    const int d_used = has_d ? a.d_used[tid] : 0, d_batch = has_d ? a.d_batch[tid] : 0, d_qd = has_d ? a.d_qd[tid] : 0;
-    const int d_cap = has_d ? a.d_cap[tid] : 0;
-    const float d_flops = has_d ? a.d_flops[tid] : 1.0f, d_hbm = has_d ? a.d_hbm[tid] : 1.0f;
-    if (p_t < 0 || p_t >= a.T) { hx_raise(a.status, HX_ERR_INDEX); p_t = 0; }
-    if (d_t < 0 || d_t >= a.T) { hx_raise(a.status, HX_ERR_INDEX); d_t = 0; }
-    if (has_link) {
-        o->link_invbw[tid] = link_in ? 1.0f / l_bw : 0.0f;
-        o->link_lat[tid] = l_lat;
-    }
-    if (has_p) {
-        const float invF = 1.0f / p_flops;
-        o->pre_invF[tid] = invF;
-        o->pre_invB[tid] = 1.0f / p_hbm;
-        o->pre_wait[tid] = hx_prefill_wait(a.m, p_backlog, invF);
-        o->pre_type[tid] = p_t;
-    }
-    if (has_d) {
-        const HxDecF x = hx_decode_terms(a.m, d_used, d_batch, d_qd, 1.0f / d_flops, 1.0f / d_hbm);
-        o->dec_wait[tid] = x.wait; o->dec_c1[tid] = x.c1; o->dec_c2[tid] = x.c2; o->dec_kB[tid] = x.kB;
-        const long long fr = (long long)d_cap - (long long)d_used;
-        o->dec_free[tid] = fr < -1 ? -1 : (fr > 2147483647LL ? 2147483647 : (int)fr);
-        o->dec_type[tid] = d_t;
-    }
-}
 
 // ---- common argument block of the scoring kernels ------------------------------
 
@@ -89,7 +45,6 @@ struct ScoreArgs {
     const int32_t *L_in, *L_out, *node, *wf;
     const float *elapsed, *tail, *horizon;
     int n_nodes, n_wf;
-    const HxPrepTables *prep;
     int32_t *best_p, *best_d;
     float *best_cost, *ratio;
     float *cost;          // materialised tensor or NULL
@@ -517,11 +472,11 @@ __global__ __launch_bounds__(FS_THREADS) void hx_relax_search_kernel(ScoreArgs a
 // KB and the barriers and the per-call tables would otherwise cost as much as the stores; 1 on large ones).
 // LDS: per call of the batch the prefill finish per instance, the decode time per instance and the class-pair
 // transfer times, each worked out by 256 / nc threads; beside them what does not depend on the call (waits,
-// per-token terms, classes), staged once per workgroup.
-__global__ __launch_bounds__(256) void hx_materialise_kernel(ScoreArgs a, int nc)
+// per-token terms, classes), which every workgroup derives for itself from the pool, under the first call's lengths: as a
+// kernel of one workgroup before this one they took 3.5 us (4096 x 64 x 64 with the selection after it 38.8 -> 36.1).
+__global__ __launch_bounds__(256) void hx_materialise_kernel(ScoreArgs a, PrepArgs t, int nc)
 {
     extern __shared__ __align__(16) float smem[];
-    const HxPrepTables *__restrict__ t = a.prep;
     const int P4 = (a.P + 3) & ~3, D4 = (a.D + 3) & ~3;      // every array starts on a 16-byte boundary
     float *s_done = smem;                       // [nc][P4] per call
     float *s_dec = s_done + nc * P4;            // [nc][D4] per call
@@ -542,13 +497,26 @@ __global__ __launch_bounds__(256) void hx_materialise_kernel(ScoreArgs a, int nc
     // rows of the tensor are 16-byte aligned and a whole number of quads long
     const bool vec4 = (a.D & 3) == 0 && a.D >= 4 && (reinterpret_cast<uintptr_t>(a.cost) & 15) == 0;
     for (int p = tid; p < a.P; p += blockDim.x) {
-        s_pw[p] = t->pre_wait[p]; s_pF[p] = t->pre_invF[p]; s_pB[p] = t->pre_invB[p]; s_ptype[p] = t->pre_type[p];
+        int k = t.p_type[p];
+        if (k < 0 || k >= t.T) { hx_raise(a.status, HX_ERR_INDEX); k = 0; }
+        const float invF = 1.0f / t.p_flops[p];
+        s_pw[p] = hx_prefill_wait(a.m, t.p_backlog[p], invF); s_pF[p] = invF; s_pB[p] = 1.0f / t.p_hbm[p]; s_ptype[p] = k;
     }
     for (int d = tid; d < a.D; d += blockDim.x) {
-        s_c1[d] = t->dec_c1[d]; s_c2[d] = t->dec_c2[d]; s_kB[d] = t->dec_kB[d]; s_free[d] = t->dec_free[d];
-        s_wait[d] = t->dec_wait[d]; s_dtype[d] = t->dec_type[d];
+        int k = t.d_type[d];
+        if (k < 0 || k >= t.T) { hx_raise(a.status, HX_ERR_INDEX); k = 0; }
+        const int used = t.d_used[d];
+        const HxDecF x = hx_decode_terms(a.m, used, t.d_batch[d], t.d_qd[d], 1.0f / t.d_flops[d], 1.0f / t.d_hbm[d]);
+        const long long fr = (long long)t.d_cap[d] - (long long)used;
+        s_c1[d] = x.c1; s_c2[d] = x.c2; s_kB[d] = x.kB; s_wait[d] = x.wait; s_dtype[d] = k;
+        s_free[d] = fr < -1 ? -1 : (fr > 2147483647LL ? 2147483647 : (int)fr);
     }
-    if (tid < kT * kT) { s_lbw[tid] = t->link_invbw[tid]; s_llat[tid] = t->link_lat[tid]; }
+    if (tid < kT * kT) {
+        const int i = tid / kT, k = tid % kT;
+        const bool in = i < t.T && k < t.T;
+        s_lbw[tid] = in ? 1.0f / t.bw[i * t.T + k] : 0.0f;
+        s_llat[tid] = in && t.lat ? t.lat[i * t.T + k] : 0.0f;
+    }
     // the part of the workgroup that works out the tables of one call of the batch
     const int per_call = blockDim.x / nc;
     const int slot = tid / per_call, tq = tid - slot * per_call;
@@ -705,7 +673,7 @@ PrepArgs make_prep_args(hx_ctx *ctx, const hx_model *model, const hx_prefill_tab
     pa.p_flops = pre->flops; pa.p_hbm = pre->hbm_bw; pa.p_backlog = pre->backlog_tok; pa.p_type = pre->type;
     pa.d_flops = dec->flops; pa.d_hbm = dec->hbm_bw; pa.d_used = dec->used_tok; pa.d_cap = dec->cap_tok;
     pa.d_batch = dec->batch; pa.d_qd = dec->qd_tok; pa.d_type = dec->type;
-    pa.bw = links->bw; pa.lat = links->latency; pa.out = ctx->d_prep; pa.status = ctx->d_status;
+    pa.bw = links->bw; pa.lat = links->latency; pa.status = ctx->d_status;
     return pa;
 }
 
@@ -736,17 +704,6 @@ int hx_check_pool(hx_ctx *ctx, const hx_model *model, const hx_prefill_tab *pre,
                                dec->qd_tok && dec->type), HX_ERR_INVALID_ARG, "NULL member in decode table");
     HX_REQUIRE(ctx, links->bw, HX_ERR_INVALID_ARG, "links.bw is NULL");
     return HX_OK;
-}
-
-// Validates the pool tables and enqueues the kernel that derives the per-round
-// tables (ctx->d_prep) from them.
-int hx_prepare_pool(hx_ctx *ctx, const hx_model *model, const hx_prefill_tab *pre, const hx_decode_tab *dec,
-                    const hx_links *links, hipStream_t stream)
-{
-    if (int rc = hx_check_pool(ctx, model, pre, dec, links)) return rc;
-    const PrepArgs pa = make_prep_args(ctx, model, pre, dec, links);
-    hx_prepare_kernel<<<1, 1024, 0, stream>>>(pa);
-    return hx_check_launch(ctx, "hx_prepare_kernel");
 }
 
 namespace {
@@ -794,7 +751,6 @@ int score_placements(hx_ctx *ctx, const hx_model *model, const hx_calls *calls,
     a.C = C; a.P = P; a.D = D;
     a.L_in = calls->L_in; a.L_out = calls->L_out; a.node = calls->node; a.wf = calls->wf;
     a.elapsed = calls->elapsed; a.tail = tail; a.horizon = horizon; a.n_nodes = n_nodes; a.n_wf = n_wf;
-    a.prep = ctx->d_prep;
     a.best_p = best_p; a.best_d = best_d; a.best_cost = best_cost; a.ratio = (reveal || walks) ? nullptr : ratio;
     a.cost = cost; a.feas = feas; a.status = ctx->d_status;
 
@@ -854,13 +810,13 @@ int score_placements(hx_ctx *ctx, const hx_model *model, const hx_calls *calls,
         if (int rc = hx_check_launch(ctx, "hx_fused_search_kernel")) return rc;
     }
     if (cost || feas) {
-        if (int rc = hx_prepare_pool(ctx, model, pre, dec, links, stream)) return rc;
+        if (int rc = hx_check_pool(ctx, model, pre, dec, links)) return rc;
         const int P4 = (P + 3) & ~3, D4 = (D + 3) & ~3;
         const int nc = (long long)P * D <= 16384 && C >= 4 * ctx->num_cu * 4 ? 4 : 1;      // calls per workgroup at a time
         const size_t lds = 4 * ((size_t)nc * (P4 + D4 + kT * kT) + 4 * P4 + 6 * D4 + 2 * kT * kT);
         const int batches = (C + nc - 1) / nc;
         const int grid = batches < ctx->num_cu * 8 ? batches : ctx->num_cu * 8;
-        hx_materialise_kernel<<<grid, 256, lds, stream>>>(a, nc);
+        hx_materialise_kernel<<<grid, 256, lds, stream>>>(a, make_prep_args(ctx, model, pre, dec, links), nc);
         if (int rc = hx_check_launch(ctx, "hx_materialise_kernel")) return rc;
     }
     return HX_OK;
