@@ -445,3 +445,25 @@ def test_debug_validation_counts_bad_elements(ctx):
     # an empty round and an empty pool are fine
     none = dict(calls, n=0)
     assert not any(ctx.hx_validate_round(none, dict(pre, n=0), dict(dec, n=0), links).values())
+
+
+# the selection where a wavefront or a workgroup takes a call: rows of one quad, of a wavefront's eight quads a lane and one
+# more, the longest for a wavefront and the next; an array that begins off a 16-byte boundary; ties, rows without a pair
+@pytest.mark.parametrize("C", [1, 3, 130])
+@pytest.mark.parametrize("P,D", [(1, 4), (2, 2), (3, 5), (32, 64), (36, 57), (64, 64), (4, 1025), (65, 64)])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_select_by_wavefronts_and_by_workgroups(ctx, C, P, D, offset):
+    import torch
+    rng = np.random.default_rng(C * 1000 + P * D)
+    cost = rng.integers(1, 40 + P * D, (C, P * D)).astype(np.float32)
+    cost[rng.random(cost.shape) < 0.2] = np.inf
+    cost[rng.random(C) < 0.2] = np.inf
+    room = torch.empty(C * P * D + offset, device="cuda:0")
+    room[offset:] = dev(cost.reshape(-1))
+    bp = torch.full((C,), -9, dtype=torch.int32, device="cuda:0"); bd = bp.clone(); bc = torch.empty(C, device="cuda:0")
+    ctx.hx_select(C, P, D, room[offset:], bp, bd, bc)
+    ctx.hx_stream_status()
+    at, low = cost.argmin(1), cost.min(1)
+    none = ~np.isfinite(low)
+    assert np.array_equal(bc.cpu().numpy(), low)
+    assert np.array_equal(bp.cpu().numpy(), np.where(none, -1, at // D)) and np.array_equal(bd.cpu().numpy(), np.where(none, -1, at % D))
