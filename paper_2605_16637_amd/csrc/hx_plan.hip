@@ -8,6 +8,7 @@
 #include "hx_search.hpp"
 
 #include <cmath>
+#include <cstdlib>
 #include <type_traits>
 
 namespace {
@@ -354,10 +355,34 @@ __global__ __launch_bounds__(1024) void hx_rank_within_kernel(int32_t *rank, int
 // Whole plans, before (every call whose pair a pick touched searched again, pair by pair, by one of 16 wavefronts) and now:
 // 64 calls on 8 + 8 instances 338 -> 85 us, 256 on 64 + 64 2500 -> 465, 256 on 256 + 256 3860 -> 1640, 1024 on 64 + 64
 // 20100 -> 6320, 1024 on 256 + 256 30600 -> 16900.  (256 on 64 + 64 with four wavefronts instead of eight: 500.)
+// With what a stage does not change in registers (transfers, where a group's arrivals lie) and the divisions of a
+// commit by multiplication: 64 on 8 + 8 82 -> 78, 256 on 64 + 64 461 -> 443, 256 on 16 + 16 375 -> 346.  (The links of the
+// prefill instances in registers as well: 452 for the second.)
 constexpr int GREEDY_THREADS = 8 * HX_WAVE;                  // two wavefronts per SIMD
 constexpr int GREEDY_MAX_THREADS = HX_GREEDY_MAX_CALLS;      // a lane per call at least
 constexpr int GREEDY_K = HX_GREEDY_MAX_INSTANCES / HX_WAVE;
+constexpr int GREEDY_ROWS = 8;                               // groups of entries a lane reads at a time, at most
 constexpr int GREEDY_MAX_G = 16;                             // lanes per call at most: a row of lanes (a power of two)
+
+// Unsigned division by a number known beforehand, exact for every 32-bit dividend: T. Granlund, P. Montgomery, "Division by
+// invariant integers using multiplication" (1994), section 4.
+struct HxDivisor {
+    unsigned mul;
+    int sh1, sh2;
+    HxDivisor() = default;
+    explicit HxDivisor(unsigned d)
+    {
+        int l = 0;
+        while (l < 32 && (1ull << l) < d) ++l;
+        mul = (unsigned)((((1ull << l) - d) << 32) / d + 1);
+        sh1 = l < 1 ? l : 1; sh2 = l > 1 ? l - 1 : 0;
+    }
+    __host__ __device__ unsigned divide(unsigned n) const
+    {
+        const unsigned t = (unsigned)(((unsigned long long)mul * n) >> 32);
+        return (t + ((n - t) >> sh1)) >> sh2;
+    }
+};
 
 struct GreedyArgs {
     HxModelF m;
@@ -368,6 +393,8 @@ struct GreedyArgs {
     const float *p_flops, *p_hbm, *d_flops, *d_hbm, *bw, *lat;
     const int32_t *p_backlog, *p_type, *d_used, *d_cap, *d_batch, *d_qd, *d_type;
     int tokens_per_seq, max_batch;
+    HxDivisor by_tokens;                              // by tokens_per_seq
+    float inv_bbar;                                   // 1 / m.bbar where multiplying by it is the division (a power of two), else 0
     int32_t *best_p, *best_d, *rank;
     float *best_cost, *ratio;
     int32_t *backlog_out, *used_out, *batch_out, *qd_out;
@@ -586,6 +613,21 @@ __global__ __launch_bounds__(THREADS) void hx_plan_greedy_kernel(GreedyArgs a, i
         float m[TT];
         float best = INFINITY;
         unsigned ratio_bits = 0;
+        // what a stage does not change and a pick reads: the transfers to the classes of the lane's rows (few classes: in
+        // registers), and where the arrivals at the classes of its first groups lie
+        float x[TT <= 4 ? TT : 1][TT];
+        if constexpr (TT <= 4) {
+#pragma unroll
+            for (int u = 0; u < TT; ++u) {
+                const float2 *l = s.link_to + (((u << lg) + sub) & (kT - 1)) * kT;
+#pragma unroll
+                for (int i = 0; i < TT; ++i) x[u][i] = hx_transfer(cf, l[i].x, l[i].y);
+            }
+        }
+        constexpr int KEPT = THREADS > GREEDY_THREADS ? 0 : GREEDY_ROWS;      // (as the registers allow)
+        int off0[KEPT + 1];
+#pragma unroll
+        for (int u = 0; u < KEPT; ++u) off0[u] = my_goff[(u < per_lane ? u : 0) << lg];
 
         // r[k] of the lane's call, its lanes a class each
         auto arrivals = [&]() {
@@ -598,8 +640,11 @@ __global__ __launch_bounds__(THREADS) void hx_plan_greedy_kernel(GreedyArgs a, i
                     r[u] = INFINITY;
 #pragma unroll
                     for (int i = 0; i < TT; i += 2) {         // a class without instances, or beyond T: +inf
-                        const float4 x = *(const float4 *)(l + i);
-                        r[u] = fminf(r[u], fminf(m[i] + hx_transfer(cf, x.x, x.y), m[i + 1] + hx_transfer(cf, x.z, x.w)));
+                        if constexpr (TT <= 4) r[u] = fminf(r[u], fminf(m[i] + x[u][i], m[i + 1] + x[u][i + 1]));
+                        else {
+                            const float4 y = *(const float4 *)(l + i);
+                            r[u] = fminf(r[u], fminf(m[i] + hx_transfer(cf, y.x, y.y), m[i + 1] + hx_transfer(cf, y.z, y.w)));
+                        }
                     }
                 }
                 if (alive) {                                  // (a picked call's may be being read)
@@ -633,7 +678,7 @@ __global__ __launch_bounds__(THREADS) void hx_plan_greedy_kernel(GreedyArgs a, i
 #pragma unroll
                 for (int u = 0; u < N; ++u) {
                     const int at_row = row + u < per_lane ? row + u : 0;
-                    off[u] = my_goff[at_row << lg];
+                    off[u] = u < KEPT && row == 0 ? off0[u < KEPT ? u : 0] : my_goff[at_row << lg];
                     w[u] = my_w[at_row << lg];
                     t[u] = N > 2 ? *(const float4 *)(my_dec + at_row * dec_row) : decode_times(sub + (at_row << lg));
                 }
@@ -775,10 +820,10 @@ __global__ __launch_bounds__(THREADS) void hx_plan_greedy_kernel(GreedyArgs a, i
                     // ceil(us / tokens_per_seq), rounded towards 0: both numbers are below 2^31, so 32 unsigned bits do
                     const int num = n_us < 0 ? n_us + (a.tokens_per_seq - 1) : 0;
                     const unsigned top = n_us < 0 ? (unsigned)(num < 0 ? -num : num) : (unsigned)n_us + (unsigned)a.tokens_per_seq - 1u;
-                    const unsigned quot = top / (unsigned)a.tokens_per_seq;
+                    const unsigned quot = a.by_tokens.divide(top);
                     const int n_batch = num < 0 ? -(int)quot : (quot > (unsigned)a.max_batch ? a.max_batch : (int)quot);
                     // the derived table entries, by the function that made them
-                    const HxDecF x = hx_decode_terms(a.m, n_us, n_batch, n_qd, d_F[j], d_B[j]);
+                    const HxDecF x = hx_decode_terms(a.m, n_us, n_batch, n_qd, d_F[j], d_B[j], KEPT ? a.inv_bbar : 0.0f);
                     const int n_fr = max(__builtin_elementwise_sub_sat(d_cap[j], n_us), -1);
                     const int ld = d & (HX_WAVE - 1);
                     if (lane == ld) {
@@ -1002,7 +1047,9 @@ extern "C" int hx_plan_greedy(hx_ctx *ctx, const hx_model *model, const hx_calls
     a.p_flops = pre->flops; a.p_hbm = pre->hbm_bw; a.p_backlog = pre->backlog_tok; a.p_type = pre->type;
     a.d_flops = dec->flops; a.d_hbm = dec->hbm_bw; a.d_used = dec->used_tok; a.d_cap = dec->cap_tok;
     a.d_batch = dec->batch; a.d_qd = dec->qd_tok; a.d_type = dec->type;
-    a.tokens_per_seq = tokens_per_seq; a.max_batch = max_batch;
+    a.tokens_per_seq = tokens_per_seq; a.max_batch = max_batch; a.by_tokens = HxDivisor((unsigned)tokens_per_seq);
+    int exponent = 0;
+    a.inv_bbar = std::frexp(a.m.bbar, &exponent) == 0.5f && std::abs(exponent) < 64 ? 1.0f / a.m.bbar : 0.0f;
     a.best_p = best_p; a.best_d = best_d; a.rank = rank; a.best_cost = best_cost; a.ratio = ratio;
     a.backlog_out = backlog_tok_out; a.used_out = used_tok_out; a.batch_out = batch_out; a.qd_out = qd_tok_out;
     a.status = ctx->d_status;

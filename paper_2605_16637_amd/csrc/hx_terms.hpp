@@ -78,13 +78,16 @@ struct HxDecF {
     float kB;     // kappa/B
 };
 
+// inv_bbar: 1 / m.bbar where multiplying by it rounds as the division does (bbar a power of two), else 0
 __device__ __forceinline__ HxDecF hx_decode_terms(const HxModelF &m, int used_tok, int batch, int qd_tok,
-                                                  float invF, float invB)
+                                                  float invF, float invB, float inv_bbar = 0.0f)
 {
     HxDecF d;
     float resident = fmaf(m.kappa, (float)used_tok, m.omega) * invB;
     float step = fmaxf((m.phi * (float)batch) * invF, resident);
-    d.wait = ((float)qd_tok * step) / m.bbar;
+    const float queued = (float)qd_tok * step;
+    if (inv_bbar != 0.0f) d.wait = queued * inv_bbar;
+    else d.wait = queued / m.bbar;
     d.c1 = (m.phi * ((float)batch + 1.0f)) * invF;
     d.c2 = resident;
     d.kB = m.kappa * invB;

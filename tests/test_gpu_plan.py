@@ -211,6 +211,37 @@ def test_greedy_plan_with_rates_of_every_instance(ctx, C, P, D, T, seed):
     check_plan_stepwise(synth.MODEL, L, O, elapsed, node, wf, tail, hor, pre, dec, links, got)
 
 
+# the batch after each pick is a division by tokens_per_seq, the availability hint one by the nominal batch (a
+# multiplication where that is a power of two)
+@pytest.mark.parametrize("tokens_per_seq", [1, 3, 2047, 4096, 2 ** 31 - 1])
+@pytest.mark.parametrize("bbar", [48.0, 0.25])
+def test_greedy_plan_divides_exactly(ctx, tokens_per_seq, bbar):
+    import torch
+    from paper_2605_16637_amd import binding
+    rng = np.random.default_rng(tokens_per_seq % 1000)
+    C, P, D, model = 40, 5, 9, dict(synth.MODEL, nominal_batch=bbar)
+    types, pre, dec, links = random_pool(rng, P, D, 3)
+    dec["cap_tok"] = (dec["used_tok"] + rng.integers(2000, 2 ** 28, D)).astype(np.int32)
+    L, O = synth.gen_lengths(rng, C)
+    elapsed = rng.uniform(0, 20, C).astype(np.float32)
+    node, wf = np.arange(C, dtype=np.int32), rng.integers(0, 3, C).astype(np.int32)
+    tail = rng.uniform(0, 5, C).astype(np.float32); hor = rng.uniform(5, 50, 3).astype(np.float32)
+    if tokens_per_seq == 4096:                  # the whole plan, with the method's own rule
+        got = run_greedy(ctx, model, L, O, elapsed, node, wf, tail, hor, pre, dec, links)
+        check_plan_stepwise(model, L, O, elapsed, node, wf, tail, hor, pre, dec, links, got)
+    calls = binding.to_device(dict(n=C, L_in=L, L_out=O, node=node, wf=wf, elapsed=elapsed))
+    dp, dd = (binding.to_device({**{k: np.asarray(v) for k, v in t.items()}, "n": n}) for t, n in ((pre, P), (dec, D)))
+    out = [torch.empty(n, dtype=t, device="cuda:0") for n, t in ((C, torch.int32), (C, torch.int32), (C, torch.float32), (C, torch.float32),
+                                                                 (C, torch.int32), (P, torch.int32), (D, torch.int32), (D, torch.int32), (D, torch.int32))]
+    ctx.hx_plan_greedy(model, calls, dp, dd, binding.to_device(links), dev(tail), dev(hor), *out, tokens_per_seq=tokens_per_seq,
+                       max_batch=10 ** 6)
+    ctx.hx_stream_status()
+    used, batch = out[6].cpu().numpy().astype(np.int64), out[7].cpu().numpy()
+    took = np.isin(np.arange(D), out[1].cpu().numpy())
+    assert took.any()
+    assert np.array_equal(batch, np.where(took, np.minimum(-(-used // tokens_per_seq), 10 ** 6), dec["batch"]))
+
+
 # Plans that begin with more decode times than the workgroup's memory keeps and end with few enough: up to 512 calls with small
 # and large pools, and more
 @pytest.mark.parametrize("C,P,D,T,seed", [(512, 8, 64, 8, 1), (400, 66, 90, 4, 2), (1024, 4, 18, 3, 3)])
