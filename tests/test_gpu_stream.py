@@ -294,6 +294,62 @@ def test_round_in_one_call_equals_its_four_calls(ctx, P, D, n_live, rounds, cap)
         other.close()
 
 
+@pytest.mark.parametrize("C", [500, 3000])          # committed by one workgroup and by several
+@pytest.mark.parametrize("depth", [80, 0])          # sweeps enough, and none
+def test_round_whose_walks_hand_over(ctx, C, depth):
+    # new nodes with 40 parents on a chain of 60 that costs next to nothing: all parents grow, their walks are cut short, the graph is finished level by
+    # level before the round's commit forms the ratios of calls all along the chain, as by the separate calls
+    import torch
+    from paper_2605_16637_amd import binding
+    rng = np.random.default_rng(C + depth)
+    P, D, n_chain, n_new = 9, 12, 60, 5
+    types, links, pre, dec = synth.gen_pool(rng, P, D, 3, *synth.gen_lengths(rng, 2000), near_capacity=False)
+    d_links, tF, tB = binding.to_device(links), dev(types["flops"]), dev(types["hbm_bw"])
+    L, O = synth.gen_lengths(rng, C)
+    nL, nO = synth.gen_lengths(rng, n_new)
+    calls = binding.to_device(dict(n=C, L_in=L, L_out=O, node=rng.integers(0, n_chain + n_new, C).astype(np.int32),
+                                   wf=np.zeros(C, np.int32), elapsed=rng.uniform(0, 9, C).astype(np.float32)))
+    prow = np.arange(n_new + 1, dtype=np.int32) * 40
+    pcol = np.concatenate([rng.permutation(n_chain)[:40] for _ in range(n_new)]).astype(np.int32)
+    zeros = np.zeros(n_new, np.int32)
+    outs, codes = [], []
+    for one in (True, False):
+        c = binding.Context(0)
+        try:
+            c.hx_dag_reserve(200, 400, 1, depth)
+            c.hx_dag_append(dev(np.concatenate([[0], np.arange(n_chain)]).astype(np.int32)), dev(np.arange(n_chain - 1, dtype=np.int32)),
+                            dev(np.linspace(1e-4, 2e-4, n_chain).astype(np.float32)), dev(np.zeros(n_chain, np.int32)))
+            c.hx_stream_status()
+            d_pre, d_dec = binding.to_device(pre), binding.to_device(dec)
+            bp, bd = (torch.empty(C, dtype=torch.int32, device="cuda:0") for _ in range(2))
+            bc, ratio, cost = torch.empty(C, device="cuda:0"), torch.empty(C, device="cuda:0"), torch.empty(n_new, device="cuda:0")
+            if one:
+                c.hx_round(synth.MODEL, calls, d_pre, d_dec, d_links, bp, bd, bc, ratio=ratio, n_wf=1, parent_row_ptr=dev(prow),
+                           parent_col_idx=dev(pcol), new_L_in=dev(nL), new_L_out=dev(nO), new_wf=dev(zeros), new_cost=cost,
+                           type_flops=tF, type_hbm_bw=tB)
+            else:
+                c.hx_node_cost(synth.MODEL, dev(nL), dev(nO), tF, tB, d_links, cost)
+                c.hx_dag_append(dev(prow), dev(pcol), cost, dev(zeros))
+                _, g_tail, _, g_hor, _ = c.hx_dag_view(1)
+                c.hx_score_placements(synth.MODEL, calls, d_pre, d_dec, d_links, tail=g_tail, horizon=g_hor, best_p=bp, best_d=bd,
+                                      best_cost=bc, ratio=ratio)
+                c.hx_commit(calls, bp, bd, d_pre["backlog_tok"], d_dec["used_tok"], d_dec["batch"], d_dec["qd_tok"])
+            try:
+                c.hx_stream_status()
+                codes.append(0)
+            except binding.HxError as e:
+                codes.append(e.code)
+            g_rem, g_tail, g_level, g_hor, _ = c.hx_dag_view(1)
+            outs.append([x.cpu().numpy() for x in (bp, bd, bc, ratio, d_pre["backlog_tok"], d_dec["used_tok"])] +
+                        [fetch(g_rem), fetch(g_tail), fetch(g_level), fetch(g_hor)])
+        finally:
+            c.close()
+    assert codes == ([0, 0] if depth == 80 else [-4, -4])
+    if depth == 80:                     # (cut short, the two graphs may have come differently far)
+        for x, y in zip(*outs):
+            assert np.array_equal(x, y)
+
+
 def _round_buffers(torch, binding, rnd, seed):
     """Device copies of one synthetic round: inputs, the outputs of the reveal and of the search, drains."""
     d = rnd.dag
