@@ -468,7 +468,8 @@ __global__ __launch_bounds__(256) void hx_append_init_kernel(AppendArgs a, NodeC
         const int w = hx_append_wf(a, i);
         if (w < 0) hx_raise(a.status, HX_ERR_INDEX);
         if (r0 < 0 || r1 > a.n_new_edges || r0 > r1) { hx_raise(a.status, HX_ERR_INDEX); r0 = r1 = min(max(r0, 0), a.n_new_edges); }
-        a.rem[v] = c; a.tail[v] = 0.0f; a.level[v] = 0; a.mark[v] = 0;
+        a.rem[v] = c + 0.0f;                              // (-0.0, whose bits are above every number's, is 0)
+        a.tail[v] = 0.0f; a.level[v] = 0; a.mark[v] = 0;
         a.prow[v + 1] = a.e_old + r1;
         int up[HX_CHAIN], second = -1;
         up[0] = -1;

@@ -413,6 +413,31 @@ def test_append_of_any_graph(ctx, reach, most, cross):
         check()
 
 
+@pytest.mark.parametrize("reach,most", [(1, 1), (3, 2), (9, 6)])
+def test_costs_of_minus_zero_are_zeros(ctx, reach, most):
+    """A cost of -0.0 is not below 0: whatever is appended under such a node later raises its rem as it does any other's."""
+    rng = np.random.default_rng(20 + reach)
+    ctx.hx_dag_reserve(700, 4000, 1, 700)
+    prow, pcol, cost = [0], [], np.zeros(0, np.float32)
+    for n_new in (1, 40, 1, 200, 300):
+        n0, e0 = cost.size, len(pcol)
+        for v in range(n0, n0 + n_new):
+            pcol.extend(rng.choice(np.arange(max(0, v - reach), v), min(v, reach, int(rng.integers(1, most + 1))), replace=False).tolist())
+            prow.append(len(pcol))
+        c = rng.choice(np.array([-0.0, 0.0, 0.25, 1.5], np.float32), n_new)
+        c[0] = -0.0
+        cost = np.concatenate([cost, c])
+        ctx.hx_dag_append(dev(np.array(prow[n0:], np.int32) - e0), dev(np.array(pcol[e0:], np.int32)), dev(c), dev(np.zeros(n_new, np.int32)))
+        ctx.hx_stream_status()
+        want = o.critical_path_by_parents(np.array(prow, np.int32), np.array(pcol, np.int32), cost.astype(np.float64), np.zeros(cost.size, np.int32), 1,
+                                          round_f32=True)
+        got = view(ctx, cost.size, 1)
+        assert np.array_equal(got[2], want[2])
+        for k in (0, 1, 3):
+            assert np.array_equal(got[k].astype(np.float64), want[k]), k
+        assert not np.signbit(got[0]).any()
+
+
 def test_append_errors(ctx):
     from paper_2605_16637_amd import binding
     ctx.hx_dag_reserve(8, 8, 2, 4)
