@@ -53,7 +53,7 @@ extern "C" {
 #endif
 
 #define HX_OK               0
-#define HX_ERR_INVALID_ARG (-1)  /* NULL where a pointer is required, negative size, bad flag      */
+#define HX_ERR_INVALID_ARG (-1)  /* NULL for a required pointer, negative size, bad flag, cost < 0  */
 #define HX_ERR_SHAPE       (-2)  /* a size beyond HX_MAX_TYPES / HX_MAX_INSTANCES / int32 indexing */
 #define HX_ERR_NOT_DAG     (-3)  /* successor not later than its node / no fixed point in time      */
 #define HX_ERR_CAPACITY    (-4)  /* reserved store, scratch or sweep limit exceeded                 */
@@ -231,7 +231,8 @@ int hx_dag_reserve(hx_ctx *ctx, int32_t max_nodes, int32_t max_edges, int32_t ma
  *   parent_col_idx device [n_new_edges] parents of each new node; a parent id
  *                  must be smaller than the child's id (else the edge is
  *                  skipped and HX_ERR_NOT_DAG raised in the stream status)
- *   new_cost       device [n_new] >= 0
+ *   new_cost       device [n_new] >= 0 (a cost below 0 or NaN counts as 0, and
+ *                  HX_ERR_INVALID_ARG is raised in the stream status)
  *   new_wf         device [n_new] workflow ids, 0 .. max_wf-1
  * HX_ERR_CAPACITY if the reserved store would overflow.
  */
@@ -247,7 +248,8 @@ int hx_dag_append(hx_ctx *ctx, int32_t n_new, int32_t n_new_edges,
  * but the levels, which do not depend on costs.  Results equal a full
  * recomputation, bit for bit.
  *   node_ids device [n], 0 .. nodes appended so far - 1 (others are skipped,
- *            HX_ERR_INDEX in the stream status); cost device [n] >= 0.
+ *            HX_ERR_INDEX in the stream status); cost device [n] >= 0 (a cost
+ *            below 0 or NaN is skipped, HX_ERR_INVALID_ARG in the status).
  * Work grows with the whole graph, not with n: meant for the occasional
  * correction, not for every round.
  */

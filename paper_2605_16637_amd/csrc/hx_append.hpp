@@ -28,6 +28,10 @@ struct AppendArgs {
 
 __device__ __forceinline__ float hx_node_rec_cost(const int4 &rec) { return __int_as_float(rec.x); }
 
+// A cost a node can have: not below 0, and a number.  By its bits, above +inf's of which lie the NaNs and everything with a sign
+// (-0.0 is 0).  Tails and rems are raised on their bits, so no other cost may get into the graph.
+__device__ __forceinline__ bool hx_cost_ok(unsigned bits) { return bits <= 0x7f800000u || bits == 0x80000000u; }
+
 // non-negative fp32 values order like their bit patterns
 __device__ __forceinline__ bool hx_raise_max_f32(float *addr, float v)
 {

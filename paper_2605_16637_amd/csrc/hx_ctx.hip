@@ -442,6 +442,7 @@ extern "C" int hx_stream_status(hx_ctx *ctx, void *stream_)
         const char *what = code == HX_ERR_NOT_DAG ? "an edge breaks the DAG order, or no fixed point within the sweep limit"
                          : code == HX_ERR_INDEX ? "an index held in a device array is out of range"
                          : code == HX_ERR_OVERFLOW ? "an instance counter exceeded INT32_MAX"
+                         : code == HX_ERR_INVALID_ARG ? "the cost of a node is below 0 or no number"
                          : code == HX_ERR_CAPACITY ? "a limit was hit on the device: propagation did not finish within max_depth sweeps, or an interval list is full"
                                                    : "device status";
         return hx_fail(ctx, code, "%s", what);

@@ -457,13 +457,16 @@ __global__ __launch_bounds__(256) void hx_append_init_kernel(AppendArgs a, NodeC
     if (blockIdx.x == 0 && threadIdx.x == 0) { a.counters[a.czero] = 0; a.counters[a.cout] = 0; }
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < a.n_new; i += gridDim.x * blockDim.x) {
         const int v = a.n_old + i;
-        float c;
+        unsigned bits;                                    // (no float may be the NaN)
         if constexpr (COST) {
-            c = hx_node_cost_one(nc.m, s_tab, nc.T, nc.L_in[i], nc.L_out[i]);
-            nc.cost[i] = c;
+            const float x = hx_node_cost_one(nc.m, s_tab, nc.T, nc.L_in[i], nc.L_out[i]);
+            nc.cost[i] = x;
+            bits = __float_as_uint(x);
         } else {
-            c = a.new_cost[i];
+            bits = ((const unsigned *)a.new_cost)[i];
         }
+        if (!hx_cost_ok(bits)) { hx_raise(a.status, HX_ERR_INVALID_ARG); bits = 0; }
+        const float c = __uint_as_float(bits);
         int r0 = a.new_row_ptr[i], r1 = a.new_row_ptr[i + 1];
         const int w = hx_append_wf(a, i);
         if (w < 0) hx_raise(a.status, HX_ERR_INDEX);
@@ -556,7 +559,7 @@ __global__ __launch_bounds__(1024) void hx_append_tail_kernel(AppendArgs a, int3
     }
 }
 
-// Cost of existing nodes replaced by observed values (an id outside the graph is skipped and reported), and what the costs
+// Cost of existing nodes replaced by observed values (an id outside the graph, or a cost below 0, is skipped and reported), and what the costs
 // determine back to its starting point: no horizons, no tails, those of nodes with children marked as not reached.
 __global__ __launch_bounds__(256) void hx_refresh_begin_kernel(AppendArgs a, int n, const int32_t *ids, const float *value, int n_wf)
 {
@@ -564,7 +567,8 @@ __global__ __launch_bounds__(256) void hx_refresh_begin_kernel(AppendArgs a, int
     if (i < n) {
         const int v = ids[i];
         if (v < 0 || v >= a.n_new) hx_raise(a.status, HX_ERR_INDEX);
-        else a.rec[v].x = __float_as_int(value[i]);
+        else if (const int bits = ((const int *)value)[i]; hx_cost_ok((unsigned)bits)) a.rec[v].x = bits;
+        else hx_raise(a.status, HX_ERR_INVALID_ARG);
     }
     if (i < a.n_new) ((int *)a.tail)[i] = a.level[i] > 0 ? -1 : 0;
     if (i < n_wf) a.horizon[i] = 0.0f;
@@ -578,7 +582,7 @@ __global__ __launch_bounds__(256) void hx_refresh_end_kernel(AppendArgs a)
     if (v >= a.n_new) return;
     const int4 me = a.rec[v];
     const int t = ((const int *)a.tail)[v];
-    if (t < 0) a.tail[v] = 0.0f;                          // (never reached: the sweeps have run out and said so)
+    if (t < 0) a.tail[v] = 0.0f;                          // (never reached: the sweeps ran out, which the status says)
     const float r = hx_node_rec_cost(me) + __int_as_float(max(t, 0));
     a.rem[v] = r;
     if ((me.w & HX_NODE_TOP) && me.y >= 0) hx_raise_max_f32(&a.horizon[me.y], r);

@@ -438,6 +438,41 @@ def test_costs_of_minus_zero_are_zeros(ctx, reach, most):
         assert not np.signbit(got[0]).any()
 
 
+# below zero, and what is no number with the sign of each kind
+@pytest.mark.parametrize("bits", [0xbf800000, 0x80000001, 0xff800000, 0x7fc00000, 0xffc00000])
+def test_costs_below_zero_are_reported(ctx, bits):
+    """Such a cost is not taken (a new node's counts as 0, an observed one changes nothing) and the stream status says so; all
+    other costs of the call are."""
+    from paper_2605_16637_amd import binding
+    bad = np.array([bits], np.uint32).view(np.float32)[0]
+
+    def reported():
+        with pytest.raises(binding.HxError) as e:
+            ctx.hx_stream_status()
+        assert e.value.code == -1
+
+    # 0 <- 1 <- 2 <- 3 and 1 <- 4; the leaf 3 is what everything above hangs on
+    prow, pcol, wf = np.array([0, 0, 1, 2, 3, 4], np.int32), np.array([0, 1, 2, 1], np.int32), np.zeros(5, np.int32)
+
+    def check(cost):
+        want = o.critical_path_by_parents(prow, pcol, np.array(cost, np.float64), wf, 1, round_f32=True)
+        got = view(ctx, 5, 1)
+        assert np.array_equal(got[2], want[2])
+        for k in (0, 1, 3):
+            assert np.array_equal(got[k].astype(np.float64), want[k]), k
+
+    ctx.hx_dag_reserve(8, 8, 1, 8)
+    ctx.hx_dag_append(dev(prow), dev(pcol), dev(np.array([1, bad, 2, 4, 0.5], np.float32)), dev(wf))
+    reported()
+    check([1, 0, 2, 4, 0.5])
+    ctx.hx_dag_set_cost(dev(np.array([1, 3, 0], np.int32)), dev(np.array([3, bad, 2], np.float32)))
+    reported()
+    check([2, 3, 2, 4, 0.5])
+    ctx.hx_dag_set_cost(dev(np.array([3, 4], np.int32)), dev(np.array([np.inf, 0.0], np.float32)))       # without limit: a cost
+    ctx.hx_stream_status()
+    check([2, 3, 2, np.inf, 0])
+
+
 def test_append_errors(ctx):
     from paper_2605_16637_amd import binding
     ctx.hx_dag_reserve(8, 8, 2, 4)
