@@ -109,6 +109,10 @@ __device__ __forceinline__ void hx_push_parent_scoped(const AppendArgs &a, int u
 // those in a pass of their own.
 constexpr int RELAX_STACK = 16;
 constexpr int RELAX_STEPS = 1024;
+// Parents beyond the second are raised this many at a time, their answers under way together.  One at a time and so: appending 50
+// graphs of 8 layers of 32 nodes, all of a layer above all of the next, 6.8 and 5.7 ms; one such graph 2.1 and 1.4; 40 graphs of
+// 200 nodes with up to 8 parents 3.4 and 3.0.
+constexpr int RELAX_MANY = 4;
 
 // block, n_blocks: the workgroup's place among those that walk (the launch may hold other workgroups too)
 template <bool REFRESH>
@@ -179,13 +183,20 @@ __device__ __forceinline__ void hx_append_relax_body(const AppendArgs &a, int bl
                 for (int k = 0; k < HX_CHAIN; ++k) {
                     if (!((many >> k) & 1)) continue;
                     const int s = k ? up[k ? k - 1 : 0] : v;
-                    const int e1 = a.prow[s + 1];
-                    for (int e = a.prow[s] + 2; e < e1; ++e) {
-                        const int p = a.pcol[e];
-                        if (p < 0) continue;
-                        bool grew = hx_raise_tail(a, p, src_r[k]);
-                        if (!REFRESH) grew = src_lv[k] + 1 > atomicMax(&a.level[p], src_lv[k] + 1) || grew;
-                        if (grew) wait(p);
+                    const int32_t *others = a.pcol + a.prow[s] + 2;
+                    for (int left = a.prow[s + 1] - a.prow[s] - 2; left > 0; left -= RELAX_MANY, others += RELAX_MANY) {
+                        int p[RELAX_MANY], p_t[RELAX_MANY], p_l[RELAX_MANY];
+#pragma unroll
+                        for (int j = 0; j < RELAX_MANY; ++j) p[j] = j < left ? others[j] : -1;
+#pragma unroll
+                        for (int j = 0; j < RELAX_MANY; ++j)
+                            if (p[j] >= 0) {
+                                p_t[j] = atomicMax((int *)&a.tail[p[j]], __float_as_int(src_r[k]));
+                                if (!REFRESH) p_l[j] = atomicMax(&a.level[p[j]], src_lv[k] + 1);
+                            }
+#pragma unroll
+                        for (int j = 0; j < RELAX_MANY; ++j)
+                            if (p[j] >= 0 && (__float_as_int(src_r[k]) > p_t[j] || (!REFRESH && src_lv[k] + 1 > p_l[j]))) wait(p[j]);
                     }
                 }
             }

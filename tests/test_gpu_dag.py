@@ -473,6 +473,46 @@ def test_costs_below_zero_are_reported(ctx, bits):
     check([2, 3, 2, np.inf, 0])
 
 
+# a node's parents beyond the second are raised four at a time: every remainder, one of them named twice, one not an earlier node
+@pytest.mark.parametrize("parents", [2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 19, 20])
+@pytest.mark.parametrize("odd", ["", "twice", "no parent"])
+def test_append_of_a_node_with_parents(ctx, parents, odd):
+    from paper_2605_16637_amd import binding
+    rng = np.random.default_rng(parents)
+    n0 = parents + 3                                         # parents of one child each, over them a root, beside them two others
+    row = np.concatenate([[0, 0], np.arange(1, n0)]).astype(np.int32)
+    col = np.zeros(n0 - 1, np.int32)
+    cost = rng.uniform(0.1, 2.0, n0 + 2).astype(np.float32)
+    up = 1 + rng.permutation(n0 - 1)[:parents].astype(np.int32)
+    if odd == "twice":
+        up[-1] = up[0]
+    given, kept = up.copy(), up
+    if odd == "no parent":
+        given[parents // 2] = n0 + 5
+        kept = np.delete(up, parents // 2)
+    ctx.hx_dag_reserve(n0 + 2, 2 * n0 + 2 * parents, 1, 8)
+    ctx.hx_dag_append(dev(row), dev(col), dev(cost[:n0]), dev(np.zeros(n0, np.int32)))
+    # the node, and a child of it, in one batch
+    ctx.hx_dag_append(dev(np.array([0, parents, parents + 1], np.int32)), dev(np.append(given, n0).astype(np.int32)), dev(cost[n0:]),
+                      dev(np.zeros(2, np.int32)))
+    if odd == "no parent":
+        with pytest.raises(binding.HxError) as e:
+            ctx.hx_stream_status()
+        assert e.value.code == -3
+    ctx.hx_stream_status()
+    prow = np.concatenate([row, [n0 - 1 + kept.size, n0 + kept.size]]).astype(np.int32)
+    pcol = np.concatenate([col, kept, [n0]]).astype(np.int32)
+    for again in (False, True):
+        want = o.critical_path_by_parents(prow, pcol, cost.astype(np.float64), np.zeros(n0 + 2, np.int32), 1, round_f32=True)
+        got = view(ctx, n0 + 2, 1)
+        assert np.array_equal(got[2], want[2])
+        for k in (0, 1, 3):
+            assert np.array_equal(got[k].astype(np.float64), want[k]), k
+        cost[n0:] = [0.25, 7.0]
+        ctx.hx_dag_set_cost(dev(np.array([n0, n0 + 1], np.int32)), dev(cost[n0:]))
+        ctx.hx_stream_status()
+
+
 def test_append_errors(ctx):
     from paper_2605_16637_amd import binding
     ctx.hx_dag_reserve(8, 8, 2, 4)
