@@ -110,9 +110,10 @@ __device__ __forceinline__ void hx_push_parent_scoped(const AppendArgs &a, int u
 constexpr int RELAX_STACK = 16;
 constexpr int RELAX_STEPS = 1024;
 // Parents beyond the second are raised this many at a time, their answers under way together.  One at a time and so: appending 50
-// graphs of 8 layers of 32 nodes, all of a layer above all of the next, 6.8 and 5.7 ms; one such graph 2.1 and 1.4; 40 graphs of
-// 200 nodes with up to 8 parents 3.4 and 3.0.
-constexpr int RELAX_MANY = 4;
+// graphs of 8 layers of 32 nodes, all of a layer above all of the next, 6.8 and 5.6 ms; one such graph 2.1 and 1.5; 40 graphs of
+// 200 nodes with up to 8 parents 3.4 and 2.8.  Four at a time take 82 registers instead of 78, a wavefront a SIMD less beside the
+// search: a session of eight rounds 570 us instead of 525.
+constexpr int RELAX_MANY = 3;
 
 // block, n_blocks: the workgroup's place among those that walk (the launch may hold other workgroups too)
 template <bool REFRESH>
@@ -178,26 +179,25 @@ __device__ __forceinline__ void hx_append_relax_body(const AppendArgs &a, int bl
 #pragma unroll
             for (int k = 0; k < HX_CHAIN; ++k)
                 if (q[k] >= 0 && (__float_as_int(src_r[k]) > old_t[k] || (!REFRESH && src_lv[k] + 1 > old_l[k]))) wait(q[k]);
-            if (many) {
+            for (; many; many &= many - 1) {
+                const int k = __builtin_ctz(many);
+                const int s = k == 0 ? v : k == 1 ? up[0] : k == 2 ? up[1] : up[2];
+                const float s_r = k == 0 ? src_r[0] : k == 1 ? src_r[1] : k == 2 ? src_r[2] : src_r[3];
+                const int s_lv = src_lv[0] + k;
+                const int32_t *others = a.pcol + a.prow[s] + 2;
+                for (int left = a.prow[s + 1] - a.prow[s] - 2; left > 0; left -= RELAX_MANY, others += RELAX_MANY) {
+                    int p[RELAX_MANY], p_t[RELAX_MANY], p_l[RELAX_MANY];
 #pragma unroll
-                for (int k = 0; k < HX_CHAIN; ++k) {
-                    if (!((many >> k) & 1)) continue;
-                    const int s = k ? up[k ? k - 1 : 0] : v;
-                    const int32_t *others = a.pcol + a.prow[s] + 2;
-                    for (int left = a.prow[s + 1] - a.prow[s] - 2; left > 0; left -= RELAX_MANY, others += RELAX_MANY) {
-                        int p[RELAX_MANY], p_t[RELAX_MANY], p_l[RELAX_MANY];
+                    for (int j = 0; j < RELAX_MANY; ++j) p[j] = j < left ? others[j] : -1;
 #pragma unroll
-                        for (int j = 0; j < RELAX_MANY; ++j) p[j] = j < left ? others[j] : -1;
+                    for (int j = 0; j < RELAX_MANY; ++j)
+                        if (p[j] >= 0) {
+                            p_t[j] = atomicMax((int *)&a.tail[p[j]], __float_as_int(s_r));
+                            if (!REFRESH) p_l[j] = atomicMax(&a.level[p[j]], s_lv + 1);
+                        }
 #pragma unroll
-                        for (int j = 0; j < RELAX_MANY; ++j)
-                            if (p[j] >= 0) {
-                                p_t[j] = atomicMax((int *)&a.tail[p[j]], __float_as_int(src_r[k]));
-                                if (!REFRESH) p_l[j] = atomicMax(&a.level[p[j]], src_lv[k] + 1);
-                            }
-#pragma unroll
-                        for (int j = 0; j < RELAX_MANY; ++j)
-                            if (p[j] >= 0 && (__float_as_int(src_r[k]) > p_t[j] || (!REFRESH && src_lv[k] + 1 > p_l[j]))) wait(p[j]);
-                    }
+                    for (int j = 0; j < RELAX_MANY; ++j)
+                        if (p[j] >= 0 && (__float_as_int(s_r) > p_t[j] || (!REFRESH && s_lv + 1 > p_l[j]))) wait(p[j]);
                 }
             }
             if (live) {

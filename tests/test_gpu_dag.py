@@ -473,7 +473,7 @@ def test_costs_below_zero_are_reported(ctx, bits):
     check([2, 3, 2, np.inf, 0])
 
 
-# a node's parents beyond the second are raised four at a time: every remainder, one of them named twice, one not an earlier node
+# a node's parents beyond the second are raised three at a time: every remainder, one of them named twice, one not an earlier node
 @pytest.mark.parametrize("parents", [2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 19, 20])
 @pytest.mark.parametrize("odd", ["", "twice", "no parent"])
 def test_append_of_a_node_with_parents(ctx, parents, odd):
