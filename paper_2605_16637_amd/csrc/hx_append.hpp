@@ -21,6 +21,7 @@ struct AppendArgs {
     int32_t *level, *prow, *pcol, *mark;
     int32_t *list_in, *list_out;
     int32_t *counters;      // [0..2] rotating list sizes
+    int leaves;             // a refresh: only nodes without children walk
     int cin, cout, czero;   // which counter is read, appended to, cleared
     uint32_t epoch;
     int32_t *status;
@@ -104,9 +105,9 @@ __device__ __forceinline__ void hx_push_parent_scoped(const AppendArgs &a, int u
 // what they ask for lies above the point where a walk stops; two: as four.  Further parents queued in LDS for any idle lane
 // of the wavefront: 30 and 59, three times the code.)
 //
-// REFRESH: all costs new, levels as they are.  Only the nodes without children walk -- their walks reach every other
-// node, whose tail's mark of -1 the first to come raises -- and raise tails alone; rem and the horizons follow from
-// those in a pass of their own.
+// REFRESH: all costs new, levels as they are.  The walks raise tails alone; rem and the horizons follow from those in a pass of
+// their own.  Either every node walks, with what its tail is by now, or (leaves) only the nodes without children: their walks
+// reach every other node, whose tail's mark of -1 the first to come raises.
 constexpr int RELAX_STACK = 16;
 constexpr int RELAX_STEPS = 1024;
 // Parents beyond the second are raised this many at a time, their answers under way together.  One at a time and so: appending 50
@@ -125,9 +126,11 @@ __device__ __forceinline__ void hx_append_relax_body(const AppendArgs &a, int bl
         int stack[RELAX_STACK];
         int sp = 0, steps = 0;
         int v = a.n_old + i;
-        if (REFRESH && a.level[v] != 0) continue;
+        if (REFRESH && a.leaves && a.level[v] != 0) continue;
         int4 me = a.rec[v], above = a.chain[v];
-        float r = hx_node_rec_cost(me) + 0.0f;               // rem of v as far as this walk knows
+        float t = 0.0f;
+        if (REFRESH && !a.leaves) t = __int_as_float(max(__hip_atomic_load((const int *)&a.tail[v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), 0));
+        float r = hx_node_rec_cost(me) + t;                  // rem of v as far as this walk knows
         int lv = 0;
         for (;;) {
             const int up[HX_CHAIN] = {above.x, above.y, above.z, above.w};

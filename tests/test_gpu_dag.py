@@ -513,6 +513,83 @@ def test_append_of_a_node_with_parents(ctx, parents, odd):
         ctx.hx_stream_status()
 
 
+def wide_graph(kind):
+    """Parent lists (row, col) of graphs whose nodes without children are few and whose nodes have several parents."""
+    rng = np.random.default_rng(len(kind))
+    if kind == "near parents":                               # 20 workflows of 1000 nodes, up to three parents among the eight before
+        parents = [sorted(set((rng.integers(max(0, v - 8), v, 3)).tolist())) if v else [] for v in range(1000)]
+        copies = 20
+    else:                                                    # 20 of 40 layers of 10, all of a layer above all of the next
+        parents = [list(range(v // 10 * 10 - 10, v // 10 * 10)) if v >= 10 else [] for v in range(400)]
+        copies = 20
+    size = len(parents)
+    deg, one = np.array([len(p) for p in parents]), np.array([u for p in parents for u in p])
+    row = np.concatenate([[0], np.cumsum(np.tile(deg, copies))]).astype(np.int32)
+    return row, (one + size * np.arange(copies)[:, None]).astype(np.int32).reshape(-1), np.repeat(np.arange(copies, dtype=np.int32), size)
+
+
+@pytest.mark.parametrize("kind", ["near parents", "layers"])
+def test_observed_costs_where_few_nodes_have_no_children(ctx, kind):
+    """New costs are carried up by every node of such a graph, not by its few leaves alone: their walks would visit all of it one after the
+    other (54 and 8 ms here; appending the graph, where every node walks, takes 9.2 and 3.8)."""
+    import torch
+    row, col, wf = wide_graph(kind)
+    n, n_wf = wf.size, int(wf.max()) + 1
+    rng = np.random.default_rng(4)
+    cost = rng.uniform(0.1, 2.0, n).astype(np.float32)
+    ids = np.arange(0, n, 7, dtype=np.int32)
+    new = rng.uniform(0.05, 3.0, ids.size).astype(np.float32)
+    g = [dev(x) for x in (row, col, cost, wf, ids, new)]
+
+    def ms(fn):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record(); fn(); b.record()
+        ctx.hx_stream_status()
+        return a.elapsed_time(b)
+
+    append, refresh = [], []
+    for _ in range(3):
+        ctx.hx_dag_reserve(n, col.size, n_wf, 2000)
+        torch.cuda.synchronize()
+        append.append(ms(lambda: ctx.hx_dag_append(*g[:4])))
+        refresh.append(ms(lambda: ctx.hx_dag_set_cost(g[4], g[5])))
+    cost[ids] = new
+    want = o.critical_path_by_parents(row, col, cost.astype(np.float64), wf, n_wf, round_f32=True)
+    got = view(ctx, n, n_wf)
+    assert np.array_equal(got[2], want[2])
+    for k in (0, 1, 3):
+        assert np.array_equal(got[k].astype(np.float64), want[k]), k
+    # with every node walking a refresh is the append without its first kernel: half as much again at most
+    assert min(refresh) < 1.5 * min(append), (refresh, append)
+
+
+@pytest.mark.parametrize("per_node", [1, 2, 3])
+def test_observed_costs_of_a_large_graph(ctx, per_node):
+    """More nodes than a refresh lets walk together: the nodes without children alone walk (up to two edges a node), or all do."""
+    rng = np.random.default_rng(per_node)
+    n_wf, size = 30000, 10
+    n = n_wf * size
+    rank = np.tile(np.arange(size), n_wf)
+    deg = np.minimum(rank, per_node)
+    row = np.zeros(n + 1, np.int32); row[1:] = np.cumsum(deg)
+    first = np.repeat(np.arange(n) - rank, deg)              # a node's parents: among those before it in its workflow, some twice
+    col = (first + (rng.random(first.size) * np.repeat(rank, deg)).astype(np.int64)).astype(np.int32)
+    wf = np.repeat(np.arange(n_wf, dtype=np.int32), size)
+    cost = rng.choice(np.array([0.0, 0.25, 1.0, 3.0], np.float32), n)
+    ctx.hx_dag_reserve(n, col.size, n_wf, 16)
+    ctx.hx_dag_append(dev(row), dev(col), dev(cost), dev(wf))
+    for _ in range(2):
+        ids = rng.choice(n, n // 3, replace=False).astype(np.int32)
+        cost[ids] = rng.choice(np.array([0.0, 0.5, 2.0], np.float32), ids.size)
+        ctx.hx_dag_set_cost(dev(ids), dev(cost[ids]))
+        ctx.hx_stream_status()
+        want = o.critical_path_revealed(row, col, cost.astype(np.float64), wf, n_wf, round_f32=True)
+        got = view(ctx, n, n_wf)
+        assert np.array_equal(got[2], want[2])
+        for k in (0, 1, 3):
+            assert np.array_equal(got[k].astype(np.float64), want[k]), k
+
+
 def test_append_errors(ctx):
     from paper_2605_16637_amd import binding
     ctx.hx_dag_reserve(8, 8, 2, 4)
