@@ -584,9 +584,9 @@ __global__ __launch_bounds__(256) void hx_select_wave_kernel(ScoreArgs a)
 {
     constexpr int U = 8;
     const int lane = threadIdx.x & (HX_WAVE - 1);
-    const int wave = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (blockDim.x / HX_WAVE) + threadIdx.x / HX_WAVE));
+    const unsigned wave = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (blockDim.x / HX_WAVE) + threadIdx.x / HX_WAVE));
     const int n4 = (a.P * a.D) >> 2;
-    for (int c = wave; c < a.C; c += gridDim.x * (blockDim.x / HX_WAVE)) {
+    for (unsigned c = wave; c < (unsigned)a.C; c += gridDim.x * (blockDim.x / HX_WAVE)) {       // (may step past 2^31)
         const float4 *row = reinterpret_cast<const float4 *>(a.cost + (size_t)c * ((size_t)n4 * 4));
         float bv = INFINITY;
         int bi = 0x7fffffff;
@@ -622,7 +622,7 @@ __global__ __launch_bounds__(256) void hx_select_kernel(ScoreArgs a)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n = a.P * a.D;
     const bool vec4 = (n & 3) == 0 && (reinterpret_cast<uintptr_t>(a.cost) & 15) == 0;
-    for (int c = blockIdx.x; c < a.C; c += gridDim.x) {
+    for (unsigned c = blockIdx.x; c < (unsigned)a.C; c += gridDim.x) {
         const float *row = a.cost + (size_t)c * n;
         float bv = INFINITY;
         int bi = 0x7fffffff;
@@ -928,7 +928,7 @@ extern "C" int hx_select(hx_ctx *ctx, int32_t C, int32_t P, int32_t D, const flo
     const int most = ctx->num_cu * 8;
     const bool quads = ((long long)P * D & 3) == 0 && (reinterpret_cast<uintptr_t>(cost) & 15) == 0;
     if (quads && (long long)P * D <= SELECT_WAVE) {
-        const int grid = (C + 3) / 4;
+        const int grid = C / 4 + (C % 4 != 0);
         hx_select_wave_kernel<<<grid < most ? grid : most, 256, 0, stream>>>(a);
         return hx_check_launch(ctx, "hx_select_wave_kernel");
     }

@@ -467,3 +467,16 @@ def test_select_by_wavefronts_and_by_workgroups(ctx, C, P, D, offset):
     none = ~np.isfinite(low)
     assert np.array_equal(bc.cpu().numpy(), low)
     assert np.array_equal(bp.cpu().numpy(), np.where(none, -1, at // D)) and np.array_equal(bd.cpu().numpy(), np.where(none, -1, at % D))
+
+
+# the last numbers of calls that 32 bits hold: what a wavefront or a workgroup takes next lies beyond them
+@pytest.mark.parametrize("C", [2**31 - 8000, 2**31 - 1])
+def test_select_of_as_many_calls_as_there_can_be(ctx, C):
+    import torch
+    i32 = dict(dtype=torch.int32, device="cuda:0")
+    bp, bd = torch.full((C,), -9, **i32), torch.full((C,), -9, **i32)
+    bc = torch.full((C,), -9.0, device="cuda:0")
+    ctx.hx_select(C, 0, 3, None, bp, bd, bc)
+    ctx.hx_stream_status()
+    for got, want in ((bp, -1), (bd, -1), (bc, float("inf"))):
+        assert all(bool((part == want).all()) for part in got.split(1 << 28))
