@@ -478,7 +478,9 @@ int hx_urgency(hx_ctx *ctx, const hx_calls *calls, const float *best_cost,
  * ratio [C] device in (as written by hx_score_placements or hx_select; +inf =
  * nothing feasible, ranked first), rank [C] device out.  Up to 10240 calls every
  * call is compared with every call, up to 28672 with those that lie between the
- * same two of 255 sampled ones (no scratch).  Beyond that the calls are
+ * same two of 255 sampled ones (no scratch; the samples' places depend on C alone,
+ * and a queue that puts most calls between two of them takes longer: up to 0.65 ms
+ * instead of 0.03).  Beyond that the calls are
  * split into 257 buckets by 256 sampled splitters and compared within their
  * bucket; the library then keeps 8 bytes of scratch per call, and a call with a
  * larger C than any before it allocates, after waiting for the device, and is

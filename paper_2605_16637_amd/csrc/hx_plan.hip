@@ -85,16 +85,21 @@ __global__ __launch_bounds__(256) void hx_rank_count_kernel(const float *ratio, 
 // Beyond RANK_PAIRS calls, up to RANK_CUT: one launch of a workgroup per bucket.  RANK_CUTS calls, one from each of as
 // many stretches of the queue and anywhere in it, are ordered by counting; workgroup b takes the calls between the b-th of
 // them and the next.  It reads the whole queue, counts the calls ahead of its bucket, gathers the bucket's members in LDS and counts among those.  Keys
-// are unique (they end in the call index), so the buckets stay balanced however many ratios are equal; should one
-// outgrow the LDS all the same, its members are counted against the whole queue instead.
+// are unique (they end in the call index), so the buckets stay balanced however many ratios are equal.  Up to RANK_BY_PAIRS members
+// are compared with each other, more are sorted; should they outgrow the LDS, the queue is sorted a part at a time (what is not of the
+// bucket at the end) and every member's place looked up in each.
 // Bound: two round trips and the ordering of the cuts (7 us together), then the pass over the queue and the largest bucket,
 // some six times the others, by pairs.  Launches back to back, all pairs of calls / cuts / the sample sort below: 8192
-// calls 8.9 / 9.3 / -, 12000 14.0 / 12.5 / -, 16384 21.3 / 13.4 / -, 24000 - / 20.0 / 26.8, 32768 - / 34.0 / 33.4.
+// calls 8.9 / 9.3 / -, 12000 14.0 / 12 to 16 / -, 16384 21.3 / 14 to 18 / -, 24000 - / 19 to 24 / 27 to 30, 32768 - / 34.0 / 33.4 (the
+// largest bucket differs from queue to queue).  Members among 16384 calls, by pairs and sorted: 500 21 and 22 us, 700 31 and 22, 1000 48 and
+// 28, 4000 461 and 46.  A queue whose dividers all lie above the other calls: 168 us of 10241 calls, 275 of 16384, 640 of 28672, the
+// lookups, whose LDS reads lie anywhere, two thirds of it (members counted against the whole queue by pairs: 7 to 57 ms).
 // (Cuts compared as 32-bit words with the ties by index, four at a time: 1.5 us more; workgroups of 512 threads: 0.5
 // less on 2048 calls, 3 more on 16384.)
 constexpr int RANK_CUT = 28 * 1024;
 constexpr int RANK_CUTS = 255;                   // buckets 0 .. RANK_CUTS
-constexpr int RANK_MEMBERS = 4096;               // members of a bucket that LDS holds
+constexpr int RANK_MEMBERS = 4096;               // members of a bucket that LDS holds (a power of two)
+constexpr int RANK_BY_PAIRS = 576;               // members compared with each other
 constexpr int RANK_READ = 8;                     // calls a thread has in flight
 
 __global__ __launch_bounds__(RANK_THREADS) void hx_rank_cut_kernel(const float *ratio, int32_t *rank, int C)
@@ -160,31 +165,64 @@ __global__ __launch_bounds__(RANK_THREADS) void hx_rank_cut_kernel(const float *
     __syncthreads();
     const int n = s_n;
     higher = s_higher;
-    if (n > RANK_MEMBERS) {
-        for (int c = tid; c < C; c += RANK_THREADS) {
-            const unsigned long long mine = hx_rank_key64(hx_load_bits(ratio, c), c);
-            if (mine < low || mine >= high) continue;
+    if (__builtin_expect(n <= RANK_BY_PAIRS, 1)) {
+        // 64 members at a time, a lane each, against a share of the bucket per wavefront
+        const int share = (n + WAVES - 1) / WAVES, end = min((wave + 1) * share, n);
+        for (int m0 = 0; m0 < n; m0 += HX_WAVE) {
+            const unsigned long long mine = s_key[min(m0 + lane, n - 1)];
             int ahead = 0;
-#pragma unroll 8
-            for (int k = 0; k < C; ++k) ahead += hx_rank_key64(hx_load_bits(ratio, k), k) > mine;
-            rank[c] = ahead;
+#pragma unroll 4
+            for (int k = wave * share; k < end; ++k) ahead += s_key[k] > mine;
+            if (ahead) atomicAdd(&s_ahead[lane], ahead);
+            __syncthreads();
+            if (wave == 0) {
+                if (m0 + lane < n) rank[0xffffffffu - (unsigned)(mine & 0xffffffffull)] = higher + s_ahead[lane];
+                s_ahead[lane] = 0;
+            }
+            __syncthreads();
         }
         return;
     }
-    // 64 members at a time, a lane each, against a share of the bucket per wavefront
-    const int share = (n + WAVES - 1) / WAVES, end = min((wave + 1) * share, n);
-    for (int m0 = 0; m0 < n; m0 += HX_WAVE) {
-        const unsigned long long mine = s_key[min(m0 + lane, n - 1)];
-        int ahead = 0;
-#pragma unroll 4
-        for (int k = wave * share; k < end; ++k) ahead += s_key[k] > mine;
-        if (ahead) atomicAdd(&s_ahead[lane], ahead);
-        __syncthreads();
-        if (wave == 0) {
-            if (m0 + lane < n) rank[0xffffffffu - (unsigned)(mine & 0xffffffffull)] = higher + s_ahead[lane];
-            s_ahead[lane] = 0;
+    const bool all = n <= RANK_MEMBERS;                      // the members gathered above are all there are
+    int room = RANK_MEMBERS;
+    if (all) {
+        while (room >> 1 >= n) room >>= 1;
+        for (int i = n + tid; i < room; i += RANK_THREADS) s_key[i] = 0ull;
+    }
+    for (int from = 0; from < (all ? 1 : C); from += RANK_MEMBERS) {
+        if (!all) {
+            for (int i = tid; i < RANK_MEMBERS; i += RANK_THREADS) {
+                const int c = min(from + i, C - 1);
+                const unsigned long long key = hx_rank_key64(hx_load_bits(ratio, c), c);
+                s_key[i] = from + i < C && key >= low && key < high ? key : 0ull;
+            }
         }
         __syncthreads();
+        // into decreasing order: bitonic merges
+        for (int size = 2; size <= room; size <<= 1)
+            for (int stride = size >> 1; stride > 0; stride >>= 1) {
+                for (int i = tid; i < room >> 1; i += RANK_THREADS) {
+                    const int lo = 2 * i - (i & (stride - 1)), hi = lo + stride;
+                    const unsigned long long x = s_key[lo], y = s_key[hi];
+                    if ((x < y) == ((lo & size) == 0)) { s_key[lo] = y; s_key[hi] = x; }
+                }
+                __syncthreads();
+            }
+        if (all)
+            for (int i = tid; i < n; i += RANK_THREADS) rank[0xffffffffu - (unsigned)(s_key[i] & 0xffffffffull)] = higher + i;
+        else {
+            for (int c = tid; c < C; c += RANK_THREADS) {    // a call's places are added up by one thread
+                const unsigned long long mine = hx_rank_key64(hx_load_bits(ratio, c), c);
+                if (mine < low || mine >= high) continue;
+                int ahead = 0;
+                for (int step = RANK_MEMBERS; step > 0; step >>= 1) {
+                    const int next = min(ahead + step, RANK_MEMBERS);      // (the last key may be looked at more than once)
+                    ahead = s_key[next - 1] > mine ? next : ahead;
+                }
+                rank[c] = (from ? rank[c] : higher) + ahead;
+            }
+            __syncthreads();
+        }
     }
 }
 

@@ -105,6 +105,63 @@ def test_rank_between_cuts(ctx, C, kind):
     assert np.array_equal(rank[:C].cpu().numpy(), want) and bool((rank[C:] == -1).all())
 
 
+# A queue whose dividers all lie above the other calls.  The workgroup that gets the bucket sorts it 4096 calls at a time and looks
+# every call up in each part, some 92 us a part (7 of them at most) beside the 11 to 25 us of a queue that divides well: 15 to 26
+# times that.  Counted pair by pair it was 600 to 2000 times.
+@pytest.mark.parametrize("C", [10241, 16384, 28672])
+def test_rank_time_of_one_bucket(ctx, C):
+    import torch
+    rng = np.random.default_rng(C)
+    even = rng.random(C).astype(np.float32)
+    t = np.arange(255, dtype=np.int64)
+    begin = t * C // 256
+    size = (t + 1) * C // 256 - begin
+    uneven = even.copy()
+    uneven[begin + ((t * 2654435761 % 2 ** 32 >> 8) * size >> 24)] += 2
+    rank = torch.empty(C, dtype=torch.int32, device="cuda:0")
+    times = []
+    for r in (dev(even), dev(uneven)):
+        run = ctx.prepare(lambda: ctx.hx_rank(r, rank))
+        run()
+        best = np.inf
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(4):
+                run()
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b) / 4)
+        times.append(best)
+    assert times[1] < 100 * times[0], times
+
+
+# members of one bucket around what a workgroup counts by pairs, what it sorts at once and what it sorts in parts: 0, 1 or some
+# above all dividers, the others between the first two, below all or in one run
+@pytest.mark.parametrize("n", [1, 63, 575, 576, 577, 1023, 1024, 1025, 2047, 2049, 4095, 4096, 4097, 8200])
+@pytest.mark.parametrize("where", ["above", "between", "below"])
+def test_rank_with_a_bucket_of(ctx, n, where):
+    import torch
+    C = 12000
+    rng = np.random.default_rng(n)
+    t = np.arange(255, dtype=np.int64)
+    begin = t * C // 256
+    size = (t + 1) * C // 256 - begin
+    cut = begin + ((t * 2654435761 % 2 ** 32 >> 8) * size >> 24)
+    # dividers at 1 .. 255; the n members between two of them (or at an end), some ratios among them equal; all other calls spread
+    r = rng.uniform(1, 255, C)
+    r[cut] = rng.permutation(np.arange(1, 256))
+    members = rng.choice(np.setdiff1d(np.arange(C), cut), n, replace=False)
+    r[members] = {"above": 300, "between": 100.25, "below": -5}[where] + rng.integers(0, max(2, n // 2), n) / (4 * n + 8)
+    r = r.astype(np.float32)
+    rank = torch.full((C + 64,), -1, dtype=torch.int32, device="cuda:0")
+    ctx.hx_rank(dev(r), rank[:C])
+    ctx.hx_stream_status()
+    order = np.argsort(-r.astype(np.float64), kind="stable")
+    want = np.empty(C, np.int64); want[order] = np.arange(C)
+    assert np.array_equal(rank[:C].cpu().numpy(), want) and bool((rank[C:] == -1).all())
+
+
 def run_greedy(ctx, model, L, O, elapsed, node, wf, tail, hor, pre, dec, links):
     import torch
     from paper_2605_16637_amd import binding
