@@ -22,8 +22,9 @@ namespace {
 
 // ---- standalone node cost -----------------------------------------------------
 
-// NN nodes a thread at a time, 256 apart, so that every load is coalesced and NN of each kind are in flight.
-template <int NN, int TT>
+// NN nodes a thread at a time, 256 apart, so that every load is coalesced and NN of each kind are in flight.  AT_ONCE: all pairs of
+// classes at once.
+template <int NN, int TT, bool AT_ONCE = false>
 __global__ __launch_bounds__(256) void hx_node_cost_kernel(NodeCostArgs a)
 {
     __shared__ CostTables s_tab;
@@ -44,7 +45,8 @@ __global__ __launch_bounds__(256) void hx_node_cost_kernel(NodeCostArgs a)
     hx_cost_tables_fill(s_tab, a, tid);
     __syncthreads();
     for (; at < a.n; at += step) {
-        hx_node_cost_eval<NN, TT>(a.m, s_tab, a.T, L, O, c);
+        if constexpr (AT_ONCE) c[0] = hx_node_cost_at_once(a.m, s_tab, a.T, L[0], O[0]);
+        else hx_node_cost_eval<NN, TT>(a.m, s_tab, a.T, L, O, c);
 #pragma unroll
         for (int n = 0; n < NN; ++n)
             if (at + n * 256 < a.n) a.cost[at + n * 256] = c[n];
@@ -647,13 +649,17 @@ extern "C" int hx_node_cost(hx_ctx *ctx, const hx_model *model, int32_t n,
     if (n == 0) return HX_OK;
     HxDeviceGuard guard(ctx->device);
     HX_REQUIRE(ctx, guard.ok, HX_ERR_DEVICE, "cannot select device %d", ctx->device);
-    // four nodes a thread once that still gives every compute unit a workgroup (20000 nodes 3.7 us with one a thread, the 20
-    // workgroups there would be with four wait for the same loads); at most eight workgroups each
-    const int nn = n >= ctx->num_cu * 1024 ? 4 : 1;
+    // Four nodes a thread where there are many (launches in a graph, one and four a thread: 262144 nodes of 4 classes 3.1 and 3.5 us, 400000
+    // 3.6 and 3.5; 400000 of 5 and of 8 4.1 and 4.8, 5.3 and 6.7; 786432 5.3 and 5.3, 7.8 and 7.3), at most eight workgroups a
+    // compute unit.  More than four classes of few nodes: all pairs at once (65536 nodes of 5, 6, 7, 8 classes 3.0, 3.0, 3.0, 3.1 us, one
+    // class after the other 3.1, 3.3, 3.7, 4.0; 131072 3.3, 3.4, 3.4, 3.5 and 3.2, 3.4, 3.8, 4.1; 200000 5.1 to 5.6 and 3.4 to 4.4).
+    const int nn = n >= ctx->num_cu * (n_types > 4 ? 3072 : 1536) ? 4 : 1;
+    const bool at_once = n_types > 4 && n <= ctx->num_cu * (n_types > 5 ? 512 : 256);
     int grid = (int)(((long long)n + 256 * nn - 1) / (256 * nn));
     grid = grid > ctx->num_cu * 8 ? ctx->num_cu * 8 : grid;
     hipStream_t stream = (hipStream_t)stream_;
-    if (nn == 1) hx_node_cost_kernel<1, kT><<<grid, 256, 0, stream>>>(a);
+    if (at_once) hx_node_cost_kernel<1, kT, true><<<grid, 256, 0, stream>>>(a);
+    else if (nn == 1) hx_node_cost_kernel<1, kT><<<grid, 256, 0, stream>>>(a);
     else if (n_types <= 4) hx_node_cost_kernel<4, 4><<<grid, 256, 0, stream>>>(a);
     else hx_node_cost_kernel<4, kT><<<grid, 256, 0, stream>>>(a);
     return hx_check_launch(ctx, "hx_node_cost_kernel");

@@ -71,8 +71,9 @@ def test_node_cost_and_critical_path(ctx, name, seed):
 
 @pytest.mark.parametrize("T", [1, 3, 4, 5, 8])
 def test_node_cost_of_many_nodes(ctx, T):
-    # From 262144 nodes on (256 compute units) a thread takes four; beyond 2097152 it comes back for more.  Any part of the
-    # array on its own, short enough for a node a thread, has the same bits, and nothing is written past the end.
+    # From 393216 nodes on (256 compute units; 786432 if there are more than four classes) a thread takes four; beyond 2097152 it comes
+    # back for more; more than four classes are taken all at once up to 65536 or 131072 nodes.  Any part of the array on its own,
+    # short enough for a node a thread, has the same bits, and nothing is written past the end.
     import torch
     from paper_2605_16637_amd import binding
     rng = np.random.default_rng(T)
@@ -91,7 +92,7 @@ def test_node_cost_of_many_nodes(ctx, T):
         return out[:n].cpu().numpy()
 
     parts = np.concatenate([cost(i, min(200000, most - i)) for i in range(0, most, 200000)])
-    for n in (262144, 262145, 524287, most):
+    for n in (1, 65536, 65537, 131072, 131073, 262144, 262145, 393215, 393217, 524287, 786431, 786433, most):
         assert np.array_equal(cost(0, n), parts[:n])
     some = rng.choice(most, 2000, replace=False)
     assert_costs_close(parts[some], o.node_cost(synth.MODEL, L[some], O[some], types, links), "node cost")
