@@ -394,8 +394,9 @@ __global__ __launch_bounds__(1024) void hx_rank_within_kernel(int32_t *rank, int
 // 64 calls on 8 + 8 instances 338 -> 85 us, 256 on 64 + 64 2500 -> 465, 256 on 256 + 256 3860 -> 1640, 1024 on 64 + 64
 // 20100 -> 6320, 1024 on 256 + 256 30600 -> 16900.  (256 on 64 + 64 with four wavefronts instead of eight: 500.)
 // With what a stage does not change in registers (transfers, where a group's arrivals lie) and the divisions of a
-// commit by multiplication: 64 on 8 + 8 82 -> 78, 256 on 64 + 64 461 -> 443, 256 on 16 + 16 375 -> 346.  (The links of the
-// prefill instances in registers as well: 452 for the second.)
+// commit by multiplication: 64 on 8 + 8 82 -> 78, 256 on 64 + 64 465 -> 443, 256 on 16 + 16 375 -> 350,
+// 256 on 256 + 256 1646 -> 1625; with a nominal batch that is no power of two (48), whose division stays one, 465 -> 458, 376 -> 352 and
+// 1644 -> 1633.  (The links of the prefill instances in registers as well: 452 for the second.)
 constexpr int GREEDY_THREADS = 8 * HX_WAVE;                  // two wavefronts per SIMD
 constexpr int GREEDY_MAX_THREADS = HX_GREEDY_MAX_CALLS;      // a lane per call at least
 constexpr int GREEDY_K = HX_GREEDY_MAX_INSTANCES / HX_WAVE;
@@ -705,7 +706,8 @@ __global__ __launch_bounds__(THREADS) void hx_plan_greedy_kernel(GreedyArgs a, i
                                decode_time(fr.z, c1.z, c2.z, kB.z), decode_time(fr.w, c1.w, c2.w, kB.w));
         };
         // The lowest cost of the lane's call and its ratio, Eq. (2).  N of the lane's groups at a time, read together (past
-        // the last the lane's first once more).
+        // the last the lane's first once more).  Where the arrivals of the first lie is known but for two at a time: such a search
+        // has many rows, and asking at each whether it is the first cost more (256 calls on 256 + 256 1645 -> 1670 us).
         auto search_by = [&](auto n_) {
             constexpr int N = decltype(n_)::value;
             float v = INFINITY;
@@ -716,7 +718,7 @@ __global__ __launch_bounds__(THREADS) void hx_plan_greedy_kernel(GreedyArgs a, i
 #pragma unroll
                 for (int u = 0; u < N; ++u) {
                     const int at_row = row + u < per_lane ? row + u : 0;
-                    off[u] = u < KEPT && row == 0 ? off0[u < KEPT ? u : 0] : my_goff[at_row << lg];
+                    off[u] = N > 2 && u < KEPT && row == 0 ? off0[u < KEPT ? u : 0] : my_goff[at_row << lg];
                     w[u] = my_w[at_row << lg];
                     t[u] = N > 2 ? *(const float4 *)(my_dec + at_row * dec_row) : decode_times(sub + (at_row << lg));
                 }
