@@ -84,7 +84,10 @@ __device__ __forceinline__ unsigned long long hx_wave_sum_i31(int x)
 
 // One call a lane into the workgroup's counters, by LDS atomics; all lanes of the wavefront take part.  Lanes that meet on a
 // counter are serialised there, and scored on one snapshot most calls of a round choose the same instance: where all of
-// a wavefront do, one lane adds their sum (16384 calls on 256 + 256 as part of a round 20.6 -> 18.9 us).  False: a pair or a length out of range.
+// a wavefront do, one lane adds their sum (16384 calls on 256 + 256 as part of a round 20.6 -> 18.9 us).  Not in a round of
+// CA_SINGLY calls, which meet nobody else's: one call 2.83 us instead of 2.70, 32 on one instance 2.93 instead of 2.79 (128 2.96 instead of
+// 3.04).  False: a pair or a length out of range.
+constexpr int CA_SINGLY = HX_WAVE;
 __device__ __forceinline__ bool hx_commit_call(const CommitArgs &a, unsigned long long *acc, int p, int d, int L, int O)
 {
     bool valid = p >= 0 && d >= 0;                          // otherwise the call stays queued
@@ -93,8 +96,8 @@ __device__ __forceinline__ bool hx_commit_call(const CommitArgs &a, unsigned lon
     const unsigned long long m = __builtin_amdgcn_ballot_w64(valid);
     if (m == 0) return !bad;
     const int lead = __builtin_ctzll(m), lane = threadIdx.x & (HX_WAVE - 1);
-    const bool one_p = __builtin_amdgcn_ballot_w64(valid && p != __builtin_amdgcn_readlane(p, lead)) == 0;
-    const bool one_d = __builtin_amdgcn_ballot_w64(valid && d != __builtin_amdgcn_readlane(d, lead)) == 0;
+    const bool one_p = a.C > CA_SINGLY && __builtin_amdgcn_ballot_w64(valid && p != __builtin_amdgcn_readlane(p, lead)) == 0;
+    const bool one_d = a.C > CA_SINGLY && __builtin_amdgcn_ballot_w64(valid && d != __builtin_amdgcn_readlane(d, lead)) == 0;
     const unsigned long long all_L = one_p || one_d ? hx_wave_sum_i31(valid ? L : 0) : 0ull;
     if (one_p ? lane == lead : valid) atomicAdd(&acc[p], one_p ? all_L : (unsigned long long)L);
     if (one_d) {

@@ -746,6 +746,29 @@ def test_commit_at_the_lines_between_its_kernels(ctx, C, P, D, hot):
             assert np.array_equal(got.cpu().numpy(), w)
 
 
+# One instance on a side, so that all calls of a wavefront meet there and their lengths are added by halves of 16 bits: lengths around
+# the carry from one to the other, whole wavefronts, ragged ones, one alone; rounds of either commit kernel
+@pytest.mark.parametrize("C", [1, 2, 63, 64, 65, 128, 2047, 2048, 2049, 8192, 16384])
+@pytest.mark.parametrize("P,D", [(1, 1), (1, 3), (3, 1), (3, 3)])
+def test_commit_of_long_calls_on_one_instance(ctx, C, P, D):
+    from paper_2605_16637_amd import binding
+    rng = np.random.default_rng(C + 10 * P + D)
+    L, O = (rng.choice(np.array([0, 1, 65534, 65535, 65536, 65537], np.int32), C) for _ in range(2))
+    for x in (L, O):
+        x[rng.integers(0, C, 4)] = [1 << 20, (1 << 20) - 1, 3 << 16, 1 << 17]
+    assert int(L.sum(dtype=np.int64)) + int(O.sum(dtype=np.int64)) < 2**31 - 4096        # no counter overflows
+    # where there are three instances: all but some calls on the last
+    bp, bd = (np.where(rng.random(C) < 0.02, rng.integers(-1, n, C), n - 1).astype(np.int32) for n in (P, D))
+    st = [rng.integers(0, 999, n).astype(np.int32) for n in (P, D, D, D)]
+    want = o.commit(L, O, bp, bd, *st, *[np.zeros(n, np.int32) for n in (P, D, D)])
+    assert want[4] == 0
+    g = [dev(x.copy()) for x in st]
+    ctx.hx_commit(binding.to_device(dict(n=C, L_in=L, L_out=O)), dev(bp), dev(bd), *g)
+    ctx.hx_stream_status()
+    for got, w in zip(g, want[:4]):
+        assert np.array_equal(got.cpu().numpy(), w)
+
+
 # sweeps inside a workgroup's slice and over the whole graph: a workflow that fills a slice or does not fit one, more successors
 # than a node has slots, rows at the very end of the id array, an edge into another slice, nodes of no workflow, and
 # two graphs in a row (what the workgroups share has to be clear again)
