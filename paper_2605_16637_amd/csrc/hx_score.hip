@@ -575,14 +575,18 @@ __global__ __launch_bounds__(256) void hx_materialise_kernel(ScoreArgs a, PrepAr
         }
     }
 }
-// Up to SELECT_WAVE pairs in whole quads: a wavefront takes a call, eight 16-byte loads of it in flight per lane, and reduces it
-// without a barrier; the workgroup per call below spends most of a short row on its reduction.  Launches back to back, workgroup
-// and wavefront: 16384 calls x 8 x 8 14.9 -> 7.2 us, 4096 x 16 x 16 5.9 -> 3.8, 4096 x 64 x 64 12.3 -> 11.4 (5.9 TB/s),
-// 64 x 4 x 4 3.9 -> 3.4; longer rows leave too few wavefronts: 256 x 128 x 128 4.9 and 5.5, 512 x 256 x 256 21 and 27.
+// Up to SELECT_WAVE pairs in whole quads: a wavefront takes a call, U 16-byte loads of it in flight per lane, and reduces it
+// without a barrier; the workgroup per call below spends most of a short row on its reduction.  Launches back to back (us), workgroup
+// and wavefront, U = 1 up to a quad a lane, else 8: 16384 calls x 8 x 8 15.7 and 4.3, 4096 x 16 x 16 6.0 and 2.7, 64 x 4 x 4 3.1 and 2.4,
+// 64 x 64 x 64 3.5 and 2.9, 4096 x 64 x 64 12.8 and 11.8 (67 MB at 5.7 TB/s, more than a copy from memory reaches: just written, they lie in the
+// last-level cache).  (U = 8 for short rows too: the same quad eight times, 7.5 us for 16384 x 8 x 8, and 3.2 for 64 x 4 x 4, rows that share a
+// cache line.)  Longer rows are more turns of one wavefront, a chain of memory round trips that the workgroup splits: 64 calls x 80 x 100 4.0
+// and 3.7, 96 x 128 4.3 and 4.5, 256 x 128 6.3 and 8.5; 1024 calls x 65 x 64 4.2 and 4.4, x 80 x 100 6.7 and 6.0, x 128 x 128 12.6 and
+// 12.1; 4096 x 128 x 128 41 and 43.  At 4096 pairs the wavefront wins for any number of calls, at twice that within 11 % either way.
 constexpr int SELECT_WAVE = 4096;
+template <int U>
 __global__ __launch_bounds__(256) void hx_select_wave_kernel(ScoreArgs a)
 {
-    constexpr int U = 8;
     const int lane = threadIdx.x & (HX_WAVE - 1);
     const unsigned wave = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (blockDim.x / HX_WAVE) + threadIdx.x / HX_WAVE));
     const int n4 = (a.P * a.D) >> 2;
@@ -929,7 +933,8 @@ extern "C" int hx_select(hx_ctx *ctx, int32_t C, int32_t P, int32_t D, const flo
     const bool quads = ((long long)P * D & 3) == 0 && (reinterpret_cast<uintptr_t>(cost) & 15) == 0;
     if (quads && (long long)P * D <= SELECT_WAVE) {
         const int grid = C / 4 + (C % 4 != 0);
-        hx_select_wave_kernel<<<grid < most ? grid : most, 256, 0, stream>>>(a);
+        if (P * D <= 4 * HX_WAVE) hx_select_wave_kernel<1><<<grid < most ? grid : most, 256, 0, stream>>>(a);
+        else hx_select_wave_kernel<8><<<grid < most ? grid : most, 256, 0, stream>>>(a);
         return hx_check_launch(ctx, "hx_select_wave_kernel");
     }
     const int grid = C < most ? C : most;

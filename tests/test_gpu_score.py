@@ -447,10 +447,10 @@ def test_debug_validation_counts_bad_elements(ctx):
     assert not any(ctx.hx_validate_round(none, dict(pre, n=0), dict(dec, n=0), links).values())
 
 
-# the selection where a wavefront or a workgroup takes a call: rows of one quad, of a wavefront's eight quads a lane and one
-# more, the longest for a wavefront and the next; an array that begins off a 16-byte boundary; ties, rows without a pair
+# the selection where a wavefront or a workgroup takes a call: rows of one quad, of a wavefront's quad a lane and one more, of its
+# eight quads a lane and one more, the longest for a wavefront and the next; an array that begins off a 16-byte boundary; ties, rows without a pair
 @pytest.mark.parametrize("C", [1, 3, 130])
-@pytest.mark.parametrize("P,D", [(1, 4), (2, 2), (3, 5), (32, 64), (36, 57), (64, 64), (4, 1025), (65, 64)])
+@pytest.mark.parametrize("P,D", [(1, 4), (2, 2), (3, 5), (63, 4), (16, 16), (65, 4), (32, 64), (36, 57), (64, 64), (4, 1025), (65, 64)])
 @pytest.mark.parametrize("offset", [0, 1])
 def test_select_by_wavefronts_and_by_workgroups(ctx, C, P, D, offset):
     import torch
