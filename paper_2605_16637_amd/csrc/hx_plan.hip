@@ -89,23 +89,25 @@ __global__ __launch_bounds__(256) void hx_rank_count_kernel(const float *ratio, 
 // are compared with each other, more are sorted; should they outgrow the LDS, the queue is sorted a part at a time (what is not of the
 // bucket at the end) and every member's place looked up in each.
 // Bound: two round trips and the ordering of the cuts (7 us together), then the pass over the queue and the largest bucket,
-// some six times the others, by pairs.  Launches back to back, all pairs of calls / cuts / the sample sort below: 8192
-// calls 8.9 / 9.3 / -, 12000 14.0 / 12 to 16 / -, 16384 21.3 / 14 to 18 / -, 24000 - / 19 to 24 / 27 to 30, 32768 - / 34.0 / 33.4 (the
-// largest bucket differs from queue to queue).  Members among 16384 calls, by pairs and sorted: 500 21 and 22 us, 700 31 and 22, 1000 48 and
-// 28, 4000 461 and 46.  A queue whose dividers all lie above the other calls: 168 us of 10241 calls, 275 of 16384, 640 of 28672, the
+// some six times the others (it differs from queue to queue).  Launches back to back, random ratios, all pairs of calls / cuts / the sample
+// sort below: 10241 calls 13.3 / 12 (10 to 14) / -, 12000 15.1 / 12.7 (up to 14.5) / -, 16384 22.4 / 14.3 (up to 18.9) / -, 24000 - / 18.7 (up
+// to 25) / 23 to 35, 28000 - / 22.8 (up to 26.6) / 25 to 35.  Members of one bucket among 16384 calls, by pairs and sorted: 300 10.5 and -, 500 12.1
+// and 19, 700 17.0 and 19.7, 800 22.1 and 20.0, 1000 25 and 20, 4000 - and 43 (by pairs 64 members at a time, with two barriers each: 500
+// 16.0, 700 23).  A queue whose dividers all lie above the other calls: 168 us of 10241 calls, 275 of 16384, 640 of 28672, the
 // lookups, whose LDS reads lie anywhere, two thirds of it (members counted against the whole queue by pairs: 7 to 57 ms).
 // (Cuts compared as 32-bit words with the ties by index, four at a time: 1.5 us more; workgroups of 512 threads: 0.5
 // less on 2048 calls, 3 more on 16384.)
 constexpr int RANK_CUT = 28 * 1024;
 constexpr int RANK_CUTS = 255;                   // buckets 0 .. RANK_CUTS
 constexpr int RANK_MEMBERS = 4096;               // members of a bucket that LDS holds (a power of two)
-constexpr int RANK_BY_PAIRS = 576;               // members compared with each other
+constexpr int RANK_BY_PAIRS = 768;               // members compared with each other
+constexpr int RANK_GROUPS = 4;                   // of 64 members, in flight together
 constexpr int RANK_READ = 8;                     // calls a thread has in flight
 
 __global__ __launch_bounds__(RANK_THREADS) void hx_rank_cut_kernel(const float *ratio, int32_t *rank, int C)
 {
     __shared__ unsigned long long s_cut[RANK_CUTS + 1], s_key[RANK_MEMBERS], s_low, s_high;
-    __shared__ int s_place[RANK_CUTS + 1], s_higher, s_n, s_ahead[HX_WAVE];
+    __shared__ int s_place[RANK_CUTS + 1], s_higher, s_n, s_ahead[RANK_BY_PAIRS];
     const int tid = threadIdx.x, lane = tid & (HX_WAVE - 1), b = blockIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     constexpr int WAVES = RANK_THREADS / HX_WAVE;
@@ -116,7 +118,7 @@ __global__ __launch_bounds__(RANK_THREADS) void hx_rank_cut_kernel(const float *
         s_cut[tid] = tid < RANK_CUTS ? hx_rank_key64(hx_load_bits(ratio, c), c) : 0ull;
         s_place[tid] = 0;
     }
-    if (tid < HX_WAVE) s_ahead[tid] = 0;
+    for (int i = tid; i < RANK_BY_PAIRS; i += RANK_THREADS) s_ahead[i] = 0;
     if (tid == 0) { s_higher = 0; s_n = 0; s_low = 0ull; s_high = ~0ull; }
     unsigned bits[RANK_READ];                    // the first calls are on their way while the cuts are ordered
     auto load = [&](int base) {
@@ -166,21 +168,25 @@ __global__ __launch_bounds__(RANK_THREADS) void hx_rank_cut_kernel(const float *
     const int n = s_n;
     higher = s_higher;
     if (__builtin_expect(n <= RANK_BY_PAIRS, 1)) {
-        // 64 members at a time, a lane each, against a share of the bucket per wavefront
+        // every wavefront takes a share of the bucket and compares all members with it, RANK_GROUPS in each lane at a time
         const int share = (n + WAVES - 1) / WAVES, end = min((wave + 1) * share, n);
-        for (int m0 = 0; m0 < n; m0 += HX_WAVE) {
-            const unsigned long long mine = s_key[min(m0 + lane, n - 1)];
-            int ahead = 0;
+        for (int m0 = 0; m0 < n; m0 += RANK_GROUPS * HX_WAVE) {
+            unsigned long long mine[RANK_GROUPS];
+            int ahead[RANK_GROUPS];
+#pragma unroll
+            for (int g = 0; g < RANK_GROUPS; ++g) { mine[g] = s_key[min(m0 + g * HX_WAVE + lane, n - 1)]; ahead[g] = 0; }
 #pragma unroll 4
-            for (int k = wave * share; k < end; ++k) ahead += s_key[k] > mine;
-            if (ahead) atomicAdd(&s_ahead[lane], ahead);
-            __syncthreads();
-            if (wave == 0) {
-                if (m0 + lane < n) rank[0xffffffffu - (unsigned)(mine & 0xffffffffull)] = higher + s_ahead[lane];
-                s_ahead[lane] = 0;
+            for (int k = wave * share; k < end; ++k) {
+                const unsigned long long key = s_key[k];
+#pragma unroll
+                for (int g = 0; g < RANK_GROUPS; ++g) ahead[g] += key > mine[g];
             }
-            __syncthreads();
+#pragma unroll
+            for (int g = 0; g < RANK_GROUPS; ++g)
+                if (m0 + g * HX_WAVE + lane < n && ahead[g]) atomicAdd(&s_ahead[m0 + g * HX_WAVE + lane], ahead[g]);
         }
+        __syncthreads();
+        for (int i = tid; i < n; i += RANK_THREADS) rank[0xffffffffu - (unsigned)(s_key[i] & 0xffffffffull)] = higher + s_ahead[i];
         return;
     }
     const bool all = n <= RANK_MEMBERS;                      // the members gathered above are all there are

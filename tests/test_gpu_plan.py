@@ -138,7 +138,7 @@ def test_rank_time_of_one_bucket(ctx, C):
 
 # members of one bucket around what a workgroup counts by pairs, what it sorts at once and what it sorts in parts: 0, 1 or some
 # above all dividers, the others between the first two, below all or in one run
-@pytest.mark.parametrize("n", [1, 63, 575, 576, 577, 1023, 1024, 1025, 2047, 2049, 4095, 4096, 4097, 8200])
+@pytest.mark.parametrize("n", [1, 63, 65, 255, 257, 575, 767, 768, 769, 1023, 1024, 1025, 2047, 2049, 4095, 4096, 4097, 8200])
 @pytest.mark.parametrize("where", ["above", "between", "below"])
 def test_rank_with_a_bucket_of(ctx, n, where):
     import torch
