@@ -49,10 +49,8 @@ __device__ __forceinline__ bool hx_raise_tail(const AppendArgs &a, int u, float 
 // push the (new) rem and level of node v to its parent u; enqueue u if it grew.  The lanes of a
 // wavefront that enqueue at the same moment take their list slots with one atomic between them
 // (the list counter is a single address: one atomic per lane would serialise the whole sweep).
-// SCOPED: the list entry is written with a device-scope store (for the single-workgroup loop,
-// whose later steps read the list back).
-template <bool SCOPED>
-__device__ __forceinline__ void hx_push_parent_t(const AppendArgs &a, int u, float rem_v, int level_v)
+// The list entry is written with a device-scope store: later steps of the single-workgroup loop read the list back.
+__device__ __forceinline__ void hx_push_parent(const AppendArgs &a, int u, float rem_v, int level_v)
 {
     bool grew = hx_raise_tail(a, u, rem_v);
     int old = atomicMax(&a.level[u], level_v + 1);
@@ -66,9 +64,8 @@ __device__ __forceinline__ void hx_push_parent_t(const AppendArgs &a, int u, flo
         if (lane == leader) base = atomicAdd(&a.counters[a.cout], __popcll(m));
         base = __shfl(base, leader);
         if (want) {
-            const int slot = base + __popcll(m & ((1ull << lane) - 1ull));   // at most one entry per node and sweep:
-            if (SCOPED) __hip_atomic_store(&a.list_out[slot], u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            else a.list_out[slot] = u;                                        // never beyond cap_nodes
+            const int slot = base + __popcll(m & ((1ull << lane) - 1ull));   // at most one entry per node and sweep: never beyond cap_nodes
+            __hip_atomic_store(&a.list_out[slot], u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
 }
@@ -80,11 +77,6 @@ __device__ __forceinline__ void hx_enqueue(const AppendArgs &a, int u)
         const int slot = atomicAdd(&a.counters[a.cout], 1);
         a.list_out[slot] = u;
     }
-}
-
-__device__ __forceinline__ void hx_push_parent_scoped(const AppendArgs &a, int u, float rem_v, int level_v)
-{
-    hx_push_parent_t<true>(a, u, rem_v, level_v);
 }
 
 // Second phase of an append (a kernel boundary after init, so that a new node whose parent is

@@ -212,9 +212,9 @@ __global__ __launch_bounds__(CA_THREADS) void hx_commit_add_kernel(CommitArgs a,
 
 int commit_threads(int C) { return C <= CA_FEW_CALLS ? CA_FEW : CA_THREADS; }
 
-// Both steps in one workgroup, for rounds small enough that one compute unit adds them up as fast as a launch
-// takes: the additions go into the workgroup's LDS counters with LDS atomics, and the same threads then apply
-// the drains -- no global accumulators, one launch instead of two.  Same integer results.
+// Additions and drains in one workgroup, for rounds that one compute unit adds up sooner than several have met: the
+// additions go into the workgroup's LDS counters, and the same threads then apply the drains -- no global accumulators and
+// no ticket.  Same integer results.
 constexpr int COMMIT_ONE_THREADS = 1024;
 // Rounds of at most this many calls are committed by the one-workgroup kernel: no device atomics and their answers, but the
 // lanes of all calls meet in one compute unit's LDS.  One workgroup and several (us; placements spread, all on three

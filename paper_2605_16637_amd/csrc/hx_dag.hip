@@ -68,9 +68,9 @@ void hx_cp_local_kernel(CpArgs a, int wpb)
 
 // The same pass with the standalone node cost worked out while staging instead of being read:
 // one launch for what hx_node_cost_kernel and hx_cp_local_kernel do one after the other.  The
-// evaluation of 64 class pairs per node wants more registers than seven blocks per compute unit
-// leave; the launch is meant for the graphs of a scheduling round (tens of thousands of nodes,
-// spread over all compute units), where the latency of a launch counts and residency does not.
+// staging with the cost's sums in flight takes 102 registers, four wavefronts a SIMD; the launch is
+// meant for the graphs of a scheduling round (tens of thousands of nodes, spread over all compute
+// units), where the latency of a launch counts and residency does not.
 __global__ __launch_bounds__(CP_THREADS)
 void hx_cp_cost_kernel(CpArgs a, NodeCostArgs nc, int wpb)
 {
@@ -547,7 +547,7 @@ __global__ __launch_bounds__(1024) void hx_append_tail_kernel(AppendArgs a, int3
             if (me.y >= 0) hx_raise_max_f32(&a.horizon[me.y], r);
             for (int e = a.prow[u]; e < a.prow[u + 1]; ++e) {
                 int q = a.pcol[e];
-                if (q >= 0) hx_push_parent_scoped(a, q, r, lv);
+                if (q >= 0) hx_push_parent(a, q, r, lv);
             }
         }
         __threadfence();
