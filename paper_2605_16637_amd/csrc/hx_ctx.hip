@@ -88,7 +88,7 @@ __device__ __forceinline__ unsigned long long hx_wave_sum_i31(int x)
 // CA_SINGLY calls, which meet nobody else's: one call 2.83 us instead of 2.70, 32 on one instance 2.93 instead of 2.79 (128 2.96 instead of
 // 3.04).  False: a pair or a length out of range.
 constexpr int CA_SINGLY = HX_WAVE;
-__device__ __forceinline__ bool hx_commit_call(const CommitArgs &a, unsigned long long *acc, int p, int d, int L, int O)
+__device__ __forceinline__ bool hx_commit_call(const CommitArgs &a, bool singly, unsigned long long *acc, int p, int d, int L, int O)
 {
     bool valid = p >= 0 && d >= 0;                          // otherwise the call stays queued
     const bool bad = valid && (p >= a.P || d >= a.D || L < 0 || O < 0);
@@ -96,8 +96,8 @@ __device__ __forceinline__ bool hx_commit_call(const CommitArgs &a, unsigned lon
     const unsigned long long m = __builtin_amdgcn_ballot_w64(valid);
     if (m == 0) return !bad;
     const int lead = __builtin_ctzll(m), lane = threadIdx.x & (HX_WAVE - 1);
-    const bool one_p = a.C > CA_SINGLY && __builtin_amdgcn_ballot_w64(valid && p != __builtin_amdgcn_readlane(p, lead)) == 0;
-    const bool one_d = a.C > CA_SINGLY && __builtin_amdgcn_ballot_w64(valid && d != __builtin_amdgcn_readlane(d, lead)) == 0;
+    const bool one_p = !singly && __builtin_amdgcn_ballot_w64(valid && p != __builtin_amdgcn_readlane(p, lead)) == 0;
+    const bool one_d = !singly && __builtin_amdgcn_ballot_w64(valid && d != __builtin_amdgcn_readlane(d, lead)) == 0;
     const unsigned long long all_L = one_p || one_d ? hx_wave_sum_i31(valid ? L : 0) : 0ull;
     if (one_p ? lane == lead : valid) atomicAdd(&acc[p], one_p ? all_L : (unsigned long long)L);
     if (one_d) {
@@ -177,7 +177,7 @@ __global__ __launch_bounds__(CA_THREADS) void hx_commit_add_kernel(CommitArgs a,
         const long long c = at + threadIdx.x;
         int p = -1, d = -1, L = 0, O = 0;
         if (c < a.C) { p = a.best_p[c]; d = a.best_d[c]; L = a.L_in[c]; O = a.L_out[c]; }
-        if (!hx_commit_call(a, s_acc, p, d, L, O)) bad = true;
+        if (!hx_commit_call(a, false, s_acc, p, d, L, O)) bad = true;
     }
     if (bad) hx_raise(a.status, HX_ERR_INDEX);
     __syncthreads();
@@ -236,7 +236,7 @@ __global__ __launch_bounds__(COMMIT_ONE_THREADS) void hx_commit_one_kernel(Commi
         if (c < a.C) { p = a.best_p[c]; d = a.best_d[c]; L = a.L_in[c]; O = a.L_out[c]; }
         if (rt.ratio && c < a.C)
             hx_projected_ratio(rt.node, rt.wf, rt.elapsed, rt.tail, rt.horizon, rt.n_nodes, rt.n_wf, c, rt.best_cost[c], a.status, rt.ratio);
-        if (!hx_commit_call(a, s_acc, p, d, L, O)) bad = true;
+        if (!hx_commit_call(a, a.C <= CA_SINGLY, s_acc, p, d, L, O)) bad = true;
     }
     if (bad) hx_raise(a.status, HX_ERR_INDEX);
     __syncthreads();
