@@ -64,24 +64,6 @@ __device__ __forceinline__ int hx_add_sat_drain(int cur, unsigned long long add,
     return left < 0 ? 0 : (left > 2147483647LL ? 2147483647 : (int)left);
 }
 
-// sum over the wavefront; all lanes take part, all have the result
-__device__ __forceinline__ unsigned hx_wave_sum(unsigned x)
-{
-    x += (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false);      // row_shr 1, 2, 4, 8
-    x += (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false);
-    x += (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false);
-    x += (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false);
-    x += (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false);      // row_bcast 15, 31
-    x += (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false);
-    return (unsigned)__builtin_amdgcn_readlane((int)x, HX_WAVE - 1);
-}
-
-// of values below 2^31, in 64 bits: by halves, 64 of which fit 32 bits
-__device__ __forceinline__ unsigned long long hx_wave_sum_i31(int x)
-{
-    return (unsigned long long)hx_wave_sum((unsigned)x & 0xffffu) + ((unsigned long long)hx_wave_sum((unsigned)x >> 16) << 16);
-}
-
 // One call a lane into the workgroup's counters, by LDS atomics; all lanes of the wavefront take part.  Lanes that meet on a
 // counter are serialised there, and scored on one snapshot most calls of a round choose the same instance: where all of
 // a wavefront do, one lane adds their sum (16384 calls on 256 + 256 as part of a round 20.6 -> 18.9 us).  Not in a round of

@@ -278,6 +278,9 @@ struct TlOut {
     int *sorted;     // [D][nt] the n occupancies in increasing order
     float *G;        // [D][HX_TAB] first-room table
     int *meta;       // [D][8] what the scoring kernel reads first of an instance: n, m (+flag), capacity, decode terms c1, c2, kB
+    // for the search of the best alone
+    int *least;      // [D][nt] least occupancy of an entry and those before it
+    int *step;       // [2][D][4] what that leaves free at eight entries, in increasing order, and the time of the entry after each (hx_step_word)
 };
 
 // Workgroup d: everything the scoring kernel needs of instance d -- its timeline, built in LDS; the timeline's
@@ -803,6 +806,348 @@ __global__ __launch_bounds__(64) void hx_decode_finish_kernel(DecodeFinishArgs a
     a.best_d[c] = d; a.best_start[c] = S; a.best_cost[c] = v;
     if (a.ratio)
         hx_projected_ratio(a.node, a.wf, a.elapsed, a.tail, a.horizon, a.n_nodes, a.n_wf, c, v, a.status, a.ratio);
+}
+
+// ---- the best instance of every call, where nobody asks for the pairs ---------------------
+//
+// A pair costs its start plus its decode time, and no start is before the instance's first moment with room for the call, nor that
+// before now.  So the decode time alone bounds the cost from below, and an instance whose bound is beyond the best cost found so
+// far need not be looked at.  A wavefront takes a call, its lanes the instances, and looks at one instance after the other in
+// the order of their bounds; that instance's timeline is then read by all lanes, an entry each.  After DB_CLOSER instances
+// every bound is made a closer one, from what eight steps say of the room there has been (hx_step_word); after DB_EXACT those that
+// still matter the closest, the first moment with room itself (a bisection a lane); after DB_ALL -- room in pieces that are all
+// too short -- every lane searches the instances it has left for itself.
+// Of 8192 free calls on 256 instances with 113 to 137 entries each one in 1.13 instances is looked at with the steps, 3.3 by the decode
+// time alone; where every instance is full for ten seconds 56 and 90, and 3 with the bisection.
+//
+// What bounds it: instruction issue, some 200 vector and 200 scalar instructions a call, and the chain of a call's memory round trips,
+// 2.9 and 1.9 us for the first and the second call of a wavefront.  That pass (as many calls locked as free): the occupancies
+// 15.6 -> 6.7 us, the search 29.4 -> 13.8 and no third kernel of 4.8, against all pairs through tables of first moments with room;
+// 500 calls on 1024 instances 63 -> 22, 500 on 300 with lists of 250 that are full for ten seconds 108 -> 53.  Slower where rooms
+// come in pieces that are shorter than any decode time: 2000 calls on 64 such instances 24 -> 44, 300 on 1024 86 -> 180.
+
+// Up to some moment no more than `room` tokens have been free, and `time_bits` is when that may change: as the upper halves of two
+// floats, the first as its complement.  A call that needs more than the room has no start before that time; by halves, as far as the two
+// differ there, no start before a time that is not later.  Such a call's word, without a time and with the lower half set, is below this one.
+__device__ __forceinline__ unsigned hx_step_word(unsigned room, int time_bits)
+{
+    return ~(__float_as_uint((float)room) | 0xffffu) | ((unsigned)time_bits >> 16);
+}
+
+// Workgroup d: the occupancy of instance d over time, an entry an event that lies ahead; those that lie behind (most sequences
+// have begun) only add to what is held now.  Several events of one moment are several entries, all with what is held
+// after the last.  No running sum: an event adds up those not after it while it counts those before it.
+// Bound: two memory round trips (the record, the intervals) and the comparisons, n^2 of them on one compute unit.
+constexpr int DO_THREADS = 512;
+constexpr int DO_EVENTS = 2 * HX_MAX_INTERVALS + 42;      // and a filler for the shares of several lanes
+static_assert(HX_MAX_INTERVALS <= DO_THREADS, "an interval a thread");
+__global__ __launch_bounds__(DO_THREADS) void hx_decode_occupancy_kernel(DecodeArgs a, TlOut o, int nt)
+{
+    __shared__ __align__(16) u64 s_key[DO_EVENTS];         // time, event: unique
+    __shared__ __align__(16) int s_delta[DO_EVENTS];
+    __shared__ __align__(16) int2 s_e[2 * HX_MAX_INTERVALS + 1];
+    __shared__ int s_least[2 * HX_MAX_INTERVALS + 1];
+    __shared__ u64 s_now, s_all;                           // tokens held now; now or later
+    __shared__ int s_n;
+    const int tid = threadIdx.x, lane = tid & (HX_WAVE - 1), d = blockIdx.x;
+    // the intervals are asked for before it is known how many there are
+    const size_t at = (size_t)d * a.stride + tid;
+    const bool room = tid < a.stride;
+    const float st = room ? a.iv_start[at] : 0.0f, en = room ? a.iv_end[at] : 0.0f;
+    const int tk = room ? a.iv_tok[at] : 0;
+    int cnt = a.iv_count[d];
+    const float flops = a.d_flops[d], hbm = a.d_hbm[d];
+    const int used = a.d_used[d], batch = a.d_batch[d], cap = a.d_cap[d];
+    for (int i = tid; i < DO_EVENTS; i += DO_THREADS) { s_key[i] = ~0ull; s_delta[i] = 0; }
+    if (tid == 0) { s_now = 0; s_all = 0; s_n = 0; }
+    __syncthreads();
+    if (cnt < 0 || cnt > a.stride) {
+        if (tid == 0) hx_raise(a.status, HX_ERR_INDEX);
+        cnt = cnt < 0 ? 0 : a.stride;
+    }
+    // anything else (NaN times included) holds nothing, and what has ended holds nothing any more
+    const bool holds = tid < cnt && st < en && tk > 0 && en > 0.0f;
+    const bool later = holds && st > 0.0f;
+    const u64 m_end = __builtin_amdgcn_ballot_w64(holds), m_start = __builtin_amdgcn_ballot_w64(later);
+    if (m_end) {
+        const u64 sum_now = hx_wave_sum_i31(holds && !later ? tk : 0), sum_all = hx_wave_sum_i31(holds ? tk : 0);
+        int first = 0;
+        if (lane == 0) {
+            first = atomicAdd(&s_n, __popcll(m_end) + __popcll(m_start));
+            atomicAdd(&s_now, sum_now); atomicAdd(&s_all, sum_all);
+        }
+        first = __builtin_amdgcn_readfirstlane(first);
+        const u64 below = (1ull << lane) - 1ull;
+        const int i_end = first + __popcll(m_end & below), i_start = first + __popcll(m_end) + __popcll(m_start & below);
+        if (holds) { s_key[i_end] = ((u64)__float_as_uint(en) << 32) | (unsigned)i_end; s_delta[i_end] = -tk; }
+        if (later) { s_key[i_start] = ((u64)__float_as_uint(st) << 32) | (unsigned)i_start; s_delta[i_start] = tk; }
+    }
+    __syncthreads();
+    const int n = s_n;
+    const u64 held = s_now;
+    auto clamped = [&](long long occ) {
+        if (occ > (long long)INT_MAX) { hx_raise(a.status, HX_ERR_OVERFLOW); occ = INT_MAX; }
+        return (int)occ;
+    };
+    if (tid == 0) s_e[0] = make_int2(0, clamped((long long)held));
+    if (s_all <= (u64)INT_MAX) {                           // every occupancy fits 32 bits
+        const int parts = hx_count_parts(n, DO_THREADS);
+        const int share = ((n + parts - 1) / parts + 7) & ~7;
+        for (int i = tid / parts; i < n; i += DO_THREADS / parts) {
+            const u64 mine = s_key[i];
+            const unsigned t = (unsigned)(mine >> 32);
+            int place = 0, sum = 0;
+            const int j_lo = (tid & (parts - 1)) * share;
+            for (int j = j_lo; j < j_lo + share; j += 8) { // (past the last event the filler: never, nothing)
+                u64 key[8];
+                int delta[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) { key[u] = s_key[j + u]; delta[u] = s_delta[j + u]; }
+#pragma unroll
+                for (int u = 0; u < 8; ++u) { place += key[u] < mine; sum += (unsigned)(key[u] >> 32) <= t ? delta[u] : 0; }
+            }
+            place = hx_parts_sum(place, parts); sum = hx_parts_sum(sum, parts);
+            if ((tid & (parts - 1)) == 0) s_e[place + 1] = make_int2((int)t, (int)held + sum);
+        }
+    } else {
+        for (int i = tid; i < n; i += DO_THREADS) {
+            const u64 mine = s_key[i];
+            const unsigned t = (unsigned)(mine >> 32);
+            int place = 0;
+            long long sum = 0;
+            for (int j = 0; j < n; ++j) { place += s_key[j] < mine; sum += (unsigned)(s_key[j] >> 32) <= t ? s_delta[j] : 0; }
+            s_e[place + 1] = make_int2((int)t, clamped((long long)held + sum));
+        }
+    }
+    __syncthreads();
+    const int n_e = n + 1;
+    int2 *const e = o.e + (size_t)d * nt;
+    for (int i = tid; i < hx_tl_len(n_e); i += DO_THREADS) e[i] = i < n_e ? s_e[i] : make_int2(0x7f800000, 0);
+    if (tid < HX_WAVE) {
+        const int per = (n_e + HX_WAVE - 1) / HX_WAVE, lo = min(tid * per, n_e), hi = min(lo + per, n_e);
+        int least = INT_MAX;
+        for (int i = lo; i < hi; ++i) least = min(least, s_e[i].y);
+#pragma unroll
+        for (int off = 1; off < HX_WAVE; off <<= 1) {
+            const int up = __shfl_up(least, off);
+            if (tid >= off) least = min(least, up);
+        }
+        int run = __shfl_up(least, 1);
+        if (tid == 0) run = INT_MAX;
+        for (int i = lo; i < hi; ++i) { run = min(run, s_e[i].y); s_least[i] = run; }
+        hx_wave_sync();
+        for (int i = tid; i < n_e; i += HX_WAVE) o.least[(size_t)d * nt + i] = s_least[i];
+        if (tid < 8) {
+            const int i = tid * n / 8;
+            o.step[((tid >> 2) * a.D + d) * 4 + (tid & 3)] = n > 0 ? hx_step_word((unsigned)max((long long)cap - s_least[i], 0ll), s_e[i + 1].x) : 0;
+        }
+    }
+    if (tid == DO_THREADS - 1) {
+        const HxDecF x = hx_decode_terms(a.m, used, batch, 0, 1.0f / flops, 1.0f / hbm);
+        int4 *meta = (int4 *)(o.meta + 8 * d);
+        meta[0] = make_int4(n_e, 0, cap, __float_as_int(x.c1));
+        meta[1] = make_int4(__float_as_int(x.c2), __float_as_int(x.kB), 0, 0);
+    }
+}
+
+// The earliest start on one timeline, by a wavefront: an entry a lane, 64 at a time.  A run of entries with room begins where the one
+// before it has none, and is a start if the run's end, the next entry without room, is far enough: the comparisons of
+// hx_earliest_start, which tests a run at each of its entries, at the last of them, whose successor is the latest.
+// e: nt entries may be read, n of them count; next: the lane's of the first 64.  Uniform in everything but the lane.
+__device__ __forceinline__ float hx_earliest_start_wave(const int2 *__restrict__ e, int nt, int2 next, int n, int thr, float T, int lane)
+{
+    float rs = INFINITY;                                   // where the run that is open begins
+    for (int i0 = 0; i0 < n; i0 += HX_WAVE) {
+        const int2 x = next;
+        next = e[min(i0 + HX_WAVE + lane, nt - 1)];
+        const bool in = i0 + lane < n;
+        const float t = in ? __int_as_float(x.x) : INFINITY;      // behind the last entry: never, which ends every run
+        const u64 room = __builtin_amdgcn_ballot_w64(in && x.y <= thr);
+        const bool open = rs < INFINITY;
+        if (open && room != ~0ull) {
+            if (hx_lane_value(t, __builtin_ctzll(~room)) >= rs + T) return rs;
+            rs = INFINITY;
+        }
+        const u64 starts = room & ~(room << 1) & ~(open ? 1ull : 0ull);
+        if (starts == 0) continue;
+        const u64 ends = ~room >> lane;
+        const int len = ends ? __builtin_ctzll(ends) : HX_WAVE;
+        const float t_end = __shfl(t, lane + len);         // (a run up to the last lane: not looked at)
+        const u64 hits = __builtin_amdgcn_ballot_w64(((starts >> lane) & 1) != 0 && lane + len < HX_WAVE && t_end >= t + T);
+        if (hits) return hx_lane_value(t, __builtin_ctzll(hits));
+        if (room >> (HX_WAVE - 1)) rs = hx_lane_value(t, HX_WAVE - 1 - __builtin_clzll(starts));
+    }
+    return rs;                                             // it lasts
+}
+
+constexpr int DB_THREADS = 256;
+constexpr int DB_PER_CU = 6;               // workgroups a compute unit at most: 4 16.0 us, 5 14.7, 6 13.8, 7 14.4, 8 14.8 (the last ones wait for a place)
+constexpr int DB_CLOSER = 1, DB_EXACT = 6, DB_ALL = 16;
+// K: instances a lane
+template <int K>
+__global__ __launch_bounds__(DB_THREADS) void hx_decode_best_kernel(DecodeArgs a, DecodeFinishArgs f, TlOut o, int nt)
+{
+    const int lane = threadIdx.x & (HX_WAVE - 1);
+    const int wave = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (DB_THREADS / HX_WAVE) + threadIdx.x / HX_WAVE));
+    const int n_waves = gridDim.x * (DB_THREADS / HX_WAVE);
+    // the lane's instances' decode terms and capacities: read from here where they are wanted, they cost no registers
+    __shared__ __align__(16) int4 s_inst[K * HX_WAVE];
+    for (int d = threadIdx.x; d < K * HX_WAVE; d += DB_THREADS) {
+        const int4 *meta = (const int4 *)(o.meta + 8 * min(d, a.D - 1));
+        const int4 x = meta[0], y = meta[1];
+        s_inst[d] = make_int4(x.w, y.x, y.y, d < a.D ? x.z : -1);      // no instance: nothing fits
+    }
+    __shared__ __align__(16) uint4 s_step[2][K * HX_WAVE];
+    for (int i = threadIdx.x; i < 2 * K * HX_WAVE; i += DB_THREADS)
+        s_step[i / (K * HX_WAVE)][i % (K * HX_WAVE)] = ((const uint4 *)o.step)[i / (K * HX_WAVE) * a.D + min(i % (K * HX_WAVE), a.D - 1)];
+    // What the next call says of itself travels while this one is placed: a lane each for L, O, lock, node, workflow and elapsed, and of the
+    // results for instance, start, cost and ratio, so that either is one instruction.
+    const int32_t *const none = a.L_in;                    // (of what there is not; not used)
+    const int32_t *in = lane == 0 ? a.L_in : lane == 1 ? a.L_out : none;
+    if (lane == 2 && a.lock) in = a.lock;
+    if (f.ratio) in = lane == 3 ? f.node : lane == 4 ? f.wf : lane == 5 ? (const int32_t *)f.elapsed : in;
+    int32_t *const out = lane == 0 ? f.best_d : lane == 1 ? (int32_t *)f.best_start : lane == 2 ? (int32_t *)f.best_cost : (int32_t *)f.ratio;
+    const bool writes = lane < (f.ratio ? 4 : 3);
+    int next = wave < a.Q ? in[wave] : 0;
+    __syncthreads();
+    for (int c = wave; c < a.Q; c += n_waves) {
+        const int L = __builtin_amdgcn_readlane(next, 0), O = __builtin_amdgcn_readlane(next, 1);
+        const int lk = a.lock ? __builtin_amdgcn_readlane(next, 2) : -1;
+        const int nd = __builtin_amdgcn_readlane(next, 3), w = __builtin_amdgcn_readlane(next, 4);
+        const float el = hx_lane_value(__int_as_float(next), 5);
+        const bool ratio_ok = f.ratio && nd >= 0 && nd < f.n_nodes && w >= 0 && w < f.n_wf;
+        float graph = 1.0f;                                // lane 0: the tail of its node, lane 1: the horizon of its workflow
+        if (ratio_ok) graph = *(lane == 0 ? f.tail + nd : f.horizon + w);
+        if (c + n_waves < a.Q) next = in[c + n_waves];
+        const bool ok = L >= 0 && O >= 0 && lk >= -1 && lk < a.D;
+        const HxCallF cf = hx_call_terms(a.m, ok ? L : 0, ok ? O : 0);
+        const long long need = (long long)L + (long long)O;
+        float best = INFINITY, best_S = INFINITY;
+        int best_d = -1;
+        auto threshold = [&](int cap_d) {                  // tokens the call may find held, < 0: never fits
+            const long long left = (long long)cap_d - need;
+            return left < 0 ? -1 : (left > (long long)INT_MAX ? INT_MAX : (int)left);
+        };
+        auto time_on = [&](const int4 &x) { return hx_decode_time(cf, __int_as_float(x.x), __int_as_float(x.y), __int_as_float(x.z)); };
+        auto look = [&](int d) {
+            const int2 *e = o.e + (size_t)d * nt;
+            const int2 first = e[min(lane, nt - 1)];       // asked for beside the record
+            const HxInst it = hx_inst_load(o, d);
+            const float T = hx_decode_time(cf, it.c1, it.c2, it.kB);
+            const int thr = threshold(it.cap);
+            const float S = hx_earliest_start_wave(e, nt, first, it.n, thr, T, lane);
+            const float v = S + T;                         // +inf when there is no start
+            if (v < best || (v == best && d < best_d)) { best = v; best_S = S; best_d = d; }
+        };
+        if (ok && lk >= 0) look(lk);
+        else if (ok) {
+            float bound[K];
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                const int4 x = s_inst[k * HX_WAVE + lane];
+                bound[k] = hx_fits(L, O, x.w) ? time_on(x) : INFINITY;
+            }
+            for (int looked = 1;; ++looked) {
+                float low = bound[0];
+#pragma unroll
+                for (int k = 1; k < K; ++k) low = fminf(low, bound[k]);
+                low = hx_wave_min(low);
+                if (!(low <= best) || !(low < INFINITY)) break;
+                int d = INT_MAX;
+#pragma unroll
+                for (int k = K - 1; k >= 0; --k) {
+                    const u64 b = __builtin_amdgcn_ballot_w64(bound[k] == low);
+                    d = b ? k * HX_WAVE + __builtin_ctzll(b) : d;
+                }
+                if (low == best && d > best_d) break;      // it could only be as good, and is not the lower instance
+                look(d);
+#pragma unroll
+                for (int k = 0; k < K; ++k) bound[k] = k * HX_WAVE + lane == d ? INFINITY : bound[k];
+                if (looked == DB_CLOSER) {
+                    // a closer bound: while the least that has been held leaves no room there is no start
+                    const unsigned me = hx_step_word((unsigned)L + (unsigned)O, 0) | 0xffffu;
+#pragma unroll
+                    for (int k = 0; k < K; ++k) {
+                        const uint4 x = s_step[0][k * HX_WAVE + lane], y = s_step[1][k * HX_WAVE + lane];
+                        unsigned t = me < x.x ? x.x : 0u;
+                        t = me < x.y ? x.y : t; t = me < x.z ? x.z : t; t = me < x.w ? x.w : t;
+                        t = me < y.x ? y.x : t; t = me < y.y ? y.y : t; t = me < y.z ? y.z : t; t = me < y.w ? y.w : t;
+                        bound[k] = __uint_as_float(t << 16) + bound[k];
+                    }
+                } else if (looked == DB_EXACT) {
+                    // the closest, where the other one is not beyond the best: the instance's first entry with room
+                    int lo[K], hi[K];
+                    bool any = false;
+#pragma unroll
+                    for (int k = 0; k < K; ++k) {
+                        const bool on = bound[k] <= best && bound[k] < INFINITY;
+                        lo[k] = 0;
+                        hi[k] = on ? o.meta[8 * (k * HX_WAVE + lane)] - 1 : 0;      // (the last entry has room: everything has ended)
+                        any = any || on;
+                    }
+                    if (__builtin_amdgcn_ballot_w64(any) == 0) break;
+                    for (;;) {
+                        bool going = false;
+#pragma unroll
+                        for (int k = 0; k < K; ++k) {
+                            if (lo[k] >= hi[k]) continue;
+                            const int mid = (lo[k] + hi[k]) >> 1;
+                            if (o.least[(unsigned)(k * HX_WAVE + lane) * (unsigned)nt + mid] <= threshold(s_inst[k * HX_WAVE + lane].w)) hi[k] = mid;
+                            else lo[k] = mid + 1;
+                            going = going || lo[k] < hi[k];
+                        }
+                        if (__builtin_amdgcn_ballot_w64(going) == 0) break;
+                    }
+#pragma unroll
+                    for (int k = 0; k < K; ++k)
+                        if (lo[k] > 0)
+                            bound[k] = __int_as_float(o.e[(unsigned)(k * HX_WAVE + lane) * (unsigned)nt + lo[k]].x) + time_on(s_inst[k * HX_WAVE + lane]);
+                } else if (looked == DB_ALL) {
+                    float v = INFINITY, S = INFINITY;
+                    int at = INT_MAX;
+#pragma unroll 1
+                    for (int d0 = 0; d0 < a.D; d0 += HX_WAVE) {
+                        float b = INFINITY;
+#pragma unroll
+                        for (int k = 0; k < K; ++k) b = k * HX_WAVE == d0 ? bound[k] : b;
+                        const bool on = b <= best && b < INFINITY;
+                        // (the comparisons of hx_earliest_start)
+                        const int dl = min(d0 + lane, a.D - 1);
+                        const int4 x = s_inst[d0 + lane];
+                        const int thr = threshold(x.w), n = on ? o.meta[8 * dl] : 0;
+                        const float T = time_on(x);
+                        const int4 *e = (const int4 *)(o.e + (size_t)dl * nt);
+                        float rs = INFINITY, got = INFINITY;
+                        int4 q = e[0];
+                        for (int i = 0; __builtin_amdgcn_ballot_w64(i < n && !(got < INFINITY)) != 0; i += 2) {
+                            const int4 next = e[i < n ? (i >> 1) + 1 : 0];
+                            const float before = got;
+                            rs = q.y <= thr ? fminf(rs, __int_as_float(q.x)) : INFINITY;
+                            got = fminf(got, __int_as_float(q.z) >= rs + T ? rs : INFINITY);
+                            rs = q.w <= thr ? fminf(rs, __int_as_float(q.z)) : INFINITY;
+                            got = fminf(got, __int_as_float(next.x) >= rs + T ? rs : INFINITY);
+                            got = i < n ? got : before;
+                            q = next;
+                        }
+                        if (on && got + T < v) { v = got + T; S = got; at = dl; }
+                    }
+                    const float all = hx_wave_min(v);
+                    const int d_all = hx_wave_min(v == all && all < INFINITY ? at : INT_MAX);
+                    if (d_all != INT_MAX && (all < best || (all == best && d_all < best_d))) {
+                        best = all; best_d = d_all;
+                        best_S = hx_lane_value(S, d_all & (HX_WAVE - 1));
+                    }
+                    break;
+                }
+            }
+        }
+        if (!ok || (f.ratio && !ratio_ok)) {
+            if (lane == 0) hx_raise(a.status, HX_ERR_INDEX);
+        }
+        const int ratio = (int)hx_ratio_bits(el, best, hx_lane_value(graph, 0), hx_lane_value(graph, 1), ratio_ok);
+        const int result = lane == 0 ? best_d : lane == 1 ? __float_as_int(best_S) : lane == 2 ? __float_as_int(best) : ratio;
+        if (writes) out[c] = result;
+    }
 }
 
 // ---- recomputing greedy of the decode stage, one workgroup -----------------------------
@@ -1453,11 +1798,13 @@ extern "C" int hx_decode_score(hx_ctx *ctx, const hx_model *model, const hx_call
     HX_REQUIRE(ctx, guard.ok, HX_ERR_DEVICE, "cannot select device %d", ctx->device);
     hipStream_t stream = (hipStream_t)stream_;
     const int ne = 2 * iv->stride + 1, nt = hx_tl_len(ne);
+    // Without the pairs' matrices only the best instance of a call is wanted, which few pairs decide.
+    const bool pairs = start || cost;
     // Groups of instances: enough workgroups (tiles of 256 calls x groups) to fill the chip several times over,
     // at most 64 groups (the finish kernel reads one partial result per group and call).
     const int tiles = (Q + DS_THREADS - 1) / DS_THREADS;
     int n_groups = 0, gd = 1;
-    if (D > 0) {
+    if (D > 0 && pairs) {
         n_groups = (8 * ctx->num_cu + tiles - 1) / tiles;
         if (n_groups > 64) n_groups = 64;
         if (n_groups > D) n_groups = D;
@@ -1466,9 +1813,10 @@ extern "C" int hx_decode_score(hx_ctx *ctx, const hx_model *model, const hx_call
     }
     const int per = D > 0 ? (Q + D - 1) / D : Q;
     // words of scratch per pass: the free list (D slices of `per` places) and three partial results per group and call
-    const size_t part_need = (size_t)(D > 0 ? D : 1) * per + 3 * (size_t)(n_groups > 0 ? n_groups : 1) * Q;
+    const size_t part_need = pairs && D > 0 ? (size_t)D * per + 3 * (size_t)n_groups * Q : 0;
     const size_t tl_need = (size_t)(D > 0 ? D : 1) * nt;
-    if (part_need > ctx->dpart_cap || tl_need > ctx->dtl_cap || D > ctx->dtab_cap) {
+    const int tab_need = pairs ? D : 0;
+    if (part_need > ctx->dpart_cap || tl_need > ctx->dtl_cap || tab_need > ctx->dtab_cap) {
         // grown, never shrunk; work queued on the old blocks has to finish before they go
         HX_HIP(ctx, hipDeviceSynchronize());
         if (part_need > ctx->dpart_cap) {
@@ -1484,7 +1832,7 @@ extern "C" int hx_decode_score(hx_ctx *ctx, const hx_model *model, const hx_call
             HX_HIP(ctx, hipMalloc((void **)&ctx->d_dtl, tl_need * 24 + (2 + 8) * (size_t)HX_MAX_INSTANCES * sizeof(int) + 64));
             ctx->dtl_cap = tl_need;
         }
-        if (D > ctx->dtab_cap) {
+        if (tab_need > ctx->dtab_cap) {
             if (ctx->d_dtab) { HX_HIP(ctx, hipFree(ctx->d_dtab)); ctx->d_dtab = nullptr; ctx->dtab_cap = 0; }
             const int want = D < 64 ? 64 : D;
             HX_HIP(ctx, hipMalloc((void **)&ctx->d_dtab, (size_t)want * HX_TAB * sizeof(float)));
@@ -1501,14 +1849,21 @@ extern "C" int hx_decode_score(hx_ctx *ctx, const hx_model *model, const hx_call
         o.n = (int *)p;         p += (size_t)HX_MAX_INSTANCES * sizeof(int);
         n_free = (int32_t *)p;  p += (size_t)HX_MAX_INSTANCES * sizeof(int);
         o.meta = (int *)p;      p += 8 * (size_t)HX_MAX_INSTANCES * sizeof(int);
-        o.sorted = (int *)p;    p += cap * 4;
-        o.seg = (int *)p;       p += cap * 4;
+        o.sorted = (int *)p;    o.least = o.sorted;    p += cap * 4;
+        o.seg = (int *)p;       o.step = o.seg;    p += cap * 4;
         o.G = ctx->d_dtab;
     }
     int32_t *free_c = ctx->d_dpart;
-    float *part_cost = (float *)(ctx->d_dpart + (size_t)(D > 0 ? D : 1) * per);
-    float *part_start = part_cost + (size_t)(n_groups > 0 ? n_groups : 1) * Q;
-    int32_t *part_d = (int32_t *)(part_start + (size_t)(n_groups > 0 ? n_groups : 1) * Q);
+    float *part_cost = (float *)(ctx->d_dpart + (size_t)D * per);
+    float *part_start = part_cost + (size_t)n_groups * Q;
+    int32_t *part_d = (int32_t *)(part_start + (size_t)n_groups * Q);
+    DecodeFinishArgs f{};
+    f.Q = Q; f.D = D; f.n_groups = n_groups;
+    f.L_in = queue->L_in; f.L_out = queue->L_out; f.lock = lock;
+    f.part_cost = part_cost; f.part_start = part_start; f.part_d = part_d;
+    f.node = queue->node; f.wf = queue->wf; f.elapsed = queue->elapsed; f.tail = tail; f.horizon = horizon;
+    f.n_nodes = n_nodes; f.n_wf = n_wf;
+    f.best_d = best_d; f.best_start = best_start; f.best_cost = best_cost; f.ratio = ratio; f.status = ctx->d_status;
     if (D > 0) {
         DecodeArgs a{};
         a.m = to_model(model); a.Q = Q; a.D = D; a.stride = iv->stride;
@@ -1518,18 +1873,21 @@ extern "C" int hx_decode_score(hx_ctx *ctx, const hx_model *model, const hx_call
         a.start = start; a.cost = cost; a.status = ctx->d_status;
         a.free_c = free_c; a.n_free = n_free; a.per = per;
         a.gd = gd; a.n_groups = n_groups; a.part_cost = part_cost; a.part_start = part_start; a.part_d = part_d;
+        if (!pairs) {
+            hx_decode_occupancy_kernel<<<D, DO_THREADS, 0, stream>>>(a, o, nt);
+            // a wavefront per call, as many as the chip holds
+            const int waves = DB_THREADS / HX_WAVE, most = DB_PER_CU * ctx->num_cu;
+            const int grid = Q / waves + (Q % waves != 0) < most ? Q / waves + (Q % waves != 0) : most;
+            if (D <= HX_WAVE) hx_decode_best_kernel<1><<<grid, DB_THREADS, 0, stream>>>(a, f, o, nt);
+            else if (D <= 4 * HX_WAVE) hx_decode_best_kernel<4><<<grid, DB_THREADS, 0, stream>>>(a, f, o, nt);
+            else hx_decode_best_kernel<HX_MAX_INSTANCES / HX_WAVE><<<grid, DB_THREADS, 0, stream>>>(a, f, o, nt);
+            return hx_check_launch(ctx, "hx_decode_score kernels");
+        }
         const size_t lds = hx_scratch_bytes(ne) + hx_align16((size_t)nt * 8);
         hx_decode_timeline_kernel<<<D, TL_THREADS, lds, stream>>>(a, o, nt);
         const int n_lock = lock ? tiles : 0;
         hx_decode_score_kernel<<<n_lock + tiles * n_groups, DS_THREADS, 0, stream>>>(a, o, nt, n_lock);
     }
-    DecodeFinishArgs f{};
-    f.Q = Q; f.D = D; f.n_groups = n_groups;
-    f.L_in = queue->L_in; f.L_out = queue->L_out; f.lock = lock;
-    f.part_cost = part_cost; f.part_start = part_start; f.part_d = part_d;
-    f.node = queue->node; f.wf = queue->wf; f.elapsed = queue->elapsed; f.tail = tail; f.horizon = horizon;
-    f.n_nodes = n_nodes; f.n_wf = n_wf;
-    f.best_d = best_d; f.best_start = best_start; f.best_cost = best_cost; f.ratio = ratio; f.status = ctx->d_status;
     hx_decode_finish_kernel<<<(Q + 63) / 64, 64, 0, stream>>>(f);
     return hx_check_launch(ctx, "hx_decode_score kernels");
 }

@@ -159,6 +159,65 @@ def test_decode_score_matches_oracle(ctx, Q, D, stride, res, plan, seed):
     assert_costs_close(got2["best_cost"][same], want2.best_cost[same], "best cost of free calls")
 
 
+def _crowd(iv, dec, kind):
+    """The lists of a decode round made harder: every instance full for ten seconds more, room in pieces of 0.3 s until all is over,
+    events of many at the same moments, or lists with entries that hold nothing."""
+    K, D = int(iv["stride"]), len(dec["flops"])
+    st, en, tk = (np.asarray(iv[x]).reshape(D, K).copy() for x in ("start", "end", "tok"))
+    cnt, cap = np.asarray(iv["count"]).copy(), np.asarray(dec["cap_tok"])
+    for d in range(D):
+        if kind == "late":
+            now = st[d, :cnt[d]] <= 0
+            tk[d, :cnt[d]] = tk[d, :cnt[d]] * (0.999 * cap[d] / max(int(tk[d, :cnt[d]][now].sum()), 1))
+            en[d] += 10
+        elif kind == "pieces":
+            st[d], en[d], tk[d] = np.arange(K) + 0.3, np.arange(K) + 1.0, cap[d]
+            cnt[d] = K
+    if kind == "same":
+        st, en = np.round(st), np.round(en) + 1
+    if kind == "empty":
+        en[:, ::3] = st[:, ::3]
+        tk[:, 1::4] = 0
+        en[:, 2::5] = -1.0
+        en[:, 3::7] = np.inf
+        cnt[::2] = 0
+    return dict(stride=K, count=cnt, start=st.reshape(-1).astype(np.float32), end=en.reshape(-1).astype(np.float32), tok=tk.reshape(-1))
+
+
+# a lane takes 1, 4 or 16 instances; a timeline is read 64 entries at a time (resident + 1 entries without planned ones)
+@pytest.mark.parametrize("Q,D,res,plan,kind", [(48, 1, 62, 0, ""), (300, 2, 63, 0, "late"), (300, 63, 64, 0, "late"), (200, 64, 127, 0, "late"),
+                                               (150, 65, 128, 20, "late"), (700, 256, 30, 90, ""), (150, 257, 40, 20, "same"),
+                                               (100, 1024, 12, 6, "late"), (200, 64, 28, 0, "pieces"), (120, 300, 70, 0, "pieces"),
+                                               (300, 20, 24, 24, "empty"), (200, 3, 300, 211, "same"), (13000, 40, 20, 10, "")])
+def test_best_alone_is_the_best_of_the_pairs(ctx, Q, D, res, plan, kind):
+    """Without the matrices few pairs are looked at; best instance, start, cost and ratio are those of the pass that forms all of them
+    (compared with the oracle above) bit for bit."""
+    rng = np.random.default_rng(Q + D)
+    r, lock, iv = synth.make_decode_round("decode_tiny", Q + D, n_wf=max(8, Q // 8), Q=Q, D=D, T=min(8, D), stride=res + plan,
+                                          n_resident=res, n_planned=plan, lock_fraction=0.2)
+    L, O = np.array(r.calls["L_in"]), np.array(r.calls["L_out"])
+    O[::17] = 0                                    # decodes nothing: any moment with room will do
+    L[5::23] += int(np.median(r.dec["cap_tok"]))   # fits nowhere, or only where all has ended
+    L[7], lock[11], lock[13] = -1, D, -2           # no place
+    iv = _crowd(iv, r.dec, kind)
+    tail, hor = rng.uniform(0, 5, r.dag.n_nodes), rng.uniform(10, 60, r.dag.n_wf)
+    import torch
+    from paper_2605_16637_amd import binding
+    q, dd, div = dev_queue(L, O, r.calls["node"], r.calls["wf"], r.calls["elapsed"]), dev_dec(r.dec), dev_iv(iv)
+    tail, hor = dev(tail.astype(np.float32)), dev(hor.astype(np.float32))
+    for lk in (dev(lock), None):
+        got = []
+        for pairs in (dict(start=torch.empty(Q * D, device="cuda:0"), cost=torch.empty(Q * D, device="cuda:0")), {}):
+            out = [torch.full((Q,), -9, dtype=t, device="cuda:0") for t in (torch.int32, torch.float32, torch.float32, torch.float32)]
+            ctx.hx_decode_score(r.model, q, lk, dd, div, *out[:3], tail=tail, horizon=hor, ratio=out[3], **pairs)
+            with pytest.raises(binding.HxError) as err:        # the calls without a place
+                ctx.hx_stream_status()
+            assert "HX_ERR_INDEX" in str(err.value)
+            got.append([x.view(torch.int32) for x in out])
+        for x, y in zip(*got):
+            assert torch.equal(x, y)
+
+
 def test_decode_score_is_the_same_every_time(ctx):
     # no atomics, no dependence on which workgroup runs first: two passes over the same input agree bit for bit,
     # also with another pass of another shape in between (the scratch is reused)
