@@ -71,13 +71,20 @@ void hx_cp_local_kernel(CpArgs a, int wpb)
 // staging with the cost's sums in flight takes 102 registers, four wavefronts a SIMD; the launch is
 // meant for the graphs of a scheduling round (tens of thousands of nodes, spread over all compute
 // units), where the latency of a launch counts and residency does not.
+// WAVES: `wpv` workflows to a wavefront where all of a workgroup's are small enough (hx_cp_wave).
+template <bool WAVES>
 __global__ __launch_bounds__(CP_THREADS)
-void hx_cp_cost_kernel(CpArgs a, NodeCostArgs nc, int wpb)
+void hx_cp_cost_kernel(CpArgs a, NodeCostArgs nc, int wpb, int wpv)
 {
-    __shared__ CpNode s_node[CP_NMAX_COST + 1];
+    __shared__ union {
+        CpNode node[CP_NMAX_COST + 1];
+        CpWave wave[CP_THREADS / HX_WAVE];
+    } s;
     __shared__ int s_any;
     __shared__ CostTables s_tab;
-    hx_cp_local_body<CP_NMAX_COST, true, false>(a, wpb, s_node, s_any, &nc, &s_tab, (int)blockIdx.x);
+    if constexpr (WAVES)
+        if (hx_cp_waves_body<CP_THREADS>(a, wpv, s.wave, nc, s_tab, (int)blockIdx.x)) return;
+    hx_cp_local_body<CP_NMAX_COST, true, false>(a, wpb, s.node, s_any, &nc, &s_tab, (int)blockIdx.x);
 }
 
 // ---- critical path, level-synchronous sweeps ------------------------------------------
@@ -100,16 +107,33 @@ constexpr int CS_NPT = CS_NMAX / CS_THREADS;
 enum : int { SY_AGAIN = 0, SY_OVER = 1, SY_LEFT = 2, SY_STUCK = 3, SY_COUNT = 32, SY_GO = 64 };
 static_assert(SY_GO + 2 == HX_SYNC_WORDS, "two words each for the last two");
 
-__global__ __launch_bounds__(CS_THREADS) void hx_cp_sweep_slices_kernel(CpArgs a, int wpb, int max_sweeps, int32_t *sync)
+// WAVES: `wpv` workflows to a wavefront where all of a workgroup's are small enough (hx_cp_wave); an edge between two
+// wavefronts' workflows is then one that the second kernel follows.
+template <bool WAVES>
+__global__ __launch_bounds__(CS_THREADS) void hx_cp_sweep_slices_kernel(CpArgs a, int wpb, int wpv, int max_sweeps, int32_t *sync)
 {
-    __shared__ int2 s_val[CS_NMAX + 1];                    // (rem, level) of node n0 + i at i + 1; 0: the empty successor
+    __shared__ union {
+        int2 val[CS_NMAX + 1];                             // (rem, level) of node n0 + i at i + 1; 0: the empty successor
+        CpWave wave[CS_THREADS / HX_WAVE];
+    } s_lds;
+    int2 *const s_val = s_lds.val;
     __shared__ int s_changed[3];
     const int tid = threadIdx.x;
-    const int w1 = min(((int)blockIdx.x + 1) * wpb, a.n_wf);
+    int w1 = min(((int)blockIdx.x + 1) * wpb, a.n_wf);
     bool odd = false, over = false;                        // over: not every node has been given a value
-    if (tid == 0) s_val[0] = make_int2(0, -1);
+    if constexpr (WAVES) {
+        const int lane = tid & (HX_WAVE - 1), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+        const int wa = min((int)blockIdx.x * wpb + wave * wpv, a.n_wf), wb = min(wa + wpv, a.n_wf);
+        const int p = hx_cp_wave_bounds(a, wa, wb, lane);
+        if (!__syncthreads_or(hx_cp_wave_odd(a, p, wb - wa, lane))) {
+            const CwFound f = hx_cp_wave<false, true>(a, wa, wb, p, s_lds.wave[wave], max_sweeps, nullptr, nullptr, lane);
+            odd = f.not_dag || f.bad_index; over = f.over;
+            w1 = 0;                                        // (no slice)
+        }
+    }
+    if (w1 && tid == 0) s_val[0] = make_int2(0, -1);
     // nodes that belong to no workflow are swept too
-    if (blockIdx.x == 0) over = a.wf_ptr[0] != 0 || a.wf_ptr[a.n_wf] != a.n_nodes;
+    if (blockIdx.x == 0) over = over || a.wf_ptr[0] != 0 || a.wf_ptr[a.n_wf] != a.n_nodes;
     for (int wa = (int)blockIdx.x * wpb; wa < w1;) {
         // the run [wa, wb): as many of the slice's workflows as fit
         int wb = w1;
@@ -665,6 +689,21 @@ extern "C" int hx_node_cost(hx_ctx *ctx, const hx_model *model, int32_t n,
     return hx_check_launch(ctx, "hx_node_cost_kernel");
 }
 
+// Workflows a wavefront takes (hx_cp_wave), one each as long as that fills the chip with wavefronts and no more than fit its lanes.
+// 0: workgroups take slices, where workflows are too large on the average, or nodes are more than `most` a compute unit.
+static int wave_workflows(const hx_ctx *ctx, int n_nodes, int n_wf, int most)
+{
+    if (n_wf == 0 || n_nodes > 48LL * n_wf || n_nodes > (long long)most * ctx->num_cu) return 0;
+    const long long fit = n_nodes > 0 ? 56LL * n_wf / n_nodes : 32, spread = n_wf / (8 * ctx->num_cu);
+    const long long n = fit < spread ? fit : spread;
+    return (int)(n < 1 ? 1 : (n > 32 ? 32 : n));
+}
+// Launches in a graph, slices and wavefronts (us).  With the node cost of 4 classes: 20000 nodes 10.1 and 6.2, 82000 10.7 and 6.8, 200000
+// 11.2 and 11.6, 1.8 million 29 and 67; of 8 classes 200000 15.8 and 14.0, 240000 in workflows of 8 13.8 and 15.6.  Sweeps: 20000 12.8 and
+// 7.3, 200000 14.0 and 10.0, 320000 15.6 and 13.4, 440000 15.9 and 15.7, 600000 18.0 and 19.8.  1000 workflows of 30 to 60 nodes 14.5 and 6.4;
+// of 24 to 70, a tenth of which are too large, 13.4 and 13.0, sweeps 11.6 and 12.5.
+constexpr int CW_MOST_COST = 384, CW_MOST_SWEEPS = 1536;
+
 extern "C" int hx_critical_path(hx_ctx *ctx, int32_t n_nodes, int32_t n_edges,
                                 const int32_t *succ_row_ptr, const int32_t *succ_col_idx,
                                 const float *node_cost, int32_t n_wf, const int32_t *wf_ptr,
@@ -699,8 +738,11 @@ extern "C" int hx_critical_path(hx_ctx *ctx, int32_t n_nodes, int32_t n_edges,
     long long fit = n_nodes > 0 && n_wf > 0 ? (long long)(CS_NMAX * 2 / 3) * n_wf / n_nodes : 1;
     const long long spread = (n_wf + ctx->num_cu - 1) / ctx->num_cu;
     fit = fit > spread ? spread : fit;
-    const int wpb = (int)(fit < 1 ? 1 : fit);
-    hx_cp_sweep_slices_kernel<<<n_wf > 0 ? (n_wf + wpb - 1) / wpb : 1, CS_THREADS, 0, stream>>>(a, wpb, max_sweeps, ctx->d_sync);
+    const int wpv = wave_workflows(ctx, n_nodes, n_wf, CW_MOST_SWEEPS);
+    const int wpb = wpv ? wpv * (CS_THREADS / HX_WAVE) : (int)(fit < 1 ? 1 : fit);
+    const int n_slices = n_wf > 0 ? (n_wf + wpb - 1) / wpb : 1;
+    if (wpv) hx_cp_sweep_slices_kernel<true><<<n_slices, CS_THREADS, 0, stream>>>(a, wpb, wpv, max_sweeps, ctx->d_sync);
+    else hx_cp_sweep_slices_kernel<false><<<n_slices, CS_THREADS, 0, stream>>>(a, wpb, 0, max_sweeps, ctx->d_sync);
     if (int rc = hx_check_launch(ctx, "hx_cp_sweep_slices_kernel")) return rc;
     const long long most = n_nodes > n_wf ? n_nodes : n_wf;      // (workflows may be empty)
     int grid = (int)((most + CG_THREADS - 1) / CG_THREADS);
@@ -749,6 +791,7 @@ int hx_horizons_plan(hx_ctx *ctx, const hx_model *model, int32_t n_nodes, int32_
     fit = fit > spread ? (spread < 1 ? 1 : spread) : fit;
     plan->wpb = (int)(fit < 1 ? 1 : (fit > CP_WPB ? CP_WPB : fit));
     plan->grid = (n_wf + plan->wpb - 1) / plan->wpb;
+    plan->wpv = wave_workflows(ctx, n_nodes, n_wf, CW_MOST_COST);
     return HX_OK;
 }
 
@@ -767,7 +810,10 @@ extern "C" int hx_horizons(hx_ctx *ctx, const hx_model *model, int32_t n_nodes, 
     if (plan.grid == 0) return HX_OK;
     HxDeviceGuard guard(ctx->device);
     HX_REQUIRE(ctx, guard.ok, HX_ERR_DEVICE, "cannot select device %d", ctx->device);
-    hx_cp_cost_kernel<<<plan.grid, CP_THREADS, 0, (hipStream_t)stream_>>>(plan.a, plan.nc, plan.wpb);
+    const int wpb = plan.wpv ? plan.wpv * (CP_THREADS / HX_WAVE) : plan.wpb;
+    const int grid = (n_wf + wpb - 1) / wpb;
+    if (plan.wpv) hx_cp_cost_kernel<true><<<grid, CP_THREADS, 0, (hipStream_t)stream_>>>(plan.a, plan.nc, wpb, plan.wpv);
+    else hx_cp_cost_kernel<false><<<grid, CP_THREADS, 0, (hipStream_t)stream_>>>(plan.a, plan.nc, wpb, 0);
     return hx_check_launch(ctx, "hx_cp_cost_kernel");
 }
 

@@ -430,22 +430,27 @@ __global__ __launch_bounds__(FS_THREADS) void hx_fused_search_kernel(ScoreArgs a
 // the first n_reveal workgroups take workflows exactly as hx_cp_cost_kernel's do (same body, a node per thread, the
 // cost's decode classes one after the other to stay within the search's registers), the others search.  Same
 // results as the two kernels, one launch and the gap before it less: both halves are chains of memory round trips,
-// which run side by side.  The reveal's chain is the longer one, so its workgroups come first.
+// which run side by side.  The reveal's chain is the longer one, so its workgroups come first.  Six wavefronts a SIMD, so that
+// three workgroups are on a compute unit: 16384 calls on 256 + 256 with 82000 nodes 14.6 -> 12.5 us (85 registers, two workgroups: 16.1).
 constexpr int RV_NMAX = 512;             // nodes staged per run of a reveal workgroup
 
 struct RevealLds {
-    CpNode node[RV_NMAX + 1];
+    union {
+        CpNode node[RV_NMAX + 1];
+        CpWave wave[FS_WAVES];
+    };
     CostTables tab;
     int any;
 };
 
 template <int CALLS>
-__global__ __launch_bounds__(FS_THREADS) void hx_reveal_search_kernel(ScoreArgs a, PrepArgs pa, CpArgs cp, NodeCostArgs nc, int wpb,
-                                                                      int n_reveal)
+__global__ __launch_bounds__(FS_THREADS, 6) void hx_reveal_search_kernel(ScoreArgs a, PrepArgs pa, CpArgs cp, NodeCostArgs nc, int wpb,
+                                                                      int wpv, int n_reveal)
 {
     extern __shared__ __align__(16) float smem[];
     if ((int)blockIdx.x < n_reveal) {
         RevealLds *l = (RevealLds *)smem;
+        if (wpv && hx_cp_waves_body<FS_THREADS>(cp, wpv, l->wave, nc, l->tab, (int)blockIdx.x)) return;
         hx_cp_local_body<RV_NMAX, true, false, FS_THREADS>(cp, wpb, l->node, l->any, &nc, &l->tab, (int)blockIdx.x);
         return;
     }
@@ -830,10 +835,11 @@ int score_placements(hx_ctx *ctx, const hx_model *model, const hx_calls *calls,
             // not this way if the reveal's units are too large for its staging area
             const long long nodes_per_unit = (long long)reveal->a.n_nodes * reveal->wpb / (reveal->a.n_wf > 0 ? reveal->a.n_wf : 1);
             if (nodes_per_unit > RV_NMAX * 7 / 10) return HX_OK;
+            const int wpb = reveal->wpv ? reveal->wpv * FS_WAVES : reveal->wpb, n_reveal = (reveal->a.n_wf + wpb - 1) / wpb;
             const size_t lds_both = lds > sizeof(RevealLds) ? lds : sizeof(RevealLds);
             by_calls([&](auto calls) {
-                hx_reveal_search_kernel<calls()><<<reveal->grid + n_search, FS_THREADS, lds_both, stream>>>(
-                    a, pa, reveal->a, reveal->nc, reveal->wpb, reveal->grid);
+                hx_reveal_search_kernel<calls()><<<n_reveal + n_search, FS_THREADS, lds_both, stream>>>(
+                    a, pa, reveal->a, reveal->nc, wpb, reveal->wpv, n_reveal);
             });
             if (int rc = hx_check_launch(ctx, "hx_reveal_search_kernel")) return rc;
             *revealed = true;

@@ -288,6 +288,36 @@ def test_horizons_in_one_launch_wide_nodes_and_runs(ctx, sizes, fan_out, seed):
     assert_cp_bit_exact(got, want)
 
 
+@pytest.mark.parametrize("sizes,fan_out,seed", [
+    ([64] * 5 + [1] * 40, 3, 1), ([63, 64, 1, 64, 2, 62] * 60, 2, 2),     # a wavefront's lanes, just filled
+    ([65] + [3] * 40, 3, 3),                                               # one workflow too large for them
+    ([0, 0, 64, 0, 1, 0] * 9, 3, 4), ([2, 1], 2, 5), ([4], 3, 6),          # empty ones; fewer edges than one load takes
+    ([30] * 40 + [2], 9, 7), ([40] * 20, 30, 8), ([64] * 12, 63, 9),       # successors beyond four: in LDS, more than there is room for
+    ([8] * 9000, 3, 10), ([20] * 5000, 3, 11)])                            # several workflows a wavefront
+def test_small_workflows_by_wavefronts(ctx, sizes, fan_out, seed):
+    """Wavefronts of whole workflows: in one launch with the node cost, and in the sweeps (nodes renumbered backwards)."""
+    rng = np.random.default_rng(seed)
+    rnd = synth.make_round("tiny", 1)
+    row_ptr, col, wf_ptr = _random_forest(rng, sizes, fan_out)
+    n = len(row_ptr) - 1
+    L_in, L_out = rng.integers(64, 8000, n).astype(np.int32), rng.integers(16, 2000, n).astype(np.int32)
+    gcost, got = gpu_horizons(ctx, rnd, row_ptr, col, L_in, L_out, wf_ptr)
+    want = o.critical_path(row_ptr, col, gcost.astype(np.float64), wf_ptr, round_f32=True)
+    assert_cp_bit_exact(got, want)
+    # node v of a workflow [s, e) becomes s + e - 1 - v
+    wf = np.repeat(np.arange(len(sizes)), sizes)
+    to = wf_ptr[wf] + wf_ptr[wf + 1] - 1 - np.arange(n)
+    src = np.repeat(np.arange(n), np.diff(row_ptr))
+    order = np.lexsort((to[col], to[src]))
+    back_ptr = np.concatenate([[0], np.cumsum(np.bincount(to[src], minlength=n))]).astype(np.int32)
+    cost = np.empty_like(gcost)
+    cost[to] = gcost
+    back = gpu_cp(ctx, back_ptr, to[col][order].astype(np.int32), cost, wf_ptr, max_sweeps=80)
+    for x, y in zip(back[:3], got[:3]):
+        assert np.array_equal(x[to], y)
+    assert np.array_equal(back[3], got[3])
+
+
 def fetch(raw):
     """Copy a borrowed device array of the context to the host (device-to-device copy into a tensor first)."""
     import ctypes
