@@ -11,6 +11,7 @@ import os
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libhx.so")
+MARSHAL_PATH = os.path.join(_HERE, "hx_marshal.so")
 
 HX_OK = 0
 ERRORS = {-1: "HX_ERR_INVALID_ARG", -2: "HX_ERR_SHAPE", -3: "HX_ERR_NOT_DAG", -4: "HX_ERR_CAPACITY",
@@ -118,8 +119,9 @@ class RawArray:
         return self._n
 
 
-def _ptr(t, dtype=None, n=None):
-    """Device pointer of a contiguous CUDA tensor (None -> NULL), after checks."""
+def _ptr_other(t, dtype=None, n=None):
+    """Device pointer of a contiguous CUDA tensor (None -> NULL), after checks.  ``_ptr`` is the same in native code for plain
+    tensors that pass, and calls this for everything else."""
     if t is None:
         return None
     if isinstance(t, RawArray):
@@ -137,10 +139,35 @@ def _ptr(t, dtype=None, n=None):
     return C.c_void_p(t.data_ptr())
 
 
+def _load_marshal():
+    """``hx_marshal.address`` (csrc/hx_marshal.cpp, built in-tree beside the library)."""
+    import importlib.machinery
+    import importlib.util
+
+    import torch  # noqa: F401  (its libraries are what the module links to)
+    if not os.path.exists(MARSHAL_PATH):
+        raise ImportError(f"{MARSHAL_PATH} is not built: run `python -m paper_2605_16637_amd.build` "
+                          "(or __graft_entry__.build()) first")
+    loader = importlib.machinery.ExtensionFileLoader("hx_marshal", MARSHAL_PATH)
+    module = importlib.util.module_from_spec(importlib.util.spec_from_loader("hx_marshal", loader))
+    loader.exec_module(module)
+    module.set_up(C.c_void_p, _ptr_other)
+    return module.address
+
+
+def _ptr(*args):
+    """``hx_marshal.address`` from its first use on."""
+    global _ptr
+    _ptr = _load_marshal()
+    return _ptr(*args)
+
+
 def _stream(stream=None):
-    torch = _torch()
-    s = torch.cuda.current_stream() if stream is None else stream
-    return C.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return C.c_void_p(stream.cuda_stream)
+    c = _torch()._C
+    # the raw handle of torch.cuda.current_stream(), without the object around it
+    return C.c_void_p(c._cuda_getCurrentRawStream(c._cuda_getDevice()))
 
 
 def make_model(m: dict) -> hx_model:

@@ -9,6 +9,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libhx.so")
 CALIB_LIB = os.path.join(HERE, "libhx_calib.so")      # the benchmark's calibration kernels, a library of their own
+MARSHAL_LIB = os.path.join(HERE, "hx_marshal.so")     # host code of the binding (hx_marshal.cpp), a Python module
 SOURCES = ["hx_ctx.hip", "hx_score.hip", "hx_dag.hip", "hx_plan.hip", "hx_decode.hip"]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -32,7 +33,20 @@ HOST_SANITIZE = ["-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize
 def build(verbose: bool = False, out: str = LIB, extra_flags=()) -> str:
     if out == LIB:
         _compile(["hipcc", *FLAGS, "-o", CALIB_LIB, os.path.join(CSRC, "hx_calib.hip")], verbose)
+        _compile(_marshal_command(), verbose)
     return _compile(["hipcc", *FLAGS, *extra_flags, "-o", out, *[os.path.join(CSRC, s) for s in SOURCES]], verbose, out)
+
+
+def _marshal_command():
+    import sysconfig
+
+    import torch
+    from torch.utils.cpp_extension import include_paths
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    include = [*include_paths(), sysconfig.get_paths()["include"]]
+    return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
+            *[x for p in include for x in ("-isystem", p)], "-o", MARSHAL_LIB, os.path.join(CSRC, "hx_marshal.cpp"),
+            "-L" + lib, "-ltorch_python", "-ltorch_cpu", "-lc10"]
 
 
 def _compile(cmd, verbose, out=None) -> str:

@@ -1,0 +1,65 @@
+// The binding's look at one tensor, in native code: is it a contiguous tensor in device memory, of this type, with that many elements,
+// and where does it lie.  Asked in Python these are five attributes of some 110 ns each and an object, a third to a half of what a call
+// with ten tensors costs its caller; a pass of two calls over 20000 nodes, whose kernels take 11 us, 23.8 -> 14.7 us.
+#include <Python.h>
+
+#include <torch/csrc/Dtype.h>
+#include <torch/csrc/Exceptions.h>
+#include <torch/csrc/autograd/python_variable.h>
+
+namespace {
+
+PyObject *g_pointer = nullptr;      // ctypes.c_void_p
+PyObject *g_other = nullptr;        // the same in Python: answers for whatever is not a plain tensor that passes, and raises
+
+// address(tensor, dtype=None, n=None) -> c_void_p, or None for None
+PyObject *address(PyObject *, PyObject *const *args, Py_ssize_t n_args)
+{
+    HANDLE_TH_ERRORS
+    PyObject *t = n_args > 0 ? args[0] : nullptr, *dtype = n_args > 1 ? args[1] : Py_None, *n = n_args > 2 ? args[2] : Py_None;
+    if (t == Py_None) Py_RETURN_NONE;
+    if (t && g_pointer && n_args <= 3 && THPVariable_CheckExact(t) && (dtype == Py_None || THPDtype_Check(dtype)) &&
+        (n == Py_None || PyLong_CheckExact(n))) {
+        const at::Tensor &x = THPVariable_Unpack(t);
+        bool fine = x.is_cuda() && x.is_contiguous() &&
+                    (dtype == Py_None || reinterpret_cast<THPDtype *>(dtype)->scalar_type == x.scalar_type());
+        if (fine && n != Py_None) {
+            const long long want = PyLong_AsLongLong(n);
+            if (want == -1 && PyErr_Occurred()) return nullptr;
+            fine = x.numel() >= want;
+        }
+        if (fine) {
+            PyObject *at = PyLong_FromVoidPtr(x.data_ptr());
+            if (!at) return nullptr;
+            PyObject *p = PyObject_CallFunctionObjArgs(g_pointer, at, nullptr);
+            Py_DECREF(at);
+            return p;
+        }
+    }
+    if (!g_other) {
+        PyErr_SetString(PyExc_RuntimeError, "set_up() has not been called");
+        return nullptr;
+    }
+    return PyObject_Vectorcall(g_other, args, n_args, nullptr);
+    END_HANDLE_TH_ERRORS
+}
+
+// set_up(c_void_p, other)
+PyObject *set_up(PyObject *, PyObject *args)
+{
+    PyObject *pointer, *other;
+    if (!PyArg_ParseTuple(args, "OO", &pointer, &other)) return nullptr;
+    Py_INCREF(pointer); Py_INCREF(other);
+    Py_XDECREF(g_pointer); Py_XDECREF(g_other);
+    g_pointer = pointer; g_other = other;
+    Py_RETURN_NONE;
+}
+
+PyMethodDef methods[] = {{"address", (PyCFunction)(void (*)())address, METH_FASTCALL, "where a tensor lies, after checks"},
+                         {"set_up", set_up, METH_VARARGS, "what addresses are made of, and who answers for other arguments"},
+                         {nullptr, nullptr, 0, nullptr}};
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "hx_marshal", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
+
+}  // namespace
+
+PyMODINIT_FUNC PyInit_hx_marshal(void) { return PyModule_Create(&module); }
