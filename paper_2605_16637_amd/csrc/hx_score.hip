@@ -479,6 +479,9 @@ __global__ __launch_bounds__(FS_THREADS) void hx_relax_search_kernel(ScoreArgs a
 // transfer times, each worked out by 256 / nc threads; beside them what does not depend on the call (waits,
 // per-token terms, classes), which every workgroup derives for itself from the pool, under the first call's lengths: as a
 // kernel of one workgroup before this one they took 3.5 us (4096 x 64 x 64 with the selection after it 38.8 -> 36.1).
+// Bound: the stores (a plain fill of 4096 x 64 x 64 takes 12.3 us), and before the first of them one memory round trip and the tables'
+// divisions, in which no workgroup writes: everything is asked for together (4096 x 64 x 64 15.5 -> 14.6 us, 64 x 8 x 8 4.1 -> 3.7; prefill
+// instances, decode instances, links and calls one after the other before).
 __global__ __launch_bounds__(256) void hx_materialise_kernel(ScoreArgs a, PrepArgs t, int nc)
 {
     extern __shared__ __align__(16) float smem[];
@@ -501,40 +504,51 @@ __global__ __launch_bounds__(256) void hx_materialise_kernel(ScoreArgs a, PrepAr
     const int tid = threadIdx.x;
     // rows of the tensor are 16-byte aligned and a whole number of quads long
     const bool vec4 = (a.D & 3) == 0 && a.D >= 4 && (reinterpret_cast<uintptr_t>(a.cost) & 15) == 0;
-    for (int p = tid; p < a.P; p += blockDim.x) {
-        int k = t.p_type[p];
-        if (k < 0 || k >= t.T) { hx_raise(a.status, HX_ERR_INDEX); k = 0; }
-        const float invF = 1.0f / t.p_flops[p];
-        s_pw[p] = hx_prefill_wait(a.m, t.p_backlog[p], invF); s_pF[p] = invF; s_pB[p] = 1.0f / t.p_hbm[p]; s_ptype[p] = k;
-    }
-    for (int d = tid; d < a.D; d += blockDim.x) {
-        int k = t.d_type[d];
-        if (k < 0 || k >= t.T) { hx_raise(a.status, HX_ERR_INDEX); k = 0; }
-        const int used = t.d_used[d];
-        const HxDecF x = hx_decode_terms(a.m, used, t.d_batch[d], t.d_qd[d], 1.0f / t.d_flops[d], 1.0f / t.d_hbm[d]);
-        const long long fr = (long long)t.d_cap[d] - (long long)used;
-        s_c1[d] = x.c1; s_c2[d] = x.c2; s_kB[d] = x.kB; s_wait[d] = x.wait; s_dtype[d] = k;
-        s_free[d] = fr < -1 ? -1 : (fr > 2147483647LL ? 2147483647 : (int)fr);
-    }
-    if (tid < kT * kT) {
-        const int i = tid / kT, k = tid % kT;
-        const bool in = i < t.T && k < t.T;
-        s_lbw[tid] = in ? 1.0f / t.bw[i * t.T + k] : 0.0f;
-        s_llat[tid] = in && t.lat ? t.lat[i * t.T + k] : 0.0f;
-    }
     // the part of the workgroup that works out the tables of one call of the batch
     const int per_call = blockDim.x / nc;
     const int slot = tid / per_call, tq = tid - slot * per_call;
+    // everything is asked for before the first of it is used: the first calls' lengths, the links, an instance of either side a thread
+    const int c_first = min((int)(blockIdx.x * nc) + slot, a.C - 1);
+    int L = a.L_in[c_first], O = a.L_out[c_first];
+    const bool link_in = tid < kT * kT && tid / kT < t.T && tid % kT < t.T;
+    const int link_at = (tid / kT) * t.T + tid % kT;
+    const float l_bw = link_in ? t.bw[link_at] : 1.0f;
+    const float l_lat = link_in && t.lat ? t.lat[link_at] : 0.0f;
+    for (int i0 = 0; i0 < max(a.P, a.D); i0 += (int)blockDim.x) {
+        const int i = i0 + tid;
+        const bool hp = i < a.P, hd = i < a.D;
+        const int p = hp ? i : 0, d = hd ? i : 0;
+        const float pf = t.p_flops[p], pb = t.p_hbm[p], df = t.d_flops[d], db = t.d_hbm[d];
+        const int bl = t.p_backlog[p], used = t.d_used[d], cap = t.d_cap[d], batch = t.d_batch[d], qd = t.d_qd[d];
+        int kp = t.p_type[p], kd = t.d_type[d];
+        if (kp < 0 || kp >= t.T) { if (hp) hx_raise(a.status, HX_ERR_INDEX); kp = 0; }
+        if (kd < 0 || kd >= t.T) { if (hd) hx_raise(a.status, HX_ERR_INDEX); kd = 0; }
+        if (hp) {
+            const float invF = 1.0f / pf;
+            s_pw[p] = hx_prefill_wait(a.m, bl, invF); s_pF[p] = invF; s_pB[p] = 1.0f / pb; s_ptype[p] = kp;
+        }
+        if (hd) {
+            const HxDecF x = hx_decode_terms(a.m, used, batch, qd, 1.0f / df, 1.0f / db);
+            const long long fr = (long long)cap - (long long)used;
+            s_c1[d] = x.c1; s_c2[d] = x.c2; s_kB[d] = x.kB; s_wait[d] = x.wait; s_dtype[d] = kd;
+            s_free[d] = fr < -1 ? -1 : (fr > 2147483647LL ? 2147483647 : (int)fr);
+        }
+    }
+    if (tid < kT * kT) { s_lbw[tid] = link_in ? 1.0f / l_bw : 0.0f; s_llat[tid] = l_lat; }
     for (int c0 = blockIdx.x * nc; c0 < a.C; c0 += gridDim.x * nc) {
         const int cs = c0 + slot;
         const bool live = cs < a.C;
-        const int L = live ? a.L_in[cs] : 0, O = live ? a.L_out[cs] : 0;
         const HxCallF cf = hx_call_terms(a.m, L, O);
+        const int L_now = L, O_now = O;
+        if (c0 + (int)(gridDim.x * nc) < a.C) {            // the next calls' lengths
+            const int c_next = min(cs + (int)(gridDim.x * nc), a.C - 1);
+            L = a.L_in[c_next]; O = a.L_out[c_next];
+        }
         __syncthreads();
         if (live) {
             for (int p = tq; p < a.P; p += per_call) s_done[slot * P4 + p] = hx_prefill_done(cf, s_pw[p], s_pF[p], s_pB[p]);
             for (int d = tq; d < a.D; d += per_call) {
-                const bool fits = hx_fits(L, O, s_free[d]);
+                const bool fits = hx_fits(L_now, O_now, s_free[d]);
                 s_dec[slot * D4 + d] = fits ? hx_decode_time(cf, s_c1[d], s_c2[d], s_kB[d]) : INFINITY;
                 if (a.feas) a.feas[(size_t)cs * a.D + d] = fits ? 1 : 0;
             }
