@@ -64,13 +64,33 @@ __device__ __forceinline__ int hx_add_sat_drain(int cur, unsigned long long add,
     return left < 0 ? 0 : (left > 2147483647LL ? 2147483647 : (int)left);
 }
 
-// One call a lane into the workgroup's counters, by LDS atomics; all lanes of the wavefront take part.  Lanes that meet on a
-// counter are serialised there, and scored on one snapshot most calls of a round choose the same instance: where all of
-// a wavefront do, one lane adds their sum (16384 calls on 256 + 256 as part of a round 20.6 -> 18.9 us).  Not in a round of
+// The workgroup's counters, each in 2^LG places beside each other, a lane's by its number: lanes that meet on a place are added one after
+// the other (64 of them some 80 cycles, and there is one LDS for all wavefronts), and scored on one snapshot most calls of a round
+// choose one of a few instances.  One place and eight in one workgroup (us; placements spread, on three instances, on one): 2048 calls on
+// 256 + 256 3.8, 5.0, 4.2 and 3.8, 3.8, 3.8; 1024 on 64 + 64 3.0, 3.7, 3.2 and 3.1, 3.1, 3.1.  One and four in several workgroups: 4096 calls
+// 4.6, 5.1, 4.7 and 4.5, 4.6, 4.7; 16384 on 256 + 256 5.1, 5.7, 5.3 and 5.2, 5.1, 5.4.
+template <int LG>
+struct CommitCounters {
+    unsigned long long *at;
+    __device__ __forceinline__ void clear(int n) const { for (int i = threadIdx.x; i < n << LG; i += blockDim.x) at[i] = 0ull; }
+    __device__ __forceinline__ void add(int i, unsigned long long x) const { atomicAdd(&at[(i << LG) + (threadIdx.x & ((1 << LG) - 1))], x); }
+    // neighbouring threads ask for neighbouring counters: each begins at another of its places
+    __device__ __forceinline__ unsigned long long sum(int i) const
+    {
+        unsigned long long x = 0ull;
+#pragma unroll
+        for (int r = 0; r < 1 << LG; ++r) x += at[(i << LG) + ((r + threadIdx.x) & ((1 << LG) - 1))];
+        return x;
+    }
+};
+
+// One call a lane into the workgroup's counters, by LDS atomics; all lanes of the wavefront take part.  Where all of a wavefront's calls
+// meet on one instance one lane adds their sum (16384 calls on 256 + 256 as part of a round 20.6 -> 18.9 us).  Not in a round of
 // CA_SINGLY calls, which meet nobody else's: one call 2.83 us instead of 2.70, 32 on one instance 2.93 instead of 2.79 (128 2.96 instead of
 // 3.04).  False: a pair or a length out of range.
 constexpr int CA_SINGLY = HX_WAVE;
-__device__ __forceinline__ bool hx_commit_call(const CommitArgs &a, bool singly, unsigned long long *acc, int p, int d, int L, int O)
+template <int LG>
+__device__ __forceinline__ bool hx_commit_call(const CommitArgs &a, bool singly, const CommitCounters<LG> &acc, int p, int d, int L, int O)
 {
     bool valid = p >= 0 && d >= 0;                          // otherwise the call stays queued
     const bool bad = valid && (p >= a.P || d >= a.D || L < 0 || O < 0);
@@ -81,13 +101,13 @@ __device__ __forceinline__ bool hx_commit_call(const CommitArgs &a, bool singly,
     const bool one_p = !singly && __builtin_amdgcn_ballot_w64(valid && p != __builtin_amdgcn_readlane(p, lead)) == 0;
     const bool one_d = !singly && __builtin_amdgcn_ballot_w64(valid && d != __builtin_amdgcn_readlane(d, lead)) == 0;
     const unsigned long long all_L = one_p || one_d ? hx_wave_sum_i31(valid ? L : 0) : 0ull;
-    if (one_p ? lane == lead : valid) atomicAdd(&acc[p], one_p ? all_L : (unsigned long long)L);
+    if (one_p ? lane == lead : valid) acc.add(p, one_p ? all_L : (unsigned long long)L);
     if (one_d) {
         const unsigned long long all_O = hx_wave_sum_i31(valid ? O : 0);
-        if (lane == lead) { atomicAdd(&acc[a.P + d], all_L + all_O); atomicAdd(&acc[a.P + a.D + d], all_O); }
+        if (lane == lead) { acc.add(a.P + d, all_L + all_O); acc.add(a.P + a.D + d, all_O); }
     } else if (valid) {
-        atomicAdd(&acc[a.P + d], (unsigned long long)L + (unsigned long long)O);
-        atomicAdd(&acc[a.P + a.D + d], (unsigned long long)O);
+        acc.add(a.P + d, (unsigned long long)L + (unsigned long long)O);
+        acc.add(a.P + a.D + d, (unsigned long long)O);
     }
     return !bad;
 }
@@ -138,6 +158,7 @@ constexpr int CA_FEW_CALLS = 8192;
 // The ratios are formed by workgroups of their own after the first n_add, CA_FOLD calls each: their gathers are random reads,
 // which many compute units do sooner than few.
 constexpr int CA_FOLD = 256;
+template <int LG>
 __global__ __launch_bounds__(CA_THREADS) void hx_commit_add_kernel(CommitArgs a, RatioArgs rt, int n_add)
 {
     if ((int)blockIdx.x >= n_add) {
@@ -149,9 +170,10 @@ __global__ __launch_bounds__(CA_THREADS) void hx_commit_add_kernel(CommitArgs a,
     }
     __shared__ unsigned long long s_acc[3 * HX_MAX_INSTANCES];
     const int n_acc = a.P + 2 * a.D;
+    const CommitCounters<LG> acc{s_acc};
     InstanceState own;
     own.load(a, threadIdx.x);
-    for (int i = threadIdx.x; i < n_acc; i += blockDim.x) s_acc[i] = 0ull;
+    acc.clear(n_acc);
     __syncthreads();
     bool bad = false;
     const int stride = n_add * blockDim.x;
@@ -159,13 +181,13 @@ __global__ __launch_bounds__(CA_THREADS) void hx_commit_add_kernel(CommitArgs a,
         const long long c = at + threadIdx.x;
         int p = -1, d = -1, L = 0, O = 0;
         if (c < a.C) { p = a.best_p[c]; d = a.best_d[c]; L = a.L_in[c]; O = a.L_out[c]; }
-        if (!hx_commit_call(a, false, s_acc, p, d, L, O)) bad = true;
+        if (!hx_commit_call(a, false, acc, p, d, L, O)) bad = true;
     }
     if (bad) hx_raise(a.status, HX_ERR_INDEX);
     __syncthreads();
     unsigned long long seen = 0ull;
     for (int i = threadIdx.x; i < n_acc; i += blockDim.x)
-        if (s_acc[i]) seen ^= atomicAdd(&a.acc[i], s_acc[i]);
+        if (const unsigned long long x = acc.sum(i)) seen ^= atomicAdd(&a.acc[i], x);
     if (!a.ticket) return;
     // The workgroup that delivers last applies the drains: no second launch.  Everything the workgroups
     // exchange goes through device-scope atomics (the sums above, the ticket, and the accumulators read back with
@@ -202,13 +224,18 @@ constexpr int COMMIT_ONE_THREADS = 1024;
 // lanes of all calls meet in one compute unit's LDS.  One workgroup and several (us; placements spread, all on three
 // instances): 1537 calls 3.3, 4.5 and 4.2, 4.8; 2048 3.4, 5.0 and 4.6, 5.0; 4096 4.5, 7.4 and 4.6, 5.0.
 constexpr int HX_COMMIT_ONE_LAUNCH = 2048;
+// From this many calls on eight places a counter and no question whether a wavefront's calls meet (with it 2048 calls 4.4 to 4.8), as long
+// as the places fit LDS; below, clearing and adding up the places takes longer than lanes that meet.
+constexpr int COMMIT_ONE_APART = 512;
+template <int LG>
 __global__ __launch_bounds__(COMMIT_ONE_THREADS) void hx_commit_one_kernel(CommitArgs a, RatioArgs rt)
 {
-    __shared__ unsigned long long s_acc[3 * HX_MAX_INSTANCES];
+    __shared__ unsigned long long s_acc[LG == 3 ? 2 * 3 * HX_MAX_INSTANCES : 3 * HX_MAX_INSTANCES];
     const int n_acc = a.P + 2 * a.D;
+    const CommitCounters<LG> acc{s_acc};
     InstanceState own;
     own.load(a, threadIdx.x);
-    for (int i = threadIdx.x; i < n_acc; i += COMMIT_ONE_THREADS) s_acc[i] = 0ull;
+    acc.clear(n_acc);
     __syncthreads();
     bool bad = false;
     const int rounds = (a.C + COMMIT_ONE_THREADS - 1) / COMMIT_ONE_THREADS;     // the same trip count for every lane
@@ -218,12 +245,12 @@ __global__ __launch_bounds__(COMMIT_ONE_THREADS) void hx_commit_one_kernel(Commi
         if (c < a.C) { p = a.best_p[c]; d = a.best_d[c]; L = a.L_in[c]; O = a.L_out[c]; }
         if (rt.ratio && c < a.C)
             hx_projected_ratio(rt.node, rt.wf, rt.elapsed, rt.tail, rt.horizon, rt.n_nodes, rt.n_wf, c, rt.best_cost[c], a.status, rt.ratio);
-        if (!hx_commit_call(a, a.C <= CA_SINGLY, s_acc, p, d, L, O)) bad = true;
+        if (!hx_commit_call(a, LG == 3 || a.C <= CA_SINGLY, acc, p, d, L, O)) bad = true;
     }
     if (bad) hx_raise(a.status, HX_ERR_INDEX);
     __syncthreads();
     const int i = threadIdx.x;
-    own.apply(a, i, i < a.P ? s_acc[i] : 0ull, i < a.D ? s_acc[a.P + i] : 0ull, i < a.D ? s_acc[a.P + a.D + i] : 0ull);
+    own.apply(a, i, i < a.P ? acc.sum(i) : 0ull, i < a.D ? acc.sum(a.P + i) : 0ull, i < a.D ? acc.sum(a.P + a.D + i) : 0ull);
 }
 
 __global__ __launch_bounds__(256) void hx_commit_drain_kernel(CommitArgs a)
@@ -461,7 +488,8 @@ int commit_round(hx_ctx *ctx, const hx_calls *calls, const int32_t *best_p, cons
     CommitArgs a{C, P, D, calls->L_in, calls->L_out, best_p, best_d, backlog_tok, used_tok, batch, qd_tok,
                  drain_prefill, drain_decode_q, release_tok, tokens_per_seq, max_batch, ctx->d_acc, ctx->d_status, nullptr};
     if (C <= HX_COMMIT_ONE_LAUNCH) {
-        hx_commit_one_kernel<<<1, COMMIT_ONE_THREADS, 0, stream>>>(a, rt);
+        if (C > COMMIT_ONE_APART && P + 2 * D <= 3 * HX_MAX_INSTANCES / 4) hx_commit_one_kernel<3><<<1, COMMIT_ONE_THREADS, 0, stream>>>(a, rt);
+        else hx_commit_one_kernel<0><<<1, COMMIT_ONE_THREADS, 0, stream>>>(a, rt);
         return hx_check_launch(ctx, "hx_commit_one_kernel");
     }
     const int threads = commit_threads(C);
@@ -470,7 +498,8 @@ int commit_round(hx_ctx *ctx, const hx_calls *calls, const int32_t *best_p, cons
     a.ticket = ctx->d_ticket;                  // the workgroup that finishes last applies the drains
     int fold = rt.ratio ? C / CA_FOLD + (C % CA_FOLD != 0) : 0;
     fold = fold > ctx->num_cu ? ctx->num_cu : fold;
-    hx_commit_add_kernel<<<grid + fold, threads, 0, stream>>>(a, rt, grid);
+    if (P + 2 * D <= 3 * HX_MAX_INSTANCES / 4) hx_commit_add_kernel<2><<<grid + fold, threads, 0, stream>>>(a, rt, grid);
+    else hx_commit_add_kernel<0><<<grid + fold, threads, 0, stream>>>(a, rt, grid);
     return hx_check_launch(ctx, "hx_commit_add_kernel");
 }
 
@@ -524,7 +553,7 @@ extern "C" int hx_commit_static(const hx_calls *calls, const int32_t *best_p, co
         const int threads = commit_threads(C);
         int grid = C / threads + (C % threads != 0);
         grid = grid > 256 ? 256 : grid;
-        hx_commit_add_kernel<<<grid, threads, 0, stream>>>(a, RatioArgs{}, grid);
+        hx_commit_add_kernel<0><<<grid, threads, 0, stream>>>(a, RatioArgs{}, grid);
     }
     const int n_inst = P > D ? P : D;
     hx_commit_drain_kernel<<<(n_inst + 255) / 256, 256, 0, stream>>>(a);

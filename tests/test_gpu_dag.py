@@ -755,7 +755,8 @@ def test_commit_matches_oracle(ctx, C):
 
 # where the commit's kernel or its workgroups change (2048 and 8192 calls), more instances on one side than a workgroup has
 # threads, and placements that all meet on few instances (hot) or none
-@pytest.mark.parametrize("C,P,D,hot", [(1, 1, 1, 0), (2048, 5, 1024, 0), (2049, 1024, 3, 0), (2049, 4, 4, 1), (8192, 600, 513, 0),
+@pytest.mark.parametrize("C,P,D,hot", [(512, 256, 256, 1), (513, 256, 256, 1), (513, 257, 256, 1), (2049, 256, 256, 1), (2049, 256, 257, 1),
+                                        (1, 1, 1, 0), (2048, 5, 1024, 0), (2049, 1024, 3, 0), (2049, 4, 4, 1), (8192, 600, 513, 0),
                                        (8193, 64, 64, 1), (8193, 1024, 1024, 0), (0, 600, 700, 0)])
 def test_commit_at_the_lines_between_its_kernels(ctx, C, P, D, hot):
     from paper_2605_16637_amd import binding
