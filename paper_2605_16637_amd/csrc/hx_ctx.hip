@@ -158,16 +158,18 @@ constexpr int CA_FEW_CALLS = 8192;
 // The ratios are formed by workgroups of their own after the first n_add, CA_FOLD calls each: their gathers are random reads,
 // which many compute units do sooner than few.
 constexpr int CA_FOLD = 256;
+__device__ __forceinline__ void hx_commit_fold(const CommitArgs &a, const RatioArgs &rt, int n_add)
+{
+    const int step = ((int)gridDim.x - n_add) * CA_FOLD;
+    if (threadIdx.x >= CA_FOLD) return;
+    for (long long c = ((long long)blockIdx.x - n_add) * CA_FOLD + threadIdx.x; c < a.C; c += step)
+        hx_projected_ratio(rt.node, rt.wf, rt.elapsed, rt.tail, rt.horizon, rt.n_nodes, rt.n_wf, (int)c, rt.best_cost[c], a.status, rt.ratio);
+}
+
 template <int LG>
 __global__ __launch_bounds__(CA_THREADS) void hx_commit_add_kernel(CommitArgs a, RatioArgs rt, int n_add)
 {
-    if ((int)blockIdx.x >= n_add) {
-        const int step = ((int)gridDim.x - n_add) * CA_FOLD;
-        if (threadIdx.x >= CA_FOLD) return;
-        for (long long c = ((long long)blockIdx.x - n_add) * CA_FOLD + threadIdx.x; c < a.C; c += step)
-            hx_projected_ratio(rt.node, rt.wf, rt.elapsed, rt.tail, rt.horizon, rt.n_nodes, rt.n_wf, (int)c, rt.best_cost[c], a.status, rt.ratio);
-        return;
-    }
+    if ((int)blockIdx.x >= n_add) { hx_commit_fold(a, rt, n_add); return; }
     __shared__ unsigned long long s_acc[3 * HX_MAX_INSTANCES];
     const int n_acc = a.P + 2 * a.D;
     const CommitCounters<LG> acc{s_acc};
@@ -221,15 +223,19 @@ int commit_threads(int C) { return C <= CA_FEW_CALLS ? CA_FEW : CA_THREADS; }
 // no ticket.  Same integer results.
 constexpr int COMMIT_ONE_THREADS = 1024;
 // Rounds of at most this many calls are committed by the one-workgroup kernel: no device atomics and their answers, but the
-// lanes of all calls meet in one compute unit's LDS.  One workgroup and several (us; placements spread, all on three
-// instances): 1537 calls 3.3, 4.5 and 4.2, 4.8; 2048 3.4, 5.0 and 4.6, 5.0; 4096 4.5, 7.4 and 4.6, 5.0.
+// calls' bytes pass through one compute unit.  One workgroup and several (us; placements spread, all on three instances): 1537 calls 3.4, 3.5
+// and 4.2, 4.8; 4096 4.3, 4.3 and 4.5, 4.6, but as part of a round, with the ratios beside them, 11.7 and 11.2 (3000 calls 11.3 either way).
 constexpr int HX_COMMIT_ONE_LAUNCH = 2048;
 // From this many calls on eight places a counter and no question whether a wavefront's calls meet (with it 2048 calls 4.4 to 4.8), as long
 // as the places fit LDS; below, clearing and adding up the places takes longer than lanes that meet.
 constexpr int COMMIT_ONE_APART = 512;
+// From this many calls on the ratios are other workgroups': whole rounds of 300, 900, 1500 and 2048 calls 10.2 -> 9.8 us, 10.4 -> 9.9,
+// 10.5 -> 9.7, 12.4 -> 10.7 against all by the one that adds.
+constexpr int COMMIT_ONE_FOLD = 256;
 template <int LG>
 __global__ __launch_bounds__(COMMIT_ONE_THREADS) void hx_commit_one_kernel(CommitArgs a, RatioArgs rt)
 {
+    if (blockIdx.x > 0) { hx_commit_fold(a, rt, 1); return; }
     __shared__ unsigned long long s_acc[LG == 3 ? 2 * 3 * HX_MAX_INSTANCES : 3 * HX_MAX_INSTANCES];
     const int n_acc = a.P + 2 * a.D;
     const CommitCounters<LG> acc{s_acc};
@@ -243,7 +249,7 @@ __global__ __launch_bounds__(COMMIT_ONE_THREADS) void hx_commit_one_kernel(Commi
         const int c = it * COMMIT_ONE_THREADS + threadIdx.x;
         int p = -1, d = -1, L = 0, O = 0;
         if (c < a.C) { p = a.best_p[c]; d = a.best_d[c]; L = a.L_in[c]; O = a.L_out[c]; }
-        if (rt.ratio && c < a.C)
+        if (rt.ratio && gridDim.x == 1 && c < a.C)
             hx_projected_ratio(rt.node, rt.wf, rt.elapsed, rt.tail, rt.horizon, rt.n_nodes, rt.n_wf, c, rt.best_cost[c], a.status, rt.ratio);
         if (!hx_commit_call(a, LG == 3 || a.C <= CA_SINGLY, acc, p, d, L, O)) bad = true;
     }
@@ -488,8 +494,9 @@ int commit_round(hx_ctx *ctx, const hx_calls *calls, const int32_t *best_p, cons
     CommitArgs a{C, P, D, calls->L_in, calls->L_out, best_p, best_d, backlog_tok, used_tok, batch, qd_tok,
                  drain_prefill, drain_decode_q, release_tok, tokens_per_seq, max_batch, ctx->d_acc, ctx->d_status, nullptr};
     if (C <= HX_COMMIT_ONE_LAUNCH) {
-        if (C > COMMIT_ONE_APART && P + 2 * D <= 3 * HX_MAX_INSTANCES / 4) hx_commit_one_kernel<3><<<1, COMMIT_ONE_THREADS, 0, stream>>>(a, rt);
-        else hx_commit_one_kernel<0><<<1, COMMIT_ONE_THREADS, 0, stream>>>(a, rt);
+        const int grid = rt.ratio && C > COMMIT_ONE_FOLD ? 1 + C / CA_FOLD + (C % CA_FOLD != 0) : 1;
+        if (C > COMMIT_ONE_APART && P + 2 * D <= 3 * HX_MAX_INSTANCES / 4) hx_commit_one_kernel<3><<<grid, COMMIT_ONE_THREADS, 0, stream>>>(a, rt);
+        else hx_commit_one_kernel<0><<<grid, COMMIT_ONE_THREADS, 0, stream>>>(a, rt);
         return hx_check_launch(ctx, "hx_commit_one_kernel");
     }
     const int threads = commit_threads(C);
