@@ -38,11 +38,9 @@ def search_ops(C, P, D, T):
     return float(C) * (21 * P + 13.5 * D + 3 * T * T)
 
 
-# Vector ops of the decode-stage search for one (call, instance) pair.  A free call goes through the instance's
-# first-room table: 6 per step of the bisection for its threshold's rank, 8 per stretch of the timeline, 24 for
-# the call's decode time, threshold and the comparison with its best so far.  A locked call scans its one
-# instance's timeline entry by entry, 7 per entry.
-DECODE_OPS_BISECT_STEP, DECODE_OPS_STRETCH, DECODE_OPS_PAIR, DECODE_OPS_ENTRY = 6.0, 8.0, 24.0, 7.0
+# Vector ops of the decode-stage search.  Every free (call, instance) pair is bounded by its decode time: 7 for that, whether the call
+# fits at all, and the minimum.  A call looks at one timeline at least, entry by entry: 3 each (room, a run's end, far enough).
+DECODE_OPS_BOUND, DECODE_OPS_ENTRY = 7.0, 3.0
 HBM_PEAK_GBS = 8000.0
 
 
@@ -56,7 +54,7 @@ def source_sha(files):
 
 
 FUSED_SOURCES = ("hx_score.hip", "hx_search.hpp", "hx_terms.hpp", "hx_common.hpp", "hx_cp.hpp", "hx_append.hpp")
-CP_SOURCES = ("hx_dag.hip", "hx_cp.hpp", "hx_append.hpp", "hx_terms.hpp", "hx_common.hpp")
+CP_SOURCES = ("hx_dag.hip", "hx_cp.hpp", "hx_search.hpp", "hx_append.hpp", "hx_terms.hpp", "hx_common.hpp")
 
 
 def profiled_traffic(summary, sources, key="traffic_bytes_per_launch"):
@@ -412,30 +410,22 @@ def decode_leg(torch, ctx, synth, binding, seed):
     ctx.hx_stream_status()
     n_free, locked_on = int((lock < 0).sum()), np.bincount(lock[lock >= 0], minlength=D)
     legal = n_free * D + int((lock >= 0).sum())
-    # per instance: timeline entries = distinct event times from now on (the past folds onto now), and
-    # stretches = 1 + the entries where occupancy rises
+    # per instance: timeline entries = now and the events that lie ahead
     K = iv["stride"]
-    n_tl, m_tl = np.zeros(D, np.int64), np.zeros(D, np.int64)
+    n_tl = np.zeros(D, np.int64)
     for d in range(D):
         k = int(iv["count"][d])
-        st = np.maximum(iv["start"][d * K:d * K + k].astype(np.float64), 0.0)
-        en = np.maximum(iv["end"][d * K:d * K + k].astype(np.float64), 0.0)
-        tk = iv["tok"][d * K:d * K + k].astype(np.int64)
-        t = np.unique(np.concatenate([[0.0], st, en]))
-        occ = np.array([tk[(st <= x) & (x < en)].sum() for x in t])
-        n_tl[d], m_tl[d] = t.size, 1 + int((occ[1:] > occ[:-1]).sum())
-    table = (n_tl <= 512) & (m_tl * (n_tl + 1) <= 4096)
-    per_free = np.where(table, DECODE_OPS_BISECT_STEP * np.ceil(np.log2(n_tl + 1)) + DECODE_OPS_STRETCH * m_tl, DECODE_OPS_ENTRY * n_tl) \
-        + DECODE_OPS_PAIR
-    ops = float(n_free * per_free.sum() + (locked_on * (DECODE_OPS_ENTRY * n_tl + DECODE_OPS_PAIR)).sum())
+        st, en, tk = (iv[x][d * K:d * K + k] for x in ("start", "end", "tok"))
+        holds = (st < en) & (tk > 0) & (en > 0)
+        n_tl[d] = 1 + int(holds.sum()) + int((holds & (st > 0)).sum())
+    ops = DECODE_OPS_BOUND * n_free * D + DECODE_OPS_ENTRY * (n_free * float(n_tl.mean()) + float((locked_on * n_tl).sum()))
     out["one pass"] = {"workload": "%d calls x %d instances, %d..%d intervals each, %d%% of the calls locked"
                                    % (Q, D, int(iv["count"].min()), int(iv["count"].max()), round(100 * float((lock >= 0).mean()))),
                        "score_us": score_s * 1e6, "score_and_rank_us": both_s * 1e6,
                        "legal_pairs": legal, "legal_pairs_per_s": legal / score_s,
-                       "timeline_entries_mean": float(n_tl.mean()), "stretches_mean": float(m_tl.mean()),
-                       "instances_searched_by_table": int(table.sum()),
-                       "roofline": {"kernel": "hx_decode_timeline_kernel + hx_decode_score_kernel + hx_decode_finish_kernel", "bound": "alu",
-                                    "ops_per_free_pair_mean": float(per_free.mean()), "achieved": ops / score_s / 1e12,
+                       "timeline_entries_mean": float(n_tl.mean()),
+                       "roofline": {"kernel": "hx_decode_occupancy_kernel + hx_decode_best_kernel", "bound": "alu",
+                                    "ops": ops, "achieved": ops / score_s / 1e12,
                                     "peak": ALU_PEAK_TOPS, "unit": "T lane-ops/s", "frac": ops / score_s / 1e12 / ALU_PEAK_TOPS},
                        "waiting_fraction_of_placed": float(((bs > 0) & (bd >= 0)).float().sum().item() / max(1, int((bd >= 0).sum().item())))}
     rng = np.random.default_rng(seed)
