@@ -93,7 +93,9 @@ __device__ __forceinline__ void hx_enqueue(const AppendArgs &a, int u)
 // carries is its own path and not what it finds (only further parents wait for theirs); and the wavefronts are spread
 // over the compute units.  72 K new nodes beside a search of 23 us: 40 us with a round trip of device atomics a level, each
 // answer part of the next raise, and a horizon raised at every visit; now 30 (on their own 33 -> 27).  The refresh of 812 K
-// nodes, where every node walked and raised four values: 157 us, now 44.  (Eight first parents at a time: 42 and 60, most of
+// nodes, where every node walked and raised four values: 157 us, now 44.  A walk visits 1.6 nodes on the average, but the longest in a
+// wavefront five or six further parents, one after the other: where it has ended, what it needs to go on from the nearest second
+// parent comes with that one's raise, its record with the next four (30 -> 28 beside the search, the refresh 44 -> 41).  (Eight first parents at a time: 42 and 60, most of
 // what they ask for lies above the point where a walk stops; two: as four.  Further parents queued in LDS for any idle lane
 // of the wavefront: 30 and 59, three times the code.)
 //
@@ -119,13 +121,14 @@ __device__ __forceinline__ void hx_append_relax_body(const AppendArgs &a, int bl
         int sp = 0, steps = 0;
         int v = a.n_old + i;
         if (REFRESH && a.leaves && a.level[v] != 0) continue;
-        int4 me = a.rec[v], above = a.chain[v];
-        float t = 0.0f;
-        if (REFRESH && !a.leaves) t = __int_as_float(max(__hip_atomic_load((const int *)&a.tail[v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), 0));
-        float r = hx_node_rec_cost(me) + t;                  // rem of v as far as this walk knows
+        int4 above = a.chain[v];
+        float t = 0.0f;                                      // tail and level of v as far as this walk knows
         int lv = 0;
+        bool raise_rem = false;                              // rem of v is to be raised with them (else it has been)
+        if (REFRESH && !a.leaves) t = __int_as_float(max(__hip_atomic_load((const int *)&a.tail[v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), 0));
         for (;;) {
             const int up[HX_CHAIN] = {above.x, above.y, above.z, above.w};
+            const int4 me = a.rec[v];
             int4 rec[HX_CHAIN];
             int tl[HX_CHAIN], lvl[HX_CHAIN];
 #pragma unroll
@@ -137,48 +140,58 @@ __device__ __forceinline__ void hx_append_relax_body(const AppendArgs &a, int bl
             }
             if (up[HX_CHAIN - 1] >= 0) above = a.chain[up[HX_CHAIN - 1]];
             // up the chain: source k is v or up[k - 1], its first parent up[k]
-            int q[HX_CHAIN], src_lv[HX_CHAIN];
+            float r = hx_node_rec_cost(me) + t;
+            if (!REFRESH && raise_rem) hx_raise_max_f32(&a.rem[v], r);
+            int q[HX_CHAIN];
             float src_r[HX_CHAIN];
             bool live = true, tail_up = true;
             unsigned many = 0;
 #pragma unroll
             for (int k = 0; k < HX_CHAIN; ++k) {
                 const int4 src = k ? rec[k ? k - 1 : 0] : me;
-                q[k] = live ? src.z : -1; src_r[k] = r; src_lv[k] = lv;
+                q[k] = live ? src.z : -1; src_r[k] = r;
                 many |= live && (src.w & HX_NODE_MANY) ? 1u << k : 0u;
                 if (!REFRESH && tail_up && (src.w & HX_NODE_TOP) && src.y >= 0) hx_raise_max_f32(&a.horizon[src.y], r);
-                const int t = up[k];
-                live = live && t >= 0;
+                const int u = up[k];
+                live = live && u >= 0;
                 tail_up = live && __float_as_int(r) > tl[k];
-                const bool level_up = !REFRESH && live && lv + 1 > lvl[k];
-                if (tail_up) atomicMax((int *)&a.tail[t], __float_as_int(r));
-                if (level_up) atomicMax(&a.level[t], lv + 1);
+                const bool level_up = !REFRESH && live && lv + k + 1 > lvl[k];
+                if (tail_up) atomicMax((int *)&a.tail[u], __float_as_int(r));
+                if (level_up) atomicMax(&a.level[u], lv + k + 1);
                 r = hx_node_rec_cost(rec[k]) + r;
-                lv += 1;
-                if (!REFRESH && tail_up) hx_raise_max_f32(&a.rem[t], r);
+                if (!REFRESH && tail_up) hx_raise_max_f32(&a.rem[u], r);
                 live = tail_up || level_up;
                 steps += live;
             }
-            // second parents, then the others of nodes with more
-            int old_t[HX_CHAIN], old_l[HX_CHAIN];
+            // second parents, then the others of nodes with more.  What a walk that has ended needs to go on from the first of the
+            // second parents is asked for along with the raises' answers.
+            int old_t[HX_CHAIN], old_l[HX_CHAIN], pick = -1;
 #pragma unroll
-            for (int k = 0; k < HX_CHAIN; ++k)
+            for (int k = HX_CHAIN - 1; k >= 0; --k)
                 if (q[k] >= 0) {
                     old_t[k] = atomicMax((int *)&a.tail[q[k]], __float_as_int(src_r[k]));
-                    if (!REFRESH) old_l[k] = atomicMax(&a.level[q[k]], src_lv[k] + 1);
+                    if (!REFRESH) old_l[k] = atomicMax(&a.level[q[k]], lv + k + 1);
+                    pick = q[k];
                 }
+            if (!live && pick >= 0) above = a.chain[pick];
+            int next_t = -1, next_lv = 0;                    // the picked one's tail (-1: not raised) and level
             auto wait = [&](int node) {
                 if (steps >= RELAX_STEPS || sp >= RELAX_STACK) hx_enqueue(a, node);
                 else stack[sp++] = node;
             };
 #pragma unroll
             for (int k = 0; k < HX_CHAIN; ++k)
-                if (q[k] >= 0 && (__float_as_int(src_r[k]) > old_t[k] || (!REFRESH && src_lv[k] + 1 > old_l[k]))) wait(q[k]);
+                if (q[k] >= 0 && (__float_as_int(src_r[k]) > old_t[k] || (!REFRESH && lv + k + 1 > old_l[k]))) {
+                    if (!live && steps < RELAX_STEPS && q[k] == pick) {
+                        next_t = max(next_t, max(__float_as_int(src_r[k]), old_t[k]));
+                        if (!REFRESH) next_lv = max(next_lv, max(lv + k + 1, old_l[k]));
+                    } else wait(q[k]);
+                }
             for (; many; many &= many - 1) {
                 const int k = __builtin_ctz(many);
                 const int s = k == 0 ? v : k == 1 ? up[0] : k == 2 ? up[1] : up[2];
                 const float s_r = k == 0 ? src_r[0] : k == 1 ? src_r[1] : k == 2 ? src_r[2] : src_r[3];
-                const int s_lv = src_lv[0] + k;
+                const int s_lv = lv + k;
                 const int32_t *others = a.pcol + a.prow[s] + 2;
                 for (int left = a.prow[s + 1] - a.prow[s] - 2; left > 0; left -= RELAX_MANY, others += RELAX_MANY) {
                     int p[RELAX_MANY], p_t[RELAX_MANY], p_l[RELAX_MANY];
@@ -197,19 +210,23 @@ __device__ __forceinline__ void hx_append_relax_body(const AppendArgs &a, int bl
             }
             if (live) {
                 v = up[HX_CHAIN - 1];
-                if (steps < RELAX_STEPS) { me = rec[HX_CHAIN - 1]; continue; }
+                if (steps < RELAX_STEPS) { t = src_r[HX_CHAIN - 1]; lv += HX_CHAIN; raise_rem = false; continue; }
                 hx_enqueue(a, v);
+            }
+            raise_rem = true;
+            ++steps;
+            if (next_t >= 0) {
+                v = pick;
+                t = __int_as_float(next_t);
+                lv = next_lv;
+                continue;
             }
             if (sp == 0) break;
             // a further parent, with what it holds by now
             v = stack[--sp];
-            ++steps;
-            me = a.rec[v]; above = a.chain[v];
-            r = hx_node_rec_cost(me) + __hip_atomic_load(&a.tail[v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (!REFRESH) {
-                lv = __hip_atomic_load(&a.level[v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                hx_raise_max_f32(&a.rem[v], r);
-            }
+            above = a.chain[v];
+            t = __hip_atomic_load(&a.tail[v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (!REFRESH) lv = __hip_atomic_load(&a.level[v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
 }

@@ -544,6 +544,53 @@ def test_append_of_a_node_with_parents(ctx, parents, odd):
         ctx.hx_stream_status()
 
 
+# a walk that has ended goes on from the nearest second parent it raised: one for several nodes above, each its own, the nearest one with
+# nothing to raise, and a row of them, one walk along it up to and beyond the walk's 1024 steps
+@pytest.mark.parametrize("kind", ["shared", "own", "nearest higher", "row"])
+@pytest.mark.parametrize("above", [1, 2, 3, 4, 5, 8, 9])
+def test_append_goes_on_from_second_parents(ctx, kind, above):
+    rng = np.random.default_rng(above)
+    if kind == "row":                                        # first parent the root, which the first child raises; second the node before
+        n = {1: 3, 2: 5, 3: 64, 4: 1023, 5: 1024, 8: 1025, 9: 1500}[above] + 2
+        parents, sizes = [[], [0]] + [[0, v - 1] for v in range(2, n)], [n]
+    else:                                                    # rows over a root; on them a chain, each node a second parent at a row's end; below it a node
+        rows, parents = above if kind == "own" else 1 if kind == "shared" else 2, [[]]
+        for k in range(rows):
+            for j in range(5):
+                parents.append([0 if j == 0 else len(parents) - 1])
+        ends = [5 * (k + 1) for k in range(rows)]
+        for k in range(above):
+            parents.append([len(parents) - 1 if k else 0, ends[(above - 1 - k) % rows]])
+        parents.append([len(parents) - 1])
+        n = len(parents)
+        sizes = [n - 1, 1]
+    row = np.cumsum([0] + [len(p) for p in parents]).astype(np.int32)
+    col = np.array([u for p in parents for u in p], np.int32)
+    cost = rng.uniform(0.5, 2.0, n).astype(np.float32)
+    if kind == "nearest higher":
+        sizes = [n - 1, 1, 1]
+        row = np.append(row, row[-1] + 1).astype(np.int32)   # first a child of the nearest second parent that no path through the chain exceeds
+        col = np.append(col[:row[n - 1]], [ends[0], col[-1]]).astype(np.int32)
+        cost = np.append(cost, cost[:1]).astype(np.float32)
+        cost[n - 1] = 1000.0
+        n += 1
+    wf = np.zeros(n, np.int32)
+    ctx.hx_dag_reserve(n, col.size, 1, n)
+    v = 0
+    for k in sizes:
+        ctx.hx_dag_append(dev(row[v:v + k + 1] - row[v]), dev(col[row[v]:row[v + k]]), dev(cost[v:v + k]), dev(wf[v:v + k]))
+        v += k
+    for again in (False, True):
+        ctx.hx_stream_status()
+        want = o.critical_path_by_parents(row, col, cost.astype(np.float64), wf, 1, round_f32=True)
+        got = view(ctx, n, 1)
+        assert np.array_equal(got[2], want[2])
+        for k in (0, 1, 3):
+            assert np.array_equal(got[k].astype(np.float64), want[k]), k
+        cost[n - 1] = 3.0
+        ctx.hx_dag_set_cost(dev(np.array([n - 1], np.int32)), dev(cost[n - 1:]))
+
+
 def wide_graph(kind):
     """Parent lists (row, col) of graphs whose nodes without children are few and whose nodes have several parents."""
     rng = np.random.default_rng(len(kind))
