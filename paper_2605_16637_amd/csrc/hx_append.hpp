@@ -94,9 +94,10 @@ __device__ __forceinline__ void hx_enqueue(const AppendArgs &a, int u)
 // over the compute units.  72 K new nodes beside a search of 23 us: 40 us with a round trip of device atomics a level, each
 // answer part of the next raise, and a horizon raised at every visit; now 30 (on their own 33 -> 27).  The refresh of 812 K
 // nodes, where every node walked and raised four values: 157 us, now 44.  A walk visits 1.6 nodes on the average, but the longest in a
-// wavefront five or six further parents, one after the other: where it has ended, what it needs to go on from the nearest second
-// parent comes with that one's raise, its record with the next four (30 -> 28 beside the search, the refresh 44 -> 41).  (Eight first parents at a time: 42 and 60, most of
-// what they ask for lies above the point where a walk stops; two: as four.  Further parents queued in LDS for any idle lane
+// wavefront five or six further parents, one after the other: where it has ended, what it needs to go on from the highest second
+// parent comes with that one's raise, its record with the next four (30 -> 28 beside the search, the refresh 44 -> 41).  The highest, as
+// it carries the longest path: from the nearest, 20 graphs of 1000 nodes with up to three parents 5.0 -> 6.1 ms (now 4.9).
+// (Eight first parents at a time: 42 and 60, most of what they ask for lies above the point where a walk stops; two: as four.  Further parents queued in LDS for any idle lane
 // of the wavefront: 30 and 59, three times the code.)
 //
 // REFRESH: all costs new, levels as they are.  The walks raise tails alone; rem and the horizons follow from those in a pass of
@@ -163,11 +164,11 @@ __device__ __forceinline__ void hx_append_relax_body(const AppendArgs &a, int bl
                 live = tail_up || level_up;
                 steps += live;
             }
-            // second parents, then the others of nodes with more.  What a walk that has ended needs to go on from the first of the
-            // second parents is asked for along with the raises' answers.
+            // second parents, then the others of nodes with more.  What a walk that has ended needs to go on from the highest
+            // of the second parents is asked for along with the raises' answers.
             int old_t[HX_CHAIN], old_l[HX_CHAIN], pick = -1;
 #pragma unroll
-            for (int k = HX_CHAIN - 1; k >= 0; --k)
+            for (int k = 0; k < HX_CHAIN; ++k)
                 if (q[k] >= 0) {
                     old_t[k] = atomicMax((int *)&a.tail[q[k]], __float_as_int(src_r[k]));
                     if (!REFRESH) old_l[k] = atomicMax(&a.level[q[k]], lv + k + 1);

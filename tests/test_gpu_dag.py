@@ -544,9 +544,9 @@ def test_append_of_a_node_with_parents(ctx, parents, odd):
         ctx.hx_stream_status()
 
 
-# a walk that has ended goes on from the nearest second parent it raised: one for several nodes above, each its own, the nearest one with
-# nothing to raise, and a row of them, one walk along it up to and beyond the walk's 1024 steps
-@pytest.mark.parametrize("kind", ["shared", "own", "nearest higher", "row"])
+# a walk that has ended goes on from the highest second parent above it: one for several nodes, each its own, some with nothing
+# to raise, and a row of them, one walk along it up to and beyond the walk's 1024 steps
+@pytest.mark.parametrize("kind", ["shared", "own", "some higher", "row"])
 @pytest.mark.parametrize("above", [1, 2, 3, 4, 5, 8, 9])
 def test_append_goes_on_from_second_parents(ctx, kind, above):
     rng = np.random.default_rng(above)
@@ -567,9 +567,9 @@ def test_append_goes_on_from_second_parents(ctx, kind, above):
     row = np.cumsum([0] + [len(p) for p in parents]).astype(np.int32)
     col = np.array([u for p in parents for u in p], np.int32)
     cost = rng.uniform(0.5, 2.0, n).astype(np.float32)
-    if kind == "nearest higher":
+    if kind == "some higher":
         sizes = [n - 1, 1, 1]
-        row = np.append(row, row[-1] + 1).astype(np.int32)   # first a child of the nearest second parent that no path through the chain exceeds
+        row = np.append(row, row[-1] + 1).astype(np.int32)   # first a child of one of the second parents that no path through the chain exceeds
         col = np.append(col[:row[n - 1]], [ends[0], col[-1]]).astype(np.int32)
         cost = np.append(cost, cost[:1]).astype(np.float32)
         cost[n - 1] = 1000.0
