@@ -614,9 +614,14 @@ __global__ __launch_bounds__(256) void hx_refresh_end_kernel(AppendArgs a)
     if ((me.w & HX_NODE_TOP) && me.y >= 0) hx_raise_max_f32(&a.horizon[me.y], r);
 }
 
-__global__ __launch_bounds__(256) void hx_fill_i32_kernel(int32_t *p, size_t n, int32_t v)
+// An empty graph: the horizon of every workflow 0, the first row's bound 0, the list counters 0.  (One launch: behind the wait for
+// the device the host is what the next kernels wait for.)
+__global__ __launch_bounds__(256) void hx_reserve_kernel(float *horizon, size_t n_wf, int32_t *row_ptr, int32_t *counters)
 {
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = v;
+    const size_t at = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
+    if (at == 0) row_ptr[0] = 0;
+    if (at < 4) counters[at] = 0;
+    for (size_t i = at; i < n_wf; i += (size_t)gridDim.x * blockDim.x) horizon[i] = 0.0f;
 }
 
 template <typename T>
@@ -851,11 +856,8 @@ extern "C" int hx_dag_reserve(hx_ctx *ctx, int32_t max_nodes, int32_t max_edges,
     if (!keep) { g.room_nodes = max_nodes; g.room_edges = max_edges; g.room_wf = max_wf; }
     g.cap_nodes = max_nodes; g.cap_edges = max_edges; g.cap_wf = max_wf; g.max_depth = max_depth;
     g.n_nodes = 0; g.n_edges = 0; g.epoch = 0;
-    // horizon of every workflow starts at 0; parent_row_ptr[0] = 0 (fill kernels, no memset nodes)
-    hx_fill_i32_kernel<<<256, 256, 0, stream>>>((int32_t *)g.horizon, W, 0);
-    hx_fill_i32_kernel<<<1, 64, 0, stream>>>(g.parent_row_ptr, 1, 0);
-    hx_fill_i32_kernel<<<1, 64, 0, stream>>>(g.counters, 4, 0);
-    return hx_check_launch(ctx, "hx_fill_i32_kernel");
+    hx_reserve_kernel<<<256, 256, 0, stream>>>(g.horizon, W, g.parent_row_ptr, g.counters);      // (a kernel, no memset nodes)
+    return hx_check_launch(ctx, "hx_reserve_kernel");
 }
 
 namespace {
