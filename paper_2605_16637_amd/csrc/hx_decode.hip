@@ -824,7 +824,8 @@ __global__ __launch_bounds__(64) void hx_decode_finish_kernel(DecodeFinishArgs a
 // 2.9 and 1.9 us for the first and the second call of a wavefront.  That pass (as many calls locked as free): the occupancies
 // 15.6 -> 6.7 us, the search 29.4 -> 13.8 and no third kernel of 4.8, against all pairs through tables of first moments with room;
 // 500 calls on 1024 instances 63 -> 22, 500 on 300 with lists of 250 that are full for ten seconds 108 -> 53.  Slower where rooms
-// come in pieces that are shorter than any decode time: 2000 calls on 64 such instances 24 -> 44, 300 on 1024 86 -> 180.
+// come in pieces that are shorter than any decode time: 2000 calls on 64 such instances 24 -> 30, 300 on 1024 83 -> 129 (33 and 163 when every
+// lane read two entries at a time of the instances it has left; eight entries of four of them at a time: as of one).
 
 // Up to some moment no more than `room` tokens have been free, and `time_bits` is when that may change: as the upper halves of two
 // floats, the first as its complement.  A call that needs more than the room has no start before that time; by halves, as far as the two
@@ -1117,17 +1118,23 @@ __global__ __launch_bounds__(DB_THREADS) void hx_decode_best_kernel(DecodeArgs a
                         const int thr = threshold(x.w), n = on ? o.meta[8 * dl] : 0;
                         const float T = time_on(x);
                         const int4 *e = (const int4 *)(o.e + (size_t)dl * nt);
+                        // (eight entries at a time: a lane's are the lines of its own instance, and a round trip brings them all)
                         float rs = INFINITY, got = INFINITY;
-                        int4 q = e[0];
-                        for (int i = 0; __builtin_amdgcn_ballot_w64(i < n && !(got < INFINITY)) != 0; i += 2) {
-                            const int4 next = e[i < n ? (i >> 1) + 1 : 0];
-                            const float before = got;
-                            rs = q.y <= thr ? fminf(rs, __int_as_float(q.x)) : INFINITY;
-                            got = fminf(got, __int_as_float(q.z) >= rs + T ? rs : INFINITY);
-                            rs = q.w <= thr ? fminf(rs, __int_as_float(q.z)) : INFINITY;
-                            got = fminf(got, __int_as_float(next.x) >= rs + T ? rs : INFINITY);
+                        for (int i = 0; __builtin_amdgcn_ballot_w64(i < n && !(got < INFINITY)) != 0; i += 8) {
+                            const int4 *g = e + (i < n ? i >> 1 : 0);
+                            int4 q[4];
+#pragma unroll
+                            for (int u = 0; u < 4; ++u) q[u] = g[u];
+                            const float after = __int_as_float(g[4].x), before = got;
+#pragma unroll
+                            for (int u = 0; u < 4; ++u) {
+                                const float then = u < 3 ? __int_as_float(q[u < 3 ? u + 1 : 3].x) : after;
+                                rs = q[u].y <= thr ? fminf(rs, __int_as_float(q[u].x)) : INFINITY;
+                                got = fminf(got, __int_as_float(q[u].z) >= rs + T ? rs : INFINITY);
+                                rs = q[u].w <= thr ? fminf(rs, __int_as_float(q[u].z)) : INFINITY;
+                                got = fminf(got, then >= rs + T ? rs : INFINITY);
+                            }
                             got = i < n ? got : before;
-                            q = next;
                         }
                         if (on && got + T < v) { v = got + T; S = got; at = dl; }
                     }

@@ -188,6 +188,7 @@ def _crowd(iv, dec, kind):
 @pytest.mark.parametrize("Q,D,res,plan,kind", [(48, 1, 62, 0, ""), (300, 2, 63, 0, "late"), (300, 63, 64, 0, "late"), (200, 64, 127, 0, "late"),
                                                (150, 65, 128, 20, "late"), (700, 256, 30, 90, ""), (150, 257, 40, 20, "same"),
                                                (100, 1024, 12, 6, "late"), (200, 64, 28, 0, "pieces"), (120, 300, 70, 0, "pieces"),
+                                               (60, 40, 3, 0, "pieces"), (60, 70, 4, 0, "pieces"), (60, 40, 7, 0, "pieces"), (60, 20, 8, 0, "pieces"),
                                                (300, 20, 24, 24, "empty"), (200, 3, 300, 211, "same"), (13000, 40, 20, 10, "")])
 def test_best_alone_is_the_best_of_the_pairs(ctx, Q, D, res, plan, kind):
     """Without the matrices few pairs are looked at; best instance, start, cost and ratio are those of the pass that forms all of them
