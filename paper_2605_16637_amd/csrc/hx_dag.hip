@@ -968,12 +968,12 @@ int hx_dag_append_begin(hx_ctx *ctx, const hx_model *model, int32_t n_new, int32
 }
 
 // A refresh of a graph of more than this many nodes for every compute unit starts at the nodes without children, if it has at most
-// two edges a node; else every node walks.  Fewer walks count where the device cannot work on all of them at a time: with every node
-// and so, 812 K nodes of a live system's workflows 71 and 44 us, 200 K nodes of trees 26 and 19, 800 K nodes of 1.7 edges
-// 243 and 174; 80 K nodes of trees 17 and 15, 20 K of 1.1 edges 59 and 85, 6 K of 1.2 9 and 17 ms.  But a walk from below reaches a
-// node once for every path that still raises it, one thread for all above a leaf: 800 K nodes of 2.3 edges 427 and 391 us, of 3.3 1.1 and
-// 3.3 ms; 20 graphs of 40 layers of 10 3.3 and 8, 20 of 1000 nodes with up to three parents 8.9 and 54 (4.0 and 44 when every
-// node's walk raised four values and waited at each).
+// two edges a node; else every node walks.  Fewer walks count where the device cannot work on all of them at a time: whole refreshes with every
+// node and so, 812 K nodes of a live system's workflows 67 and 63 us, 200 K nodes of trees 25 and 20, 800 K nodes of 1.4 edges
+// 164 and 83, of 1.6 191 and 116, of 2.0 228 and 167; 80 K nodes of trees 19 and 17, 20 K of 1.0 edges 24 and 21.  But a walk from below reaches a
+// node once for every path that still raises it, one thread for all above a leaf: 20 graphs of 40 layers of 10 3.2 and
+// 7.9 ms, 20 of 1000 nodes with up to three parents (1.8 edges a node) 4.7 and 9.7; with walks that read a further parent back from
+// the stack, 800 K nodes of 2.3 edges 427 and 391 us, of 3.3 1.1 and 3.3 ms, 6 K of 1.2 9 and 17.
 constexpr int REFRESH_LEAVES_NODES = 512;
 
 extern "C" int hx_dag_set_cost(hx_ctx *ctx, int32_t n, const int32_t *node_ids, const float *cost, void *stream_)
