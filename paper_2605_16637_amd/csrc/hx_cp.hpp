@@ -135,7 +135,7 @@ struct CpArgs {
 };
 
 constexpr int CP_THREADS = 256;      // threads per block
-constexpr int CP_WPB = 64;           // at most this many workflows per block, one walking lane each
+constexpr int CP_WPB = 64;           // at most this many workflows per run, one walking lane each: what the last wavefront of a block has
 constexpr int CP_NMAX = 1400;        // nodes staged per block
 constexpr int CP_NMAX_COST = 1344;   // the same where the block also holds the class tables of the node cost
 constexpr int CP_DEG = 4;            // successors a walking lane combines per step
@@ -215,7 +215,8 @@ __device__ __forceinline__ bool hx_cp_walk(const CpArgs &a, char *base, int n0, 
 //         workflow of the same block -- shows in the largest offset the lane
 //         has followed.  tail takes the place of the node's first successors.
 //  store  every thread writes rem, level and tail of a few nodes, coalesced.
-// Workflows that together exceed CP_NMAX nodes are taken in several runs, each
+// Workflows that together exceed CP_NMAX nodes, or are more than CP_WPB (a caller
+// may hand a block any number of them), are taken in several runs, each
 // as long as fits, one after the other; a single workflow of more than CP_NMAX
 // nodes is walked in global memory by one lane (and so is every workflow, a
 // lane each, of a graph with fewer than CP_DEG edges in all).
@@ -232,6 +233,7 @@ __device__ __forceinline__ void hx_cp_local_body(const CpArgs &a, int wpb, CpNod
     bool tab_ready = !COST;
     constexpr int CP_NMAX = NMAX;             // nodes staged per run
     constexpr int CP_NPT = (NMAX + NT - 1) / NT;
+    static_assert(CP_WPB <= HX_WAVE && NT % HX_WAVE == 0, "a walking lane for every workflow of a run, whichever wavefront has them");
     const int tid = threadIdx.x;
     const int w0 = block * wpb;
     const int w1 = min(w0 + wpb, a.n_wf);
@@ -243,13 +245,13 @@ __device__ __forceinline__ void hx_cp_local_body(const CpArgs &a, int wpb, CpNod
 
     // the first run's bounds are read before anything is written: uniform loads of memory the kernel
     // has not touched go through the scalar cache
-    const int n0_first = w0 < w1 ? a.wf_ptr[w0] : 0, n1_first = w0 < w1 ? a.wf_ptr[w1] : 0;
+    const int n0_first = w0 < w1 ? a.wf_ptr[w0] : 0, n1_first = w0 < w1 ? a.wf_ptr[min(w1, w0 + CP_WPB)] : 0;
     for (int wa = w0; wa < w1;) {
         // the run [wa, wb): normally all of the block's workflows
-        int wb = w1;
+        int wb = min(w1, wa + CP_WPB);
         // a walking lane's own bounds are asked for together with the run's (none of them waits for the other)
         int ws = 0, we = 0;
-        if (wl >= 0 && wl < w1 - wa) { ws = a.wf_ptr[wa + wl]; we = a.wf_ptr[wa + wl + 1]; }
+        if (wl >= 0 && wl < wb - wa) { ws = a.wf_ptr[wa + wl]; we = a.wf_ptr[wa + wl + 1]; }
         const int n0 = wa == w0 ? n0_first : a.wf_ptr[wa];
         int n1 = wa == w0 ? n1_first : a.wf_ptr[wb];
         if (n0 >= 0 && n1 >= n0 && n1 - n0 > CP_NMAX) {

@@ -71,7 +71,8 @@ void hx_cp_local_kernel(CpArgs a, int wpb)
 // staging with the cost's sums in flight takes 102 registers, four wavefronts a SIMD; the launch is
 // meant for the graphs of a scheduling round (tens of thousands of nodes, spread over all compute
 // units), where the latency of a launch counts and residency does not.
-// WAVES: `wpv` workflows to a wavefront where all of a workgroup's are small enough (hx_cp_wave).
+// WAVES: `wpv` workflows to a wavefront where all of a workgroup's are small enough (hx_cp_wave); else the workgroup
+// takes its `wpb` = 4 * wpv workflows, which may be more than CP_WPB, in runs of at most that many.
 template <bool WAVES>
 __global__ __launch_bounds__(CP_THREADS)
 void hx_cp_cost_kernel(CpArgs a, NodeCostArgs nc, int wpb, int wpv)

@@ -427,7 +427,7 @@ __global__ __launch_bounds__(FS_THREADS) void hx_fused_search_kernel(ScoreArgs a
 //
 // The horizon refresh (node cost + critical path, what hx_cp_cost_kernel does) and the search do not depend on each
 // other -- only the ratio needs both, and it is formed by the commit kernel that follows -- so they share a launch:
-// the first n_reveal workgroups take workflows exactly as hx_cp_cost_kernel's do (same body, a node per thread, the
+// the first n_reveal workgroups take workflows exactly as hx_cp_cost_kernel's do (same bodies, a node per lane or thread, the
 // cost's decode classes one after the other to stay within the search's registers), the others search.  Same
 // results as the two kernels, one launch and the gap before it less: both halves are chains of memory round trips,
 // which run side by side.  The reveal's chain is the longer one, so its workgroups come first.  Six wavefronts a SIMD, so that

@@ -67,3 +67,21 @@ def assert_search_matches(rnd_model, L_in, L_out, pre, dec, links, ores, gp, gd,
         assert np.isfinite(alt) and alt <= ores.best_cost[i] * (1 + REL), \
             f"call {c}: GPU chose ({gp[i]},{gd[i]}) cost {alt}, oracle ({ores.best_p[i]},{ores.best_d[i]}) cost {ores.best_cost[i]}"
     return len(diff)
+
+
+def many_small_workflows(n_wf, size, large, stride):
+    """Row and workflow bounds and successors of n_wf workflows of `size` nodes, but of `large` one in each odd run of `stride` workflows, at another place in each; a node's successors are the next two of its workflow."""
+    sizes = np.full(n_wf, size, np.int64)
+    runs = np.arange(1, n_wf // stride, 2)
+    sizes[runs * stride + runs * 7 % stride] = large
+    wf_ptr = np.concatenate([[0], np.cumsum(sizes)])
+    v, end = np.arange(wf_ptr[-1]), np.repeat(wf_ptr[1:], sizes)
+    there = v[:, None] + np.array([1, 2]) < end[:, None]
+    row_ptr = np.concatenate([[0], np.cumsum(there.sum(1))])
+    return row_ptr.astype(np.int32), (v[:, None] + np.array([1, 2]))[there].astype(np.int32), wf_ptr.astype(np.int32)
+
+
+# (workflows, nodes of each, of the large ones, workflows to an odd run): many workflows a wavefront and several runs a workgroup, some of
+# which have a workflow that no wavefront can take; runs as long as the workgroups', so that each of their numbers is met
+FALLBACKS = [(18432, 4, 65, 36), (18432, 4, 65, 72), (40000, 2, 65, 76), (40000, 2, 200, 300), (70000, 1, 65, 128), (70000, 1, 65, 256),
+             (20000, 0, 65, 128)]

@@ -6,7 +6,7 @@ import pytest
 
 from oracle import hx_oracle as o
 from paper_2605_16637_amd import synth
-from gpu_helpers import assert_costs_close, dev
+from gpu_helpers import FALLBACKS, assert_costs_close, dev, many_small_workflows
 
 pytestmark = pytest.mark.gpu
 
@@ -316,6 +316,37 @@ def test_small_workflows_by_wavefronts(ctx, sizes, fan_out, seed):
     for x, y in zip(back[:3], got[:3]):
         assert np.array_equal(x[to], y)
     assert np.array_equal(back[3], got[3])
+
+
+@pytest.mark.parametrize("graph", FALLBACKS)
+def test_workgroups_with_a_workflow_too_large_for_a_wavefront(ctx, graph):
+    """Many small workflows, some of a workgroup's too large for its wavefronts: every workflow of that workgroup is walked all the same."""
+    rng = np.random.default_rng(graph[0])
+    rnd = synth.make_round("tiny", 1)
+    row_ptr, col, wf_ptr = many_small_workflows(*graph)
+    n = len(row_ptr) - 1
+    L_in, L_out = rng.integers(64, 8000, n).astype(np.int32), rng.integers(16, 2000, n).astype(np.int32)
+    gcost, got = gpu_horizons(ctx, rnd, row_ptr, col, L_in, L_out, wf_ptr)
+    want = o.critical_path(row_ptr, col, gcost.astype(np.float64), wf_ptr, round_f32=True)
+    assert_cp_bit_exact(got, want)
+    assert_cp_bit_exact(gpu_cp(ctx, row_ptr, col, gcost, wf_ptr), want)
+    assert_cp_bit_exact(gpu_cp(ctx, row_ptr, col, gcost, wf_ptr, max_sweeps=graph[2] + 2), want)
+    # one bound that is none: the two workflows beside it get no values, all others theirs, and it is reported
+    from paper_2605_16637_amd import binding
+    k = graph[3] + 5
+    bad = wf_ptr.copy()
+    bad[k] = -5
+    _, odd = gpu_horizons(ctx, rnd, row_ptr, col, L_in, L_out, bad, check=False)
+    with pytest.raises(binding.HxError) as e:
+        ctx.hx_stream_status()
+    assert e.value.code == -6      # HX_ERR_INDEX
+    keep = np.ones(n, bool)
+    keep[wf_ptr[k - 1]:wf_ptr[k + 1]] = False
+    for x, y in zip(odd[:3], want[:3]):
+        assert np.array_equal(x[keep].astype(np.float64), y[keep])
+    keep = np.ones(len(wf_ptr) - 1, bool)
+    keep[k - 1:k + 1] = False
+    assert np.array_equal(odd[3][keep].astype(np.float64), want[3][keep])
 
 
 def fetch(raw):

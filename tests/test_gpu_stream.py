@@ -10,7 +10,7 @@ import pytest
 
 from oracle import hx_oracle as o
 from paper_2605_16637_amd import synth
-from gpu_helpers import REL, assert_costs_close, assert_search_matches, dev, dev_tables
+from gpu_helpers import FALLBACKS, REL, assert_costs_close, assert_search_matches, dev, dev_tables, many_small_workflows
 from test_gpu_dag import fetch
 
 pytestmark = pytest.mark.gpu
@@ -432,6 +432,34 @@ def test_round_with_its_whole_graph_equals_its_three_calls(ctx, name, override):
     assert e2.value.code == -7
     for x, y in zip(_round_state(a)[5:8] + _round_state(a)[9:], _round_state(b)[5:8] + _round_state(b)[9:]):
         assert np.array_equal(x, y)
+
+
+@pytest.mark.parametrize("graph", FALLBACKS)
+def test_round_with_workflows_too_large_for_a_wavefront(ctx, graph):
+    # many small workflows, some of a workgroup's too large for its wavefronts: all of them are walked, in the round's own launch too
+    import torch
+    from paper_2605_16637_amd import binding
+    rng = np.random.default_rng(graph[0])
+    rnd = synth.make_round("tiny", 1)
+    links = binding.to_device(rnd.links)
+    row_ptr, col, wf_ptr = many_small_workflows(*graph)
+    n, n_wf, C = len(row_ptr) - 1, len(wf_ptr) - 1, rnd.calls["n"]
+    rnd.calls["node"] = rng.integers(0, n, C).astype(np.int32)
+    rnd.calls["wf"] = (np.searchsorted(wf_ptr, rnd.calls["node"], side="right") - 1).astype(np.int32)
+    b = _round_buffers(torch, binding, rnd, 7)
+    mark = lambda k, **kw: torch.full((k,), -1, device="cuda:0", **kw)
+    b["graph"] = g = dict(succ_row_ptr=dev(row_ptr), succ_col_idx=dev(col), wf_ptr=dev(wf_ptr),
+                          L_in=dev(rng.integers(64, 8000, n).astype(np.int32)), L_out=dev(rng.integers(16, 2000, n).astype(np.int32)),
+                          node_cost=mark(n, dtype=torch.float32), rem=mark(n, dtype=torch.float32), tail=mark(n, dtype=torch.float32),
+                          level=mark(n, dtype=torch.int32), horizon=mark(n_wf, dtype=torch.float32))
+    ctx.hx_round(rnd.model, b["calls"], b["pre"], b["dec"], links, b["bp"], b["bd"], b["bc"], ratio=b["ratio"],
+                 type_flops=dev(rnd.types["flops"]), type_hbm_bw=dev(rnd.types["hbm_bw"]), graph=g)
+    ctx.hx_stream_status()
+    want = o.critical_path(row_ptr, col, g["node_cost"].cpu().numpy().astype(np.float64), wf_ptr, round_f32=True)
+    for k, w in zip(("rem", "tail", "level", "horizon"), want):
+        assert np.array_equal(g[k].cpu().numpy().astype(np.float64), w), k
+    ratio = o.urgency(rnd.calls["elapsed"], b["bc"].cpu().numpy().astype(np.float64), rnd.calls["node"], rnd.calls["wf"], want[1], want[3])
+    assert np.allclose(b["ratio"].cpu().numpy(), ratio, rtol=REL)
 
 
 def test_round_takes_one_form_of_reveal(ctx):
