@@ -139,20 +139,36 @@ def _ptr_other(t, dtype=None, n=None):
     return C.c_void_p(t.data_ptr())
 
 
+def marshal_built_for() -> str:
+    """What ``hx_marshal.so`` has to be built for to be used here: it reads torch's and Python's own structures."""
+    import sys
+
+    import torch
+    return f"torch {torch.__version__}, {sys.implementation.cache_tag}"
+
+
 def _load_marshal():
-    """``hx_marshal.address`` (csrc/hx_marshal.cpp, built in-tree beside the library)."""
+    """``hx_marshal.address`` (csrc/hx_marshal.cpp, built in-tree beside the library) -- or, where that module is missing or was built for
+    another torch or Python, ``_ptr_other``, which takes longer and is otherwise the same, and a warning."""
     import importlib.machinery
     import importlib.util
+    import warnings
 
-    import torch  # noqa: F401  (its libraries are what the module links to)
-    if not os.path.exists(MARSHAL_PATH):
-        raise ImportError(f"{MARSHAL_PATH} is not built: run `python -m paper_2605_16637_amd.build` "
-                          "(or __graft_entry__.build()) first")
-    loader = importlib.machinery.ExtensionFileLoader("hx_marshal", MARSHAL_PATH)
-    module = importlib.util.module_from_spec(importlib.util.spec_from_loader("hx_marshal", loader))
-    loader.exec_module(module)
-    module.set_up(C.c_void_p, _ptr_other)
-    return module.address
+    want = marshal_built_for()     # (imports torch, whose libraries the module links to)
+    try:
+        loader = importlib.machinery.ExtensionFileLoader("hx_marshal", MARSHAL_PATH)
+        module = importlib.util.module_from_spec(importlib.util.spec_from_loader("hx_marshal", loader))
+        loader.exec_module(module)
+        got = getattr(module, "built_for", "something else")
+        why = None if got == want else f"was built for {got}, here is {want}"
+    except ImportError as e:
+        why = f"cannot be loaded: {e}"
+    if why is None:
+        module.set_up(C.c_void_p, _ptr_other)
+        return module.address
+    warnings.warn(f"{MARSHAL_PATH} {why}; tensors are looked at in Python, some 0.8 us each, until "
+                  "`python -m paper_2605_16637_amd.build` has built it", RuntimeWarning, stacklevel=3)
+    return _ptr_other
 
 
 def _ptr(*args):

@@ -33,7 +33,10 @@ HOST_SANITIZE = ["-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize
 def build(verbose: bool = False, out: str = LIB, extra_flags=()) -> str:
     if out == LIB:
         _compile(["hipcc", *FLAGS, "-o", CALIB_LIB, os.path.join(CSRC, "hx_calib.hip")], verbose)
-        _compile(_marshal_command(), verbose)
+        try:
+            _compile(_marshal_command(), verbose)
+        except (OSError, subprocess.CalledProcessError) as e:      # no g++, or no headers of Python's or torch's: the binding does without
+            print(f"{MARSHAL_LIB} has not been built: {e}")
     return _compile(["hipcc", *FLAGS, *extra_flags, "-o", out, *[os.path.join(CSRC, s) for s in SOURCES]], verbose, out)
 
 
@@ -42,9 +45,12 @@ def _marshal_command():
 
     import torch
     from torch.utils.cpp_extension import include_paths
+
+    from .binding import marshal_built_for
     lib = os.path.join(os.path.dirname(torch.__file__), "lib")
     include = [*include_paths(), sysconfig.get_paths()["include"]]
     return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
+            f'-DHX_BUILT_FOR="{marshal_built_for()}"',
             *[x for p in include for x in ("-isystem", p)], "-o", MARSHAL_LIB, os.path.join(CSRC, "hx_marshal.cpp"),
             "-L" + lib, "-ltorch_python", "-ltorch_cpu", "-lc10"]
 

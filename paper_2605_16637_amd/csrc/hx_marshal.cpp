@@ -62,4 +62,10 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "hx_marshal", nullptr, -1, methods,
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit_hx_marshal(void) { return PyModule_Create(&module); }
+// Touches nothing of torch's: the binding asks `built_for` before it uses the module.
+PyMODINIT_FUNC PyInit_hx_marshal(void)
+{
+    PyObject *m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "built_for", HX_BUILT_FOR) < 0) Py_CLEAR(m);
+    return m;
+}
