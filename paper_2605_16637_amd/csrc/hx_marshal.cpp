@@ -24,9 +24,9 @@ PyObject *address(PyObject *, PyObject *const *args, Py_ssize_t n_args)
         bool fine = x.is_cuda() && x.is_contiguous() &&
                     (dtype == Py_None || reinterpret_cast<THPDtype *>(dtype)->scalar_type == x.scalar_type());
         if (fine && n != Py_None) {
-            const long long want = PyLong_AsLongLong(n);
-            if (want == -1 && PyErr_Occurred()) return nullptr;
-            fine = x.numel() >= want;
+            int beyond;                                    // 64 bits, to either side
+            const long long want = PyLong_AsLongLongAndOverflow(n, &beyond);
+            fine = !beyond && x.numel() >= want;
         }
         if (fine) {
             PyObject *at = PyLong_FromVoidPtr(x.data_ptr());

@@ -219,6 +219,46 @@ def test_best_alone_is_the_best_of_the_pairs(ctx, Q, D, res, plan, kind):
             assert torch.equal(x, y)
 
 
+@pytest.mark.parametrize("Q,D,stride,beyond", [(200, 5, 7, False), (300, 70, 200, False), (100, 300, 511, False),
+                                               (200, 5, 9, True), (300, 70, 200, True), (100, 300, 511, True)])
+def test_intervals_whose_tokens_exceed_32_bits(ctx, Q, D, stride, beyond):
+    # one after the other their sum is beyond 32 bits and no occupancy is; three at a time it is: reported, and for every call no room
+    import torch
+    from paper_2605_16637_amd import binding
+    r, lock, iv = synth.make_decode_round("decode_tiny", stride, n_wf=max(8, Q // 8), Q=Q, D=D, T=min(4, D), stride=stride,
+                                          n_resident=1, n_planned=2, lock_fraction=0.2)
+    rng = np.random.default_rng(D)
+    dec = {k: np.array(v) for k, v in r.dec.items()}
+    dec["cap_tok"] = (2**30 + rng.integers(0, 3000, D)).astype(np.int32)
+    st = np.tile(np.arange(stride, dtype=np.float64) / 4, (D, 1)) - rng.integers(0, 8, (D, 1)) / 4
+    en = st + np.where(rng.random((D, stride)) < 0.3, 0.125, 0.25)
+    if beyond:
+        en[:, 2:-2:3] += 1.0
+    iv = dict(stride=stride, count=np.full(D, stride, np.int32), start=st.reshape(-1), end=en.reshape(-1), tok=np.full(D * stride, 2**30, np.int32))
+    L, O = r.calls["L_in"], np.minimum(r.calls["L_out"], 1 + np.arange(Q) % 40).astype(np.int32)
+    want = o.decode_score(r.model, L, O, lock, dec, iv, want_all=True)
+    assert np.isfinite(want.best_cost).all() and len(np.unique(want.best_start)) > 2
+    got = []
+    for pairs in (True, False):
+        f32 = dict(dtype=torch.float32, device="cuda:0")
+        out = [torch.full((Q,), -9, dtype=torch.int32, device="cuda:0"), torch.full((Q,), -9.0, **f32), torch.full((Q,), -9.0, **f32)]
+        mats = dict(start=torch.empty(Q * D, **f32), cost=torch.empty(Q * D, **f32)) if pairs else {}
+        ctx.hx_decode_score(r.model, dev_queue(L, O), dev(lock), dev_dec(dec), dev_iv(iv), *out, **mats)
+        if beyond:
+            with pytest.raises(binding.HxError) as e:
+                ctx.hx_stream_status()
+            assert e.value.code == -7      # HX_ERR_OVERFLOW
+        else:
+            ctx.hx_stream_status()
+        got.append([x.cpu().numpy() for x in out])
+        if pairs:
+            full = dict(best_d=got[0][0], best_start=got[0][1], best_cost=got[0][2],
+                        **{k: v.cpu().numpy().reshape(Q, D) for k, v in mats.items()})
+            assert check_score(r.model, L, O, lock, dec, iv, full, want) <= max(2, Q * D // 2000)
+    for x, y in zip(*got):
+        assert np.array_equal(x, y)
+
+
 def test_decode_score_is_the_same_every_time(ctx):
     # no atomics, no dependence on which workgroup runs first: two passes over the same input agree bit for bit,
     # also with another pass of another shape in between (the scratch is reused)
