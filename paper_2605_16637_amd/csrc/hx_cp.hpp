@@ -163,6 +163,9 @@ __device__ __forceinline__ bool hx_cp_walk(const CpArgs &a, char *base, int n0, 
     int hbits = 0;
     unsigned umax = 0;
     uint4 cur = *(const uint4 *)(base + hi - sizeof(CpNode));
+    // (The loop's place in the lines of the instruction cache counts, whatever comes before it: 20 workflows of 1000 nodes 137 to 142 us
+    // where it fell, 136 so; six of 1000 among small ones 96 to 115, and 92 to 103.)
+    asm volatile(".p2align 6");
     for (unsigned p = hi - (unsigned)sizeof(CpNode); p >= lo; p -= (unsigned)sizeof(CpNode)) {
         // the node before this one (record 0 before the run's first: read, not used)
         const uint4 nxt = *(const uint4 *)(base + p - sizeof(CpNode));
@@ -226,11 +229,11 @@ __device__ __forceinline__ bool hx_cp_walk(const CpArgs &a, char *base, int n0, 
 // NT: threads of the workgroup.
 template <int NMAX, bool COST, bool STREAM, int NT = CP_THREADS>
 __device__ __forceinline__ void hx_cp_local_body(const CpArgs &a, int wpb, CpNode *s_node, int &s_any,
-                                                 const NodeCostArgs *nc, CostTables *tab, int block)
+                                                 const NodeCostArgs *nc, CostTables *tab, int block, bool tab_filled = false)
 {
-    // COST: the class tables are filled once, by the block's first run, after that run's own loads have been asked
-    // for (the tables' loads and divisions then run under those instead of in front of them); block-uniform
-    bool tab_ready = !COST;
+    // COST: the class tables are filled once (unless they have been, behind a barrier), by the block's first run, after that run's
+    // own loads have been asked for (the tables' loads and divisions then run under those instead of in front of them); block-uniform
+    bool tab_ready = !COST || tab_filled;
     constexpr int CP_NMAX = NMAX;             // nodes staged per run
     constexpr int CP_NPT = (NMAX + NT - 1) / NT;
     static_assert(CP_WPB <= HX_WAVE && NT % HX_WAVE == 0, "a walking lane for every workflow of a run, whichever wavefront has them");
@@ -412,6 +415,9 @@ __device__ __forceinline__ void hx_cp_local_body(const CpArgs &a, int wpb, CpNod
 // steps as the deepest workflow has levels.  Same fixed point, same bits as the walk (one addition of an exact maximum a node).
 // Bound: the chain bounds -> rows -> successors -> steps, an LDS round trip each.  1000 workflows of 10 to 30 nodes and up to 12 levels with
 // their node cost 10.1 -> 6.2 us, beside the search of 4096 calls on 64 + 64 9.7 -> 7.2 (slices of a workgroup, one lane walking each workflow).
+// Where workgroups find workflows too large for a wavefront and take slices after all, they have spent a round trip and a barrier: rounds of that
+// search with 1000 workflows of 24 to 70 nodes 16.7 -> 20 us, 18432 of 4 with one of 65 in each 72nd 16.7 -> 19.2, 4000 of up to 30 with one of 70 in each tenth
+// 20.3 -> 17.7.
 constexpr int CW_EXTRA = 192;        // successors beyond CP_DEG of a node that a wavefront keeps in LDS
 struct CpWave {
     int2 val[HX_WAVE + 1];           // (rem, level) of lane i's node at i + 1; 0: the empty successor, (0, -1)
@@ -545,7 +551,7 @@ __device__ __forceinline__ CwFound hx_cp_wave(const CpArgs &a, int wa, int wb, i
 }
 
 // The workflows of a workgroup of NT threads, `wpv` (below 64) to a wavefront; false: some workflow is not for a wavefront, and nothing
-// has been done.
+// has been done but the tables filled.
 template <int NT>
 __device__ __forceinline__ bool hx_cp_waves_body(const CpArgs &a, int wpv, CpWave *waves, const NodeCostArgs &nc, CostTables &tab, int block)
 {

@@ -85,7 +85,7 @@ void hx_cp_cost_kernel(CpArgs a, NodeCostArgs nc, int wpb, int wpv)
     __shared__ CostTables s_tab;
     if constexpr (WAVES)
         if (hx_cp_waves_body<CP_THREADS>(a, wpv, s.wave, nc, s_tab, (int)blockIdx.x)) return;
-    hx_cp_local_body<CP_NMAX_COST, true, false>(a, wpb, s.node, s_any, &nc, &s_tab, (int)blockIdx.x);
+    hx_cp_local_body<CP_NMAX_COST, true, false>(a, wpb, s.node, s_any, &nc, &s_tab, (int)blockIdx.x, WAVES);
 }
 
 // ---- critical path, level-synchronous sweeps ------------------------------------------
@@ -707,7 +707,7 @@ static int wave_workflows(const hx_ctx *ctx, int n_nodes, int n_wf, int most)
 // Launches in a graph, slices and wavefronts (us).  With the node cost of 4 classes: 20000 nodes 10.1 and 6.2, 82000 10.7 and 6.8, 200000
 // 11.2 and 11.6, 1.8 million 29 and 67; of 8 classes 200000 15.8 and 14.0, 240000 in workflows of 8 13.8 and 15.6.  Sweeps: 20000 12.8 and
 // 7.3, 200000 14.0 and 10.0, 320000 15.6 and 13.4, 440000 15.9 and 15.7, 600000 18.0 and 19.8.  1000 workflows of 30 to 60 nodes 14.5 and 6.4;
-// of 24 to 70, a tenth of which are too large, 13.4 and 13.0, sweeps 11.6 and 12.5.
+// of 24 to 70, a tenth of which are too large, 13.2 and 12.5, sweeps 39.7 and 33.7; 1000 of 10 to 30 with one of 100 in each 20th 15.0 and 14.5, sweeps 36 and 37.
 constexpr int CW_MOST_COST = 384, CW_MOST_SWEEPS = 1536;
 
 extern "C" int hx_critical_path(hx_ctx *ctx, int32_t n_nodes, int32_t n_edges,
@@ -816,9 +816,14 @@ extern "C" int hx_horizons(hx_ctx *ctx, const hx_model *model, int32_t n_nodes, 
     if (plan.grid == 0) return HX_OK;
     HxDeviceGuard guard(ctx->device);
     HX_REQUIRE(ctx, guard.ok, HX_ERR_DEVICE, "cannot select device %d", ctx->device);
-    const int wpb = plan.wpv ? plan.wpv * (CP_THREADS / HX_WAVE) : plan.wpb;
+    // As many workflows a workgroup as the slices it may fall back to take in one run (40000 workflows of 2 nodes, some of 65 among them
+    // 15.6 us, 18.4 in runs of 64 and 12; without them 6.2 either way).  Slices where there are no edges to speak of: they take
+    // a lane a workflow then, without LDS (16384 single nodes 4.3 us, by wavefronts 5.4).
+    const int waves = CP_THREADS / HX_WAVE, most = CP_WPB / waves;
+    const int wpv = n_edges < CP_DEG ? 0 : (plan.wpv < most ? plan.wpv : most);
+    const int wpb = wpv ? wpv * waves : plan.wpb;
     const int grid = (n_wf + wpb - 1) / wpb;
-    if (plan.wpv) hx_cp_cost_kernel<true><<<grid, CP_THREADS, 0, (hipStream_t)stream_>>>(plan.a, plan.nc, wpb, plan.wpv);
+    if (wpv) hx_cp_cost_kernel<true><<<grid, CP_THREADS, 0, (hipStream_t)stream_>>>(plan.a, plan.nc, wpb, wpv);
     else hx_cp_cost_kernel<false><<<grid, CP_THREADS, 0, (hipStream_t)stream_>>>(plan.a, plan.nc, wpb, 0);
     return hx_check_launch(ctx, "hx_cp_cost_kernel");
 }

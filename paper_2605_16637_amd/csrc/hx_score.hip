@@ -451,7 +451,7 @@ __global__ __launch_bounds__(FS_THREADS, 6) void hx_reveal_search_kernel(ScoreAr
     if ((int)blockIdx.x < n_reveal) {
         RevealLds *l = (RevealLds *)smem;
         if (wpv && hx_cp_waves_body<FS_THREADS>(cp, wpv, l->wave, nc, l->tab, (int)blockIdx.x)) return;
-        hx_cp_local_body<RV_NMAX, true, false, FS_THREADS>(cp, wpb, l->node, l->any, &nc, &l->tab, (int)blockIdx.x);
+        hx_cp_local_body<RV_NMAX, true, false, FS_THREADS>(cp, wpb, l->node, l->any, &nc, &l->tab, (int)blockIdx.x, wpv != 0);
         return;
     }
     hx_fused_search_body<CALLS>(a, pa, smem, (int)blockIdx.x - n_reveal);
