@@ -241,6 +241,8 @@ struct DecodeArgs {
     int gd, n_groups;
     float *part_cost, *part_start;
     int32_t *part_d;
+    // Pairs that the occupancy kernel tries: `tries` calls an instance, the n-th of all of them call (n & try_mask) * try_step.
+    int tries, try_mask, try_step;
     int32_t *status;
 };
 
@@ -815,17 +817,23 @@ __global__ __launch_bounds__(64) void hx_decode_finish_kernel(DecodeFinishArgs a
 // far need not be looked at.  A wavefront takes a call, its lanes the instances, and looks at one instance after the other in
 // the order of their bounds; that instance's timeline is then read by all lanes, an entry each.  After DB_CLOSER instances
 // every bound is made a closer one, from what eight steps say of the room there has been (hx_step_word); after DB_EXACT those that
-// still matter the closest, the first moment with room itself (a bisection a lane); after DB_ALL -- room in pieces that are all
-// too short -- every lane searches the instances it has left for itself.
+// still matter the closest, the first moment with room itself (a bisection a lane, between two of the steps); after DB_ALL -- room that is
+// too short again and again -- every lane searches the instances it has left for itself.
 // Of 8192 free calls on 256 instances with 113 to 137 entries each one in 1.13 instances is looked at with the steps, 3.3 by the decode
 // time alone; where every instance is full for ten seconds 56 and 90, and 3 with the bisection.
 //
+// Where room comes in pieces that are too short for most calls no bound helps.  Whether it does is tried beforehand: the occupancy kernel
+// searches each instance for a few calls of the queue, and where more than DB_EVERY_PAIR in sixteen of these pairs have room
+// before their start all workgroups take their calls through all instances instead (hx_decode_every_pair).
+//
 // What bounds it: instruction issue, some 200 vector and 200 scalar instructions a call, and the chain of a call's memory round trips,
-// 2.9 and 1.9 us for the first and the second call of a wavefront.  That pass (as many calls locked as free): the occupancies
-// 15.6 -> 6.7 us, the search 29.4 -> 13.8 and no third kernel of 4.8, against all pairs through tables of first moments with room;
-// 500 calls on 1024 instances 63 -> 22, 500 on 300 with lists of 250 that are full for ten seconds 108 -> 53.  Slower where rooms
-// come in pieces that are shorter than any decode time: 2000 calls on 64 such instances 24 -> 30, 300 on 1024 83 -> 129 (33 and 163 when every
-// lane read two entries at a time of the instances it has left; eight entries of four of them at a time: as of one).
+// 2.9 and 1.9 us for the first and the second call of a wavefront.  Whole passes (us; the pairs all formed through tables of first moments
+// with room, as hx_decode_score_kernel does; so; and before the last three of the following): 16384 calls, half of them locked, on 256 instances with 120
+// intervals 46, 20.4, 19.8; 500 on 1024 with 50 60, 16.3, 15.5; 16384 on 512 with 60 57, 26, 35.  Full for ten seconds: the first 46, 53, 59; 16384
+// on 300 46, 53, 90; 4000 on 512 39, 30, 57; 16384 on 1024 106, 126, 157.  In pieces of 0.3 s: 2000 on 64 with 28 18, 12.5, 30; 16384 on 256 with 28 72, 79,
+// 338; 4000 on 1024 with 28 88, 116, 461; 300 on 1024 with 120 180, 92, 319.  What these three are: the pairs tried beforehand (0.4 us of every pass), the
+// bisection between two steps and from the fifth instance on (the sixth before), and eight instances a lane for 257 to 512.
+// (Of 4 and 8 s, for which some of the calls are too long, it stays slower than all pairs by tables: 3000 on 100 27, 40, 43; 300 on 64 19, 33, 33.)
 
 // Up to some moment no more than `room` tokens have been free, and `time_bits` is when that may change: as the upper halves of two
 // floats, the first as its complement.  A call that needs more than the room has no start before that time; by halves, as far as the two
@@ -835,10 +843,50 @@ __device__ __forceinline__ unsigned hx_step_word(unsigned room, int time_bits)
     return ~(__float_as_uint((float)room) | 0xffffu) | ((unsigned)time_bits >> 16);
 }
 
+// The earliest start on one timeline, by a wavefront: an entry a lane, 64 at a time.  A run of entries with room begins where the one
+// before it has none, and is a start if the run's end, the next entry without room, is far enough: the comparisons of
+// hx_earliest_start, which tests a run at each of its entries, at the last of them, whose successor is the latest.
+// e: nt entries may be read, n of them count; next: the lane's of the first 64; room_at: the first entry with room, for however long.
+// Uniform in everything but the lane.
+__device__ __forceinline__ float hx_earliest_start_wave(const int2 *__restrict__ e, int nt, int2 next, int n, int thr, float T, int lane,
+                                                        float &room_at)
+{
+    room_at = INFINITY;
+    float rs = INFINITY;                                   // where the run that is open begins
+    for (int i0 = 0; i0 < n; i0 += HX_WAVE) {
+        const int2 x = next;
+        next = e[min(i0 + HX_WAVE + lane, nt - 1)];
+        const bool in = i0 + lane < n;
+        const float t = in ? __int_as_float(x.x) : INFINITY;      // behind the last entry: never, which ends every run
+        const u64 room = __builtin_amdgcn_ballot_w64(in && x.y <= thr);
+        if (room && !(room_at < INFINITY)) room_at = hx_lane_value(t, __builtin_ctzll(room));
+        const bool open = rs < INFINITY;
+        if (open && room != ~0ull) {
+            if (hx_lane_value(t, __builtin_ctzll(~room)) >= rs + T) return rs;
+            rs = INFINITY;
+        }
+        const u64 starts = room & ~(room << 1) & ~(open ? 1ull : 0ull);
+        if (starts == 0) continue;
+        const u64 ends = ~room >> lane;
+        const int len = ends ? __builtin_ctzll(ends) : HX_WAVE;
+        const float t_end = __shfl(t, lane + len);         // (a run up to the last lane: not looked at)
+        const u64 hits = __builtin_amdgcn_ballot_w64(((starts >> lane) & 1) != 0 && lane + len < HX_WAVE && t_end >= t + T);
+        if (hits) return hx_lane_value(t, __builtin_ctzll(hits));
+        if (room >> (HX_WAVE - 1)) rs = hx_lane_value(t, HX_WAVE - 1 - __builtin_clzll(starts));
+    }
+    return rs;                                             // it lasts
+}
+
+// What is said of a pair that has been tried: there is room for the call some time; there is some before its start, for too short a time.
+constexpr unsigned DB_FITS = 1, DB_SHORT = 2;
+constexpr int DB_TRIES = 256;              // pairs tried, but at least one and at most seven an instance
+
 // Workgroup d: the occupancy of instance d over time, an entry an event that lies ahead; those that lie behind (most sequences
 // have begun) only add to what is held now.  Several events of one moment are several entries, all with what is held
 // after the last.  No running sum: an event adds up those not after it while it counts those before it.
-// Bound: two memory round trips (the record, the intervals) and the comparisons, n^2 of them on one compute unit.
+// Bound: two memory round trips (the record, the intervals) and the comparisons, n^2 of them on one compute unit.  64 registers: with two
+// more 1024 workgroups are no longer resident together (500 calls on 1024 instances 16.3 -> 17.9 us); held to 56 by eight wavefronts a
+// SIMD the comparisons have fewer reads in flight (256 instances 6.4 -> 6.7).
 constexpr int DO_THREADS = 512;
 constexpr int DO_EVENTS = 2 * HX_MAX_INTERVALS + 42;      // and a filler for the shares of several lanes
 static_assert(HX_MAX_INTERVALS <= DO_THREADS, "an interval a thread");
@@ -859,8 +907,25 @@ __global__ __launch_bounds__(DO_THREADS) void hx_decode_occupancy_kernel(DecodeA
     int cnt = a.iv_count[d];
     const float flops = a.d_flops[d], hbm = a.d_hbm[d];
     const int used = a.d_used[d], batch = a.d_batch[d], cap = a.d_cap[d];
+    // `tries` wavefronts but the first try a call of the queue each
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const bool tries = wave > 0 && wave <= a.tries;
+    const int c = tries ? ((d * a.tries + wave - 1) & a.try_mask) * a.try_step : 0;
+    const int L = a.L_in[c], O = a.L_out[c];
     for (int i = tid; i < DO_EVENTS; i += DO_THREADS) { s_key[i] = ~0ull; s_delta[i] = 0; }
     if (tid == 0) { s_now = 0; s_all = 0; s_n = 0; }
+    float T = 0.0f;
+    int thr = -1;
+    if (tries) {
+        const HxDecF x = hx_decode_terms(a.m, used, batch, 0, 1.0f / flops, 1.0f / hbm);
+        T = hx_lane_value(hx_decode_time(hx_call_terms(a.m, L, O), x.c1, x.c2, x.kB), 0);
+        if (L >= 0 && O >= 0 && hx_fits(L, O, cap)) thr = (int)((long long)cap - ((long long)L + O));
+        if (tid == HX_WAVE) {
+            int *const meta = o.meta + 8 * d;
+            *(int4 *)meta = make_int4(0, 0, cap, __float_as_int(x.c1));
+            *(int2 *)(meta + 4) = make_int2(__float_as_int(x.c2), __float_as_int(x.kB));
+        }
+    }
     __syncthreads();
     if (cnt < 0 || cnt > a.stride) {
         if (tid == 0) hx_raise(a.status, HX_ERR_INDEX);
@@ -922,6 +987,7 @@ __global__ __launch_bounds__(DO_THREADS) void hx_decode_occupancy_kernel(DecodeA
     }
     __syncthreads();
     const int n_e = n + 1;
+    if (tid == HX_WAVE) o.meta[8 * d] = n_e;
     int2 *const e = o.e + (size_t)d * nt;
     for (int i = tid; i < hx_tl_len(n_e); i += DO_THREADS) e[i] = i < n_e ? s_e[i] : make_int2(0x7f800000, 0);
     if (tid < HX_WAVE) {
@@ -943,61 +1009,128 @@ __global__ __launch_bounds__(DO_THREADS) void hx_decode_occupancy_kernel(DecodeA
             o.step[((tid >> 2) * a.D + d) * 4 + (tid & 3)] = n > 0 ? hx_step_word((unsigned)max((long long)cap - s_least[i], 0ll), s_e[i + 1].x) : 0;
         }
     }
-    if (tid == DO_THREADS - 1) {
-        const HxDecF x = hx_decode_terms(a.m, used, batch, 0, 1.0f / flops, 1.0f / hbm);
-        int4 *meta = (int4 *)(o.meta + 8 * d);
-        meta[0] = make_int4(n_e, 0, cap, __float_as_int(x.c1));
-        meta[1] = make_int4(__float_as_int(x.c2), __float_as_int(x.kB), 0, 0);
+    unsigned char *const says = (unsigned char *)(o.meta + 8 * d + 6) + wave;
+    if (!tries) {
+        if (lane == 0) *says = 0;
+        return;
     }
-}
-
-// The earliest start on one timeline, by a wavefront: an entry a lane, 64 at a time.  A run of entries with room begins where the one
-// before it has none, and is a start if the run's end, the next entry without room, is far enough: the comparisons of
-// hx_earliest_start, which tests a run at each of its entries, at the last of them, whose successor is the latest.
-// e: nt entries may be read, n of them count; next: the lane's of the first 64.  Uniform in everything but the lane.
-__device__ __forceinline__ float hx_earliest_start_wave(const int2 *__restrict__ e, int nt, int2 next, int n, int thr, float T, int lane)
-{
-    float rs = INFINITY;                                   // where the run that is open begins
-    for (int i0 = 0; i0 < n; i0 += HX_WAVE) {
-        const int2 x = next;
-        next = e[min(i0 + HX_WAVE + lane, nt - 1)];
-        const bool in = i0 + lane < n;
-        const float t = in ? __int_as_float(x.x) : INFINITY;      // behind the last entry: never, which ends every run
-        const u64 room = __builtin_amdgcn_ballot_w64(in && x.y <= thr);
-        const bool open = rs < INFINITY;
-        if (open && room != ~0ull) {
-            if (hx_lane_value(t, __builtin_ctzll(~room)) >= rs + T) return rs;
-            rs = INFINITY;
-        }
-        const u64 starts = room & ~(room << 1) & ~(open ? 1ull : 0ull);
-        if (starts == 0) continue;
-        const u64 ends = ~room >> lane;
-        const int len = ends ? __builtin_ctzll(ends) : HX_WAVE;
-        const float t_end = __shfl(t, lane + len);         // (a run up to the last lane: not looked at)
-        const u64 hits = __builtin_amdgcn_ballot_w64(((starts >> lane) & 1) != 0 && lane + len < HX_WAVE && t_end >= t + T);
-        if (hits) return hx_lane_value(t, __builtin_ctzll(hits));
-        if (room >> (HX_WAVE - 1)) rs = hx_lane_value(t, HX_WAVE - 1 - __builtin_clzll(starts));
+    unsigned what = 0;
+    if (thr >= 0) {
+        float room_at;
+        const float S = hx_earliest_start_wave(s_e, n_e, s_e[min(lane, n_e - 1)], n_e, thr, T, lane, room_at);
+        what = room_at < S ? DB_FITS | DB_SHORT : DB_FITS;
     }
-    return rs;                                             // it lasts
+    if (lane == 0) *says = (unsigned char)what;
 }
 
 constexpr int DB_THREADS = 256;
-constexpr int DB_PER_CU = 6;               // workgroups a compute unit at most: 4 16.0 us, 5 14.7, 6 13.8, 7 14.4, 8 14.8 (the last ones wait for a place)
-constexpr int DB_CLOSER = 1, DB_EXACT = 6, DB_ALL = 16;
+// Workgroups a compute unit at most: 4 16.0 us, 5 14.7, 6 13.8, 7 14.4, 8 14.8 (the last ones wait for a place).  Six also beyond 256 instances, where
+// four and three have a place: with no more than these 16384 calls on 512 and 1024 full instances 76 -> 90 and 162 -> 187, others full for no time
+// 26 -> 26 and 39 -> 36.5.
+constexpr int DB_PER_CU = 6;
+// (DB_EXACT 4, 5, 6: the first of the passes above 20.9, 20.4, 20.4, full for ten seconds 52, 53, 54.)
+constexpr int DB_CLOSER = 1, DB_EXACT = 5, DB_ALL = 16;
+// Every pair where more than so many sixteenths of those tried have room before their start: 3000 calls on 100 instances with 30 resident and 90
+// planned intervals (some 8) 18 us, every pair 36; 300 on 33 with 64 and 191 (some 12) 30 and 41; in pieces of 4 s (12) 3000 on 100 40 and
+// 27; of 2 s (14) 44 and 27.
+constexpr unsigned DB_EVERY_PAIR = 13;
+
+// The same where sixteen lanes, a row of the wavefront, search one timeline for sixteen calls: a lane loads an entry of sixteen and all
+// of the row have it in turn.  e: nt entries may be read, n of them count.
+__device__ __forceinline__ HxSlot hx_earliest_start_row(const int2 *__restrict__ e, int nt, int n, int thr, float T, bool active, int in_row)
+{
+    const bool open = active && thr >= 0;
+    float rs = INFINITY, ans = INFINITY;
+    int2 x = e[in_row];
+    for (int i0 = 0;; i0 += 16) {
+        const bool going = open && i0 < n && !(ans < INFINITY);
+        if (__builtin_amdgcn_ballot_w64(going) == 0) break;
+        const int2 next = e[i0 < n ? min(i0 + 16 + in_row, nt - 1) : 0];
+        const float keep = ans;
+#define HX_ROW(v_, u_) __builtin_amdgcn_update_dpp(0, v_, 0x150 + (u_), 0xf, 0xf, true)      // row_newbcast: all lanes take part
+#define HX_TL_STEP(u_, nxt_)                                                                   \
+        {                                                                                      \
+            const int occ = HX_ROW(x.y, u_);                                                   \
+            const float from = fminf(rs, __int_as_float(HX_ROW(x.x, u_))), then = __int_as_float(nxt_); \
+            rs = occ <= thr ? from : INFINITY;                                                 \
+            ans = fminf(ans, then >= rs + T ? rs : INFINITY);                                  \
+        }
+#define HX_TL_STEPS(u_) HX_TL_STEP(u_, HX_ROW(x.x, u_ + 1)) HX_TL_STEP(u_ + 1, HX_ROW(x.x, u_ + 2)) HX_TL_STEP(u_ + 2, HX_ROW(x.x, u_ + 3))
+        HX_TL_STEPS(0) HX_TL_STEPS(3) HX_TL_STEPS(6) HX_TL_STEPS(9) HX_TL_STEPS(12)
+        HX_TL_STEP(15, HX_ROW(next.x, 0))
+#undef HX_TL_STEPS
+#undef HX_TL_STEP
+#undef HX_ROW
+        ans = going ? ans : keep;                          // (past its own end a row goes over whatever lies there)
+        x = next;
+    }
+    const bool found = open && ans < INFINITY;
+    return HxSlot{found ? ans : INFINITY, found};
+}
+
+// All pairs of G (1, 4 or 16) calls from c0 on, by a workgroup: its lanes are G calls times instances.  Bound: the entries, nine instructions
+// each, of sixteen calls; else, with few calls, the round trips of a lane's own timeline.
+__device__ __forceinline__ void hx_decode_every_pair(const DecodeArgs &a, const DecodeFinishArgs &f, const TlOut &o, int nt, const int4 *s_inst,
+                                                     float3 (*s_best)[16], int G, int c0)
+{
+    const int lane = threadIdx.x & (HX_WAVE - 1), wave = threadIdx.x / HX_WAVE;
+    const int c = c0 + (lane & (G - 1));
+    const bool in = c < a.Q;
+    const int L = in ? a.L_in[c] : 0, O = in ? a.L_out[c] : 0, lk = in && a.lock ? a.lock[c] : -1;
+    const bool ok = in && L >= 0 && O >= 0 && lk >= -1 && lk < a.D;
+    const HxCallF cf = hx_call_terms(a.m, ok ? L : 0, ok ? O : 0);
+    float best = INFINITY, best_S = INFINITY;
+    int best_d = -1;
+    for (int d = (int)threadIdx.x / G; __builtin_amdgcn_ballot_w64(d < a.D) != 0; d += DB_THREADS / G) {
+        const int dl = min(d, a.D - 1);
+        const int4 x = s_inst[dl];
+        const int2 *e = o.e + (size_t)dl * nt;
+        const int n = o.meta[8 * dl], thr = (int)((long long)x.w - ((long long)L + O));
+        const float T = hx_decode_time(cf, __int_as_float(x.x), __int_as_float(x.y), __int_as_float(x.z));
+        const bool on = ok && d < a.D && (lk < 0 || lk == d) && hx_fits(L, O, x.w) && T <= best;
+        const HxSlot s = G == 16 ? hx_earliest_start_row(e, nt, n, thr, T, on, lane & 15) : hx_earliest_start(e, n, thr, T, on);
+        const float v = s.S + T;
+        if (on && v < best) { best = v; best_S = s.S; best_d = d; }
+    }
+    // the least; of equals the lowest instance
+    auto take = [&](float v, float S, int d) {
+        if (v < best || (v == best && (unsigned)d < (unsigned)best_d)) { best = v; best_S = S; best_d = d; }
+    };
+    for (int off = HX_WAVE / 2; off >= G; off >>= 1) {
+        const float v = __shfl_xor(best, off), S = __shfl_xor(best_S, off);
+        take(v, S, __shfl_xor(best_d, off));
+    }
+    if (lane < G) s_best[wave][lane] = make_float3(best, best_S, __int_as_float(best_d));
+    __syncthreads();
+    if ((int)threadIdx.x < G && in) {
+        for (int w = 1; w < DB_THREADS / HX_WAVE; ++w) take(s_best[w][lane].x, s_best[w][lane].y, __float_as_int(s_best[w][lane].z));
+        if (!ok) hx_raise(a.status, HX_ERR_INDEX);
+        f.best_d[c] = best_d; f.best_start[c] = best_S; f.best_cost[c] = best;
+        if (f.ratio) hx_projected_ratio(f.node, f.wf, f.elapsed, f.tail, f.horizon, f.n_nodes, f.n_wf, c, best, f.status, f.ratio);
+    }
+    __syncthreads();
+}
+
 // K: instances a lane
 template <int K>
-__global__ __launch_bounds__(DB_THREADS) void hx_decode_best_kernel(DecodeArgs a, DecodeFinishArgs f, TlOut o, int nt)
+__global__ __launch_bounds__(DB_THREADS, K <= 4 ? 6 : K == 8 ? 4 : 3) void hx_decode_best_kernel(DecodeArgs a, DecodeFinishArgs f, TlOut o, int nt, int G)
 {
     const int lane = threadIdx.x & (HX_WAVE - 1);
     const int wave = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (DB_THREADS / HX_WAVE) + threadIdx.x / HX_WAVE));
     const int n_waves = gridDim.x * (DB_THREADS / HX_WAVE);
     // the lane's instances' decode terms and capacities: read from here where they are wanted, they cost no registers
     __shared__ __align__(16) int4 s_inst[K * HX_WAVE];
+    unsigned tried = 0;                                    // of the pairs that the occupancy kernel has tried those that fit; in the upper half those with room too short
     for (int d = threadIdx.x; d < K * HX_WAVE; d += DB_THREADS) {
         const int4 *meta = (const int4 *)(o.meta + 8 * min(d, a.D - 1));
         const int4 x = meta[0], y = meta[1];
         s_inst[d] = make_int4(x.w, y.x, y.y, d < a.D ? x.z : -1);      // no instance: nothing fits
+        if (d < a.D) tried += __popc(y.z & 0x01010101 * DB_FITS) + __popc(y.w & 0x01010101 * DB_FITS)
+                              + ((__popc(y.z & 0x01010101 * DB_SHORT) + __popc(y.w & 0x01010101 * DB_SHORT)) << 16);
     }
+    __shared__ unsigned s_tried[DB_THREADS / HX_WAVE];
+    tried = hx_wave_sum(tried);
+    if (lane == 0) s_tried[threadIdx.x / HX_WAVE] = tried;
     __shared__ __align__(16) uint4 s_step[2][K * HX_WAVE];
     for (int i = threadIdx.x; i < 2 * K * HX_WAVE; i += DB_THREADS)
         s_step[i / (K * HX_WAVE)][i % (K * HX_WAVE)] = ((const uint4 *)o.step)[i / (K * HX_WAVE) * a.D + min(i % (K * HX_WAVE), a.D - 1)];
@@ -1011,6 +1144,14 @@ __global__ __launch_bounds__(DB_THREADS) void hx_decode_best_kernel(DecodeArgs a
     const bool writes = lane < (f.ratio ? 4 : 3);
     int next = wave < a.Q ? in[wave] : 0;
     __syncthreads();
+    tried = 0;
+#pragma unroll
+    for (int w = 0; w < DB_THREADS / HX_WAVE; ++w) tried += s_tried[w];
+    if (__builtin_expect((tried >> 16) * 16u > (tried & 0xffffu) * DB_EVERY_PAIR, 0)) {
+        __shared__ float3 s_best[DB_THREADS / HX_WAVE][16];
+        for (int c0 = (int)blockIdx.x * G; c0 < a.Q; c0 += (int)gridDim.x * G) hx_decode_every_pair(a, f, o, nt, s_inst, s_best, G, c0);
+        return;
+    }
     for (int c = wave; c < a.Q; c += n_waves) {
         const int L = __builtin_amdgcn_readlane(next, 0), O = __builtin_amdgcn_readlane(next, 1);
         const int lk = a.lock ? __builtin_amdgcn_readlane(next, 2) : -1;
@@ -1036,7 +1177,8 @@ __global__ __launch_bounds__(DB_THREADS) void hx_decode_best_kernel(DecodeArgs a
             const HxInst it = hx_inst_load(o, d);
             const float T = hx_decode_time(cf, it.c1, it.c2, it.kB);
             const int thr = threshold(it.cap);
-            const float S = hx_earliest_start_wave(e, nt, first, it.n, thr, T, lane);
+            float room_at;
+            const float S = hx_earliest_start_wave(e, nt, first, it.n, thr, T, lane, room_at);
             const float v = S + T;                         // +inf when there is no start
             if (v < best || (v == best && d < best_d)) { best = v; best_S = S; best_d = d; }
         };
@@ -1064,46 +1206,7 @@ __global__ __launch_bounds__(DB_THREADS) void hx_decode_best_kernel(DecodeArgs a
                 look(d);
 #pragma unroll
                 for (int k = 0; k < K; ++k) bound[k] = k * HX_WAVE + lane == d ? INFINITY : bound[k];
-                if (looked == DB_CLOSER) {
-                    // a closer bound: while the least that has been held leaves no room there is no start
-                    const unsigned me = hx_step_word((unsigned)L + (unsigned)O, 0) | 0xffffu;
-#pragma unroll
-                    for (int k = 0; k < K; ++k) {
-                        const uint4 x = s_step[0][k * HX_WAVE + lane], y = s_step[1][k * HX_WAVE + lane];
-                        unsigned t = me < x.x ? x.x : 0u;
-                        t = me < x.y ? x.y : t; t = me < x.z ? x.z : t; t = me < x.w ? x.w : t;
-                        t = me < y.x ? y.x : t; t = me < y.y ? y.y : t; t = me < y.z ? y.z : t; t = me < y.w ? y.w : t;
-                        bound[k] = __uint_as_float(t << 16) + bound[k];
-                    }
-                } else if (looked == DB_EXACT) {
-                    // the closest, where the other one is not beyond the best: the instance's first entry with room
-                    int lo[K], hi[K];
-                    bool any = false;
-#pragma unroll
-                    for (int k = 0; k < K; ++k) {
-                        const bool on = bound[k] <= best && bound[k] < INFINITY;
-                        lo[k] = 0;
-                        hi[k] = on ? o.meta[8 * (k * HX_WAVE + lane)] - 1 : 0;      // (the last entry has room: everything has ended)
-                        any = any || on;
-                    }
-                    if (__builtin_amdgcn_ballot_w64(any) == 0) break;
-                    for (;;) {
-                        bool going = false;
-#pragma unroll
-                        for (int k = 0; k < K; ++k) {
-                            if (lo[k] >= hi[k]) continue;
-                            const int mid = (lo[k] + hi[k]) >> 1;
-                            if (o.least[(unsigned)(k * HX_WAVE + lane) * (unsigned)nt + mid] <= threshold(s_inst[k * HX_WAVE + lane].w)) hi[k] = mid;
-                            else lo[k] = mid + 1;
-                            going = going || lo[k] < hi[k];
-                        }
-                        if (__builtin_amdgcn_ballot_w64(going) == 0) break;
-                    }
-#pragma unroll
-                    for (int k = 0; k < K; ++k)
-                        if (lo[k] > 0)
-                            bound[k] = __int_as_float(o.e[(unsigned)(k * HX_WAVE + lane) * (unsigned)nt + lo[k]].x) + time_on(s_inst[k * HX_WAVE + lane]);
-                } else if (looked == DB_ALL) {
+                if (looked == DB_ALL) {
                     float v = INFINITY, S = INFINITY;
                     int at = INT_MAX;
 #pragma unroll 1
@@ -1145,6 +1248,57 @@ __global__ __launch_bounds__(DB_THREADS) void hx_decode_best_kernel(DecodeArgs a
                         best_S = hx_lane_value(S, d_all & (HX_WAVE - 1));
                     }
                     break;
+                }
+                if (looked == DB_CLOSER) {
+                    // a closer bound: while the least that has been held leaves no room there is no start
+                    const unsigned me = hx_step_word((unsigned)L + (unsigned)O, 0) | 0xffffu;
+#pragma unroll
+                    for (int k = 0; k < K; ++k) {
+                        const uint4 x = s_step[0][k * HX_WAVE + lane], y = s_step[1][k * HX_WAVE + lane];
+                        unsigned t = me < x.x ? x.x : 0u;
+                        t = me < x.y ? x.y : t; t = me < x.z ? x.z : t; t = me < x.w ? x.w : t;
+                        t = me < y.x ? y.x : t; t = me < y.y ? y.y : t; t = me < y.z ? y.z : t; t = me < y.w ? y.w : t;
+                        bound[k] = __uint_as_float(t << 16) + bound[k];
+                    }
+                } else if (looked == DB_EXACT) {
+                    // the closest, where the other one is not beyond the best: the instance's first entry with room
+                    unsigned span[K];                      // the lowest place it may have, and above that the highest
+                    bool any = false;
+#pragma unroll
+                    for (int k = 0; k < K; ++k) {
+                        const bool on = bound[k] <= best && bound[k] < INFINITY;
+                        const unsigned n = on ? o.meta[8 * (k * HX_WAVE + lane)] - 1 : 0;      // (the last entry has room: everything has ended)
+                        // between the last step that surely leaves no room and the first that surely does
+                        const unsigned me = ~__float_as_uint((float)((unsigned)L + (unsigned)O)) >> 16;
+                        unsigned none = 0, perhaps = 0;
+#pragma unroll
+                        for (int h = 0; h < 2; ++h) {
+                            const uint4 x = s_step[h][k * HX_WAVE + lane];
+                            none += (x.x >> 16 > me) + (x.y >> 16 > me) + (x.z >> 16 > me) + (x.w >> 16 > me);
+                            perhaps += (x.x >> 16 >= me) + (x.y >> 16 >= me) + (x.z >> 16 >= me) + (x.w >> 16 >= me);
+                        }
+                        span[k] = on ? (perhaps * n >> 3) << 16 | (none ? ((none - 1) * n >> 3) + 1 : 0) : 0;
+                        any = any || on;
+                    }
+                    if (__builtin_amdgcn_ballot_w64(any) == 0) break;
+                    for (;;) {
+                        bool going = false;
+#pragma unroll
+                        for (int k = 0; k < K; ++k) {
+                            const unsigned lo = span[k] & 0xffffu, hi = span[k] >> 16;
+                            if (lo >= hi) continue;
+                            const unsigned mid = (lo + hi) >> 1;
+                            const bool room = o.least[(unsigned)(k * HX_WAVE + lane) * (unsigned)nt + mid] <= threshold(s_inst[k * HX_WAVE + lane].w);
+                            span[k] = room ? mid << 16 | lo : hi << 16 | (mid + 1);
+                            going = going || (room ? lo < mid : mid + 1 < hi);
+                        }
+                        if (__builtin_amdgcn_ballot_w64(going) == 0) break;
+                    }
+#pragma unroll
+                    for (int k = 0; k < K; ++k) {
+                        const unsigned lo = span[k] & 0xffffu;
+                        if (lo > 0) bound[k] = __int_as_float(o.e[(unsigned)(k * HX_WAVE + lane) * (unsigned)nt + lo].x) + time_on(s_inst[k * HX_WAVE + lane]);
+                    }
                 }
             }
         }
@@ -1881,13 +2035,23 @@ extern "C" int hx_decode_score(hx_ctx *ctx, const hx_model *model, const hx_call
         a.free_c = free_c; a.n_free = n_free; a.per = per;
         a.gd = gd; a.n_groups = n_groups; a.part_cost = part_cost; a.part_start = part_start; a.part_d = part_d;
         if (!pairs) {
+            a.tries = DB_TRIES / D < 1 ? 1 : (DB_TRIES / D < DO_THREADS / HX_WAVE - 1 ? DB_TRIES / D : DO_THREADS / HX_WAVE - 1);
+            const int n_tries = a.tries * D;
+            a.try_step = Q / n_tries > 1 ? Q / n_tries : 1;
+            a.try_mask = INT_MAX;
+            while (n_tries * a.try_step > Q && a.try_mask >= Q) a.try_mask >>= 1;       // fewer calls than tries
             hx_decode_occupancy_kernel<<<D, DO_THREADS, 0, stream>>>(a, o, nt);
-            // a wavefront per call, as many as the chip holds
-            const int waves = DB_THREADS / HX_WAVE, most = DB_PER_CU * ctx->num_cu;
-            const int grid = Q / waves + (Q % waves != 0) < most ? Q / waves + (Q % waves != 0) : most;
-            if (D <= HX_WAVE) hx_decode_best_kernel<1><<<grid, DB_THREADS, 0, stream>>>(a, f, o, nt);
-            else if (D <= 4 * HX_WAVE) hx_decode_best_kernel<4><<<grid, DB_THREADS, 0, stream>>>(a, f, o, nt);
-            else hx_decode_best_kernel<HX_MAX_INSTANCES / HX_WAVE><<<grid, DB_THREADS, 0, stream>>>(a, f, o, nt);
+            // a wavefront per call, and workgroups with a place of their own as long as there are
+            const int waves = DB_THREADS / HX_WAVE, most = DB_PER_CU * ctx->num_cu, few = 2 * ctx->num_cu;
+            int grid = Q / waves + (Q % waves != 0);
+            grid = grid < few ? (Q < few ? Q : few) : (grid < most ? grid : most);
+            // where every pair is formed, calls a workgroup takes together: as many workgroups as there are places for (16384 calls on 256 instances
+            // in pieces: 16 79 us, 4 90; 4000: 16 39, 4 30; 300 on 1024: 4 64, 1 46)
+            const int G = Q > waves * most ? 16 : (Q > few ? 4 : 1);
+            if (D <= HX_WAVE) hx_decode_best_kernel<1><<<grid, DB_THREADS, 0, stream>>>(a, f, o, nt, G);
+            else if (D <= 4 * HX_WAVE) hx_decode_best_kernel<4><<<grid, DB_THREADS, 0, stream>>>(a, f, o, nt, G);
+            else if (D <= 8 * HX_WAVE) hx_decode_best_kernel<8><<<grid, DB_THREADS, 0, stream>>>(a, f, o, nt, G);
+            else hx_decode_best_kernel<HX_MAX_INSTANCES / HX_WAVE><<<grid, DB_THREADS, 0, stream>>>(a, f, o, nt, G);
             return hx_check_launch(ctx, "hx_decode_score kernels");
         }
         const size_t lds = hx_scratch_bytes(ne) + hx_align16((size_t)nt * 8);

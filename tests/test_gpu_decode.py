@@ -160,8 +160,8 @@ def test_decode_score_matches_oracle(ctx, Q, D, stride, res, plan, seed):
 
 
 def _crowd(iv, dec, kind):
-    """The lists of a decode round made harder: every instance full for ten seconds more, room in pieces of 0.3 s until all is over,
-    events of many at the same moments, or lists with entries that hold nothing."""
+    """The lists of a decode round made harder: every instance full for ten seconds more, room in pieces of 0.3 s until all is over (on all or
+    two of three), events of many at the same moments, or lists with entries that hold nothing."""
     K, D = int(iv["stride"]), len(dec["flops"])
     st, en, tk = (np.asarray(iv[x]).reshape(D, K).copy() for x in ("start", "end", "tok"))
     cnt, cap = np.asarray(iv["count"]).copy(), np.asarray(dec["cap_tok"])
@@ -170,7 +170,7 @@ def _crowd(iv, dec, kind):
             now = st[d, :cnt[d]] <= 0
             tk[d, :cnt[d]] = tk[d, :cnt[d]] * (0.999 * cap[d] / max(int(tk[d, :cnt[d]][now].sum()), 1))
             en[d] += 10
-        elif kind == "pieces":
+        elif kind == "pieces" or kind == "most in pieces" and d % 3:
             st[d], en[d], tk[d] = np.arange(K) + 0.3, np.arange(K) + 1.0, cap[d]
             cnt[d] = K
     if kind == "same":
@@ -184,11 +184,20 @@ def _crowd(iv, dec, kind):
     return dict(stride=K, count=cnt, start=st.reshape(-1).astype(np.float32), end=en.reshape(-1).astype(np.float32), tok=tk.reshape(-1))
 
 
-# a lane takes 1, 4 or 16 instances; a timeline is read 64 entries at a time (resident + 1 entries without planned ones)
+# a lane takes 1, 4, 8 or 16 instances; a timeline is read 64 entries at a time (resident + 1 entries without planned ones)
 @pytest.mark.parametrize("Q,D,res,plan,kind", [(48, 1, 62, 0, ""), (300, 2, 63, 0, "late"), (300, 63, 64, 0, "late"), (200, 64, 127, 0, "late"),
                                                (150, 65, 128, 20, "late"), (700, 256, 30, 90, ""), (150, 257, 40, 20, "same"),
-                                               (100, 1024, 12, 6, "late"), (200, 64, 28, 0, "pieces"), (120, 300, 70, 0, "pieces"),
+                                               (100, 512, 20, 6, "late"), (100, 513, 20, 6, "late"), (100, 1024, 12, 6, "late"),
+                                               (200, 64, 28, 0, "pieces"), (120, 300, 70, 0, "pieces"),
                                                (60, 40, 3, 0, "pieces"), (60, 70, 4, 0, "pieces"), (60, 40, 7, 0, "pieces"), (60, 20, 8, 0, "pieces"),
+                                               # room too short before the start of most pairs: every pair, 1, 4 and 16 calls a workgroup
+                                               (512, 1, 8, 0, "pieces"), (513, 65, 15, 0, "pieces"), (2048, 17, 16, 0, "pieces"),
+                                               (2500, 70, 511, 0, "pieces"), (6144, 7, 17, 0, "pieces"), (6145, 3, 7, 0, "pieces"),
+                                               (6151, 17, 8, 0, "pieces"), (6200, 257, 15, 0, "pieces"), (6300, 70, 100, 0, "pieces"), (26000, 33, 16, 0, "pieces"),
+                                               # of less: as otherwise, and for many calls what is left of the instances by lanes
+                                               (60, 40, 3, 0, "most in pieces"), (60, 70, 4, 0, "most in pieces"), (60, 40, 7, 0, "most in pieces"),
+                                               (60, 20, 8, 0, "most in pieces"), (120, 300, 70, 0, "most in pieces"), (100, 600, 30, 0, "most in pieces"),
+                                               (2300, 33, 100, 0, "most in pieces"), (700, 90, 31, 0, "most in pieces"),
                                                (300, 20, 24, 24, "empty"), (200, 3, 300, 211, "same"), (13000, 40, 20, 10, "")])
 def test_best_alone_is_the_best_of_the_pairs(ctx, Q, D, res, plan, kind):
     """Without the matrices few pairs are looked at; best instance, start, cost and ratio are those of the pass that forms all of them
