@@ -91,13 +91,13 @@ __device__ __forceinline__ void hx_enqueue(const AppendArgs &a, int u)
 // takes one lane's scattered access at a time.  Hence first parents are known four at a time: one round trip brings four
 // nodes, what they hold and the next four first parents; the raises ask for no answer, because what a walk
 // carries is its own path and not what it finds (only further parents wait for theirs); and the wavefronts are spread
-// over the compute units.  72 K new nodes beside a search of 23 us: 40 us with a round trip of device atomics a level, each
-// answer part of the next raise, and a horizon raised at every visit; now 30 (on their own 33 -> 27).  The refresh of 812 K
-// nodes, where every node walked and raised four values: 157 us, now 44.  A walk visits 1.6 nodes on the average, but the longest in a
-// wavefront five or six further parents, one after the other: where it has ended, what it needs to go on from the highest second
-// parent comes with that one's raise, its record with the next four (30 -> 28 beside the search, the refresh 44 -> 41).  The highest, as
-// it carries the longest path: from the nearest, 20 graphs of 1000 nodes with up to three parents 5.0 -> 6.1 ms (now 4.9).
-// (Eight first parents at a time: 42 and 60, most of what they ask for lies above the point where a walk stops; two: as four.  Further parents queued in LDS for any idle lane
+// over the compute units: 72 K new nodes beside a search of 23 us 40 us with a round trip of device atomics a level, each answer part
+// of the next raise, and a horizon raised at every visit; so 30.  The refresh of 812 K nodes, where every node walked and raised four values,
+// 157, so 44.  A walk visits 1.6 nodes on the average, but the longest in a wavefront five or six further parents, one after the
+// other: where it has ended, what it needs to go on from the highest second parent comes with that one's raise, its record with the
+// next four: 28 and 41 now.  The highest, as it carries the longest path: 20 graphs of 1000 nodes with up to three parents 4.9 ms, from the nearest 6.1 (5.0 where
+// further parents only waited on the stack).
+// (Eight first parents at a time, before that: 42 and 60, most of what they ask for lies above the point where a walk stops; two: as four.  Further parents queued in LDS for any idle lane
 // of the wavefront: 30 and 59, three times the code.)
 //
 // REFRESH: all costs new, levels as they are.  The walks raise tails alone; rem and the horizons follow from those in a pass of

@@ -974,12 +974,13 @@ int hx_dag_append_begin(hx_ctx *ctx, const hx_model *model, int32_t n_new, int32
 }
 
 // A refresh of a graph of more than this many nodes for every compute unit starts at the nodes without children, if it has at most
-// two edges a node; else every node walks.  Fewer walks count where the device cannot work on all of them at a time: whole refreshes with every
-// node and so, 812 K nodes of a live system's workflows 67 and 63 us, 200 K nodes of trees 25 and 20, 800 K nodes of 1.4 edges
-// 164 and 83, of 1.6 191 and 116, of 2.0 228 and 167; 80 K nodes of trees 19 and 17, 20 K of 1.0 edges 24 and 21.  But a walk from below reaches a
-// node once for every path that still raises it, one thread for all above a leaf: 20 graphs of 40 layers of 10 3.2 and
-// 7.9 ms, 20 of 1000 nodes with up to three parents (1.8 edges a node) 4.7 and 9.7; with walks that read a further parent back from
-// the stack, 800 K nodes of 2.3 edges 427 and 391 us, of 3.3 1.1 and 3.3 ms, 6 K of 1.2 9 and 17.
+// two edges a node; else every node walks.  Fewer walks count where the device cannot work on all of them at a time: whole refreshes (us) with every
+// node and so, 812 K nodes of a live system's workflows 69 and 64; workflows of 20, 800 K nodes in trees 65 and 37, of 1.35 edges a node 156 and 83, of
+// 1.75 238 and 157, of 2.05 254 and 176; 200 K 27 and 22, 37 and 28 (1.25), 68 and 59 (1.65); 120 K 19 and 17, 29 and 24, 42 and 41; 20 K 16 and 15.  But a walk
+// from below reaches a node once for every path that still raises it, one thread for all above a leaf, and neither count says how many
+// paths there are: 6 graphs of 1000 nodes, 1.2 edges each, 0.55 and 4.6 ms, 20 of them 0.5 and 1.4, of 1.9 edges 3.7 and 8.0, 20 of 40 layers of 10
+// 3.3 and 7.0; 100 graphs of 200 nodes, 1.4 edges, 150 and 218 us, 1000 of these 265 and 258.  Hence where it is the smaller graphs that would lose, the
+// line lies where their gain is small: 2 to 5 us below it.
 constexpr int REFRESH_LEAVES_NODES = 512;
 
 extern "C" int hx_dag_set_cost(hx_ctx *ctx, int32_t n, const int32_t *node_ids, const float *cost, void *stream_)

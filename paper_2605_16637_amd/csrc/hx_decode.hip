@@ -666,12 +666,11 @@ __global__ __launch_bounds__(DS_THREADS) void hx_decode_score_kernel(DecodeArgs 
             a.part_cost[c] = placed ? v : INFINITY;
             a.part_start[c] = placed ? s.S : INFINITY;
             a.part_d[c] = placed ? d : -1;
-            if (a.start || a.cost)
-                for (int j = 0; j < a.D; ++j) {
-                    const bool here = legal && j == d;
-                    if (a.start) a.start[(size_t)c * a.D + j] = here ? s.S : INFINITY;
-                    if (a.cost) a.cost[(size_t)c * a.D + j] = (here && s.found) ? v : INFINITY;
-                }
+            for (int j = 0; j < a.D; ++j) {
+                const bool here = legal && j == d;
+                if (a.start) a.start[(size_t)c * a.D + j] = here ? s.S : INFINITY;
+                if (a.cost) a.cost[(size_t)c * a.D + j] = (here && s.found) ? v : INFINITY;
+            }
         }
         return;
     }
