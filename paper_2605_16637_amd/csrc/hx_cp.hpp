@@ -415,9 +415,9 @@ __device__ __forceinline__ void hx_cp_local_body(const CpArgs &a, int wpb, CpNod
 // steps as the deepest workflow has levels.  Same fixed point, same bits as the walk (one addition of an exact maximum a node).
 // Bound: the chain bounds -> rows -> successors -> steps, an LDS round trip each.  1000 workflows of 10 to 30 nodes and up to 12 levels with
 // their node cost 10.1 -> 6.2 us, beside the search of 4096 calls on 64 + 64 9.7 -> 7.2 (slices of a workgroup, one lane walking each workflow).
-// Where workgroups find workflows too large for a wavefront and take slices after all, they have spent a round trip and a barrier: rounds of that
-// search with 1000 workflows of 24 to 70 nodes 16.7 -> 20 us, 18432 of 4 with one of 65 in each 72nd 16.7 -> 19.2, 4000 of up to 30 with one of 70 in each tenth
-// 20.3 -> 17.7.
+// Where workgroups find workflows too large for a wavefront and take slices after all, they have spent a round trip and a barrier: with
+// 1000 workflows of 10 to 68 nodes that launch takes 14.2 -> 15.6 us, of 10 to 64 13.6 -> 7.2; rounds of that search with 1000 of 24 to 70 16.8 -> 17.1,
+// 18432 of 4 with one of 65 in each 72nd 16.8 -> 19.1, 4000 of up to 30 with one of 70 in each tenth 20.3 -> 17.7.
 constexpr int CW_EXTRA = 192;        // successors beyond CP_DEG of a node that a wavefront keeps in LDS
 struct CpWave {
     int2 val[HX_WAVE + 1];           // (rem, level) of lane i's node at i + 1; 0: the empty successor, (0, -1)
@@ -550,14 +550,14 @@ __device__ __forceinline__ CwFound hx_cp_wave(const CpArgs &a, int wa, int wb, i
     return f;
 }
 
-// The workflows of a workgroup of NT threads, `wpv` (below 64) to a wavefront; false: some workflow is not for a wavefront, and nothing
+// The `wpb` workflows of a workgroup of NT threads, `wpv` (below 64) to a wavefront; false: some workflow is not for a wavefront, and nothing
 // has been done but the tables filled.
 template <int NT>
-__device__ __forceinline__ bool hx_cp_waves_body(const CpArgs &a, int wpv, CpWave *waves, const NodeCostArgs &nc, CostTables &tab, int block)
+__device__ __forceinline__ bool hx_cp_waves_body(const CpArgs &a, int wpb, int wpv, CpWave *waves, const NodeCostArgs &nc, CostTables &tab, int block)
 {
     const int tid = threadIdx.x, lane = tid & (HX_WAVE - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wa = min((block * (NT / HX_WAVE) + wave) * wpv, a.n_wf), wb = min(wa + wpv, a.n_wf);
+    const int end = min((block + 1) * wpb, a.n_wf), wa = min(block * wpb + wave * wpv, end), wb = min(wa + wpv, end);
     const int p = hx_cp_wave_bounds(a, wa, wb, lane);
     hx_cost_tables_fill(tab, nc, tid);
     if (__syncthreads_or(hx_cp_wave_odd(a, p, wb - wa, lane))) return false;

@@ -84,7 +84,7 @@ void hx_cp_cost_kernel(CpArgs a, NodeCostArgs nc, int wpb, int wpv)
     __shared__ int s_any;
     __shared__ CostTables s_tab;
     if constexpr (WAVES)
-        if (hx_cp_waves_body<CP_THREADS>(a, wpv, s.wave, nc, s_tab, (int)blockIdx.x)) return;
+        if (hx_cp_waves_body<CP_THREADS>(a, wpb, wpv, s.wave, nc, s_tab, (int)blockIdx.x)) return;
     hx_cp_local_body<CP_NMAX_COST, true, false>(a, wpb, s.node, s_any, &nc, &s_tab, (int)blockIdx.x, WAVES);
 }
 

@@ -450,7 +450,7 @@ __global__ __launch_bounds__(FS_THREADS, 6) void hx_reveal_search_kernel(ScoreAr
     extern __shared__ __align__(16) float smem[];
     if ((int)blockIdx.x < n_reveal) {
         RevealLds *l = (RevealLds *)smem;
-        if (wpv && hx_cp_waves_body<FS_THREADS>(cp, wpv, l->wave, nc, l->tab, (int)blockIdx.x)) return;
+        if (wpv && hx_cp_waves_body<FS_THREADS>(cp, wpb, wpv, l->wave, nc, l->tab, (int)blockIdx.x)) return;
         hx_cp_local_body<RV_NMAX, true, false, FS_THREADS>(cp, wpb, l->node, l->any, &nc, &l->tab, (int)blockIdx.x, wpv != 0);
         return;
     }
@@ -849,7 +849,10 @@ int score_placements(hx_ctx *ctx, const hx_model *model, const hx_calls *calls,
             // not this way if the reveal's units are too large for its staging area
             const long long nodes_per_unit = (long long)reveal->a.n_nodes * reveal->wpb / (reveal->a.n_wf > 0 ? reveal->a.n_wf : 1);
             if (nodes_per_unit > RV_NMAX * 7 / 10) return HX_OK;
-            const int wpb = reveal->wpv ? reveal->wpv * FS_WAVES : reveal->wpb, n_reveal = (reveal->a.n_wf + wpb - 1) / wpb;
+            // wavefronts of a workgroup that take workflows: no more than give every compute unit a workgroup, so that one that takes its
+            // workflows as a slice after all has few (1000 workflows of 24 to 70 nodes 20 us a round with eight, 17 with four; of 10 to 30 11.2 and 11.1)
+            const int fill = reveal->wpv ? (reveal->a.n_wf + reveal->wpv * ctx->num_cu - 1) / (reveal->wpv * ctx->num_cu) : 0;
+            const int wpb = reveal->wpv ? reveal->wpv * (fill < FS_WAVES ? fill : FS_WAVES) : reveal->wpb, n_reveal = (reveal->a.n_wf + wpb - 1) / wpb;
             const size_t lds_both = lds > sizeof(RevealLds) ? lds : sizeof(RevealLds);
             by_calls([&](auto calls) {
                 hx_reveal_search_kernel<calls()><<<n_reveal + n_search, FS_THREADS, lds_both, stream>>>(

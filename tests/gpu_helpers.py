@@ -84,4 +84,4 @@ def many_small_workflows(n_wf, size, large, stride):
 # (workflows, nodes of each, of the large ones, workflows to an odd run): many workflows a wavefront and several runs a workgroup, some of
 # which have a workflow that no wavefront can take; runs as long as the workgroups', so that each of their numbers is met
 FALLBACKS = [(18432, 4, 65, 36), (18432, 4, 65, 72), (40000, 2, 65, 76), (40000, 2, 200, 300), (70000, 1, 65, 128), (70000, 1, 65, 256),
-             (20000, 0, 65, 128)]
+             (20000, 0, 65, 128), (1000, 30, 65, 4), (300, 9, 70, 4)]
