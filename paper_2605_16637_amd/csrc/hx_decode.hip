@@ -822,17 +822,17 @@ __global__ __launch_bounds__(64) void hx_decode_finish_kernel(DecodeFinishArgs a
 // time alone; where every instance is full for ten seconds 56 and 90, and 3 with the bisection.
 //
 // Where room comes in pieces that are too short for most calls no bound helps.  Whether it does is tried beforehand: the occupancy kernel
-// searches each instance for a few calls of the queue, and where more than DB_EVERY_PAIR in sixteen of these pairs have room
-// before their start all workgroups take their calls through all instances instead (hx_decode_every_pair).
+// looks at each instance for a few calls of the queue, and where for more than DB_EVERY_PAIR in sixteen of these pairs the first room there
+// is lasts too short a time all workgroups take their calls through all instances instead (hx_decode_every_pair).
 //
 // What bounds it: instruction issue, some 200 vector and 200 scalar instructions a call, and the chain of a call's memory round trips,
 // 2.9 and 1.9 us for the first and the second call of a wavefront.  Whole passes (us; the pairs all formed through tables of first moments
-// with room, as hx_decode_score_kernel does; so; and before the last three of the following): 16384 calls, half of them locked, on 256 instances with 120
-// intervals 46, 20.4, 19.8; 500 on 1024 with 50 60, 16.3, 15.5; 16384 on 512 with 60 57, 26, 35.  Full for ten seconds: the first 46, 53, 59; 16384
-// on 300 46, 53, 90; 4000 on 512 39, 30, 57; 16384 on 1024 106, 126, 157.  In pieces of 0.3 s: 2000 on 64 with 28 18, 12.5, 30; 16384 on 256 with 28 72, 79,
-// 338; 4000 on 1024 with 28 88, 116, 461; 300 on 1024 with 120 180, 92, 319.  What these three are: the pairs tried beforehand (0.4 us of every pass), the
-// bisection between two steps and from the fifth instance on (the sixth before), and eight instances a lane for 257 to 512.
-// (Of 4 and 8 s, for which some of the calls are too long, it stays slower than all pairs by tables: 3000 on 100 27, 40, 43; 300 on 64 19, 33, 33.)
+// with room, as hx_decode_score_kernel does; so; and without the last two of the following): 16384 calls, half of them locked, on 256 instances with 120
+// intervals 89, 22.5, 22.2; 500 on 1024 with 50 76, 20.8, 20.0; 16384 on 512 with 60 120, 41, 61; 3000 on 100 with 120 37, 19.7, 20.7; 1000 on 32 with
+// 500 85, 55, 52.  Full for ten seconds: the first 89, 50.5, 50.9; 500 on 300 with 250 107, 131, 145; 16384 on 300 84, 66, 106; 4000 on 512 52, 59, 84; 16384 on 1024
+// 214, 162, 180.  In pieces of 0.3 s: 2000 on 64 with 28 20, 12, 29; 16384 on 256 with 28 73, 75, 330; 4000 on 1024 with 28 90, 113, 455; 300 on 1024 with
+// 120 181, 90, 319.  What these two are: the pairs tried beforehand and eight instances a lane for 257 to 512.
+// (Of 4 and 8 s, for which some of the calls are too long, it is slower than all pairs by tables: 3000 on 100 26, 29, 31; 300 on 64 20, 24, 24.)
 
 // Up to some moment no more than `room` tokens have been free, and `time_bits` is when that may change: as the upper halves of two
 // floats, the first as its complement.  A call that needs more than the room has no start before that time; by halves, as far as the two
@@ -845,12 +845,9 @@ __device__ __forceinline__ unsigned hx_step_word(unsigned room, int time_bits)
 // The earliest start on one timeline, by a wavefront: an entry a lane, 64 at a time.  A run of entries with room begins where the one
 // before it has none, and is a start if the run's end, the next entry without room, is far enough: the comparisons of
 // hx_earliest_start, which tests a run at each of its entries, at the last of them, whose successor is the latest.
-// e: nt entries may be read, n of them count; next: the lane's of the first 64; room_at: the first entry with room, for however long.
-// Uniform in everything but the lane.
-__device__ __forceinline__ float hx_earliest_start_wave(const int2 *__restrict__ e, int nt, int2 next, int n, int thr, float T, int lane,
-                                                        float &room_at)
+// e: nt entries may be read, n of them count; next: the lane's of the first 64.  Uniform in everything but the lane.
+__device__ __forceinline__ float hx_earliest_start_wave(const int2 *__restrict__ e, int nt, int2 next, int n, int thr, float T, int lane)
 {
-    room_at = INFINITY;
     float rs = INFINITY;                                   // where the run that is open begins
     for (int i0 = 0; i0 < n; i0 += HX_WAVE) {
         const int2 x = next;
@@ -858,7 +855,6 @@ __device__ __forceinline__ float hx_earliest_start_wave(const int2 *__restrict__
         const bool in = i0 + lane < n;
         const float t = in ? __int_as_float(x.x) : INFINITY;      // behind the last entry: never, which ends every run
         const u64 room = __builtin_amdgcn_ballot_w64(in && x.y <= thr);
-        if (room && !(room_at < INFINITY)) room_at = hx_lane_value(t, __builtin_ctzll(room));
         const bool open = rs < INFINITY;
         if (open && room != ~0ull) {
             if (hx_lane_value(t, __builtin_ctzll(~room)) >= rs + T) return rs;
@@ -876,16 +872,36 @@ __device__ __forceinline__ float hx_earliest_start_wave(const int2 *__restrict__
     return rs;                                             // it lasts
 }
 
-// What is said of a pair that has been tried: there is room for the call some time; there is some before its start, for too short a time.
+// Whether the first run of entries with room is too short, so that there is room before the earliest start: that run alone is read.
+__device__ __forceinline__ bool hx_first_room_short(const int2 *e, int n, int thr, float T, int lane)
+{
+    float from = INFINITY;
+    for (int i0 = 0; i0 < n; i0 += HX_WAVE) {
+        const int2 x = e[min(i0 + lane, n - 1)];
+        const u64 room = __builtin_amdgcn_ballot_w64(i0 + lane < n && x.y <= thr);
+        int first = 0;
+        if (!(from < INFINITY)) {
+            if (room == 0) continue;
+            first = __builtin_ctzll(room);
+            from = hx_lane_value(__int_as_float(x.x), first);
+        }
+        const u64 ends = ~room >> first;
+        if (ends == 0) continue;
+        const int end = first + __builtin_ctzll(ends);
+        return i0 + end < n && hx_lane_value(__int_as_float(x.x), end) < from + T;
+    }
+    return false;
+}
+
+// What is said of a pair that has been tried: there is room for the call some time; the first there is lasts too short a time.
 constexpr unsigned DB_FITS = 1, DB_SHORT = 2;
 constexpr int DB_TRIES = 256;              // pairs tried, but at least one and at most seven an instance
 
 // Workgroup d: the occupancy of instance d over time, an entry an event that lies ahead; those that lie behind (most sequences
 // have begun) only add to what is held now.  Several events of one moment are several entries, all with what is held
 // after the last.  No running sum: an event adds up those not after it while it counts those before it.
-// Bound: two memory round trips (the record, the intervals) and the comparisons, n^2 of them on one compute unit.  64 registers: with two
-// more 1024 workgroups are no longer resident together (500 calls on 1024 instances 16.3 -> 17.9 us); held to 56 by eight wavefronts a
-// SIMD the comparisons have fewer reads in flight (256 instances 6.4 -> 6.7).
+// Bound: two memory round trips (the record, the intervals) and the comparisons, n^2 of them on one compute unit.  50 registers: with more
+// than 64 1024 workgroups are no longer resident together (500 calls on 1024 instances 16.3 -> 17.9 us).
 constexpr int DO_THREADS = 512;
 constexpr int DO_EVENTS = 2 * HX_MAX_INTERVALS + 42;      // and a filler for the shares of several lanes
 static_assert(HX_MAX_INTERVALS <= DO_THREADS, "an interval a thread");
@@ -897,6 +913,7 @@ __global__ __launch_bounds__(DO_THREADS) void hx_decode_occupancy_kernel(DecodeA
     __shared__ int s_least[2 * HX_MAX_INTERVALS + 1];
     __shared__ u64 s_now, s_all;                           // tokens held now; now or later
     __shared__ int s_n;
+    __shared__ int2 s_try[DO_THREADS / HX_WAVE];           // of the call a wavefront tries: its time, and what may be held
     const int tid = threadIdx.x, lane = tid & (HX_WAVE - 1), d = blockIdx.x;
     // the intervals are asked for before it is known how many there are
     const size_t at = (size_t)d * a.stride + tid;
@@ -906,25 +923,18 @@ __global__ __launch_bounds__(DO_THREADS) void hx_decode_occupancy_kernel(DecodeA
     int cnt = a.iv_count[d];
     const float flops = a.d_flops[d], hbm = a.d_hbm[d];
     const int used = a.d_used[d], batch = a.d_batch[d], cap = a.d_cap[d];
-    // `tries` wavefronts but the first try a call of the queue each
+    // the last `tries` wavefronts (never the first) try a call of the queue each: the last have the fewest intervals
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const bool tries = wave > 0 && wave <= a.tries;
-    const int c = tries ? ((d * a.tries + wave - 1) & a.try_mask) * a.try_step : 0;
-    const int L = a.L_in[c], O = a.L_out[c];
+    const int nth = DO_THREADS / HX_WAVE - 1 - wave;
+    const bool tries = nth < a.tries;
+    int L = 0, O = 0;
+    if (tries) {
+        int c = ((d * a.tries + nth) & a.try_mask) * a.try_step;
+        asm("" : "+v"(c));                                 // vector loads: nobody waits for them with the scalar ones
+        L = a.L_in[c]; O = a.L_out[c];
+    }
     for (int i = tid; i < DO_EVENTS; i += DO_THREADS) { s_key[i] = ~0ull; s_delta[i] = 0; }
     if (tid == 0) { s_now = 0; s_all = 0; s_n = 0; }
-    float T = 0.0f;
-    int thr = -1;
-    if (tries) {
-        const HxDecF x = hx_decode_terms(a.m, used, batch, 0, 1.0f / flops, 1.0f / hbm);
-        T = hx_lane_value(hx_decode_time(hx_call_terms(a.m, L, O), x.c1, x.c2, x.kB), 0);
-        if (L >= 0 && O >= 0 && hx_fits(L, O, cap)) thr = (int)((long long)cap - ((long long)L + O));
-        if (tid == HX_WAVE) {
-            int *const meta = o.meta + 8 * d;
-            *(int4 *)meta = make_int4(0, 0, cap, __float_as_int(x.c1));
-            *(int2 *)(meta + 4) = make_int2(__float_as_int(x.c2), __float_as_int(x.kB));
-        }
-    }
     __syncthreads();
     if (cnt < 0 || cnt > a.stride) {
         if (tid == 0) hx_raise(a.status, HX_ERR_INDEX);
@@ -947,6 +957,19 @@ __global__ __launch_bounds__(DO_THREADS) void hx_decode_occupancy_kernel(DecodeA
         if (holds) { s_key[i_end] = ((u64)__float_as_uint(en) << 32) | (unsigned)i_end; s_delta[i_end] = -tk; }
         if (later) { s_key[i_start] = ((u64)__float_as_uint(st) << 32) | (unsigned)i_start; s_delta[i_start] = tk; }
     }
+    if (tries) {                                           // (while others gather the events)
+        const HxDecF x = hx_decode_terms(a.m, used, batch, 0, 1.0f / flops, 1.0f / hbm);
+        if (lane == 0) {
+            const float T = hx_decode_time(hx_call_terms(a.m, L, O), x.c1, x.c2, x.kB);
+            const bool fits = L >= 0 && O >= 0 && hx_fits(L, O, cap);
+            s_try[nth] = make_int2(__float_as_int(T), fits ? (int)((long long)cap - ((long long)L + O)) : -1);
+            if (nth == 0) {
+                int *const meta = o.meta + 8 * d;
+                *(int4 *)meta = make_int4(0, 0, cap, __float_as_int(x.c1));
+                *(int2 *)(meta + 4) = make_int2(__float_as_int(x.c2), __float_as_int(x.kB));
+            }
+        }
+    }
     __syncthreads();
     const int n = s_n;
     const u64 held = s_now;
@@ -960,19 +983,21 @@ __global__ __launch_bounds__(DO_THREADS) void hx_decode_occupancy_kernel(DecodeA
         const int share = ((n + parts - 1) / parts + 7) & ~7;
         for (int i = tid / parts; i < n; i += DO_THREADS / parts) {
             const u64 mine = s_key[i];
-            const unsigned t = (unsigned)(mine >> 32);
+            const int t = (int)(mine >> 32), after = t + 1;      // (no time's bits are negative)
             int place = 0, sum = 0;
             const int j_lo = (tid & (parts - 1)) * share;
-            for (int j = j_lo; j < j_lo + share; j += 8) { // (past the last event the filler: never, nothing)
+            // (Past the last event the filler: before none, no tokens.  Whether an event is not after this one's moment is asked by
+            // a difference's sign: a comparison is widened to 64 bits, at 66 registers, or waits for the one condition register.)
+            for (int j = j_lo; j < j_lo + share; j += 8) {
                 u64 key[8];
                 int delta[8];
 #pragma unroll
                 for (int u = 0; u < 8; ++u) { key[u] = s_key[j + u]; delta[u] = s_delta[j + u]; }
 #pragma unroll
-                for (int u = 0; u < 8; ++u) { place += key[u] < mine; sum += (unsigned)(key[u] >> 32) <= t ? delta[u] : 0; }
+                for (int u = 0; u < 8; ++u) { place += key[u] < mine; sum += delta[u] & (((int)(key[u] >> 32) - after) >> 31); }
             }
             place = hx_parts_sum(place, parts); sum = hx_parts_sum(sum, parts);
-            if ((tid & (parts - 1)) == 0) s_e[place + 1] = make_int2((int)t, (int)held + sum);
+            if ((tid & (parts - 1)) == 0) s_e[place + 1] = make_int2(t, (int)held + sum);
         }
     } else {
         for (int i = tid; i < n; i += DO_THREADS) {
@@ -986,7 +1011,7 @@ __global__ __launch_bounds__(DO_THREADS) void hx_decode_occupancy_kernel(DecodeA
     }
     __syncthreads();
     const int n_e = n + 1;
-    if (tid == HX_WAVE) o.meta[8 * d] = n_e;
+    if (tid == DO_THREADS - HX_WAVE) o.meta[8 * d] = n_e;
     int2 *const e = o.e + (size_t)d * nt;
     for (int i = tid; i < hx_tl_len(n_e); i += DO_THREADS) e[i] = i < n_e ? s_e[i] : make_int2(0x7f800000, 0);
     if (tid < HX_WAVE) {
@@ -1014,10 +1039,10 @@ __global__ __launch_bounds__(DO_THREADS) void hx_decode_occupancy_kernel(DecodeA
         return;
     }
     unsigned what = 0;
+    const int thr = __builtin_amdgcn_readfirstlane(s_try[nth].y);      // tokens the call may find held, < 0: never fits
     if (thr >= 0) {
-        float room_at;
-        const float S = hx_earliest_start_wave(s_e, n_e, s_e[min(lane, n_e - 1)], n_e, thr, T, lane, room_at);
-        what = room_at < S ? DB_FITS | DB_SHORT : DB_FITS;
+        const float T = hx_lane_value(__int_as_float(s_try[nth].x), 0);
+        what = hx_first_room_short(s_e, n_e, thr, T, lane) ? DB_FITS | DB_SHORT : DB_FITS;
     }
     if (lane == 0) *says = (unsigned char)what;
 }
@@ -1027,11 +1052,12 @@ constexpr int DB_THREADS = 256;
 // four and three have a place: with no more than these 16384 calls on 512 and 1024 full instances 76 -> 90 and 162 -> 187, others full for no time
 // 26 -> 26 and 39 -> 36.5.
 constexpr int DB_PER_CU = 6;
-// (DB_EXACT 4, 5, 6: the first of the passes above 20.9, 20.4, 20.4, full for ten seconds 52, 53, 54.)
-constexpr int DB_CLOSER = 1, DB_EXACT = 5, DB_ALL = 16;
+// (DB_EXACT 5, 6, 7: the first of the passes above 25.4, 22.6, 22.2, full for ten seconds 48.9, 50.5, 53.5; 500 on 1024 29.5, 20.8, 20.2; 16384 on 300 full ones
+// 63, 66, 69.)
+constexpr int DB_CLOSER = 1, DB_EXACT = 6, DB_ALL = 16;
 // Every pair where more than so many sixteenths of those tried have room before their start: 3000 calls on 100 instances with 30 resident and 90
-// planned intervals (some 8) 18 us, every pair 36; 300 on 33 with 64 and 191 (some 12) 30 and 41; in pieces of 4 s (12) 3000 on 100 40 and
-// 27; of 2 s (14) 44 and 27.
+// planned intervals (some 8) 20 us, every pair 34; 300 on 33 with 64 and 191 (some 12) 22 and 37; in pieces of 4 s (12) 3000 on 100 29 and
+// 16; of 2 s (14) 33 and 17.
 constexpr unsigned DB_EVERY_PAIR = 13;
 
 // The same where sixteen lanes, a row of the wavefront, search one timeline for sixteen calls: a lane loads an entry of sixteen and all
@@ -1176,8 +1202,7 @@ __global__ __launch_bounds__(DB_THREADS, K <= 4 ? 6 : K == 8 ? 4 : 3) void hx_de
             const HxInst it = hx_inst_load(o, d);
             const float T = hx_decode_time(cf, it.c1, it.c2, it.kB);
             const int thr = threshold(it.cap);
-            float room_at;
-            const float S = hx_earliest_start_wave(e, nt, first, it.n, thr, T, lane, room_at);
+            const float S = hx_earliest_start_wave(e, nt, first, it.n, thr, T, lane);
             const float v = S + T;                         // +inf when there is no start
             if (v < best || (v == best && d < best_d)) { best = v; best_S = S; best_d = d; }
         };
