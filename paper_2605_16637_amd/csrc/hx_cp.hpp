@@ -416,8 +416,9 @@ __device__ __forceinline__ void hx_cp_local_body(const CpArgs &a, int wpb, CpNod
 // Bound: the chain bounds -> rows -> successors -> steps, an LDS round trip each.  1000 workflows of 10 to 30 nodes and up to 12 levels with
 // their node cost 10.1 -> 6.2 us, beside the search of 4096 calls on 64 + 64 9.7 -> 7.2 (slices of a workgroup, one lane walking each workflow).
 // Where workgroups find workflows too large for a wavefront and take slices after all, they have spent a round trip and a barrier: with
-// 1000 workflows of 10 to 68 nodes that launch takes 14.2 -> 15.6 us, of 10 to 64 13.6 -> 7.2; rounds of that search with 1000 of 24 to 70 16.8 -> 17.1,
-// 18432 of 4 with one of 65 in each 72nd 16.8 -> 19.1, 4000 of up to 30 with one of 70 in each tenth 20.3 -> 17.7.
+// 1000 workflows of 10 to 68 nodes that launch takes 14.2 -> 15.6 us, of 10 to 64 13.6 -> 7.2; rounds of that search with 300, 1000 and 1023 of 24 to 70 16.7 ->
+// 20.1, 18.1 -> 20.3 and 19.3 -> 16.6, with 18432 of 4 with one of 65 in each 600th and each 144th 16.2 -> 19.0 and 20.0 -> 19.5, 40000 of 2 with one of 65 in
+// each 304th 19.7 -> 21.4, 4000 of up to 30 with one of 70 in each tenth 26.0 -> 25.7; without the large ones 13 to 14 -> 10.7 to 12.
 constexpr int CW_EXTRA = 192;        // successors beyond CP_DEG of a node that a wavefront keeps in LDS
 struct CpWave {
     int2 val[HX_WAVE + 1];           // (rem, level) of lane i's node at i + 1; 0: the empty successor, (0, -1)

@@ -850,7 +850,7 @@ int score_placements(hx_ctx *ctx, const hx_model *model, const hx_calls *calls,
             const long long nodes_per_unit = (long long)reveal->a.n_nodes * reveal->wpb / (reveal->a.n_wf > 0 ? reveal->a.n_wf : 1);
             if (nodes_per_unit > RV_NMAX * 7 / 10) return HX_OK;
             // wavefronts of a workgroup that take workflows: no more than give every compute unit a workgroup, so that one that takes its
-            // workflows as a slice after all has few (1000 workflows of 24 to 70 nodes 20 us a round with eight, 17 with four; of 10 to 30 11.2 and 11.1)
+            // workflows as a slice after all has few (1023 workflows of 24 to 70 nodes 18.4 us a round with eight, 16.6 with four; of 10 to 30 12.0 and 11.5)
             const int fill = reveal->wpv ? (reveal->a.n_wf + reveal->wpv * ctx->num_cu - 1) / (reveal->wpv * ctx->num_cu) : 0;
             const int wpb = reveal->wpv ? reveal->wpv * (fill < FS_WAVES ? fill : FS_WAVES) : reveal->wpb, n_reveal = (reveal->a.n_wf + wpb - 1) / wpb;
             const size_t lds_both = lds > sizeof(RevealLds) ? lds : sizeof(RevealLds);
