@@ -416,9 +416,10 @@ __device__ __forceinline__ void hx_cp_local_body(const CpArgs &a, int wpb, CpNod
 // Bound: the chain bounds -> rows -> successors -> steps, an LDS round trip each.  1000 workflows of 10 to 30 nodes and up to 12 levels with
 // their node cost 10.1 -> 6.2 us, beside the search of 4096 calls on 64 + 64 9.7 -> 7.2 (slices of a workgroup, one lane walking each workflow).
 // Where workgroups find workflows too large for a wavefront and take slices after all, they have spent a round trip and a barrier: with
-// 1000 workflows of 10 to 68 nodes that launch takes 14.2 -> 15.6 us, of 10 to 64 13.6 -> 7.2; rounds of that search with 300, 1000 and 1023 of 24 to 70 16.7 ->
-// 20.1, 18.1 -> 20.3 and 19.3 -> 16.6, with 18432 of 4 with one of 65 in each 600th and each 144th 16.2 -> 19.0 and 20.0 -> 19.5, 40000 of 2 with one of 65 in
-// each 304th 19.7 -> 21.4, 4000 of up to 30 with one of 70 in each tenth 26.0 -> 25.7; without the large ones 13 to 14 -> 10.7 to 12.
+// 1000 workflows of 10 to 68 nodes that launch takes 14.2 -> 15.6 us, of 10 to 64 13.6 -> 7.2; rounds of that search with 300, 1000 and 2047 of 24 to 70 16.7 ->
+// 16.6, 17.2 -> 16.8 and 17.4 -> 17.3, with 18432 of 4 with one of 65 in each 600th and each 144th 16.3 -> 19.1 and 16.9 -> 19.1, 40000 of 2 with one of 65 in
+// each 304th 19.8 -> 21.4, 4000 of up to 30 with one of 70 in each tenth 24.5 -> 24.7; without the large ones 13 to 14 -> 10.7 to 12.  (Where the array of
+// successors ends with the graph, the slice with its last rows leaves those to the walk: 3.5 us more, before as now; wavefronts do not.)
 constexpr int CW_EXTRA = 192;        // successors beyond CP_DEG of a node that a wavefront keeps in LDS
 struct CpWave {
     int2 val[HX_WAVE + 1];           // (rem, level) of lane i's node at i + 1; 0: the empty successor, (0, -1)
